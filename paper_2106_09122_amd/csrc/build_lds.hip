@@ -672,9 +672,11 @@ __host__ __device__ inline OrbitGrid orbit_grid(int N) {
   return o;
 }
 
+// (columns are fewer than 2^31: 32-bit divisions)
 __device__ __forceinline__ int64_t orbit_base(const OrbitGrid& o, int64_t t) {
   if (t < o.n4) {
-    const int64_t p = o.plo + t / o.hq, q = o.qlo + t % o.hq;
+    const uint32_t r = (uint32_t)t / (uint32_t)o.hq;
+    const int64_t p = o.plo + (int64_t)r, q = o.qlo + (int64_t)((uint32_t)t - r * (uint32_t)o.hq);
     return p * o.N + q;
   }
   return (int64_t)(o.N / 2) * o.N + o.N / 2;  // centre
@@ -682,7 +684,7 @@ __device__ __forceinline__ int64_t orbit_base(const OrbitGrid& o, int64_t t) {
 
 // rotation partners of base column j0 = p N + q (k quarter turns)
 __device__ __forceinline__ int64_t orbit_member(int64_t j0, int N, int k) {
-  const int64_t p = j0 / N, q = j0 - p * N;
+  const int64_t p = (uint32_t)j0 / (uint32_t)N, q = j0 - p * N;
   switch (k) {
     case 0: return j0;
     case 1: return q * N + (N - 1 - p);
@@ -767,22 +769,28 @@ __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom
   }
 }
 
-// column sums: the partial sums of the row ranges in order, for every member
-__global__ __launch_bounds__(256) void orbit_tau_kernel(const int32_t* __restrict__ reps,
-                                                        const double* __restrict__ part,
-                                                        int nranges, int64_t nreps, int N,
+// column sums: the partial sums of the row ranges (16-bit) or tiles (float32)
+// in order, for every member
+__global__ __launch_bounds__(256) void orbit_tau_kernel(const int32_t* __restrict__ reps, OrbitGrid o,
+                                                        const double* __restrict__ part, int nparts,
                                                         double* __restrict__ tau) {
   const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (s >= nreps) return;
+  if (s >= o.nreps) return;
   double t = 0.0;
-  for (int r = 0; r < nranges; ++r) t += part[(int64_t)r * nreps + s];
+  for (int r0 = 0; r0 < nparts; r0 += 8) {  // 8 loads in flight
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = r0 + u < nparts ? part[(int64_t)(r0 + u) * o.nreps + s] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += v[u];
+  }
   const int64_t j0 = reps[s];
-  if (orbit_is_centre(j0, N)) {
+  if (orbit_is_centre(j0, o.N)) {
     tau[j0] = t;
     return;
   }
 #pragma unroll
-  for (int k = 0; k < 4; ++k) tau[orbit_member(j0, N, k)] = t;
+  for (int k = 0; k < 4; ++k) tau[orbit_member(j0, o.N, k)] = t;
 }
 
 // the bordered pair (P_k, P_{k+1}) with its zero border, as the LDS build
@@ -838,14 +846,166 @@ __device__ __forceinline__ float orbit_value(const float2* __restrict__ P2, doub
 // (the second pass).
 constexpr int kPlain = kOrbitPlain, kSumsOnly = kOrbitSumsOnly, kScaled = kOrbitScaled;
 
-// Float32 orbit build.  Wave = base column over the item's rows in tiles of
-// 32 x 32 pixels; lane (i, k) = (lane / 8, lane % 8) forms the 4 x 4 block
-// at rows 4i.., columns 4k.. of a tile.  Each lane then holds four runs of
-// four entries for every member (C0, C2 along rows; C1, C3 along the base
-// column's image columns), so every store is 16 bytes and each store
-// instruction fills eight whole 128-byte lines of one member (VEC: n % 4 ==
-// 0, every 4 x 4 block is wholly inside or outside the image, runs 16-byte
-// aligned; otherwise scalar stores).
+// 16-byte run of a column.  VEC (n a multiple of 32): the eight lanes of a tile
+// row fill a whole 128-byte line.  Otherwise the run starts at any float and
+// the lines at its ends are shared with the next tiles: ordinary stores, so
+// that their parts meet in the L2.
+template <bool VEC>
+__device__ __forceinline__ void store_run(float* p, const f32x4 v) {
+  if constexpr (VEC) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+  } else {
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    *reinterpret_cast<f32x4u*>(p) = v;
+  }
+}
+
+// The runs of one row (x[r][0..3] at row a, columns bb ..) in members 0 and 2,
+// and of the block's four columns (rows ab ..) in members 1 and 3.
+template <bool VEC>
+__device__ __forceinline__ void store_row_runs(const float* xr, float* C0, float* C2, int a, int bb,
+                                               int n, bool centre) {
+  store_run<VEC>(C0 + (int64_t)a * n + bb, (f32x4){xr[0], xr[1], xr[2], xr[3]});
+  if (!centre)
+    store_run<VEC>(C2 + (int64_t)(n - 1 - a) * n + (n - 4 - bb), (f32x4){xr[3], xr[2], xr[1], xr[0]});
+}
+
+template <bool VEC>
+__device__ __forceinline__ void store_column_runs(const float (*x)[4], float* C1, float* C3, int ab,
+                                                  int bb, int n) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = bb + q;
+    store_run<VEC>(C1 + (int64_t)b * n + (n - 4 - ab), (f32x4){x[3][q], x[2][q], x[1][q], x[0][q]});
+    store_run<VEC>(C3 + (int64_t)(n - 1 - b) * n + ab, (f32x4){x[0][q], x[1][q], x[2][q], x[3][q]});
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// the same entries one by one, for images of fewer than 4 pixels a side
+__device__ __forceinline__ void store_block_scalar(const float (*x)[4], float* C0, float* C1, float* C2,
+                                                   float* C3, int ab, int bb, int n, bool centre) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int a = ab + r, b = bb + q;
+      if (a >= n || b >= n) continue;
+      C0[(int64_t)a * n + b] = x[r][q];
+      if (centre) continue;
+      C1[(int64_t)b * n + (n - 1 - a)] = x[r][q];
+      C2[(int64_t)(n - 1 - a) * n + (n - 1 - b)] = x[r][q];
+      C3[(int64_t)(n - 1 - b) * n + a] = x[r][q];
+    }
+}
+
+// First row (column) of the 4 x 4 block that covers v0 .. v0 + 3: with n not a
+// multiple of 4 the last block of the image is moved back to end at its edge
+// (it forms up to 3 rows or columns of its neighbour again, with the same
+// values; they are summed once, by the neighbour).
+template <bool VEC>
+__device__ __forceinline__ int block_start(int v0, int n) {
+  return VEC ? v0 : max(min(v0, n - 4), 0);
+}
+
+// What a wave needs of the base column it works on (the same in every lane).
+struct OrbitCol {
+  int64_t j0;
+  double ct, st, w;
+  int k;
+  float scale;  // flux-preserving scale
+};
+
+template <int MODE>
+__device__ __forceinline__ OrbitCol load_orbit_col(const int32_t* __restrict__ reps,
+                                                   const ColGeom* __restrict__ geo,
+                                                   const float* __restrict__ colscale, int64_t sp) {
+  OrbitCol o;
+  o.j0 = reps[sp];
+  const ColGeom* g = geo + o.j0;
+  o.ct = g->ct;
+  o.st = g->st;
+  o.w = g->w;
+  o.k = g->k;
+  o.scale = (MODE == kScaled) ? colscale[o.j0] : 1.0f;
+  return o;
+}
+
+// Tiles of 32 x 32 pixels cover the image; lane (i, k) = (lane / 8, lane % 8)
+// of the wave that forms a tile takes the 4 x 4 block at its rows 4i..,
+// columns 4k...  The lane then holds four runs of four entries for every
+// member (C0, C2 along rows; C1, C3 along the base column's image columns), so
+// every store is 16 bytes and each store instruction writes eight runs of 128
+// bytes of one member.  value(ctux, mstux, stuy, ctuy) is the entry at the
+// block's pixel; the entries' sum is added to tsum.  VEC: n a multiple of 32,
+// whole lines.  Otherwise the runs are unaligned and the image's last blocks
+// overlap their neighbours (block_start), so that no entry needs a store of
+// its own.
+template <bool VEC, int MODE, typename Value>
+__device__ __forceinline__ void orbit_block(Value value, const OrbitCol& g, double c, int n, int N,
+                                            int64_t M, int ab0, int bb0, float* A, double& tsum) {
+  const bool centre = orbit_is_centre(g.j0, N);
+  float* C0 = A + g.j0 * M;
+  float* C1 = A + orbit_member(g.j0, N, 1) * M;
+  float* C2 = A + orbit_member(g.j0, N, 2) * M;
+  float* C3 = A + orbit_member(g.j0, N, 3) * M;
+  const int ab = block_start<VEC>(ab0, n), bb = block_start<VEC>(bb0, n);
+  double ctux[4], mstux[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+#pragma clang fp contract(off)
+    const double ux = (double)(bb + q) - c;
+    ctux[q] = g.ct * ux;
+    mstux[q] = (-g.st) * ux;
+  }
+  float x[4][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int a = ab + r;
+    double stuy, ctuy;
+    {
+#pragma clang fp contract(off)
+      const double uy = (double)a - c;
+      stuy = g.st * uy;
+      ctuy = g.ct * uy;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x[r][q] = 0.0f;
+      if (VEC || (a < n && bb + q < n)) {  // false for n < 4 only
+        x[r][q] = value(ctux[q], mstux[q], stuy, ctuy);
+        if constexpr (MODE == kScaled) x[r][q] *= g.scale;
+        if (VEC || (a >= ab0 && bb + q >= bb0)) tsum += (double)x[r][q];
+      }
+      if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
+    }
+    if constexpr (MODE != kSumsOnly) {  // the row's runs of C0 and C2
+      if (VEC || n >= 4) store_row_runs<VEC>(x[r], C0, C2, a, bb, n, centre);
+    }
+    // one row of the block at a time: bounds the live coordinate temporaries
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (MODE != kSumsOnly) {
+    if (!VEC && n < 4)
+      store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, centre);
+    else if (!centre)
+      store_column_runs<VEC>(x, C1, C3, ab, bb, n);
+  }
+}
+
+// Float32 orbit build, the pair in LDS.  A workgroup (blockIdx.x: item = run of
+// one bracket inside a window of 16 bases; blockIdx.y: a few bases of the
+// window) stages the pair and its waves share out the tiles of its bases, so
+// that the waves write neighbouring tiles of one column together: where n is
+// not a multiple of 32 the tiles' rows and columns share 128-byte lines, and
+// the two halves of a line meet in the L2 before it is written back.  Bound by
+// the write stream: at 128^2 (1 GiB) 226 us against 250 us with a wave per
+// column and row range; at 127^2 465 us against 2475 us with a wave per column
+// and a store per entry, 670 us with 16-byte stores, which then evicted half
+// lines.
+// Four bases give 16 waves of work from 64^2 pixels; smaller images take more,
+// so that the pair is staged for a full workgroup.
+__host__ __device__ constexpr int orbit_sub(int nt) { return nt == 1 ? 16 : nt == 2 ? 8 : 4; }
 template <bool VEC, int MODE>
 __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restrict__ cube, int K,
                                                            const ColGeom* __restrict__ geo,
@@ -853,122 +1013,48 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
                                                            const int4* __restrict__ items,
                                                            const int32_t* __restrict__ nitems,
                                                            int nb, int n, int ls, int N, int64_t M,
-                                                           int rpr, int64_t nreps,
+                                                           int nt, int64_t nreps,
                                                            float* __restrict__ A,
                                                            double* __restrict__ part,
     const float* __restrict__ colscale) {
   extern __shared__ float2 P2[];
   if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
   const int4 it = items[blockIdx.x];
-  const int bkt = it.x, first = it.y, len = it.z, w0 = it.w;
+  const int sub = orbit_sub(nt);
+  const int bkt = it.x, w0 = it.w + sub * (int)blockIdx.y;
+  const int first = max(it.y, w0), last = min(it.y + it.z, w0 + sub);
+  if (first >= last) return;  // uniform: no base of the item among these
   const bool zero_bucket = bkt == nb - 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (!zero_bucket) stage_pair(P2, cube, bkt, K, n, ls, M, tid);
   __syncthreads();
-  const int sp = w0 + wave;
-  if (sp < first || sp >= first + len) return;  // uniform per wave; no barrier below
-  const int64_t j0 = reps[sp];
-  const bool centre = orbit_is_centre(j0, N);
-  float* C0 = A + j0 * M;
-  float* C1 = A + orbit_member(j0, N, 1) * M;
-  float* C2 = A + orbit_member(j0, N, 2) * M;
-  float* C3 = A + orbit_member(j0, N, 3) * M;
-  if (zero_bucket) {  // identically zero orbit: rows [ra, rb) of every member
-    for (int x = lane; MODE != kSumsOnly && x < (rb - ra) * n; x += 64) {
-      const int64_t p = (int64_t)ra * n + x;
-      __builtin_nontemporal_store(0.0f, C0 + p);
-      if (!centre) {
-        __builtin_nontemporal_store(0.0f, C1 + p);
-        __builtin_nontemporal_store(0.0f, C2 + p);
-        __builtin_nontemporal_store(0.0f, C3 + p);
-      }
-    }
-    if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = 0.0;
-    return;
-  }
-  const ColGeom g = geo[j0];
-  const float sf = (MODE == kScaled) ? colscale[j0] : 1.0f;  // flux-preserving scale
   const double c = (double)(n - 1) * 0.5;
-  const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
   const int li = lane >> 3, lk = lane & 7;
-  double tsum = 0.0;
-  for (int a0 = ra; a0 < rb; a0 += 32) {
-    const int ab = a0 + 4 * li;
-    if (ab >= rb) continue;  // VEC: the whole block is below the range
-    for (int b0 = 0; b0 < n; b0 += 32) {
-      const int bb = b0 + 4 * lk;
-      if (bb >= n) continue;
-      double ctux[4], mstux[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma clang fp contract(off)
-        const double ux = (double)(bb + q) - c;
-        ctux[q] = g.ct * ux;
-        mstux[q] = (-g.st) * ux;
-      }
-      float x[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int a = ab + r;
-        double stuy, ctuy;
-        {
-#pragma clang fp contract(off)
-          const double uy = (double)a - c;
-          stuy = g.st * uy;
-          ctuy = g.ct * uy;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          x[r][q] = 0.0f;
-          if (VEC || (a < rb && bb + q < n)) {
-            x[r][q] = orbit_value(P2, ctux[q], mstux[q], stuy, ctuy, c, n, ls, wk0, wk1);
-            if constexpr (MODE == kScaled) x[r][q] *= sf;
-            tsum += (double)x[r][q];
-          }
-          if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
-        }
-        if constexpr (VEC && MODE != kSumsOnly) {  // the row's runs of C0 and C2
-          __builtin_nontemporal_store((f32x4){x[r][0], x[r][1], x[r][2], x[r][3]},
-                                      reinterpret_cast<f32x4*>(C0 + (int64_t)a * n + bb));
-          if (!centre)
-            __builtin_nontemporal_store((f32x4){x[r][3], x[r][2], x[r][1], x[r][0]},
-                                        reinterpret_cast<f32x4*>(C2 + (int64_t)(n - 1 - a) * n + (n - 4 - bb)));
-        }
-        // one row of the block at a time: bounds the live coordinate temporaries
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (MODE == kSumsOnly) {
-      } else if constexpr (VEC) {
-        if (!centre) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int b = bb + q;
-            __builtin_nontemporal_store((f32x4){x[3][q], x[2][q], x[1][q], x[0][q]},
-                                        reinterpret_cast<f32x4*>(C1 + (int64_t)b * n + (n - 4 - ab)));
-            __builtin_nontemporal_store((f32x4){x[0][q], x[1][q], x[2][q], x[3][q]},
-                                        reinterpret_cast<f32x4*>(C3 + (int64_t)(n - 1 - b) * n + ab));
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int a = ab + r, b = bb + q;
-            if (a >= rb || b >= n) continue;
-            __builtin_nontemporal_store(x[r][q], C0 + (int64_t)a * n + b);
-            if (centre) continue;
-            __builtin_nontemporal_store(x[r][q], C1 + (int64_t)b * n + (n - 1 - a));
-            __builtin_nontemporal_store(x[r][q], C2 + (int64_t)(n - 1 - a) * n + (n - 1 - b));
-            __builtin_nontemporal_store(x[r][q], C3 + (int64_t)(n - 1 - b) * n + a);
-          }
-      }
+  const int ntiles = nt * nt, nwork = (last - first) * ntiles;
+  if (wave >= nwork) return;  // no barrier below
+  OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, first + wave / ntiles);
+  for (int t = wave; t < nwork; t += 16) {  // uniform per wave
+    const int sp = first + t / ntiles, tile = t % ntiles;
+    const OrbitCol next = load_orbit_col<MODE>(reps, geo, colscale, first + min(t + 16, nwork - 1) / ntiles);
+    const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
+    const int ab0 = 32 * (tile / nt) + 4 * li, bb0 = 32 * (tile % nt) + 4 * lk;
+    double tsum = 0.0;
+    if (ab0 < n && bb0 < n) {
+      if (zero_bucket)  // identically zero orbit
+        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, N, M, ab0,
+                               bb0, A, tsum);
+      else
+        orbit_block<VEC, MODE>(
+            [&](double ctux, double mstux, double stuy, double ctuy) {
+              return orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
+            },
+            g, c, n, N, M, ab0, bb0, A, tsum);
     }
+    tsum = wave_sum_f64(tsum);
+    if (lane == 0) part[(int64_t)tile * nreps + sp] = tsum;
+    g = next;
   }
-  tsum = wave_sum_f64(tsum);
-  if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
 }
 
 // Float32 orbit build for pairs larger than the LDS (n > 141).  The
@@ -997,7 +1083,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // floor of the source row and column of image pixel (a, b) (tap_coords' steps)
-__device__ __forceinline__ void tap_origin(const ColGeom& g, double c, int a, int b, int& r0, int& c0) {
+template <typename G>
+__device__ __forceinline__ void tap_origin(const G& g, double c, int a, int b, int& r0, int& c0) {
 #pragma clang fp contract(off)
   const double ux = (double)b - c, uy = (double)a - c;
   const double ctux = g.ct * ux, mstux = (-g.st) * ux;
@@ -1071,154 +1158,89 @@ __device__ __forceinline__ void stage_box(float* __restrict__ Q, const float* __
   }
 }
 
+// The waves of the launch walk the (base, tile) pairs independently, tiles of
+// one base on neighbouring waves.  Nothing is shared between them; the bases
+// are taken in bracket order so that the pairs being read at one time stay in
+// the L2 (256^2: 3.7 ms, in natural order 4.6 ms).
+// The workgroup's share of the runs, a contiguous range; round i takes the next
+// 16, the waves moved on by 5 a round so that none keeps to one place of the
+// image (tiles at its corners are cheap).
+__device__ __forceinline__ uint32_t box_run(uint32_t i, int wave, uint32_t rounds) {
+  return (blockIdx.x * rounds + i) * 16 + (((uint32_t)wave + 5 * i) & 15);
+}
+
 template <bool VEC, int MODE>
 __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __restrict__ cube, int K,
                                                                const ColGeom* __restrict__ geo,
                                                                const int32_t* __restrict__ reps,
-                                                               const int4* __restrict__ items,
-                                                               const int32_t* __restrict__ nitems,
-                                                               int nb, int n, int N, int64_t M,
-                                                               int rpr, int64_t nreps,
+                                                               OrbitGrid o, int n, int64_t M, int nt, int run, uint32_t total,
                                                                float* __restrict__ A,
                                                                double* __restrict__ part,
     const float* __restrict__ colscale) {
   extern __shared__ float QS[];  // 16 regions of kFpRegion floats
-  if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
-  const int4 it = items[blockIdx.x];
-  const int bkt = it.x, first = it.y, len = it.z, w0 = it.w;
-  const bool zero_bucket = bkt == nb - 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
-  const int sp = w0 + wave;
-  if (sp < first || sp >= first + len) return;  // uniform per wave; no workgroup barrier
-  const int64_t j0 = reps[sp];
-  const bool centre = orbit_is_centre(j0, N);
-  float* C0 = A + j0 * M;
-  float* C1 = A + orbit_member(j0, N, 1) * M;
-  float* C2 = A + orbit_member(j0, N, 2) * M;
-  float* C3 = A + orbit_member(j0, N, 3) * M;
-  if (zero_bucket) {  // identically zero orbit: rows [ra, rb) of every member
-    for (int x = lane; MODE != kSumsOnly && x < (rb - ra) * n; x += 64) {
-      const int64_t p = (int64_t)ra * n + x;
-      __builtin_nontemporal_store(0.0f, C0 + p);
-      if (!centre) {
-        __builtin_nontemporal_store(0.0f, C1 + p);
-        __builtin_nontemporal_store(0.0f, C2 + p);
-        __builtin_nontemporal_store(0.0f, C3 + p);
-      }
-    }
-    if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = 0.0;
-    return;
-  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* Q = QS + wave * kFpRegion;
-  const float* Pk = cube + (int64_t)bkt * M;
-  const float* Pk1 = (K > 1) ? Pk + M : nullptr;
-  const ColGeom g = geo[j0];
-  const float sf = (MODE == kScaled) ? colscale[j0] : 1.0f;  // flux-preserving scale
   const double c = (double)(n - 1) * 0.5;
-  const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
   const int li = lane >> 3, lk = lane & 7;
-  double tsum = 0.0;
-  for (int a0 = ra; a0 < rb; a0 += 32) {
-    const int ae = (a0 + 32 < rb) ? a0 + 32 : rb;
-    const int ab = a0 + 4 * li;
-    for (int b0 = 0; b0 < n; b0 += 32) {
-      const int be = (b0 + 32 < n) ? b0 + 32 : n;
-      // the tile's box of bordered rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-      int rmin, rmax, cmin, cmax;
-      {
-        int r0, c0;
-        tap_origin(g, c, a0, b0, r0, c0);
-        rmin = rmax = r0;
-        cmin = cmax = c0;
+  const int ntiles = nt * nt;
+  const int nruns = (ntiles + run - 1) / run;
+  const uint32_t rounds = (total + 16 * gridDim.x - 1) / (16 * gridDim.x);
+  for (uint32_t i = 0; i < rounds; ++i) {  // no workgroup barrier
+    const uint32_t t = box_run(i, wave, rounds);
+    if (t >= total) continue;
+    const uint32_t sp = t / (uint32_t)nruns;
+    const int r = (int)(t - sp * (uint32_t)nruns);
+    const OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, sp);
+    double tsum = 0.0;
+    for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
+    const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
+    const int ab0 = a0 + 4 * li, bb0 = b0 + 4 * lk;
+    if (g.k < 0) {  // identically zero orbit
+      if (ab0 < n && bb0 < n)
+        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M,
+                               ab0, bb0, A, tsum);
+      continue;
+    }
+    const float* Pk = cube + (int64_t)g.k * M;
+    const float* Pk1 = (K > 1) ? Pk + M : nullptr;
+    const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
+    // the tile's pixels (from the first row and column that its blocks reach)
+    // and their box of bordered rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
+    const int at = block_start<VEC>(a0, n), bt = block_start<VEC>(b0, n);
+    const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
+    int rmin, rmax, cmin, cmax;
+    {
+      int r0, c0;
+      tap_origin(g, c, at, bt, r0, c0);
+      rmin = rmax = r0;
+      cmin = cmax = c0;
 #pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          tap_origin(g, c, (k & 1) ? ae - 1 : a0, (k & 2) ? be - 1 : b0, r0, c0);
-          rmin = min(rmin, r0);
-          rmax = max(rmax, r0);
-          cmin = min(cmin, c0);
-          cmax = max(cmax, c0);
-        }
-      }
-      const int Rlo = max(rmin + 1, 0), Clo = max(cmin + 1, 0);
-      const int bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
-      const int bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
-      const int bs = bw | 1;
-      wave_lds_sync();  // the previous tile's reads are done
-      stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
-      wave_lds_sync();  // the box is staged
-      const int base = Rlo * bs + Clo;
-      const int bb = b0 + 4 * lk;
-      if (ab >= ae || bb >= be) continue;  // VEC: the whole block is outside the tile
-      double ctux[4], mstux[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma clang fp contract(off)
-        const double ux = (double)(bb + q) - c;
-        ctux[q] = g.ct * ux;
-        mstux[q] = (-g.st) * ux;
-      }
-      float x[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int a = ab + r;
-        double stuy, ctuy;
-        {
-#pragma clang fp contract(off)
-          const double uy = (double)a - c;
-          stuy = g.st * uy;
-          ctuy = g.ct * uy;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          x[r][q] = 0.0f;
-          if (VEC || (a < ae && bb + q < be)) {
-            x[r][q] = box_value(Q, ctux[q], mstux[q], stuy, ctuy, c, n, bs, base);
-            if constexpr (MODE == kScaled) x[r][q] *= sf;
-            tsum += (double)x[r][q];
-          }
-          if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
-        }
-        if constexpr (VEC && MODE != kSumsOnly) {  // the row's runs of C0 and C2
-          __builtin_nontemporal_store((f32x4){x[r][0], x[r][1], x[r][2], x[r][3]},
-                                      reinterpret_cast<f32x4*>(C0 + (int64_t)a * n + bb));
-          if (!centre)
-            __builtin_nontemporal_store((f32x4){x[r][3], x[r][2], x[r][1], x[r][0]},
-                                        reinterpret_cast<f32x4*>(C2 + (int64_t)(n - 1 - a) * n + (n - 4 - bb)));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (MODE == kSumsOnly) {
-      } else if constexpr (VEC) {
-        if (!centre) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int b = bb + q;
-            __builtin_nontemporal_store((f32x4){x[3][q], x[2][q], x[1][q], x[0][q]},
-                                        reinterpret_cast<f32x4*>(C1 + (int64_t)b * n + (n - 4 - ab)));
-            __builtin_nontemporal_store((f32x4){x[0][q], x[1][q], x[2][q], x[3][q]},
-                                        reinterpret_cast<f32x4*>(C3 + (int64_t)(n - 1 - b) * n + ab));
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int a = ab + r, b = bb + q;
-            if (a >= ae || b >= be) continue;
-            __builtin_nontemporal_store(x[r][q], C0 + (int64_t)a * n + b);
-            if (centre) continue;
-            __builtin_nontemporal_store(x[r][q], C1 + (int64_t)b * n + (n - 1 - a));
-            __builtin_nontemporal_store(x[r][q], C2 + (int64_t)(n - 1 - a) * n + (n - 1 - b));
-            __builtin_nontemporal_store(x[r][q], C3 + (int64_t)(n - 1 - b) * n + a);
-          }
+      for (int k = 1; k < 4; ++k) {
+        tap_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, r0, c0);
+        rmin = min(rmin, r0);
+        rmax = max(rmax, r0);
+        cmin = min(cmin, c0);
+        cmax = max(cmax, c0);
       }
     }
+    const int Rlo = max(rmin + 1, 0), Clo = max(cmin + 1, 0);
+    const int bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
+    const int bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
+    const int bs = bw | 1;
+    wave_lds_sync();  // the previous tile's reads are done
+    stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
+    wave_lds_sync();  // the box is staged
+    const int base = Rlo * bs + Clo;
+    if (ab0 < ae && bb0 < be)
+      orbit_block<VEC, MODE>(
+          [&](double ctux, double mstux, double stuy, double ctuy) {
+            return box_value(Q, ctux, mstux, stuy, ctuy, c, n, bs, base);
+          },
+          g, c, n, o.N, M, ab0, bb0, A, tsum);
+    }
+    tsum = wave_sum_f64(tsum);
+    if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
   }
-  tsum = wave_sum_f64(tsum);
-  if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
 }
 
 // 16-bit orbit build (N a multiple of 8: no centre, whole blocks of 8 bases).
@@ -1382,7 +1404,8 @@ constexpr int kCbRegion = kCbSpan * (kCbSpan + 1);  // floats per wave (odd row 
 __device__ __forceinline__ int clamp_origin(int v, int Np) { return v < -3 ? -3 : (v > Np + 1 ? Np + 1 : v); }
 
 // clamped tap origin (padded row and column) of image pixel (a, b)
-__device__ __forceinline__ void cubic_origin(const ColGeom& g, double c, int a, int b, int Np,
+template <typename G>
+__device__ __forceinline__ void cubic_origin(const G& g, double c, int a, int b, int Np,
                                              int& r0, int& c0) {
 #pragma clang fp contract(off)
   const double ux = (double)b - c, uy = (double)a - c;
@@ -1398,166 +1421,91 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
                                                                  int Np,
                                                                  const ColGeom* __restrict__ geo,
                                                                  const int32_t* __restrict__ reps,
-                                                                 const int4* __restrict__ items,
-                                                                 const int32_t* __restrict__ nitems,
-                                                                 int nb, int n, int N, int64_t M,
-                                                                 int rpr, int64_t nreps,
+                                                                 OrbitGrid o, int n, int64_t M, int nt, int run, uint32_t total,
                                                                  float* __restrict__ A,
                                                                  double* __restrict__ part,
     const float* __restrict__ colscale) {
   extern __shared__ float QS[];  // 16 regions of kCbRegion floats
-  if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
-  const int4 it = items[blockIdx.x];
-  const int bkt = it.x, first = it.y, len = it.z, w0 = it.w;
-  const bool zero_bucket = bkt == nb - 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
-  const int sp = w0 + wave;
-  if (sp < first || sp >= first + len) return;  // uniform per wave; no workgroup barrier
-  const int64_t j0 = reps[sp];
-  const bool centre = orbit_is_centre(j0, N);
-  float* C0 = A + j0 * M;
-  float* C1 = A + orbit_member(j0, N, 1) * M;
-  float* C2 = A + orbit_member(j0, N, 2) * M;
-  float* C3 = A + orbit_member(j0, N, 3) * M;
-  if (zero_bucket) {  // identically zero orbit: rows [ra, rb) of every member
-    for (int x = lane; MODE != kSumsOnly && x < (rb - ra) * n; x += 64) {
-      const int64_t p = (int64_t)ra * n + x;
-      __builtin_nontemporal_store(0.0f, C0 + p);
-      if (!centre) {
-        __builtin_nontemporal_store(0.0f, C1 + p);
-        __builtin_nontemporal_store(0.0f, C2 + p);
-        __builtin_nontemporal_store(0.0f, C3 + p);
-      }
-    }
-    if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = 0.0;
-    return;
-  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* Q = QS + wave * kCbRegion;
-  const float2* src = pairs + (int64_t)bkt * Np * Np;
-  const ColGeom g = geo[j0];
-  const float sf = (MODE == kScaled) ? colscale[j0] : 1.0f;  // flux-preserving scale
   const double c = (double)(n - 1) * 0.5;
   const double pad = (double)kSplinePad;
-  const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
   const int li = lane >> 3, lk = lane & 7;
-  double tsum = 0.0;
-  for (int a0 = ra; a0 < rb; a0 += 32) {
-    const int ae = (a0 + 32 < rb) ? a0 + 32 : rb;
-    const int ab = a0 + 4 * li;
-    for (int b0 = 0; b0 < n; b0 += 32) {
-      const int be = (b0 + 32 < n) ? b0 + 32 : n;
-      // the tile's box of padded rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-      int rmin, rmax, cmin, cmax;
-      {
-        int r0, c0;
-        cubic_origin(g, c, a0, b0, Np, r0, c0);
-        rmin = rmax = r0;
-        cmin = cmax = c0;
+  const int ntiles = nt * nt;
+  const int nruns = (ntiles + run - 1) / run;
+  const uint32_t rounds = (total + 16 * gridDim.x - 1) / (16 * gridDim.x);
+  for (uint32_t i = 0; i < rounds; ++i) {  // no workgroup barrier
+    const uint32_t t = box_run(i, wave, rounds);
+    if (t >= total) continue;
+    const uint32_t sp = t / (uint32_t)nruns;
+    const int r = (int)(t - sp * (uint32_t)nruns);
+    const OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, sp);
+    double tsum = 0.0;
+    for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
+    const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
+    const int ab0 = a0 + 4 * li, bb0 = b0 + 4 * lk;
+    if (g.k < 0) {  // identically zero orbit
+      if (ab0 < n && bb0 < n)
+        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M,
+                               ab0, bb0, A, tsum);
+      continue;
+    }
+    const float2* src = pairs + (int64_t)g.k * Np * Np;
+    const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
+    // the tile's pixels (from the first row and column that its blocks reach)
+    // and their box of padded rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
+    const int at = block_start<VEC>(a0, n), bt = block_start<VEC>(b0, n);
+    const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
+    int rmin, rmax, cmin, cmax;
+    {
+      int r0, c0;
+      cubic_origin(g, c, at, bt, Np, r0, c0);
+      rmin = rmax = r0;
+      cmin = cmax = c0;
 #pragma unroll
-        for (int k = 1; k < 4; ++k) {
-          cubic_origin(g, c, (k & 1) ? ae - 1 : a0, (k & 2) ? be - 1 : b0, Np, r0, c0);
-          rmin = min(rmin, r0);
-          rmax = max(rmax, r0);
-          cmin = min(cmin, c0);
-          cmax = max(cmax, c0);
-        }
+      for (int k = 1; k < 4; ++k) {
+        cubic_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, Np, r0, c0);
+        rmin = min(rmin, r0);
+        rmax = max(rmax, r0);
+        cmin = min(cmin, c0);
+        cmax = max(cmax, c0);
       }
-      const int Rlo = rmin - 1, Clo = cmin - 1;
-      const int bh = min(rmax - rmin + 4, kCbSpan), bw = min(cmax - cmin + 4, kCbSpan);
-      const int bs = bw | 1;
-      wave_lds_sync();  // the previous tile's reads are done
-      stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
-      wave_lds_sync();  // the box is staged
-      const int bb = b0 + 4 * lk;
-      if (ab >= ae || bb >= be) continue;  // VEC: the whole block is outside the tile
-      double ctux[4], mstux[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
+    }
+    const int Rlo = rmin - 1, Clo = cmin - 1;
+    const int bh = min(rmax - rmin + 4, kCbSpan), bw = min(cmax - cmin + 4, kCbSpan);
+    const int bs = bw | 1;
+    wave_lds_sync();  // the previous tile's reads are done
+    stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
+    wave_lds_sync();  // the box is staged
+    if (ab0 < ae && bb0 < be)
+      orbit_block<VEC, MODE>(
+          [&](double ctux, double mstux, double stuy, double ctuy) {
 #pragma clang fp contract(off)
-        const double ux = (double)(bb + q) - c;
-        ctux[q] = g.ct * ux;
-        mstux[q] = (-g.st) * ux;
-      }
-      float x[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int a = ab + r;
-        double stuy, ctuy;
-        {
-#pragma clang fp contract(off)
-          const double uy = (double)a - c;
-          stuy = g.st * uy;
-          ctuy = g.ct * uy;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          x[r][q] = 0.0f;
-          if (VEC || (a < ae && bb + q < be)) {
-#pragma clang fp contract(off)
-            const double rowf = c + (mstux[q] + ctuy) + pad;
-            const double colf = c + (ctux[q] + stuy) + pad;
+            const double rowf = c + (mstux + ctuy) + pad;
+            const double colf = c + (ctux + stuy) + pad;
             const double r0f = floor(rowf), c0f = floor(colf);
             const int r0 = clamp_origin((int)r0f, Np), c0 = clamp_origin((int)c0f, Np);
             float wy[4], wx[4];
             cubic_weights(rowf - r0f, wy);
             cubic_weights(colf - c0f, wx);
-            const float* t = Q + (r0 - 1 - Rlo) * bs + (c0 - 1 - Clo);
+            const float* tp = Q + (r0 - 1 - Rlo) * bs + (c0 - 1 - Clo);
             float V = 0.0f;
 #pragma unroll
             for (int dr = 0; dr < 4; ++dr) {
-              const float* tr = t + dr * bs;
+              const float* tr = tp + dr * bs;
               float v = wx[0] * tr[0];
               v = fmaf(wx[1], tr[1], v);
               v = fmaf(wx[2], tr[2], v);
               v = fmaf(wx[3], tr[3], v);
               V = fmaf(wy[dr], v, V);
             }
-            if constexpr (MODE == kScaled) V *= sf;
-            x[r][q] = V;
-            tsum += (double)V;
-          }
-        }
-        if constexpr (VEC && MODE != kSumsOnly) {  // the row's runs of C0 and C2
-          __builtin_nontemporal_store((f32x4){x[r][0], x[r][1], x[r][2], x[r][3]},
-                                      reinterpret_cast<f32x4*>(C0 + (int64_t)a * n + bb));
-          if (!centre)
-            __builtin_nontemporal_store((f32x4){x[r][3], x[r][2], x[r][1], x[r][0]},
-                                        reinterpret_cast<f32x4*>(C2 + (int64_t)(n - 1 - a) * n + (n - 4 - bb)));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (MODE == kSumsOnly) {
-      } else if constexpr (VEC) {
-        if (!centre) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int b = bb + q;
-            __builtin_nontemporal_store((f32x4){x[3][q], x[2][q], x[1][q], x[0][q]},
-                                        reinterpret_cast<f32x4*>(C1 + (int64_t)b * n + (n - 4 - ab)));
-            __builtin_nontemporal_store((f32x4){x[0][q], x[1][q], x[2][q], x[3][q]},
-                                        reinterpret_cast<f32x4*>(C3 + (int64_t)(n - 1 - b) * n + ab));
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int a = ab + r, b = bb + q;
-            if (a >= ae || b >= be) continue;
-            __builtin_nontemporal_store(x[r][q], C0 + (int64_t)a * n + b);
-            if (centre) continue;
-            __builtin_nontemporal_store(x[r][q], C1 + (int64_t)b * n + (n - 1 - a));
-            __builtin_nontemporal_store(x[r][q], C2 + (int64_t)(n - 1 - a) * n + (n - 1 - b));
-            __builtin_nontemporal_store(x[r][q], C3 + (int64_t)(n - 1 - b) * n + a);
-          }
-      }
+            return V;
+          },
+          g, c, n, o.N, M, ab0, bb0, A, tsum);
     }
+    tsum = wave_sum_f64(tsum);
+    if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
   }
-  tsum = wave_sum_f64(tsum);
-  if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
 }
 
 // 16-bit orbit build for pairs larger than the LDS (n > 141, N a multiple of
@@ -1981,7 +1929,7 @@ static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct OrbitPlan {
   OrbitGrid o;
-  int nb, rpr, nranges;
+  int nb, rpr, nranges, nt;  // 16-bit: row ranges; float32: tiles per side
   int64_t nblk, items_max;
   int32_t* cnt;
   int4* items;
@@ -1996,6 +1944,7 @@ static OrbitPlan orbit_plan(int K, int N, int n, void* scratch) {
   pl.nb = nbuckets(K);
   pl.rpr = orbit_rows_per_range(n);
   pl.nranges = (n + pl.rpr - 1) / pl.rpr;
+  pl.nt = (n + 31) / 32;
   pl.nblk = (pl.o.nreps + kSortBlock - 1) / kSortBlock;
   pl.items_max = (pl.o.nreps + 15) / 16 + 2 * (int64_t)pl.nb + 1;
   char* p = reinterpret_cast<char*>(scratch);
@@ -2013,7 +1962,7 @@ static OrbitPlan orbit_plan(int K, int N, int n, void* scratch) {
 size_t build_orbit_scratch_bytes(int K, int N, int n) {
   const OrbitPlan pl = orbit_plan(K, N, n, nullptr);
   return al256((size_t)pl.nblk * pl.nb * 4) + al256((size_t)pl.items_max * 16 + 16) +
-         al256((size_t)pl.o.nreps * 4) + al256((size_t)pl.nranges * pl.o.nreps * 8);
+         al256((size_t)pl.o.nreps * 4) + al256((size_t)pl.nt * pl.nt * pl.o.nreps * 8);
 }
 
 static bool orbit_sort_fits(int K, int N) {
@@ -2033,10 +1982,32 @@ static hipError_t orbit_sort(const ColGeom* geo, const OrbitPlan& pl, int32_t* p
   return hipGetLastError();
 }
 
-static hipError_t orbit_finish(const OrbitPlan& pl, double* tau, hipStream_t s) {
-  orbit_tau_kernel<<<(unsigned)((pl.o.nreps + 255) / 256), 256, 0, s>>>(pl.reps, pl.part, pl.nranges,
-                                                                       pl.o.nreps, pl.o.N, tau);
+static hipError_t orbit_finish(const OrbitPlan& pl, const int32_t* reps, int nparts, double* tau,
+                               hipStream_t s) {
+  orbit_tau_kernel<<<(unsigned)((pl.o.nreps + 255) / 256), 256, 0, s>>>(reps, pl.o, pl.part, nparts, tau);
   return hipGetLastError();
+}
+
+// runs are counted in 32 bits: 2^31 tiles are a library of 2^45 bytes
+constexpr int64_t kMaxBoxRuns = (int64_t)1 << 31;
+
+// Tiles that a wave takes at a time (a run): a row of tiles when that leaves
+// every one of the 4096 resident waves 8 runs or more (the base's geometry is
+// loaded once a run: 256^2 3% faster), else single tiles, which share the work
+// out evenly (200^2 PSFs, 64^2 scene: 8% faster).
+static int box_run_tiles(const OrbitPlan& pl) {
+  return pl.o.nreps * pl.nt >= 8 * 4096 ? pl.nt : 1;
+}
+
+// Workgroups of the float32 box kernels: 16 independent waves each, one
+// workgroup per CU at a time (its box regions fill the LDS), every workgroup
+// walking a contiguous share of the runs.  4096 shares even out the CUs
+// (200^2 PSFs, 64^2 scene: 0.35 ms against 0.42 ms with 1024; 256^2: 3.76
+// against 3.96 ms), and the workgroups running at one time stay close in
+// bracket order.
+static unsigned box_grid(int64_t total) {
+  const int64_t wgs = (total + 15) / 16;
+  return (unsigned)(wgs < 4096 ? wgs : 4096);
 }
 
 static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* geo, int n, int N,
@@ -2045,16 +2016,17 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
   hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, s);
   if (e != hipSuccess) return e;
-  const bool vec = (n % 4) == 0;
-  const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
+  const bool vec = (n % 32) == 0;
   if (!pair_fits_lds(n)) {  // a staged box per 32 x 32 tile
+    const int run = box_run_tiles(pl), nruns = (pl.nt * pl.nt + run - 1) / run;
+    const int64_t total = pl.o.nreps * nruns;
+    if (total >= kMaxBoxRuns) return hipErrorInvalidValue;
     const size_t lds = (size_t)16 * kFpRegion * sizeof(float);
     auto launch = [&](auto kern) -> hipError_t {
       const void* fn = reinterpret_cast<const void*>(kern);
       hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (err != hipSuccess) return err;
-      kern<<<grid, 1024, lds, s>>>(cube, K, geo, pl.reps, pl.items, pl.nitems, pl.nb, n, N, M, pl.rpr,
-                                   pl.o.nreps, A32, pl.part, colscale);
+      kern<<<box_grid(total), 1024, lds, s>>>(cube, K, geo, pl.reps, pl.o, n, M, pl.nt, run, (uint32_t)total, A32, pl.part, colscale);
       return hipGetLastError();
     };
     switch (mode) {
@@ -2068,8 +2040,9 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
         e = vec ? launch(build_orbit_box_kernel<true, kPlain>) : launch(build_orbit_box_kernel<false, kPlain>);
     }
     if (e != hipSuccess) return e;
-    return orbit_finish(pl, tau, s);
+    return orbit_finish(pl, pl.reps, nruns, tau, s);
   }
+  const dim3 grid((unsigned)pl.items_max, (unsigned)(16 / orbit_sub(pl.nt)));
   const int ls = lds_stride(n);
   const size_t lds = (size_t)(n + 2) * ls * sizeof(float2);
   auto launch = [&](auto kern) -> hipError_t {
@@ -2077,7 +2050,7 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
     hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (err != hipSuccess) return err;
     kern<<<grid, 1024, lds, s>>>(cube, K, geo, pl.reps, pl.items, pl.nitems, pl.nb, n, ls, N, M,
-                                 pl.rpr, pl.o.nreps, A32, pl.part, colscale);
+                                 pl.nt, pl.o.nreps, A32, pl.part, colscale);
     return hipGetLastError();
   };
   switch (mode) {
@@ -2091,7 +2064,7 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
       e = vec ? launch(build_orbit_kernel<true, kPlain>) : launch(build_orbit_kernel<false, kPlain>);
   }
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, tau, s);
+  return orbit_finish(pl, pl.reps, pl.nt * pl.nt, tau, s);
 }
 
 // The two float32 passes of a flux-preserving orbit build (see the modes above).
@@ -2121,18 +2094,19 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* ge
   hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, s);
   if (e != hipSuccess) return e;
   const int Np = n + 2 * kSplinePad;
-  const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
+  const bool vec = (n % 32) == 0;
+  const int run = box_run_tiles(pl), nruns = (pl.nt * pl.nt + run - 1) / run;
+  const int64_t total = pl.o.nreps * nruns;
+  if (total >= kMaxBoxRuns) return hipErrorInvalidValue;
   const size_t lds = (size_t)16 * kCbRegion * sizeof(float);
   const float2* P = reinterpret_cast<const float2*>(pairs);
   auto launch = [&](auto kern) -> hipError_t {
     const void* fn = reinterpret_cast<const void*>(kern);
     hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (err != hipSuccess) return err;
-    kern<<<grid, 1024, lds, s>>>(P, Np, geo, pl.reps, pl.items, pl.nitems, pl.nb, n, N, M, pl.rpr,
-                                 pl.o.nreps, A32, pl.part, colscale);
+    kern<<<box_grid(total), 1024, lds, s>>>(P, Np, geo, pl.reps, pl.o, n, M, pl.nt, run, (uint32_t)total, A32, pl.part, colscale);
     return hipGetLastError();
   };
-  const bool vec = (n % 4) == 0;
   switch (mode) {
     case kSumsOnly:
       e = vec ? launch(build_cubic_orbit_kernel<true, kSumsOnly>) : launch(build_cubic_orbit_kernel<false, kSumsOnly>);
@@ -2144,7 +2118,7 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* ge
       e = vec ? launch(build_cubic_orbit_kernel<true, kPlain>) : launch(build_cubic_orbit_kernel<false, kPlain>);
   }
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, tau, s);
+  return orbit_finish(pl, pl.reps, nruns, tau, s);
 }
 
 // 16-bit orbit build: the pair (ending 16-byte aligned), then two 2 x 8 x 33 unit tiles
@@ -2201,7 +2175,7 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
     else
       e = bf ? launch(build_orbit16_box_kernel<true, false, false>) : launch(build_orbit16_box_kernel<false, false, false>);
     if (e != hipSuccess) return e;
-    return orbit_finish(pl, tau, s);
+    return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
   }
   const int ls = lds_stride(n);
   const size_t lds = orbit16_lds_bytes(n);
@@ -2219,7 +2193,7 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
   else
     e = bf ? launch(build_orbit16_kernel<true, false>) : launch(build_orbit16_kernel<false, false>);
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, tau, s);
+  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
 }
 
 bool build_cubic_orbit16_supported(int n, int K, int N) {
@@ -2252,7 +2226,7 @@ hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, co
   else
     e = bf ? launch(build_orbit16_box_kernel<true, true, false>) : launch(build_orbit16_box_kernel<false, true, false>);
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, tau, s);
+  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
 }
 
 

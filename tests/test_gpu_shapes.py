@@ -1,0 +1,70 @@
+"""Image and scene sizes at the edges of the kernels' tiles, through the C ABI,
+against the FP64 oracle.
+
+Tolerances are those of the dedicated tests: float32 entries 1e-6 relative
+(bilinear, non-negative terms; 2e-6 with the flux rescale, one more rounding of
+the scale and of the product) or of the column bound (cubic).
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+def _inputs(n, N, K, seed):
+    rng = np.random.default_rng([n, N, K, seed])
+    radii = np.linspace(0.0, 0.3 * N, K)
+    return (rng.random((K, n, n)) ** 3).astype(np.float32), radii, rng
+
+
+def _fill(lib, torch):
+    """Poison a library's buffer and build it again: an entry the build does
+    not write stays NaN."""
+    from paper_2106_09122_amd import psflib
+    lib.buf.fill_(0xFF)
+    h = psflib.build(lib.desc, lib.cube.data_ptr(), lib.radii, lib.buf.data_ptr(), lib.nbytes,
+                     torch.cuda.current_stream().cuda_stream)
+    psflib.destroy(lib.h)
+    lib.h = h
+
+
+# ------------------------------------------------ float32 orbit builds ----
+# one block, one tile and several; every remainder of 4 and sides around
+# multiples of 32 (whole lines) and 4; beyond 141 the pair no longer fits the LDS
+SIDES = [1, 2, 3, 4, 5, 6, 31, 32, 33, 34, 63, 64, 65, 67, 95, 97, 100, 127, 141, 142, 143, 161, 164]
+
+
+@pytest.mark.parametrize("n", SIDES)
+@pytest.mark.parametrize("rotate,flux", [("bilinear", "none"), ("bilinear", "preserve"), ("cubic", "none"),
+                                         ("cubic", "preserve")])
+def test_orbit_build_sides(torch, n, rotate, flux):
+    from paper_2106_09122_amd import psflib
+    for N in (5, 6):
+        cube, radii, _ = _inputs(n, N, 4, 1)
+        mode = dict(rotate=rotate, flux=flux, oob="zero")
+        A = O.build_library(cube, radii, N, 1.0, **mode)
+        lib = psflib.Library(torch.from_numpy(cube).cuda(), radii, N, 1.0, **mode)
+        _fill(lib, torch)
+        got = lib.get_columns(np.arange(N * N)).cpu().numpy().T.astype(np.float64)
+        if rotate == "bilinear":
+            tol = (2e-6 if flux == "preserve" else 1e-6) * A
+        else:
+            b = O.column_max_bound(cube, radii, N, 1.0, oob="zero", rotate="cubic")
+            if flux == "preserve":
+                A0 = O.build_library(cube, radii, N, 1.0, rotate=rotate, oob="zero")
+                t0, t1 = A0.sum(axis=0), A.sum(axis=0)
+                b = 2 * b * np.abs(np.where(t0 != 0, t1 / np.where(t0 != 0, t0, 1.0), 1.0))
+            tol = 1e-6 * b[None, :]
+        assert np.all(np.abs(got - A) <= tol + 1e-300), (n, N)
+        tau = lib.column_sums().cpu().numpy()
+        assert np.all(np.abs(tau - A.sum(axis=0)) <= np.sum(np.broadcast_to(tol, A.shape), axis=0) + 1e-300)
+        lib.close()
