@@ -14,8 +14,10 @@
 #include <math.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "psflib_internal.h"
 
@@ -341,137 +343,255 @@ hipError_t launch_matvec(int storage, const void* lib, const Cols16& cx, const f
 }
 
 // ------------------------------------------------------------ adjoint -----
-// G_j = sum_i A_ij g_i.  A workgroup owns one row block (up to kAdjF32Rows
-// rows, whose g values each thread keeps in registers) and a run of columns;
-// a column is one wave-wide dot product per wave, then a 4-wave sum in LDS.
-__device__ __forceinline__ float wave_sum(float v) {
+// G_j = sum_i A_ij g_i, bound by the stream of the library.  A workgroup stages
+// g of its row block (up to kAdjRows rows) in LDS; its waves then stream whole
+// columns (16-bit: 8-slot groups), C of them at a time in rounds of U row steps
+// (C U = kAdjLoads loads of 16 bytes per lane), the loads of the next round
+// issued before a round is used -- also over the end of a column, whose sum is
+// reduced over the wave while the next column is on its way, and before g is
+// staged.  C grows for small images, which have few row steps.  SPLIT: the
+// waves of a workgroup take the row steps of the same columns in turn and add
+// their sums through LDS, where there are too few columns for all the waves.
+// Images whose columns do not start at 16-byte boundaries take the same loads,
+// unaligned.
+constexpr int kAdjLoads = 8;
+
+// Sums of V values over the wave, each value in one set of 64 / V lanes:
+// value lane / (64 / V) is returned.  Every exchange halves the values.
+template <int V>
+__device__ __forceinline__ float wave_sums(float (&v)[V], int lane) {
+  int off = 32;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  for (int n = V; n > 1; n >>= 1, off >>= 1) {
+    const bool up = (lane & off) != 0;
+#pragma unroll
+    for (int k = 0; k < n / 2; ++k) {
+      const float keep = up ? v[k + n / 2] : v[k], send = up ? v[k] : v[k + n / 2];
+      v[k] = keep + __shfl_xor(send, off, 64);
+    }
+  }
+  for (; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+  return v[0];
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(kAdjThreads) void adjoint_f32_kernel(const float* __restrict__ A,
-                                                                  const float* __restrict__ g,
-                                                                  float* __restrict__ out,
-                                                                  int64_t M, int64_t ncols,
-                                                                  int64_t out_stride) {
-  constexpr int U = kAdjF32Rows / (4 * kAdjThreads);  // float4 per thread per column
-  __shared__ float red[2][kAdjThreads / 64];
-  const int tid = threadIdx.x;
-  const int64_t rb = blockIdx.y;
-  const int64_t row0 = rb * kAdjF32Rows;
-  f32x4 gr[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t i = row0 + 4 * ((int64_t)tid + (int64_t)kAdjThreads * u);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) gr[u][e] = (i + e < M) ? g[i + e] : 0.0f;
+// The rounds of one wave, in order: column groups first, first + stride, ...
+// below end, each in `rounds` rounds.  load(buffer, group, round) issues a
+// round's loads, use(buffer, round) multiplies them, finish(group) follows a
+// group's last round.  Two buffers in turn.
+template <typename Buf, typename Load, typename Use, typename Stage, typename Finish>
+__device__ __forceinline__ void adjoint_rounds(int64_t first, int64_t end, int64_t stride, int rounds,
+                                               Load load, Stage stage, Use use, Finish finish) {
+  Buf a, b;
+  int64_t grp = first, ngrp = first;
+  int r = 0, nr = 0;
+  if (first < end) load(a, first, 0);
+  stage();
+  auto step = [&](Buf& cur, Buf& next) {
+    nr = r + 1;
+    ngrp = grp;
+    if (nr == rounds) {
+      nr = 0;
+      ngrp += stride;
+    }
+    if (ngrp < end) load(next, ngrp, nr);
+    __builtin_amdgcn_sched_barrier(0);
+    use(cur, r);
+    if (nr == 0) finish(grp);
+    grp = ngrp;
+    r = nr;
+  };
+  while (grp < end) {
+    step(a, b);
+    if (grp >= end) break;
+    step(b, a);
   }
-  const int64_t jb = (int64_t)blockIdx.x * kAdjColsPerBlock;
-  for (int t = 0; t < kAdjColsPerBlock; ++t) {
-    const int64_t j = jb + t;
-    if (j >= ncols) break;  // uniform across the workgroup
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const float* col = A + j * M;
+}
+
+// Row steps of 256 rows (4 per lane).  The lane whose 4 rows would pass the
+// image's end reads its last 4 instead, with g staged to match: zero for the
+// rows that another lane has, and for whole steps past the end.
+template <bool VEC, int C, bool SPLIT>
+__global__ __launch_bounds__(kAdjThreads, 4) void adjoint_f32_kernel(const float* __restrict__ A,
+                                                                     const float* __restrict__ g,
+                                                                     float* __restrict__ out,
+                                                                     int64_t M, int64_t ncols,
+                                                                     int64_t block_rows, int rounds,
+                                                                     int64_t per_wg,
+                                                                     int64_t out_stride) {
+  constexpr int U = kAdjLoads / C;
+  constexpr int SUB = U >= 4 ? 4 : U;  // sums per column and component: short rounding chains
+  constexpr int NW = kAdjThreads / 64;
+  constexpr int W = SPLIT ? NW : 1;  // waves on one group of columns
+  extern __shared__ f32x4 gs[];  // [rounds * U * W steps][64]
+  __shared__ float red[2][NW][C];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = (int64_t)blockIdx.y * block_rows;
+  const int64_t groups = (ncols + C - 1) / C;
+  const int sub = SPLIT ? wave : 0;  // this wave's steps: sub + W k
+  // a lane's last first row, relative to row0 (in a last block of fewer than 4
+  // rows it lies in the block before: offsets count from `pre` rows before row0)
+  const int last = (int)(M - row0 < (1 << 24) ? M - row0 : (1 << 24)) - 4;
+  const int pre = row0 > 0 ? 4 : 0;
+  struct Buf {
+    f32x4 v[U][C];
+  };
+  auto load = [&](Buf& b, int64_t grp, int r) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t i = row0 + 4 * ((int64_t)tid + (int64_t)kAdjThreads * u);
-      f32x4 v;
-      if (VEC && i + 4 <= M) {
-        v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(col + i));
-      } else {
+      int i = 256 * (sub + W * (r * U + u)) + 4 * lane;
+      i = i < last ? i : last;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (i + e < M) ? col[i + e] : 0.0f;
+      for (int c = 0; c < C; ++c) {
+        const int64_t j = grp * C + c;
+        const float* col = A + (j < ncols ? j : ncols - 1) * M + (row0 - pre);
+        const char* p = reinterpret_cast<const char*>(col) + (uint32_t)((i + pre) * 4);
+        if constexpr (VEC)
+          b.v[u][c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+        else if (M >= 4)
+          b.v[u][c] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
+        else  // one pixel (n = 1)
+          b.v[u][c] = (f32x4){col[0], 0.0f, 0.0f, 0.0f};
       }
-      acc += v * gr[u];
     }
-    float s = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    s = wave_sum(s);
-    if ((tid & 63) == 0) red[t & 1][tid >> 6] = s;
-    __syncthreads();
-    if (tid == 0) {
-      float tot = 0.0f;
+  };
+  auto stage = [&]() {
+    for (int t = tid; t < rounds * U * W * 64; t += kAdjThreads) {
+      const int64_t i = row0 + 4 * (int64_t)t, top = M > 4 ? M - 4 : 0, i0 = i < top ? i : top;
+      f32x4 v;
 #pragma unroll
-      for (int w = 0; w < kAdjThreads / 64; ++w) tot += red[t & 1][w];
-      out[rb * out_stride + j] = tot;
+      for (int e = 0; e < 4; ++e)
+        v[e] = (4 * (int64_t)t < block_rows && i0 + e >= i && i0 + e < M) ? g[i0 + e] : 0.0f;
+      gs[t] = v;
     }
-  }
+    __syncthreads();
+  };
+  f32x4 acc[C][SUB] = {};
+  auto use = [&](const Buf& b, int r) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const f32x4 gv = gs[(sub + W * (r * U + u)) * 64 + lane];
+#pragma unroll
+      for (int c = 0; c < C; ++c) acc[c][u % SUB] += b.v[u][c] * gv;
+    }
+  };
+  int buf = 0;
+  auto finish = [&](int64_t grp) {
+    float sum[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      f32x4 a = acc[c][0];
+#pragma unroll
+      for (int u = 1; u < SUB; ++u) a += acc[c][u];
+      sum[c] = (a[0] + a[1]) + (a[2] + a[3]);
+#pragma unroll
+      for (int u = 0; u < SUB; ++u) acc[c][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    float tot = wave_sums<C>(sum, lane);
+    if constexpr (SPLIT) {
+      if (lane % (64 / C) == 0) red[buf][wave][lane / (64 / C)] = tot;
+      __syncthreads();  // the other buffer's readers are behind the previous one
+      if (tid < C && grp * C + tid < ncols) {
+        tot = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tot += red[buf][w][tid];
+        out[(int64_t)blockIdx.y * out_stride + grp * C + tid] = tot;
+      }
+      buf ^= 1;
+    } else {
+      const int64_t j = grp * C + lane / (64 / C);
+      if (lane % (64 / C) == 0 && j < ncols) out[(int64_t)blockIdx.y * out_stride + j] = tot;
+    }
+  };
+  const int64_t g0 = (int64_t)blockIdx.x * per_wg, g1 = g0 + per_wg < groups ? g0 + per_wg : groups;
+  adjoint_rounds<Buf>(g0 + (SPLIT ? 0 : wave), g1, SPLIT ? 1 : NW, rounds, load, stage, use, finish);
 }
 
-// 16-bit: the sums of group grp belong to slots 8 grp + q, i.e. columns
+// 16-bit: row steps of 64 rows (one per lane, 8 slots in 16 bytes), one group
+// at a time in rounds of U steps.  Rows past the image read its last row, with
+// a zero g.  The sums of group grp belong to slots 8 grp + q, i.e. columns
 // perm[8 grp + q]; they are written at the column's index.
-template <bool BF16>
-__global__ __launch_bounds__(kAdjThreads) void adjoint_h16_kernel(const u32x4* __restrict__ Mp,
-                                                                  const int32_t* __restrict__ perm,
-                                                                  const int32_t* __restrict__ eslot,
-                                                                  const float* __restrict__ g,
-                                                                  float* __restrict__ out,
-                                                                  int64_t M, int64_t ngroups,
-                                                                  int64_t out_stride,
-                                                                  int apply_exp) {
-  constexpr int U = kAdj16Rows / kAdjThreads;  // rows per thread
-  __shared__ float red[2][kAdjThreads / 64][8];
-  const int tid = threadIdx.x;
-  const int64_t rb = blockIdx.y;
-  const int64_t row0 = rb * kAdj16Rows;
-  float gr[U];
+template <bool BF16, int U, bool SPLIT>
+__global__ __launch_bounds__(kAdjThreads, 4) void adjoint_h16_kernel(const u32x4* __restrict__ Mp,
+                                                                     const int32_t* __restrict__ perm,
+                                                                     const int32_t* __restrict__ eslot,
+                                                                     const float* __restrict__ g,
+                                                                     float* __restrict__ out,
+                                                                     int64_t M, int64_t ngroups,
+                                                                     int64_t block_rows, int rounds,
+                                                                     int64_t per_wg,
+                                                                     int64_t out_stride,
+                                                                     int apply_exp) {
+  constexpr int SUB = 2;  // sums per slot: shorter rounding chains
+  constexpr int NW = kAdjThreads / 64;
+  constexpr int W = SPLIT ? NW : 1;  // waves on one group
+  extern __shared__ f32x4 gs4[];
+  __shared__ float red[2][NW][8];
+  float* gs = reinterpret_cast<float*>(gs4);  // [rounds * U * W steps][64]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = (int64_t)blockIdx.y * block_rows;
+  const int sub = SPLIT ? wave : 0;  // this wave's steps: sub + W k
+  const int last = (int)(M - row0 < (1 << 24) ? M - row0 : (1 << 24)) - 1;
+  struct Buf {
+    u32x4 v[U];
+  };
+  auto load = [&](Buf& b, int64_t grp, int r) {
+    const char* src = reinterpret_cast<const char*>(Mp + grp * M + row0);
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t i = row0 + tid + (int64_t)kAdjThreads * u;
-    gr[u] = (i < M) ? g[i] : 0.0f;
-  }
-  const int64_t gb = (int64_t)blockIdx.x * kAdj16GroupsPerBlock;
-  for (int t = 0; t < kAdj16GroupsPerBlock; ++t) {
-    const int64_t grp = gb + t;
-    if (grp >= ngroups) break;
-    float acc[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc[u] = 0.0f;
-    const u32x4* src = Mp + grp * M + row0 + tid;
-    if (row0 + kAdj16Rows <= M) {  // uniform: every row of the block is in the image
-      // blocks of 16 loads issued together, then consumed in order
-      for (int u0 = 0; u0 < U; u0 += 16) {
-        u32x4 p[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) p[u] = __builtin_nontemporal_load(src + (int64_t)kAdjThreads * (u0 + u));
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          float f[8];
-          unpack8<BF16>(p[u], f);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) acc[q] = fmaf(f[q], gr[u0 + u], acc[q]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int64_t i = row0 + tid + (int64_t)kAdjThreads * u;
-        if (i < M) {
-          const u32x4 p = __builtin_nontemporal_load(src + (int64_t)kAdjThreads * u);
-          float f[8];
-          unpack8<BF16>(p, f);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) acc[q] = fmaf(f[q], gr[u], acc[q]);
-        }
-      }
+    for (int u = 0; u < U; ++u) {
+      int i = 64 * (sub + W * (r * U + u)) + lane;
+      i = i < last ? i : last;
+      b.v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + (uint32_t)(i * 16)));
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = wave_sum(acc[q]);
-    if ((tid & 63) == 0) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) red[t & 1][tid >> 6][q] = acc[q];
-    }
+  };
+  auto stage = [&]() {
+    for (int t = tid; t < rounds * U * W * 64; t += kAdjThreads) gs[t] = (t <= last && t < block_rows) ? g[row0 + t] : 0.0f;
     __syncthreads();
-    if (tid < 8) {
-      const int64_t slot = grp * 8 + tid;
-      const int32_t j = perm[slot];
-      float tot = 0.0f;
+  };
+  float acc[SUB][8] = {};
+  auto use = [&](const Buf& b, int r) {
 #pragma unroll
-      for (int w = 0; w < kAdjThreads / 64; ++w) tot += red[t & 1][w][tid];
-      if (j >= 0) out[rb * out_stride + j] = apply_exp ? ldexpf(tot, eslot[slot]) : tot;
+    for (int u = 0; u < U; ++u) {
+      const float gv = gs[(sub + W * (r * U + u)) * 64 + lane];
+      float f[8];
+      unpack8<BF16>(b.v[u], f);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc[u % SUB][q] = fmaf(f[q], gv, acc[u % SUB][q]);
+      __builtin_amdgcn_sched_barrier(0);  // one load unpacked at a time
     }
-  }
+  };
+  int buf = 0;
+  auto finish = [&](int64_t grp) {
+    float sum[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      sum[q] = acc[0][q] + acc[1][q];
+      acc[0][q] = acc[1][q] = 0.0f;
+    }
+    float tot = wave_sums<8>(sum, lane);
+    bool writes = lane % 8 == 0;
+    int q = lane / 8;
+    if constexpr (SPLIT) {
+      if (writes) red[buf][wave][q] = tot;
+      __syncthreads();  // the other buffer's readers are behind the previous one
+      writes = tid < 8;
+      q = tid;
+      if (writes) {
+        tot = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) tot += red[buf][w][q];
+      }
+      buf ^= 1;
+    }
+    if (writes) {
+      const int64_t slot = grp * 8 + q;
+      const int32_t j = perm[slot];
+      if (j >= 0) out[(int64_t)blockIdx.y * out_stride + j] = apply_exp ? ldexpf(tot, eslot[slot]) : tot;
+    }
+  };
+  const int64_t g0 = (int64_t)blockIdx.x * per_wg, g1 = g0 + per_wg < ngroups ? g0 + per_wg : ngroups;
+  adjoint_rounds<Buf>(g0 + (SPLIT ? 0 : wave), g1, SPLIT ? 1 : NW, rounds, load, stage, use, finish);
 }
 
 // out[j] = 2^e_j * sum over row blocks (fixed order), or the plain sum for FP32.
@@ -487,40 +607,118 @@ __global__ __launch_bounds__(256) void reduce_cols_kernel(const float* __restric
   out[j] = exps ? ldexpf(tot, exps[j]) : tot;
 }
 
+// Launch shape: row blocks (equal, of whole row steps), columns or groups a
+// wave takes at a time, its rounds, and the column groups per workgroup.
+struct AdjShape {
+  int64_t nb, block_rows, per_wg, grid_x;
+  int c, rounds;
+  bool split;
+  size_t lds;
+};
+
+static AdjShape adj_shape(bool f32, int64_t M, int64_t units) {
+  AdjShape sh;
+  const int64_t step = f32 ? 256 : 64;  // rows per step
+  sh.nb = (M + kAdjRows - 1) / kAdjRows;
+  sh.block_rows = ((M + sh.nb - 1) / sh.nb + step - 1) / step * step;
+  sh.nb = (M + sh.block_rows - 1) / sh.block_rows;
+  const int64_t steps = (std::min(M, sh.block_rows) + step - 1) / step;
+  const int64_t waves = kAdjThreads / 64;
+  auto padded = [](int64_t n, int c) { const int64_t u = kAdjLoads / c; return (n + u - 1) / u * u; };
+  // The waves of a workgroup share columns (split) where there are far fewer
+  // columns (groups) than resident waves (128^2 PSFs, 20^2 scene, bf16: 11
+  // against 31 us), and where a column fills whole rounds of all the waves:
+  // 8 KiB at a time of one column then read better than 1 KiB of eight (128^2
+  // PSFs, 256^2 scene, fp16: 317 against 330 us; 200^2 and 128^2, fp32, whose
+  // rounds would be a fifth empty: 460 against 417 us).
+  const int64_t share = (steps + waves - 1) / waves, columns = sh.nb * units;
+  sh.split = steps >= waves && (columns < 1536 || (columns >= 2048 && share >= kAdjLoads &&
+                                                   8 * waves * padded(share, 1) <= 9 * steps));
+  const int64_t wsteps = sh.split ? share : steps;
+  // columns at a time: as few as leave at most an eighth of a column's rounds
+  // empty, but never so many that fewer than 1024 waves have work
+  // (16-bit: one group, in rounds of kAdjLoads / c steps)
+  const int cmax = f32 ? 8 : 2;
+  sh.c = 1;
+  while (sh.c < cmax && 8 * padded(wsteps, sh.c) > 9 * wsteps &&
+         padded(wsteps, 2 * sh.c) < padded(wsteps, sh.c) &&
+         (!f32 || sh.nb * units * (sh.split ? waves : 1) / (2 * sh.c) >= 1024))
+    sh.c *= 2;
+  const int64_t psteps = padded(wsteps, sh.c);
+  sh.rounds = (int)(psteps / (kAdjLoads / sh.c));
+  sh.lds = (size_t)psteps * (sh.split ? waves : 1) * step * 4;
+  // Workgroups: those resident at once (two per CU), each staging g once, or a
+  // multiple of them of about 1 MiB of the library each where it is larger than
+  // that, so that the CUs finish together (256^2, bf16: 1.22 ms against 1.30
+  // with resident workgroups only; 128^2, bf16, of 0.5 instead of 1 MiB: 89
+  // against 85 us).
+  const int64_t bytes = columns * std::min(M, sh.block_rows) * (f32 ? 4 : 16);
+  const int64_t turns = std::max<int64_t>(1, (bytes + ((int64_t)256 << 20)) / ((int64_t)512 << 20));
+  const int64_t want = std::max<int64_t>(1, 512 * turns / sh.nb);
+  const int64_t groups = f32 ? (units + sh.c - 1) / sh.c : units, quantum = sh.split ? 1 : waves;
+  sh.per_wg = std::max<int64_t>(1, ((groups + want - 1) / want + quantum - 1) / quantum) * quantum;
+  sh.grid_x = (groups + sh.per_wg - 1) / sh.per_wg;
+  return sh;
+}
+
 int64_t adjoint_partial_floats(int storage, int64_t M, int64_t ncols, int64_t ncols_pad) {
-  const int64_t rows = (storage == PSFLIB_FP32) ? kAdjF32Rows : kAdj16Rows;
-  const int64_t nb = (M + rows - 1) / rows;
+  const bool f32 = storage == PSFLIB_FP32;
+  const int64_t nb = adj_shape(f32, M, f32 ? ncols : ncols_pad / 8).nb;
   return nb > 1 ? nb * ncols_pad : 0;
 }
 
 hipError_t launch_adjoint(int storage, const void* lib, const Cols16& cx, const float* g,
                           int64_t M, int64_t ncols, int64_t ncols_pad, float* partial, float* out,
                           hipStream_t s) {
-  const int64_t rows = (storage == PSFLIB_FP32) ? kAdjF32Rows : kAdj16Rows;
-  const int64_t nb = (M + rows - 1) / rows;
-  float* dst = (nb > 1) ? partial : out;
+  const bool f32 = storage == PSFLIB_FP32;
+  const AdjShape sh = adj_shape(f32, M, f32 ? ncols : ncols_pad / 8);
+  float* dst = (sh.nb > 1) ? partial : out;
   const int64_t stride = ncols_pad;
-  if (storage == PSFLIB_FP32) {
-    const dim3 grid((unsigned)((ncols + kAdjColsPerBlock - 1) / kAdjColsPerBlock), (unsigned)nb);
+  const dim3 grid((unsigned)sh.grid_x, (unsigned)sh.nb);
+  if (f32) {
     const float* A = reinterpret_cast<const float*>(lib);
-    if (M % 4 == 0)
-      adjoint_f32_kernel<true><<<grid, kAdjThreads, 0, s>>>(A, g, dst, M, ncols, stride);
-    else
-      adjoint_f32_kernel<false><<<grid, kAdjThreads, 0, s>>>(A, g, dst, M, ncols, stride);
+    auto run = [&](auto kern) {
+      kern<<<grid, kAdjThreads, sh.lds, s>>>(A, g, dst, M, ncols, sh.block_rows, sh.rounds, sh.per_wg, stride);
+    };
+    const bool vec = M % 4 == 0;
+    auto pick = [&](auto c) {
+      constexpr int C = decltype(c)::value;
+      if (sh.split)
+        vec ? run(adjoint_f32_kernel<true, C, true>) : run(adjoint_f32_kernel<false, C, true>);
+      else
+        vec ? run(adjoint_f32_kernel<true, C, false>) : run(adjoint_f32_kernel<false, C, false>);
+    };
+    switch (sh.c) {
+      case 1: pick(std::integral_constant<int, 1>()); break;
+      case 2: pick(std::integral_constant<int, 2>()); break;
+      case 4: pick(std::integral_constant<int, 4>()); break;
+      default: pick(std::integral_constant<int, 8>()); break;
+    }
   } else {
     const int64_t ngroups = ncols_pad / 8;
-    const dim3 grid((unsigned)((ngroups + kAdj16GroupsPerBlock - 1) / kAdj16GroupsPerBlock), (unsigned)nb);
     const u32x4* Mp = reinterpret_cast<const u32x4*>(lib);
-    const int apply_exp = (nb > 1) ? 0 : 1;
-    if (storage == PSFLIB_BF16_POW2)
-      adjoint_h16_kernel<true><<<grid, kAdjThreads, 0, s>>>(Mp, cx.perm, cx.eslot, g, dst, M, ngroups, stride, apply_exp);
+    const int apply_exp = (sh.nb > 1) ? 0 : 1;
+    auto run = [&](auto kern) {
+      kern<<<grid, kAdjThreads, sh.lds, s>>>(Mp, cx.perm, cx.eslot, g, dst, M, ngroups, sh.block_rows,
+                                            sh.rounds, sh.per_wg, stride, apply_exp);
+    };
+    const bool bf = storage == PSFLIB_BF16_POW2;
+    auto pick = [&](auto c) {
+      constexpr int U = kAdjLoads / decltype(c)::value;
+      if (sh.split)
+        bf ? run(adjoint_h16_kernel<true, U, true>) : run(adjoint_h16_kernel<false, U, true>);
+      else
+        bf ? run(adjoint_h16_kernel<true, U, false>) : run(adjoint_h16_kernel<false, U, false>);
+    };
+    if (sh.c == 1)
+      pick(std::integral_constant<int, 1>());
     else
-      adjoint_h16_kernel<false><<<grid, kAdjThreads, 0, s>>>(Mp, cx.perm, cx.eslot, g, dst, M, ngroups, stride, apply_exp);
+      pick(std::integral_constant<int, 2>());
   }
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nb == 1) return e;
+  if (e != hipSuccess || sh.nb == 1) return e;
   reduce_cols_kernel<<<(unsigned)((ncols + 255) / 256), 256, 0, s>>>(
-      partial, nb, stride, ncols, storage == PSFLIB_FP32 ? nullptr : cx.exps, out);
+      partial, sh.nb, stride, ncols, f32 ? nullptr : cx.exps, out);
   return hipGetLastError();
 }
 

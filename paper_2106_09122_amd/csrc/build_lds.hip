@@ -855,7 +855,6 @@ __device__ __forceinline__ void store_run(float* p, const f32x4 v) {
   if constexpr (VEC) {
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
   } else {
-    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
     *reinterpret_cast<f32x4u*>(p) = v;
   }
 }

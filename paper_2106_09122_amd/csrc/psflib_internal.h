@@ -22,6 +22,7 @@ struct ColGeom {
 static_assert(sizeof(ColGeom) == 48, "ColGeom layout");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // at any float
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -35,11 +36,8 @@ constexpr int kMv16RowsPerThread = 8;  // 16-bit matvec rows per thread (kMv16Th
 constexpr int kMv16MaxChunkGroups = 512;  // 16-bit matvec: 8-column groups per chunk, at most
 constexpr int64_t kStageMaxCols = 32768;  // batched 16-bit: scenes staged whole in LDS up to this many columns
 constexpr int64_t kStagePairCols = 16384;  // batched 16-bit: two scenes per staging workgroup up to this many columns
-constexpr int kAdjThreads = 256;     // adjoint threads per workgroup
-constexpr int kAdjF32Rows = 16384;   // rows per FP32 adjoint row block (16 float4 per thread)
-constexpr int kAdj16Rows = 16384;    // rows per 16-bit adjoint row block (64 rows per thread)
-constexpr int kAdjColsPerBlock = 16; // FP32 adjoint: columns per workgroup
-constexpr int kAdj16GroupsPerBlock = 2;  // 16-bit adjoint: 8-column groups per workgroup
+constexpr int kAdjThreads = 512;     // adjoint threads per workgroup
+constexpr int64_t kAdjRows = 16384;  // rows per adjoint row block, at most (64 KiB of g in LDS)
 constexpr int kColPad = 64;          // 16-bit column count padded to a multiple of this
 constexpr int32_t kZeroColumnExp = PSFLIB_ZERO_COLUMN_EXPONENT;  // exponent of an identically zero column
 constexpr int kLdsCols = 16;         // LDS build: columns per work item (one wave each)
