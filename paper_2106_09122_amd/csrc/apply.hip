@@ -4,13 +4,16 @@
 //
 // A is column-major (column j is contiguous), so the forward product is a sum
 // of scaled columns.  It is split over (row block, column chunk) workgroups:
-// each thread owns 4 consecutive rows and walks the chunk's columns with 16
-// independent 16-byte non-temporal loads in flight, and writes a partial
-// image; a second kernel adds the partials of every row in chunk order.  (Doing
-// that sum in the last workgroup to finish each row block needs a device-scope
+// each thread owns 4 consecutive rows (16 bits: up to 8 rows, a row block of
+// threads apart) and walks columns with 16 independent 16-byte non-temporal
+// loads in flight; the threads of a workgroup are RT along the rows and CT along
+// the columns, whose sums are added through LDS, and it writes a partial image;
+// a second kernel adds the partials of every row in chunk order.  (Doing that
+// sum in the last workgroup to finish each row block needs a device-scope
 // release per workgroup, which writes back the XCD's L2: measured slower than
-// the extra launch.)  Sums are blocked (16 columns per inner sum) so every rounding chain
-// stays short.  Results are bitwise reproducible.
+// the extra launch.)  Few columns take one launch: workgroups of 1024 threads
+// that walk all of them.  Sums are blocked (16 columns per inner sum) so every
+// rounding chain stays short.  Results are bitwise reproducible.
 #include <math.h>
 #include <stdlib.h>
 
@@ -24,42 +27,52 @@
 namespace psflib {
 
 // ------------------------------------------------------------ forward -----
-// Split-K: workgroups own (row block, column chunk) tiles and write partial
-// images; a second kernel adds the partials of every row in chunk order, so
-// the result does not depend on scheduling.
-// Rows of one 16-column block: v[u] = A[j+u][i0..i0+3] (zero past M).
-template <bool FULL>
-__device__ __forceinline__ void load_block16(const float* __restrict__ A, int64_t M, int64_t i0,
-                                             int64_t j, f32x4* v) {
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const float* col = A + (j + u) * M + i0;
-    if constexpr (FULL) {
-      v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(col));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[u][e] = (i0 + e < M) ? col[e] : 0.0f;
-    }
-  }
+// Rows i0 .. i0 + 3 of a column, for images whose columns start at 16-byte
+// boundaries (kAligned: M % 4 == 0), at any float, or of fewer than 4 pixels
+// (kTiny: n = 1).
+constexpr int kUnaligned = 0, kAligned = 1, kTiny = 2;
+
+template <int MODE>
+__device__ __forceinline__ f32x4 load_rows(const float* __restrict__ p) {
+  if constexpr (MODE == kAligned) return __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+  if constexpr (MODE == kUnaligned) return __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(p));
+  return (f32x4){p[0], 0.0f, 0.0f, 0.0f};
 }
 
-// sum_j A[j][i0..i0+3] Z[j] over [j0, j1), in three levels: 16 columns,
-// 16 blocks of 16, then the rest, so no rounding chain exceeds ~16 + 16 +
-// (j1-j0)/256 additions.
-template <bool FULL>
-__device__ __forceinline__ f32x4 matvec_rows(const float* __restrict__ A,
-                                             const float* __restrict__ Z, int64_t M, int64_t i0,
-                                             int64_t j0, int64_t j1) {
+template <int MODE>
+__device__ __forceinline__ void store_rows(float* __restrict__ p, const f32x4 v) {
+  if constexpr (MODE == kAligned)
+    *reinterpret_cast<f32x4*>(p) = v;
+  else if constexpr (MODE == kUnaligned)
+    *reinterpret_cast<f32x4u*>(p) = v;
+  else
+    p[0] = v[0];
+}
+
+// First row of the thread whose 4 rows would start at i0: the last thread of
+// the image steps back to end with it (its first rows are its neighbour's too,
+// with the same values).
+template <int MODE>
+__device__ __forceinline__ int64_t first_row(int64_t i0, int64_t M) {
+  return MODE == kUnaligned && i0 > M - 4 ? M - 4 : i0;
+}
+
+// sum_j A[j][i0..i0+3] z(j) over the 16-column blocks c, c + CT, ... of
+// [j0, j1), in three levels: 16 columns, 16 blocks, then the rest.
+template <int MODE, int CT, typename Z>
+__device__ __forceinline__ f32x4 matvec_rows(const float* __restrict__ A, Z z, int64_t M, int64_t i0,
+                                             int64_t j0, int64_t j1, int c) {
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   f32x4 outer = zero, mid = zero;
   int nblk = 0;
-  int64_t j = j0;
-  for (; j + 16 <= j1; j += 16) {
+  int64_t j = j0 + 16 * c;
+  for (; j + 16 <= j1; j += 16 * CT) {
     f32x4 v[16];
-    load_block16<FULL>(A, M, i0, j, v);
-    f32x4 inner = v[0] * Z[j];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) inner += v[u] * Z[j + u];
+    for (int u = 0; u < 16; ++u) v[u] = load_rows<MODE>(A + (j + u) * M + i0);
+    f32x4 inner = v[0] * z(j);
+#pragma unroll
+    for (int u = 1; u < 16; ++u) inner += v[u] * z(j + u);
     mid += inner;
     if (++nblk == 16) {
       outer += mid;
@@ -68,48 +81,70 @@ __device__ __forceinline__ f32x4 matvec_rows(const float* __restrict__ A,
     }
   }
   f32x4 inner = zero;
-  for (; j < j1; ++j) {
-    const float* col = A + j * M + i0;
-    f32x4 v;
-    if constexpr (FULL) {
-      v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(col));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = (i0 + e < M) ? col[e] : 0.0f;
-    }
-    inner += v * Z[j];
-  }
+  for (; j < j1; ++j) inner += load_rows<MODE>(A + j * M + i0) * z(j);  // the chunk's last block
   mid += inner;
   return outer + mid;
 }
 
-template <bool VEC>
+// 256 threads, RT along the rows (4 RT rows per workgroup).  Small images take
+// fewer, which leaves fewer threads past the image's end and needs fewer partial
+// images for the same number of workgroups (33^2 PSFs, 200^2 scene: 85 -> 35
+// us, with the unaligned loads in place of one per float; 127^2: 236 -> 169 us).
+template <int MODE, int RT>
 __global__ __launch_bounds__(kMvThreads) void matvec_f32_kernel(const float* __restrict__ A,
                                                                 const float* __restrict__ Z,
                                                                 float* __restrict__ part,
                                                                 float* __restrict__ out,
                                                                 int64_t M, int64_t ncols,
                                                                 int64_t chunk) {
-  const int64_t i0 = ((int64_t)blockIdx.x * kMvThreads + threadIdx.x) * 4;
-  const int64_t c = blockIdx.y;
-  const int64_t nchunks = gridDim.y;
-  const int64_t j0 = c * chunk;
+  constexpr int CT = kMvThreads / RT;
+  const int r = threadIdx.x % RT, c = __builtin_amdgcn_readfirstlane(threadIdx.x / RT);
+  const int64_t row = ((int64_t)blockIdx.x * RT + r) * 4;
+  const int64_t i0 = first_row<MODE>(row, M);
+  const int64_t j0 = blockIdx.y * chunk;
   const int64_t j1 = (j0 + chunk < ncols) ? j0 + chunk : ncols;
-  // uniform across the workgroup: every row of the block is inside the image
-  const bool block_full = VEC && ((int64_t)(blockIdx.x + 1) * kMvThreads * 4 <= M);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (block_full)
-    acc = matvec_rows<true>(A, Z, M, i0, j0, j1);
-  else if (i0 < M)
-    acc = matvec_rows<false>(A, Z, M, i0, j0, j1);
-  float* dst = ((nchunks == 1) ? out : part + c * M) + i0;
-  if (block_full) {
-    *reinterpret_cast<f32x4*>(dst) = acc;
-  } else {
+  if (row < M) acc = matvec_rows<MODE, CT>(A, [=](int64_t j) { return Z[j]; }, M, i0, j0, j1, c);
+  if constexpr (CT > 1) {
+    __shared__ f32x4 red[CT][RT];
+    red[c][r] = acc;
+    __syncthreads();
+    if (c > 0) return;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (i0 + e < M) dst[e] = acc[e];
+    for (int k = 1; k < CT; ++k) acc += red[k][r];
   }
+  if (row < M) store_rows<MODE>((gridDim.y == 1 ? out : part + blockIdx.y * M) + i0, acc);
+}
+
+// One launch for few columns: 1024 threads, 16 along the rows (64 rows per
+// workgroup), every column.  The scene is staged in LDS (a wave's lanes are on
+// four columns).
+constexpr int64_t kMvOneMaxCols32 = 1024, kMvOneMaxCols16 = 2048;
+
+template <int MODE>
+__global__ __launch_bounds__(1024) void matvec_one_f32_kernel(const float* __restrict__ A,
+                                                              const float* __restrict__ Z,
+                                                              float* __restrict__ out, int64_t M,
+                                                              int64_t ncols) {
+  constexpr int RT = 16, CT = 1024 / RT;
+  __shared__ float zs[kMvOneMaxCols32];
+  __shared__ f32x4 red[CT][RT];
+  for (int j = threadIdx.x; j < ncols; j += 1024) zs[j] = Z[j];
+  __syncthreads();
+  const int r = threadIdx.x % RT, c = threadIdx.x / RT;
+  const int64_t row = ((int64_t)blockIdx.x * RT + r) * 4;
+  const int64_t i0 = first_row<MODE>(row, M);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (row < M)
+    acc = matvec_rows<MODE, CT>(A, [&](int64_t j) { return zs[j]; }, M, i0, 0, ncols, c);
+  red[c][r] = acc;
+  // halves of the column threads, in a fixed order
+#pragma unroll
+  for (int k = CT / 2; k > 0; k >>= 1) {
+    __syncthreads();
+    if (c < k) red[c][r] += red[c + k][r];
+  }
+  if (c == 0 && row < M) store_rows<MODE>(out + i0, red[0][r]);
 }
 
 // 16-bit storage: element (i, slot s) at ((s/8)*M + i)*8 + s%8, slot s holding
@@ -144,76 +179,45 @@ __device__ __forceinline__ void unpack8(const u32x4 p, float* f) {
   }
 }
 
-// Each thread owns kMv16RowsPerThread rows, kMv16Threads apart, so a
-// workgroup reads kMv16RowsPerThread * 4 KiB of every group in one piece, and
-// each broadcast of the group's 8 scene values serves that many loads.
-template <bool BF16>
-__global__ __launch_bounds__(kMv16Threads) void matvec_h16_kernel(const u32x4* __restrict__ Mp,
-                                                                  const int32_t* __restrict__ perm,
-                                                                  const int32_t* __restrict__ eslot,
-                                                                  const float* __restrict__ Z,
-                                                                  float* __restrict__ part,
-                                                                  float* __restrict__ out,
-                                                                  int64_t M, int64_t ngroups,
-                                                                  int64_t chunk_g) {
-  constexpr int R = kMv16RowsPerThread;
-  constexpr int GB = 16 / R;  // groups per block of 16 loads
-  __shared__ f32x4 zs[kMv16MaxChunkGroups * 2];
-  const int tid = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * kMv16Threads * R + tid;
-  const int64_t c = blockIdx.y;
-  const int64_t nchunks = gridDim.y;
-  const int64_t g0 = c * chunk_g;
-  const int64_t g1 = (g0 + chunk_g < ngroups) ? g0 + chunk_g : ngroups;
-  const int64_t ng = g1 - g0;
-  float* zsf = reinterpret_cast<float*>(zs);
-  for (int64_t t = tid; t < ng * 8; t += kMv16Threads) {
-    const int64_t slot = g0 * 8 + t;
-    const int32_t j = perm[slot];
-    zsf[t] = (j >= 0) ? ldexpf(Z[j], eslot[slot]) : 0.0f;
-  }
-  __syncthreads();
-  // rows past the image read row M-1 (in bounds) and are not written
-  const u32x4* src[R];
+// The sums of one thread: rows src[0..R-1] over the groups g = g0 + c GB, ...
+// in steps of CT GB (GB = 16 / R groups per block of 16 loads), in three
+// levels: 16 groups, 8 of those, then the rest.  zs holds the 8 scene values of
+// group g at 2 (g - g0).
+template <bool BF16, int R, int CT>
+__device__ __forceinline__ void matvec16_rows(const u32x4* const* src, const f32x4* __restrict__ zs,
+                                              int64_t M, int64_t g0, int64_t g1, int c, float* res) {
+  constexpr int GB = 16 / R;
+  float outer[R], mid[R], inner[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int64_t i = i0 + (int64_t)kMv16Threads * r;
-    src[r] = Mp + (i < M ? i : M - 1);
-  }
-  float outer[R], mid[R];
+  for (int r = 0; r < R; ++r) outer[r] = mid[r] = inner[r] = 0.0f;
+  auto use = [&](const u32x4* p, int64_t g) {
+    const f32x4 za = zs[2 * (g - g0)], zb = zs[2 * (g - g0) + 1];
 #pragma unroll
-  for (int r = 0; r < R; ++r) outer[r] = mid[r] = 0.0f;
-  // blocks of 16 groups per inner sum, 8 blocks per middle sum, per row
-  float inner[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) inner[r] = 0.0f;
+    for (int r = 0; r < R; ++r) {
+      float f[8];
+      unpack8<BF16>(p[r], f);
+      float acc = inner[r];
+      acc = fmaf(f[0], za.x, acc);
+      acc = fmaf(f[1], za.y, acc);
+      acc = fmaf(f[2], za.z, acc);
+      acc = fmaf(f[3], za.w, acc);
+      acc = fmaf(f[4], zb.x, acc);
+      acc = fmaf(f[5], zb.y, acc);
+      acc = fmaf(f[6], zb.z, acc);
+      acc = fmaf(f[7], zb.w, acc);
+      inner[r] = acc;
+    }
+  };
   int ing = 0, nblk = 0;
-  int64_t g = g0;
-  for (; g + GB <= g1; g += GB) {
+  int64_t g = g0 + (int64_t)c * GB;
+  for (; g + GB <= g1; g += CT * GB) {
     u32x4 p[GB][R];
 #pragma unroll
     for (int u = 0; u < GB; ++u)
 #pragma unroll
       for (int r = 0; r < R; ++r) p[u][r] = __builtin_nontemporal_load(src[r] + (g + u) * M);
 #pragma unroll
-    for (int u = 0; u < GB; ++u) {
-      const f32x4 za = zs[2 * (g - g0 + u)], zb = zs[2 * (g - g0 + u) + 1];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        float f[8];
-        unpack8<BF16>(p[u][r], f);
-        float acc = inner[r];
-        acc = fmaf(f[0], za.x, acc);
-        acc = fmaf(f[1], za.y, acc);
-        acc = fmaf(f[2], za.z, acc);
-        acc = fmaf(f[3], za.w, acc);
-        acc = fmaf(f[4], zb.x, acc);
-        acc = fmaf(f[5], zb.y, acc);
-        acc = fmaf(f[6], zb.z, acc);
-        acc = fmaf(f[7], zb.w, acc);
-        inner[r] = acc;
-      }
-    }
+    for (int u = 0; u < GB; ++u) use(p[u], g + u);
     ing += GB;
     if (ing == 16) {
 #pragma unroll
@@ -232,58 +236,101 @@ __global__ __launch_bounds__(kMv16Threads) void matvec_h16_kernel(const u32x4* _
       }
     }
   }
-  for (; g < g1; ++g) {
-    const f32x4 za = zs[2 * (g - g0)], zb = zs[2 * (g - g0) + 1];
+  for (; g < g1; ++g) {  // the chunk's last block
+    u32x4 p[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      float f[8];
-      unpack8<BF16>(__builtin_nontemporal_load(src[r] + g * M), f);
-      float acc = inner[r];
-      acc = fmaf(f[0], za.x, acc);
-      acc = fmaf(f[1], za.y, acc);
-      acc = fmaf(f[2], za.z, acc);
-      acc = fmaf(f[3], za.w, acc);
-      acc = fmaf(f[4], zb.x, acc);
-      acc = fmaf(f[5], zb.y, acc);
-      acc = fmaf(f[6], zb.z, acc);
-      acc = fmaf(f[7], zb.w, acc);
-      inner[r] = acc;
-    }
+    for (int r = 0; r < R; ++r) p[r] = __builtin_nontemporal_load(src[r] + g * M);
+    use(p, g);
   }
-  float* dst = (nchunks == 1) ? out : part + c * M;
+#pragma unroll
+  for (int r = 0; r < R; ++r) res[r] = outer[r] + (mid[r] + inner[r]);
+}
+
+// T threads, RT along the rows; each thread owns R rows, RT apart, so that a
+// workgroup reads R RT 16-byte units of every group in one piece, and each
+// broadcast of the group's 8 scene values serves R loads.  ZG: groups whose
+// scene values the LDS holds.
+template <bool BF16, int T, int R, int RT, int ZG>
+__global__ __launch_bounds__(T) void matvec_h16_kernel(const u32x4* __restrict__ Mp,
+                                                       const int32_t* __restrict__ perm,
+                                                       const int32_t* __restrict__ eslot,
+                                                       const float* __restrict__ Z,
+                                                       float* __restrict__ part,
+                                                       float* __restrict__ out, int64_t M,
+                                                       int64_t ngroups, int64_t chunk_g) {
+  constexpr int CT = T / RT;
+  __shared__ f32x4 zs[ZG * 2];
+  const int tid = threadIdx.x, t = tid % RT, c = tid / RT;
+  const int64_t i0 = (int64_t)blockIdx.x * RT * R + t;
+  const int64_t g0 = blockIdx.y * chunk_g;
+  const int64_t g1 = (g0 + chunk_g < ngroups) ? g0 + chunk_g : ngroups;
+  const int64_t ng = g1 - g0;
+  float* zsf = reinterpret_cast<float*>(zs);
+  for (int64_t k = tid; k < ng * 8; k += T) {
+    const int64_t slot = g0 * 8 + k;
+    const int32_t j = perm[slot];
+    zsf[k] = (j >= 0) ? ldexpf(Z[j], eslot[slot]) : 0.0f;
+  }
+  __syncthreads();
+  // rows past the image read row M-1 (in bounds) and are not written
+  const u32x4* src[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int64_t i = i0 + (int64_t)kMv16Threads * r;
-    if (i < M) dst[i] = outer[r] + (mid[r] + inner[r]);
+    const int64_t i = i0 + (int64_t)RT * r;
+    src[r] = Mp + (i < M ? i : M - 1);
+  }
+  float res[R];
+  matvec16_rows<BF16, R, CT>(src, zs, M, g0, g1, c, res);
+  if constexpr (CT > 1) {
+    __shared__ float red[CT][R][RT];
+#pragma unroll
+    for (int r = 0; r < R; ++r) red[c][r][t] = res[r];
+    __syncthreads();
+    if (c > 0) return;
+#pragma unroll
+    for (int k = 1; k < CT; ++k)
+#pragma unroll
+      for (int r = 0; r < R; ++r) res[r] += red[k][r][t];
+  }
+  float* dst = (gridDim.y == 1) ? out : part + blockIdx.y * M;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int64_t i = i0 + (int64_t)RT * r;
+    if (i < M) dst[i] = res[r];
   }
 }
 
-// out[i] = sum over chunks of part[chunk][i]: blocks of 16 partials loaded
-// together and added in chunk order, then the block sums in order.  One row
-// per thread, so the few megabytes of partials are spread over many waves.
+// out[i] = sum over chunks of part[chunk][i].  A workgroup is 64 rows x 4
+// quarters of the chunks (whole blocks of 16 partials, loaded together and
+// added in chunk order); the quarters' sums are added in order.
 __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restrict__ part,
                                                           int64_t nchunks, int64_t M,
                                                           float* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
+  __shared__ float red[4][64];
+  const int r = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + r;
+  const int64_t blocks = (nchunks + 15) / 16;
+  const int64_t c1 = 16 * (blocks * (q + 1) / 4) < nchunks ? 16 * (blocks * (q + 1) / 4) : nchunks;
   float total = 0.0f;
-  for (int64_t c0 = 0; c0 < nchunks; c0 += 16) {
-    float p[16];
+  if (i < M)
+    for (int64_t c0 = 16 * (blocks * q / 4); c0 < c1; c0 += 16) {
+      float p[16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) p[u] = (c0 + u < nchunks) ? part[(c0 + u) * M + i] : 0.0f;
-    float blk = p[0];
+      for (int u = 0; u < 16; ++u) p[u] = (c0 + u < c1) ? part[(c0 + u) * M + i] : 0.0f;
+      float blk = p[0];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) blk += p[u];
-    total += blk;
-  }
-  out[i] = total;
+      for (int u = 1; u < 16; ++u) blk += p[u];
+      total += blk;
+    }
+  red[q][r] = total;
+  __syncthreads();
+  if (q == 0 && i < M) out[i] = ((red[0][r] + red[1][r]) + red[2][r]) + red[3][r];
 }
 
-// Split-K shape: about kMvTargetWorkgroups{32,16} workgroups in all (FP32:
-// two per CU; 16-bit: one per CU of 8 rows x 16 B per thread and load step,
-// measured at 128^2 against 192 or 384 workgroups: 80 us against 88-94 us,
-// and against one row per thread at 768 workgroups: 85 us).  The value can be
-// overridden with PSFLIB_MV_WORKGROUPS for tuning sweeps.
+// Shape of the product: threads along the rows, rows per thread, row blocks and
+// column chunks, about 512 workgroups in all for FP32 (two per CU) and 256 for
+// the 16-bit forms (one per CU; 128^2: 80 us against 88-94 us with 192 or 384).
+// The number can be overridden with PSFLIB_MV_WORKGROUPS for tuning sweeps.
 static int64_t mv_target_workgroups(int storage) {
   static const long env = [] {
     const char* e = getenv("PSFLIB_MV_WORKGROUPS");
@@ -294,19 +341,52 @@ static int64_t mv_target_workgroups(int storage) {
 }
 
 struct MvShape {
+  bool one;  // one launch of 1024-thread workgroups over all columns
+  int rt, r;
   int64_t rowblocks, chunk, nchunks;  // chunk: columns (FP32) or 8-column groups (16-bit)
 };
 
 static MvShape mv_shape(int storage, int64_t M, int64_t ncols, int64_t ncols_pad) {
   MvShape sh;
-  const int64_t rows = (storage == PSFLIB_FP32) ? 4 * kMvThreads : kMv16Threads * kMv16RowsPerThread;
-  const int64_t units = (storage == PSFLIB_FP32) ? ncols : ncols_pad / 8;
+  const bool f32 = storage == PSFLIB_FP32;
+  const int64_t units = f32 ? ncols : ncols_pad / 8;
+  auto padded = [&](int64_t rows) { return (M + rows - 1) / rows * rows; };
+  // One launch: up to 16 columns (16-bit: 16 groups) per thread, and images of
+  // at most 256 workgroups of 64 rows (32^2: 8.3 us, the launches' rate, against
+  // 11; 128^2 PSFs, 32^2 scene, float32 12.3 against 14.9 us, bf16 9.3 against 17;
+  // 200^2 PSFs, 40^2 scene: 47 against 44 us).
+  if (M <= 16384 && (f32 ? ncols <= kMvOneMaxCols32 : ncols_pad <= kMvOneMaxCols16)) {
+    sh.one = true;
+    sh.r = f32 ? 4 : 1;
+    sh.rt = f32 ? 16 : 64;
+    sh.chunk = units;
+    sh.nchunks = 1;
+    sh.rowblocks = (M + 63) / 64;
+    return sh;
+  }
+  sh.one = false;
+  if (f32) {
+    // 1024 rows per workgroup; below 8192 rows 512 or 256, whichever leaves few
+    // threads past the end (96^2 with 1024: 52 us, with 256: 59 us; 64^2 with 512:
+    // 14.5 us, with 1024: 16.1 us; 80^2 with 256: 27 us, with 512: 32 us)
+    sh.r = 4;
+    sh.rt = M >= 8192 ? 256 : padded(512) * 32 <= M * 33 ? 128 : 64;
+  } else {
+    // 2048 rows where they leave few threads past the end, else 512, and fewer
+    // rows per thread for small images (101^2, bf16, 2048: 39 us, 512: 43 us; 96^2
+    // 37 and 33 us)
+    sh.r = 8;
+    sh.rt = M >= 8192 && padded(2048) * 24 <= M * 25 ? 256 : 64;
+    if (sh.rt == 64)
+      while (sh.r > 2 && padded(sh.r * 64) * 8 > M * 9 && padded(sh.r * 32) < padded(sh.r * 64)) sh.r /= 2;
+  }
+  const int64_t rows = (int64_t)sh.r * sh.rt;
   sh.rowblocks = (M + rows - 1) / rows;
   int64_t want = (mv_target_workgroups(storage) + sh.rowblocks - 1) / sh.rowblocks;
   if (want < 1) want = 1;
   int64_t chunk = (units + want - 1) / want;
   chunk = (chunk + 15) / 16 * 16;
-  if (storage != PSFLIB_FP32 && chunk > kMv16MaxChunkGroups) chunk = kMv16MaxChunkGroups;
+  if (!f32 && chunk > kMv16MaxChunkGroups) chunk = kMv16MaxChunkGroups;
   sh.chunk = chunk;
   sh.nchunks = (units + chunk - 1) / chunk;
   return sh;
@@ -324,21 +404,50 @@ hipError_t launch_matvec(int storage, const void* lib, const Cols16& cx, const f
   const dim3 grid((unsigned)sh.rowblocks, (unsigned)sh.nchunks);
   if (storage == PSFLIB_FP32) {
     const float* A = reinterpret_cast<const float*>(lib);
+    auto run = [&](auto mode) {
+      constexpr int MODE = decltype(mode)::value;
+      auto one = [&](auto kern) { kern<<<grid, 1024, 0, s>>>(A, Z, out, M, ncols); };
+      auto split = [&](auto kern) { kern<<<grid, kMvThreads, 0, s>>>(A, Z, partial, out, M, ncols, sh.chunk); };
+      if (sh.one)
+        one(matvec_one_f32_kernel<MODE>);
+      else
+        sh.rt == 64 ? split(matvec_f32_kernel<MODE, 64>)
+        : sh.rt == 128 ? split(matvec_f32_kernel<MODE, 128>) : split(matvec_f32_kernel<MODE, 256>);
+    };
     if (M % 4 == 0)
-      matvec_f32_kernel<true><<<grid, kMvThreads, 0, s>>>(A, Z, partial, out, M, ncols, sh.chunk);
+      run(std::integral_constant<int, kAligned>());
+    else if (M >= 4)
+      run(std::integral_constant<int, kUnaligned>());
     else
-      matvec_f32_kernel<false><<<grid, kMvThreads, 0, s>>>(A, Z, partial, out, M, ncols, sh.chunk);
+      run(std::integral_constant<int, kTiny>());
   } else {
     const int64_t ngroups = ncols_pad / 8;
     const u32x4* Mp = reinterpret_cast<const u32x4*>(lib);
+    auto run = [&](auto fmt) {
+      constexpr bool BF = decltype(fmt)::value;
+      auto go = [&](auto kern, int threads) {
+        kern<<<grid, threads, 0, s>>>(Mp, cx.perm, cx.eslot, Z, partial, out, M, ngroups, sh.chunk);
+      };
+      constexpr int T = kMv16Threads, ZG = kMv16MaxChunkGroups;
+      if (sh.one)
+        go(matvec_h16_kernel<BF, 1024, 1, 64, (int)kMvOneMaxCols16 / 8>, 1024);
+      else if (sh.rt == 256)
+        go(matvec_h16_kernel<BF, T, 8, 256, ZG>, T);
+      else if (sh.r == 8)
+        go(matvec_h16_kernel<BF, T, 8, 64, ZG>, T);
+      else if (sh.r == 4)
+        go(matvec_h16_kernel<BF, T, 4, 64, ZG>, T);
+      else
+        go(matvec_h16_kernel<BF, T, 2, 64, ZG>, T);
+    };
     if (storage == PSFLIB_BF16_POW2)
-      matvec_h16_kernel<true><<<grid, kMv16Threads, 0, s>>>(Mp, cx.perm, cx.eslot, Z, partial, out, M, ngroups, sh.chunk);
+      run(std::true_type());
     else
-      matvec_h16_kernel<false><<<grid, kMv16Threads, 0, s>>>(Mp, cx.perm, cx.eslot, Z, partial, out, M, ngroups, sh.chunk);
+      run(std::false_type());
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || sh.nchunks == 1) return e;
-  reduce_rows_kernel<<<(unsigned)((M + 255) / 256), 256, 0, s>>>(partial, sh.nchunks, M, out);
+  reduce_rows_kernel<<<(unsigned)((M + 63) / 64), 256, 0, s>>>(partial, sh.nchunks, M, out);
   return hipGetLastError();
 }
 

@@ -103,3 +103,25 @@ def test_adjoint_shapes(torch, n, N, storage):
     assert torch.all((out.double() - ref).abs() <= 1e-5 * mag + 1e-300)
     assert torch.equal(out, lib.apply_adjoint(g))  # fixed order: bitwise reproducible
     lib.close()
+
+
+# one launch (few columns) and split; one pixel, images smaller than a
+# workgroup, rows that end inside a thread's four, every row-block width, up to
+# just past 16384 rows; columns that fill no block of 16, one, and several chunks
+APPLY = [(1, 1), (1, 40), (2, 3), (3, 33), (5, 46), (8, 32), (16, 7), (17, 33), (22, 47), (32, 32), (33, 46),
+         (45, 48), (64, 33), (80, 33), (91, 40), (96, 34), (101, 35), (127, 33), (128, 32), (128, 35),
+         (129, 5), (129, 34), (182, 33)]
+
+
+@pytest.mark.parametrize("storage", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("n,N", APPLY)
+def test_apply_shapes(torch, n, N, storage):
+    print("apply", n, N, storage, flush=True)
+    lib, A, rng = _library(torch, n, N, storage)
+    Z = torch.from_numpy(rng.random(N * N).astype(np.float32)).cuda()
+    out = torch.full((n * n,), float("nan"), device="cuda")
+    lib.apply(Z, out=out)
+    ref = Z.double() @ A
+    assert torch.all((out.double() - ref).abs() <= 1e-5 * ref.abs() + 1e-300)
+    assert torch.equal(out, lib.apply(Z))
+    lib.close()
