@@ -87,9 +87,19 @@ struct GReduce {
 // live data (columns past ncols and blocks past the item read as zero), kGrpRing
 // blocks ahead of use, with no LDS and no barriers.  Accumulation is blocked
 // (64 columns, then the chunk).
+// MODE: images whose columns start at 16-byte boundaries; at any float, where
+// the lane whose 4 rows would pass the image's end takes its last 4 (its first
+// rows are the lane's before it too, with the same values; 101^2, 9 libraries:
+// 1.74 ms with a load per float); or of fewer than 4 pixels (n = 1).
 constexpr int kGrpRing = 2;
+constexpr int kGrpUnaligned = 0, kGrpAligned = 1, kGrpTiny = 2;
 
-template <bool VEC>
+template <int MODE>
+__device__ __forceinline__ int64_t grp_first_row(int64_t row, int64_t M) {
+  return MODE == kGrpUnaligned && row > M - 4 ? M - 4 : row;
+}
+
+template <int MODE>
 __device__ __forceinline__ void grouped_f32_item(const GItem& w, const f32x4* __restrict__ zpk,
                                                  int lane, int wave, float* __restrict__ part,
                                                  float* const* __restrict__ images) {
@@ -101,7 +111,7 @@ __device__ __forceinline__ void grouped_f32_item(const GItem& w, const f32x4* __
   uint32_t voff[4];
 #pragma unroll
   for (int s4 = 0; s4 < 4; ++s4)
-    voff[s4] = (uint32_t)((int64_t)(4 * s4 + q) * w.M * 4 + (m0 + 4 * n) * 4);
+    voff[s4] = (uint32_t)((int64_t)(4 * s4 + q) * w.M * 4 + grp_first_row<MODE>(m0 + 4 * n, w.M) * 4);
   const float* A = reinterpret_cast<const float*>(w.A);
   const int b0 = (int)(w.j0 / 16), b1 = (int)((w.j1 + 15) / 16);
   const int ncols = (int)w.ncols;
@@ -120,7 +130,7 @@ __device__ __forceinline__ void grouped_f32_item(const GItem& w, const f32x4* __
         (void*)(zpk + w.bpk + (int64_t)bc * 64), (short)0, live ? 1024 : 0, 0x00020000);
 #pragma unroll
     for (int s4 = 0; s4 < 4; ++s4) {
-      if (VEC) {
+      if (MODE != kGrpTiny) {
         ra[slot][s4] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(ad, voff[s4], 0, 2));
       } else {
 #pragma unroll
@@ -153,29 +163,30 @@ __device__ __forceinline__ void grouped_f32_item(const GItem& w, const f32x4* __
 #pragma unroll
     for (int t = 0; t < 4; ++t) tot[t] += acc[t];
   }
-  // lane holds scene n and MFMA rows 4q + r, i.e. image rows m0 + 16q + 4r + t
+  // lane holds scene n and MFMA rows 4q + r, i.e. the 4 rows of lane 4q + r of
+  // the loads
   if (n < w.nscenes) {
-    if (w.direct) {
-      float* img = images[w.scene0 + n];
-      const int64_t rr = m0 + 16 * q;
-      const bool whole = VEC && rr + 16 <= w.M;  // images are 16-byte aligned; M % 4 == 0
+    float* img = w.direct ? images[w.scene0 + n] : nullptr;
+    float* dst = part + w.part + (int64_t)n * kGrpThreads + 64 * wave;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const f32x4 v = {tot[0][r], tot[1][r], tot[2][r], tot[3][r]};
-        if (whole) {
-          *reinterpret_cast<f32x4*>(img + rr + 4 * r) = v;
-        } else {
+    for (int r = 0; r < 4; ++r) {
+      const f32x4 v = {tot[0][r], tot[1][r], tot[2][r], tot[3][r]};
+      const int64_t row = m0 + 4 * (4 * q + r);
+      if (row >= w.M) continue;
+      const int64_t i = grp_first_row<MODE>(row, w.M);
+      float* p = w.direct ? img + i : dst + (i - m0);
+      if constexpr (MODE == kGrpAligned) {
+        *reinterpret_cast<f32x4*>(p) = v;  // images are 16-byte aligned; M % 4 == 0
+      } else if constexpr (MODE == kGrpUnaligned) {
+        if (w.direct || i >= m0) {
+          *reinterpret_cast<f32x4u*>(p) = v;
+        } else {  // the partials start at the item's first row
 #pragma unroll
           for (int t = 0; t < 4; ++t)
-            if (rr + 4 * r + t < w.M) img[rr + 4 * r + t] = v[t];
+            if (i + t >= m0) p[t] = v[t];
         }
-      }
-    } else {
-      float* dst = part + w.part + (int64_t)n * kGrpThreads + 64 * wave + 16 * q;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const f32x4 v = {tot[0][r], tot[1][r], tot[2][r], tot[3][r]};
-        *reinterpret_cast<f32x4*>(dst + 4 * r) = v;
+      } else {
+        p[0] = v[0];
       }
     }
   }
@@ -189,9 +200,11 @@ __global__ __launch_bounds__(kGrpThreads) void grouped_f32_kernel(
   for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
     const GItem w = items[it];
     if ((w.M & 3) == 0)
-      grouped_f32_item<true>(w, zpk, lane, wave, part, images);
+      grouped_f32_item<kGrpAligned>(w, zpk, lane, wave, part, images);
+    else if (w.M >= 4)
+      grouped_f32_item<kGrpUnaligned>(w, zpk, lane, wave, part, images);
     else
-      grouped_f32_item<false>(w, zpk, lane, wave, part, images);
+      grouped_f32_item<kGrpTiny>(w, zpk, lane, wave, part, images);
   }
 }
 

@@ -125,3 +125,31 @@ def test_apply_shapes(torch, n, N, storage):
     assert torch.all((out.double() - ref).abs() <= 1e-5 * ref.abs() + 1e-300)
     assert torch.equal(out, lib.apply(Z))
     lib.close()
+
+
+# grouped plans: images of 1 to 4 pixels, rows that end 1 to 3 past a wave's or
+# an item's first row, whole and chunked columns, 1 to 17 scenes of a library
+@pytest.mark.parametrize("storage,chunks", [("fp32", (0, 16, 64)), ("bf16", (0, 8))])
+def test_grouped_shapes(torch, storage, chunks):
+    from paper_2106_09122_amd import psflib
+    sizes = [(1, 3), (2, 5), (3, 4), (7, 9), (9, 9), (17, 8), (23, 9), (33, 5), (45, 6), (15, 12)]
+    built = [_library(torch, n, N, storage) for n, N in sizes]
+    libs, As = [b[0] for b in built], [b[1] for b in built]
+    rng = np.random.default_rng(7)
+    which = [L for L in range(len(libs)) for _ in range((1, 3, 17)[L % 3])]
+    scenes = [torch.from_numpy(rng.random(libs[L].ncols).astype(np.float32)).cuda() for L in which]
+    plan = psflib.Grouped(libs, which, scenes, autotune=False)
+    for chunk in chunks:
+        plan.set_shape(chunk, 256)
+        for im in plan.images:
+            im.fill_(float("nan"))
+        plan.run()
+        torch.cuda.synchronize()
+        for b, L in enumerate(which):
+            ref = scenes[b].double() @ As[L]
+            err = (plan.images[b].double() - ref).abs()
+            # 16 bits: hi + lo parts of the scene, u^2 = 2^-16 of each value
+            assert torch.all(err <= (1e-5 if storage == "fp32" else 2.0**-15) * ref + 1e-300), (chunk, sizes[L])
+    plan.close()
+    for lib in libs:
+        lib.close()
