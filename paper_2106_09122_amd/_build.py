@@ -1,4 +1,5 @@
-"""Compile the HIP sources of psflib into ``libpsflib.so`` (gfx950), in-tree.
+"""Compile the HIP sources of psflib into ``libpsflib.so`` (gfx950) and the
+native part of the Python binding into ``_psfop.so``, in-tree.
 
 Each translation unit is compiled to an object under ``_build/`` in
 parallel, then linked into a shared library next to this file.
@@ -8,6 +9,7 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +19,8 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libpsflib.so")
 SOURCES = ["psflib.hip", "geometry.hip", "build.hip", "build_lds.hip", "apply.hip", "gemm.hip", "model.hip", "grouped.hip", "spline.hip", "flux.hip", "probe.hip"]
+BINDING = os.path.join(CSRC, "binding.cpp")
+BINDING_PATH = os.path.join(PKG_DIR, "_psfop.so")
 ARCH = "gfx950"
 
 
@@ -36,8 +40,29 @@ def compile_flags() -> list:
     ]
 
 
+def binding_commands() -> list:
+    """Commands that compile and link the native binding against libpsflib.so
+    (found next to it at run time) and the installed torch."""
+    import torch
+    t = os.path.dirname(torch.__file__)
+    obj = os.path.join(BUILD_DIR, "binding.o")
+    cxx = shutil.which("g++") or "g++"
+    return [
+        [cxx, "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+         "-DTORCH_API_INCLUDE_EXTENSION_H", "-DTORCH_EXTENSION_NAME=_psfop", "-I", INCLUDE,
+         "-isystem", os.path.join(t, "include"),
+         "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+         "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+         "-c", BINDING, "-o", obj],
+        [cxx, "-shared", "-fPIC", obj, "-o", BINDING_PATH + ".tmp", "-L", os.path.join(t, "lib"),
+         "-ltorch", "-ltorch_cpu", "-ltorch_python", "-lc10", "-lc10_hip", "-L", PKG_DIR,
+         "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN"],
+    ]
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
-    """Compile every source and link libpsflib.so; returns its path."""
+    """Compile every source, link libpsflib.so and the native binding; returns
+    the path of libpsflib.so."""
     cc = hipcc()
     os.makedirs(BUILD_DIR, exist_ok=True)
     flags = compile_flags()
@@ -52,17 +77,26 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
             print(r.stderr)
         return obj
 
+    def run(cmd, what):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"{what} failed:\n{r.stdout}\n{r.stderr}")
+
     # a failed build must not leave an older library looking current
-    if os.path.exists(LIB_PATH):
-        os.remove(LIB_PATH)
-    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES)))) as ex:
+    for path in (LIB_PATH, BINDING_PATH):
+        if os.path.exists(path):
+            os.remove(path)
+    compile_binding, link_binding = binding_commands()
+    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES) + 1))) as ex:
+        binding = ex.submit(run, compile_binding, "compiling the binding")
         objs = list(ex.map(one, SOURCES))
+        binding.result()
     tmp = LIB_PATH + ".tmp"
     cmd = [cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
+    run(cmd, "link")
     os.replace(tmp, LIB_PATH)
+    run(link_binding, "linking the binding")
+    os.replace(BINDING_PATH + ".tmp", BINDING_PATH)
     return LIB_PATH
 
 

@@ -2,8 +2,10 @@
 
 Argument marshalling only: every step of the operator runs in the HIP
 kernels of ``libpsflib.so``.  PyTorch supplies device memory (tensors) and
-the current HIP stream.  If the shared library is missing this module raises
-at import time; there is no fallback implementation.
+the current HIP stream.  The products of :class:`Library` go through the native
+module ``_psfop`` (``csrc/binding.cpp``), everything else through ctypes.  If
+either shared library is missing this module raises at import time; there is
+no fallback implementation.
 
 Low-level functions keep the C names without the ``psflib_`` prefix
 (``build``, ``apply``, ``apply_adjoint``, ``apply_batched``, ...) and take
@@ -96,6 +98,10 @@ def _load():
 
 
 _lib = _load()
+
+from . import _psfop  # noqa: E402  (after libpsflib.so and torch are loaded)
+
+_psfop.set_error(PsflibError)
 
 #: every symbol the header declares
 SYMBOLS = (
@@ -363,54 +369,20 @@ class Library:
 
     def _stream(self, stream):
         if stream is None:
-            return self.torch.cuda.current_stream(self.device).cuda_stream
+            return _psfop.current_stream(self.device)
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
-    def _vec(self, x, size, name):
-        t = self.torch
-        if not (isinstance(x, t.Tensor) and x.dtype == t.float32 and x.device == self.device
-                and x.numel() == size):
-            raise ValueError(f"{name} must be a float32 tensor on {self.device} with {size} elements")
-        return x.contiguous()
-
-    def _out(self, out, shape, name):
-        """A new output tensor, or the caller's `out` after checking that the
-        kernels can write all of it and nothing past it."""
-        t = self.torch
-        if out is None:
-            return t.empty(shape, dtype=t.float32, device=self.device)
-        numel = 1
-        for s in shape:
-            numel *= int(s)
-        if not (isinstance(out, t.Tensor) and out.dtype == t.float32 and out.device == self.device
-                and out.is_contiguous() and out.numel() == numel):
-            raise ValueError(f"{name} must be a contiguous float32 tensor on {self.device} with "
-                             f"{numel} elements")
-        return out
-
+    # The products: the input is a float32 tensor on the library's device of the
+    # right size (made contiguous), `out` None or a contiguous float32 tensor of
+    # exactly the output's size there; anything else is a ValueError.
     def apply(self, scene, out=None, stream=None):
-        Z = self._vec(scene, self.ncols, "scene")
-        out = self._out(out, (self.M,), "out")
-        apply(self.h, Z.data_ptr(), out.data_ptr(), self._stream(stream))
-        return out
+        return _psfop.apply(self, scene, out, stream)
 
     def apply_adjoint(self, g, out=None, stream=None):
-        G = self._vec(g, self.M, "g")
-        out = self._out(out, (self.ncols,), "out")
-        apply_adjoint(self.h, G.data_ptr(), out.data_ptr(), self._stream(stream))
-        return out
+        return _psfop.apply_adjoint(self, g, out, stream)
 
     def apply_batched(self, scenes, out=None, stream=None):
-        t = self.torch
-        if not (isinstance(scenes, t.Tensor) and scenes.dtype == t.float32
-                and scenes.device == self.device and scenes.dim() == 2
-                and scenes.shape[1] == self.ncols):
-            raise ValueError(f"scenes must be a float32 tensor [B][{self.ncols}] on {self.device}")
-        Zb = scenes.contiguous()
-        B = int(Zb.shape[0])
-        out = self._out(out, (B, self.M), "out")
-        apply_batched(self.h, Zb.data_ptr(), out.data_ptr(), B, self._stream(stream))
-        return out
+        return _psfop.apply_batched(self, scenes, out, stream)
 
     def column_sums(self, stream=None):
         out = self.torch.empty(self.ncols, dtype=self.torch.float64, device=self.device)
