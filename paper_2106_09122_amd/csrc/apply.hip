@@ -328,16 +328,17 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
 }
 
 // Shape of the product: threads along the rows, rows per thread, row blocks and
-// column chunks, about 512 workgroups in all for FP32 (two per CU) and 256 for
-// the 16-bit forms (one per CU; 128^2: 80 us against 88-94 us with 192 or 384).
+// column chunks, about 512 workgroups in all (two per CU), 256 for 16-bit ones
+// of 2048 rows (one per CU; 128^2: 80 us against 88-94 us with 192 or 384; those
+// of 512 rows, 91^2 PSFs with a 239^2 scene: 145 us with 512, 180 us with 256).
 // The number can be overridden with PSFLIB_MV_WORKGROUPS for tuning sweeps.
-static int64_t mv_target_workgroups(int storage) {
+static int64_t mv_target_workgroups(int rt, int r) {
   static const long env = [] {
     const char* e = getenv("PSFLIB_MV_WORKGROUPS");
     return e ? strtol(e, nullptr, 10) : 0L;
   }();
   if (env > 0) return env;
-  return storage == PSFLIB_FP32 ? kMvTargetWorkgroups32 : kMvTargetWorkgroups16;
+  return rt * r == 2048 ? kMvTargetWorkgroups16 : kMvTargetWorkgroups32;
 }
 
 struct MvShape {
@@ -373,16 +374,16 @@ static MvShape mv_shape(int storage, int64_t M, int64_t ncols, int64_t ncols_pad
     sh.rt = M >= 8192 ? 256 : padded(512) * 32 <= M * 33 ? 128 : 64;
   } else {
     // 2048 rows where they leave few threads past the end, else 512, and fewer
-    // rows per thread for small images (101^2, bf16, 2048: 39 us, 512: 43 us; 96^2
-    // 37 and 33 us)
+    // rows per thread for small images (bf16: 101^2, 2048: 39 us, 512: 43 us; 96^2
+    // 37 and 31 us)
     sh.r = 8;
-    sh.rt = M >= 8192 && padded(2048) * 24 <= M * 25 ? 256 : 64;
+    sh.rt = M >= 8192 && padded(2048) * 11 <= M * 12 ? 256 : 64;
     if (sh.rt == 64)
       while (sh.r > 2 && padded(sh.r * 64) * 8 > M * 9 && padded(sh.r * 32) < padded(sh.r * 64)) sh.r /= 2;
   }
   const int64_t rows = (int64_t)sh.r * sh.rt;
   sh.rowblocks = (M + rows - 1) / rows;
-  int64_t want = (mv_target_workgroups(storage) + sh.rowblocks - 1) / sh.rowblocks;
+  int64_t want = (mv_target_workgroups(sh.rt, sh.r) + sh.rowblocks - 1) / sh.rowblocks;
   if (want < 1) want = 1;
   int64_t chunk = (units + want - 1) / want;
   chunk = (chunk + 15) / 16 * 16;

@@ -29,8 +29,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Launch-shape constants shared between the host code and the kernels.
 constexpr int kBuildThreads = 256;   // build kernel: one workgroup per group of 8 columns
 constexpr int kMvThreads = 256;      // FP32 matvec threads per workgroup
-constexpr int kMvTargetWorkgroups32 = 512;  // split-K FP32 matvec: workgroups per launch (about)
-constexpr int kMvTargetWorkgroups16 = 256;  // split-K 16-bit matvec: workgroups per launch (about)
+constexpr int kMvTargetWorkgroups32 = 512;  // split-K matvec: workgroups per launch (about)
+constexpr int kMvTargetWorkgroups16 = 256;  // the same for 16-bit workgroups of 2048 rows
 constexpr int kMv16Threads = 256;    // 16-bit matvec threads per workgroup
 constexpr int kMv16MaxChunkGroups = 512;  // 16-bit matvec: 8-column groups per chunk, at most
 constexpr int64_t kStageMaxCols = 32768;  // batched 16-bit: scenes staged whole in LDS up to this many columns
