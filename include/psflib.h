@@ -95,13 +95,12 @@ typedef enum { PSFLIB_OOB_CLAMP = 0, PSFLIB_OOB_ZERO = 1 } psflib_oob;
  *             at ((s/8)*n*n + i)*8 + s%8, so one 16-byte load holds row i of
  *             8 slots (the operand shape of the matrix cores).  Slot s holds
  *             column perm[s]; the build picks the order so that one workgroup
- *             can write whole 16-byte groups: for N a multiple of 8 (either
- *             rotation, with or without the flux rescale) slots 32b + 8k + u
- *             hold the k-th quarter turn about the star of the u-th of the
- *             b-th eight base columns (one quadrant, sorted by radial
- *             bracket); for other N, bilinear columns without the rescale
- *             whose PSF pair fits the LDS (n <= 141) are sorted by bracket;
- *             otherwise the natural order (slot j = column j).  The slot
+ *             can write whole 16-byte groups: slot 32b + 8k + u holds the
+ *             k-th quarter turn about the star of the u-th of the b-th eight
+ *             base columns (one quadrant, and the centre of an odd scene,
+ *             sorted by radial bracket), the slots left over no column; images
+ *             above 8192 x 8192 or more than 8192 PSFs keep the natural order
+ *             (slot j = column j).  The slot
  *             order is part of the library buffer (see psflib_library_bytes);
  *             psflib_get_columns reads columns by index whatever the order.
  *             Products accumulate in float32. */

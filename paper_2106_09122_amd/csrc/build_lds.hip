@@ -24,13 +24,10 @@
 //    quarter turn of 8 base columns).  The pair is staged whole when it fits
 //    the LDS; larger pairs (up to 8192 x 8192) are read through a small box per
 //    32 x 32 pixel tile, staged by each wave in its own LDS region;
-//  * columns in bracket order (16-bit forms whose scene size is not a multiple
-//    of 8, pairs that fit the LDS): one wave per column, 16 columns per
-//    workgroup, units assembled from an LDS tile.
-// The 16-bit forms of the other builds (and of columns that need float32
-// post-processing, the flux-preserving rescale) are built as float32 columns
-// into scratch and packed by a second kernel (scale by 2^-e_j, round to
-// nearest even, 8 columns per 16 B).
+//  * columns in bracket order (sort bounds of the orbits exceeded, pairs that fit
+//    the LDS): one wave per column.  The 16-bit forms of these are built as
+//    float32 columns into scratch and packed by a second kernel (scale by
+//    2^-e_j, round to nearest even, 8 columns per 16 B).
 #include <math.h>
 
 #include <type_traits>
@@ -281,33 +278,8 @@ __global__ __launch_bounds__(1024) void build_lds_kernel(const float* __restrict
   if (lane == 0) tau[j] = tsum;
 }
 
-// ------------------------------------------- 16-bit build, slot order -----
-// The 16-bit forms store columns in groups of 8 slots.  So that one workgroup
-// can write whole 16-byte groups straight from LDS-staged PSFs, the slots
-// are ordered by radial bracket: a stable counting sort (bracket, then column
-// index) gives slot s -> column perm[s], and the buckets are cut into work
-// items along 16-slot windows.  A workgroup builds the (up to 16) columns of
-// one item from its bracket's pair, one wave per column, a few image rows at
-// a time: each wave rounds its values to the 16-bit format into an LDS tile,
-// and after a barrier every thread gathers the 8 slots of one (group, pixel)
-// and writes them as one 16-byte store (2-byte stores for the slots of a
-// group that belong to the neighbouring bucket's item).  The float32 values,
-// their rounding and the column sums are those of the float32 build.
-
+// ------------------------------------------------------- stable sort -----
 constexpr int kSortBlock = 1024;  // columns per block of the stable sort
-
-// counts of every bucket in every block of kSortBlock columns: cnt[blk][b]
-__global__ __launch_bounds__(kSortBlock) void sort_count_kernel(const ColGeom* __restrict__ geo,
-                                                                int64_t ncols, int nb,
-                                                                int32_t* __restrict__ cnt) {
-  extern __shared__ int32_t hist[];  // nb
-  for (int b = threadIdx.x; b < nb; b += kSortBlock) hist[b] = 0;
-  __syncthreads();
-  const int64_t j = (int64_t)blockIdx.x * kSortBlock + threadIdx.x;
-  if (j < ncols) atomicAdd(hist + bucket_of(geo, j, nb), 1);  // counts: order-free
-  __syncthreads();
-  for (int b = threadIdx.x; b < nb; b += kSortBlock) cnt[(int64_t)blockIdx.x * nb + b] = hist[b];
-}
 
 // One workgroup.  cnt[blk][b] becomes the first slot of bucket b's columns of
 // block blk (bucket start + the bucket's columns in earlier blocks); items
@@ -378,191 +350,6 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(int32_t* __restrict__ c
   if (tid == 1023) *nitems = s_items[1023];
 }
 
-// Slots: a column's slot is its block's first slot of the bucket plus its
-// rank among the block's earlier columns of the same bucket.  Each wave ranks
-// its 64 columns with one ballot per bucket present; then the waves take
-// their slots in order, each adding its counts to a per-bucket cursor in LDS
-// that starts at the block's first slots.  Also the slot's exponent.
-__global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(const ColGeom* __restrict__ geo,
-                                                                  int64_t ncols, int nb,
-                                                                  const int32_t* __restrict__ first,
-                                                                  int32_t* __restrict__ perm,
-                                                                  int32_t* __restrict__ slot_of,
-                                                                  int32_t* __restrict__ eslot) {
-  extern __shared__ int32_t cursor[];  // nb
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int q = tid; q < nb; q += kSortBlock) cursor[q] = first[(int64_t)blockIdx.x * nb + q];
-  const int64_t j = (int64_t)blockIdx.x * kSortBlock + tid;
-  const bool valid = j < ncols;
-  const int b = valid ? bucket_of(geo, j, nb) : -1;
-  uint64_t todo = __ballot(valid);
-  int rank = 0, count = 0;
-  while (todo) {  // uniform: one pass per bucket present in the wave
-    const int bl = __shfl(b, __builtin_ctzll(todo), 64);
-    const uint64_t m = __ballot(valid && b == bl);
-    if (valid && b == bl) {
-      rank = __popcll(m & ((1ull << lane) - 1ull));
-      count = __popcll(m);
-    }
-    todo &= ~m;
-  }
-  __syncthreads();
-  int slot = 0;
-  for (int w = 0; w < kSortBlock / 64; ++w) {
-    if (wave == w && valid) {
-      slot = cursor[b] + rank;  // every lane reads before the wave's leaders add
-      __builtin_amdgcn_wave_barrier();
-      if (rank == 0) cursor[b] += count;
-    }
-    __syncthreads();
-  }
-  if (!valid) return;
-  perm[slot] = (int32_t)j;
-  slot_of[j] = slot;
-  eslot[slot] = geo[j].e;
-}
-
-template <int E, bool FULL, bool BF16>
-__global__ __launch_bounds__(1024) void build_lds16_kernel(const float* __restrict__ cube, int K,
-                                                           const ColGeom* __restrict__ geo,
-                                                           const int32_t* __restrict__ perm,
-                                                           const int4* __restrict__ items,
-                                                           const int32_t* __restrict__ nitems,
-                                                           int nb, int n, int ls, int R, int64_t M,
-                                                           uint16_t* __restrict__ Mh,
-                                                           double* __restrict__ tau) {
-  extern __shared__ float2 P2[];  // bordered pair, (n+2) rows of stride ls; then the 16-bit tile
-  if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
-  const int4 it = items[blockIdx.x];
-  const int bkt = it.x, first = it.y, len = it.z, w0 = it.w;
-  const bool zero_bucket = bkt == nb - 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int np = n + 2;
-  uint16_t* T = reinterpret_cast<uint16_t*>(P2 + (size_t)np * ls);  // [16][R * n]
-  const int tstride = R * n;
-  if (!zero_bucket) {
-    const float* Pk = cube + (int64_t)bkt * M;
-    const float* Pk1 = (K > 1) ? Pk + M : nullptr;
-    for (int idx = tid; idx < 4 * np; idx += 1024) {
-      const int side = idx / np, t = idx % np;
-      const int pos = side == 0 ? t : side == 1 ? (np - 1) * ls + t
-                    : side == 2 ? t * ls : t * ls + np - 1;
-      P2[pos] = make_float2(0.0f, 0.0f);
-    }
-    if ((n & 3) == 0 && (reinterpret_cast<uintptr_t>(cube) & 15) == 0) {
-      const int nq = n >> 2;
-      for (int q = tid; q < n * nq; q += 1024) {
-        const int rr = q / nq, cc = 4 * (q - rr * nq);
-        const f32x4 a = *reinterpret_cast<const f32x4*>(Pk + rr * n + cc);
-        const f32x4 b = Pk1 ? *reinterpret_cast<const f32x4*>(Pk1 + rr * n + cc)
-                            : (f32x4){0.f, 0.f, 0.f, 0.f};
-        float2* dst = P2 + (rr + 1) * ls + cc + 1;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) dst[e] = make_float2(a[e], b[e]);
-      }
-    } else {
-      for (int q = tid; q < n * n; q += 1024) {
-        const int rr = q / n, cc = q - rr * n;
-        P2[(rr + 1) * ls + cc + 1] = make_float2(Pk[q], Pk1 ? Pk1[q] : 0.0f);
-      }
-    }
-  }
-  const int slot = w0 + wave;
-  const bool live = slot >= first && slot < first + len;  // uniform per wave
-  int64_t j = 0;
-  ColGeom g;
-  g.ct = 1.0; g.st = 0.0; g.w = 0.0; g.e = 0;
-  if (live) {
-    j = perm[slot];
-    g = geo[j];
-  }
-  const double c = (double)(n - 1) * 0.5;
-  const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
-  double ctux[E], mstux[E];
-#pragma unroll
-  for (int v = 0; v < E; ++v) {
-#pragma clang fp contract(off)
-    const double ux = (double)(lane + 64 * v) - c;
-    ctux[v] = g.ct * ux;
-    mstux[v] = (-g.st) * ux;
-  }
-  double tsum = 0.0;
-  // the slots of this item among the item's two groups
-  const int64_t grp0 = w0 / 8;
-  for (int a0 = 0; a0 < n; a0 += R) {
-    const int rows = (n - a0 < R) ? n - a0 : R;
-    __syncthreads();  // the pair is staged; the previous tile has been stored
-    if (live) {
-      for (int r = 0; r < rows; ++r) {
-        const int a = a0 + r;
-        double stuy, ctuy;
-        {
-#pragma clang fp contract(off)
-          const double uy = (double)a - c;
-          stuy = g.st * uy;
-          ctuy = g.ct * uy;
-        }
-#pragma unroll
-        for (int v = 0; v < E; ++v) {
-          const int b = lane + 64 * v;
-          if (FULL || b < n) {
-            float val = 0.0f;
-            if (!zero_bucket) {
-              const Tap t = tap_coords(ctux[v], mstux[v], stuy, ctuy, c, n, ls);
-              const float2 p00 = P2[t.idx], p01 = P2[t.idx + 1];
-              const float2 p10 = P2[t.idx + ls], p11 = P2[t.idx + ls + 1];
-              const float q00 = fmaf(wk1, p00.y, wk0 * p00.x);
-              const float q01 = fmaf(wk1, p01.y, wk0 * p01.x);
-              const float q10 = fmaf(wk1, p10.y, wk0 * p10.x);
-              const float q11 = fmaf(wk1, p11.y, wk0 * p11.x);
-              val = (t.gy * t.gx) * q00;
-              val = fmaf(t.gy * t.fx, q01, val);
-              val = fmaf(t.fy * t.gx, q10, val);
-              val = fmaf(t.fy * t.fx, q11, val);
-              val = t.ok ? val : 0.0f;
-            }
-            tsum += (double)val;
-            const float x = ldexpf(val, -g.e);  // exact power-of-two scaling
-            uint32_t h;
-            if constexpr (BF16) {
-              uint32_t u = __float_as_uint(x);
-              u += 0x7FFFu + ((u >> 16) & 1u);  // finite: round to nearest, ties to even
-              h = u >> 16;
-            } else {
-              h = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)x);
-            }
-            T[wave * tstride + r * n + b] = (uint16_t)h;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // (group gi, pixel p of the tile): the 8 slots of the group at that pixel
-    const int units = 2 * rows * n;
-    for (int u = tid; u < units; u += 1024) {
-      const int gi = u / (rows * n), p = u - gi * (rows * n);
-      const int s0 = 8 * gi;  // first slot of the group, relative to w0
-      const int lo = (first - w0 > s0) ? first - w0 : s0;
-      const int hi = (first + len - w0 < s0 + 8) ? first + len - w0 : s0 + 8;
-      if (lo >= hi) continue;  // no slot of this group in the item
-      const int64_t i = (int64_t)a0 * n + p;
-      uint16_t* dst = Mh + ((grp0 + gi) * M + i) * 8;
-      if (lo == s0 && hi == s0 + 8) {
-        uint32_t w[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          w[q] = (uint32_t)T[(s0 + 2 * q) * tstride + p] | ((uint32_t)T[(s0 + 2 * q + 1) * tstride + p] << 16);
-        __builtin_nontemporal_store((u32x4){w[0], w[1], w[2], w[3]}, reinterpret_cast<u32x4*>(dst));
-      } else {
-        for (int q = lo; q < hi; ++q) dst[q - s0] = T[q * tstride + p];
-      }
-    }
-  }
-  if (!live) return;
-  tsum = wave_sum_f64(tsum);
-  if (lane == 0) tau[j] = tsum;
-}
-
 // 16-bit packing: M16[g][i][u] = RN16(A32[8g+u][i] * 2^-e), zeros past ncols.
 // Two rows per thread: 8 x 8-byte loads (one per column; 512 B per wave and
 // column) and 32 contiguous bytes stored.
@@ -622,15 +409,21 @@ __global__ __launch_bounds__(256) void pack16_kernel(const float* __restrict__ A
   }
 }
 
-// Zero mantissas of the padding slots [ncols, ncols_pad): thread = (group, row).
+// Zero mantissas of the slots without a column that the 16-bit orbit builds
+// leave: the `tail` whole groups from g0 (blockIdx.y below tail), then, for an
+// odd scene, members 1 to 3 of the centre column j.
 __global__ __launch_bounds__(256) void zero_pad16_kernel(uint16_t* __restrict__ Mh, int64_t M,
-                                                         int64_t ncols, int64_t g0) {
+                                                         int64_t g0, int tail,
+                                                         const int32_t* __restrict__ slot_of,
+                                                         int64_t j) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= M) return;
-  const int64_t grp = g0 + blockIdx.y;
-  uint16_t* dst = Mh + (grp * M + i) * 8;
-  for (int q = 0; q < 8; ++q)
-    if (grp * 8 + q >= ncols) dst[q] = 0;
+  if ((int)blockIdx.y < tail) {
+    *reinterpret_cast<u32x4*>(Mh + ((g0 + blockIdx.y) * M + i) * 8) = (u32x4){0u, 0u, 0u, 0u};
+  } else {
+    const int64_t slot = slot_of[j] + 8 * (int64_t)(blockIdx.y - tail + 1);
+    Mh[(slot / 8 * M + i) * 8 + slot % 8] = 0;
+  }
 }
 
 // --------------------------------------------- rotation-orbit builds -----
@@ -715,17 +508,24 @@ __global__ __launch_bounds__(kSortBlock) void orbit_count_kernel(const ColGeom* 
   for (int b = threadIdx.x; b < nb; b += kSortBlock) cnt[(int64_t)blockIdx.x * nb + b] = hist[b];
 }
 
-// Stable placement of the base columns (as sort_scatter_kernel); with
-// `perm` set (16-bit forms, N a multiple of 8, no centre) also the slots of
-// every orbit member: base position s in block s/8 of 8 bases, member k in
-// group 4 (s/8) + k, slot 32 (s/8) + 8 k + s%8.
+// Stable placement of the base columns: a base's position is its block's first
+// position of the bracket plus its rank among the block's earlier bases of the
+// same bracket.  Each wave ranks its 64 bases with one ballot per bracket
+// present; then the waves take their positions in order, each adding its counts
+// to a per-bracket cursor in LDS that starts at the block's first positions.
+// With `perm` set (16-bit forms) also the slots of every orbit member: base
+// position s in block s/8 of 8 bases, member k in group 4 (s/8) + k, slot 32
+// (s/8) + 8 k + s%8.  Slots without a column (members 1 to 3 of the centre of an
+// odd scene, bases that fill up the last block, the slots up to ncols_pad) are
+// padding: perm -1.
 __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom* __restrict__ geo,
                                                                    OrbitGrid o, int nb,
                                                                    const int32_t* __restrict__ first,
                                                                    int32_t* __restrict__ reps,
                                                                    int32_t* __restrict__ perm,
                                                                    int32_t* __restrict__ slot_of,
-                                                                   int32_t* __restrict__ eslot) {
+                                                                   int32_t* __restrict__ eslot,
+                                                                   int64_t ncols_pad) {
   extern __shared__ int32_t cursor[];  // nb
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int q = tid; q < nb; q += kSortBlock) cursor[q] = first[(int64_t)blockIdx.x * nb + q];
@@ -754,18 +554,27 @@ __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom
     }
     __syncthreads();
   }
-  if (!valid) return;
-  reps[pos] = (int32_t)j0;
-  if (perm) {
-    const int32_t e = geo[j0].e;  // the members share the radius, hence the exponent
+  if (valid) reps[pos] = (int32_t)j0;
+  if (!perm) return;
+  const int64_t whole = (o.nreps + 7) / 8 * 8;  // bases, with those that fill up the last block
+  if (!valid) pos = (int)t;
+  if (t < whole) {
+    const int32_t e = valid ? geo[j0].e : kZeroColumnExp;  // the members share the radius
+    const bool centre = valid && orbit_is_centre(j0, o.N);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      const int64_t j = orbit_member(j0, o.N, k);
       const int32_t slot = (pos / 8) * 32 + 8 * k + pos % 8;
+      const bool column = valid && (k == 0 || !centre);
+      const int64_t j = column ? orbit_member(j0, o.N, k) : -1;
       perm[slot] = (int32_t)j;
-      slot_of[j] = slot;
+      if (column) slot_of[j] = slot;
       eslot[slot] = e;
     }
+  }
+  const int64_t tail = 4 * whole + t;  // fewer than 64 slots
+  if (tail < ncols_pad) {
+    perm[tail] = -1;
+    eslot[tail] = kZeroColumnExp;
   }
 }
 
@@ -1242,8 +1051,21 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
   }
 }
 
-// 16-bit orbit build (N a multiple of 8: no centre, whole blocks of 8 bases).
-// A window of 16 bases is two blocks; block h's member k is group
+// 16-bit store of one unit.  Non-temporal where image rows start on 64 bytes
+// (sides that are multiples of 4: 128^2 PSFs, 128^2 scene, 274 us a build against
+// 280 with plain stores; 180^2, 90^2 scene, 350 against 365).  On other sides
+// every row ends inside a 128-byte line whose rest a neighbouring tile writes
+// later: plain stores let the two meet in the L2 (101^2, 128^2 scene: 236 us
+// against 272; 181^2, 90^2 scene: 383 against 424).
+template <bool LINES>
+__device__ __forceinline__ void store_unit(uint16_t* p, const u32x4 w) {
+  if constexpr (LINES)
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+  else
+    *reinterpret_cast<u32x4*>(p) = w;
+}
+
+// 16-bit orbit build.  A window of 16 bases is two blocks; block h's member k is group
 // 4 (w0/8 + h) + k, whose unit at an image pixel holds the 8 bases' member
 // values there.  The item's rows are walked in tiles of 8 x 32 pixels: every
 // wave forms its base column's tile (lane (i, k): row i, columns 4k..4k+3),
@@ -1256,8 +1078,9 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
 // double-buffered, so that one barrier per tile suffices: a tile's buffer is
 // written again two tiles later, after every thread has passed the barrier
 // behind the copy that read it.  Slots of a block outside the item (the block
-// straddles two brackets) are left to the other item: 2-byte stores.
-template <bool BF16, bool SCALED>
+// straddles two brackets) are left to the other item: 2-byte stores.  Positions
+// past the last base, up to a whole block, are written as zeros with it.
+template <bool BF16, bool SCALED, bool LINES>
 __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __restrict__ cube, int K,
                                                              const ColGeom* __restrict__ geo,
                                                              const int32_t* __restrict__ reps,
@@ -1280,12 +1103,16 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
   uint16_t* tiles = reinterpret_cast<uint16_t*>(P2 + ((((size_t)(n + 2) * ls) + 1) & ~(size_t)1));
   if (!zero_bucket) stage_pair(P2, cube, bkt, K, n, ls, M, tid);
   const int sp = w0 + wave;
-  const bool live = sp >= first && sp < first + len;  // uniform per wave
+  // the item's positions, the last one with those that fill up its block
+  const int end = first + len == nreps ? (first + len + 7) / 8 * 8 : first + len;
+  const bool live = sp >= first && sp < end;  // uniform per wave
+  const bool base = live && sp < nreps;
+  const bool blank = zero_bucket || !base;
   const int h = wave >> 3, u = wave & 7;
   ColGeom g;
   g.ct = 1.0; g.st = 0.0; g.w = 0.0; g.e = 0;
-  if (live) g = geo[reps[sp]];
-  const float sf = (SCALED && live) ? colscale[reps[sp]] : 1.0f;  // flux-preserving scale
+  if (base) g = geo[reps[sp]];
+  const float sf = (SCALED && base) ? colscale[reps[sp]] : 1.0f;  // flux-preserving scale
   const double c = (double)(n - 1) * 0.5;
   const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
   const int64_t G0 = (int64_t)(w0 / 8) * 4;
@@ -1294,7 +1121,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
   for (int q = 0; q < 2; ++q) {
     const int s0 = w0 + 8 * q;
     lo[q] = (first > s0) ? first - s0 : 0;
-    hi[q] = (first + len < s0 + 8) ? first + len - s0 : 8;
+    hi[q] = (end < s0 + 8) ? end - s0 : 8;
   }
   const int li = lane >> 3, lk = lane & 7;
   // copy roles: threads 0..511 along rows, 512..1023 along columns
@@ -1326,8 +1153,8 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
               ctux = g.ct * ux;
               mstux = (-g.st) * ux;
             }
-            float val = zero_bucket ? 0.0f
-                                    : orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
+            float val = blank ? 0.0f
+                              : orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
             if constexpr (SCALED) val *= sf;
             tsum += (double)val;
             const float xs = ldexpf(val, -g.e);  // exact power-of-two scaling
@@ -1368,8 +1195,8 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
           }
           if (lo[cq] == 0 && hi[cq] == 8) {
             const u32x4 w = *reinterpret_cast<const u32x4*>(src);
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dA));
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dB));
+            store_unit<LINES>(dA, w);
+            store_unit<LINES>(dB, w);
           } else {
             for (int s = lo[cq]; s < hi[cq]; ++s) {
               dA[s] = src[s];
@@ -1380,7 +1207,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
       }
     }
   }
-  if (!live) return;
+  if (!base) return;
   tsum = wave_sum_f64(tsum);
   if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
 }
@@ -1507,20 +1334,20 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
   }
 }
 
-// 16-bit orbit build for pairs larger than the LDS (n > 141, N a multiple of
-// 8), bilinear or cubic-spline: build_orbit16_kernel's unit tiles and copies,
+// 16-bit orbit build for pairs that do not fit the LDS beside the unit tiles
+// (n > 133), bilinear or cubic-spline: build_orbit16_kernel's unit tiles and copies,
 // with each wave's taps read from a staged box (as build_orbit_box_kernel and
 // build_cubic_orbit_kernel) of the 32 x 32 pixels it forms as 32 / TA tiles of
 // TA x 32.  LDS: 16 box regions, then the two unit tiles; the cubic boxes are
 // larger (48 x 49 floats), so the cubic form takes 4-row tiles (each lane two
-// pixels of a tile row) where the bilinear form takes 8-row ones (four).
-template <bool BF16, bool CUBIC, bool SCALED>
+// pixels of a tile row) where the bilinear form takes 8-row ones (four).  Every
+// wave reads its own bracket's pair, so a workgroup takes a whole window of 16
+// bases whatever their brackets, and every store is a whole unit.
+template <bool BF16, bool CUBIC, bool SCALED, bool LINES>
 __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __restrict__ src0, int K,
                                                                  const ColGeom* __restrict__ geo,
                                                                  const int32_t* __restrict__ reps,
-                                                                 const int4* __restrict__ items,
-                                                                 const int32_t* __restrict__ nitems,
-                                                                 int nb, int n, int64_t M, int Np,
+                                                                 int n, int64_t M, int Np,
                                                                  int rpr, int64_t nreps,
                                                                  uint16_t* __restrict__ Mh,
                                                                  double* __restrict__ part,
@@ -1531,36 +1358,28 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
   constexpr int TILE = 2 * TA * TP * 8;    // uint16 per buffer
   constexpr int REGION = CUBIC ? kCbRegion : kFpRegion;
   extern __shared__ float QS[];
-  if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
-  const int4 it = items[blockIdx.x];
-  const int bkt = it.x, first = it.y, len = it.z, w0 = it.w;
-  const bool zero_bucket = bkt == nb - 1;
+  const int64_t w0 = (int64_t)blockIdx.x * 16;  // the window's first base position
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
   uint16_t* tiles = reinterpret_cast<uint16_t*>(QS + 16 * REGION);
   float* Q = QS + wave * REGION;
-  const int sp = w0 + wave;
-  const bool live = sp >= first && sp < first + len;  // uniform per wave
+  const int64_t sp = w0 + wave;
+  const int64_t whole = (nreps + 7) / 8 * 8;  // with the positions that fill up the last block
+  const bool live = sp < whole;  // uniform per wave
   const int h = wave >> 3, u = wave & 7;
   ColGeom g;
-  g.ct = 1.0; g.st = 0.0; g.w = 0.0; g.e = 0;
-  if (live) g = geo[reps[sp]];
-  const float sf = (SCALED && live) ? colscale[reps[sp]] : 1.0f;  // flux-preserving scale
+  g.ct = 1.0; g.st = 0.0; g.w = 0.0; g.e = 0; g.k = -1;
+  if (sp < nreps) g = geo[reps[sp]];
+  const bool blank = g.k < 0;  // an identically zero orbit, or no base
+  const float sf = (SCALED && sp < nreps) ? colscale[reps[sp]] : 1.0f;  // flux-preserving scale
   const double c = (double)(n - 1) * 0.5;
   const double pad = (double)kSplinePad;
   const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
-  const int pb = zero_bucket ? 0 : bkt;
+  const int pb = blank ? 0 : g.k;
   const float* Pk = CUBIC ? src0 : src0 + (int64_t)pb * M;  // bilinear: the sample pair
   const float* Pk1 = (!CUBIC && K > 1) ? Pk + M : nullptr;
   const float2* Pc = reinterpret_cast<const float2*>(src0) + (CUBIC ? (int64_t)pb * Np * Np : 0);  // cubic
-  const int64_t G0 = (int64_t)(w0 / 8) * 4;
-  int lo[2], hi[2];  // the item's slots of each block, relative to the block
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int s0 = w0 + 8 * q;
-    lo[q] = (first > s0) ? first - s0 : 0;
-    hi[q] = (first + len < s0 + 8) ? first + len - s0 : 8;
-  }
+  const int64_t G0 = w0 / 8 * 4;
   const int li = lane / LPR, lk = lane % LPR;
   // copy roles: threads 0..511 along rows, 512..1023 along columns; unit cu of
   // a direction is block cu / (TA TB), row and column from cu % (TA TB)
@@ -1573,7 +1392,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
     for (int b0 = 0; b0 < n; b0 += TB) {
       const int be = (b0 + TB < n) ? b0 + TB : n;
       int bs = 1, base = 0, Rlo = 0, Clo = 0;
-      if (live && !zero_bucket) {  // uniform per wave: stage the box of rows [a0, ae), columns [b0, be)
+      if (!blank) {  // uniform per wave: stage the box of rows [a0, ae), columns [b0, be)
         int rmin, rmax, cmin, cmax;
         {
           int r0, c0;
@@ -1633,7 +1452,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
                 mstux = (-g.st) * ux;
               }
               float val = 0.0f;
-              if (!zero_bucket) {
+              if (!blank) {
                 if constexpr (CUBIC) {
 #pragma clang fp contract(off)
                   const double rowf = c + (mstux + ctuy) + pad;
@@ -1674,7 +1493,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
         }
         __syncthreads();
         // one unit per thread: block cq, TA rows x 32 columns
-        if (cq < 2 && lo[cq] < hi[cq]) {
+        if (cq < 2 && w0 + 8 * cq < whole) {
           int r, cb;
           if (along_cols) {
             cb = crem / TA;
@@ -1695,22 +1514,15 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
               dA = Mh + ((G0 + 4 * cq + 0) * M + (int64_t)a * n + b) * 8;
               dB = Mh + ((G0 + 4 * cq + 2) * M + (int64_t)(n - 1 - a) * n + (n - 1 - b)) * 8;
             }
-            if (lo[cq] == 0 && hi[cq] == 8) {
-              const u32x4 w = *reinterpret_cast<const u32x4*>(src);
-              __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dA));
-              __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(dB));
-            } else {
-              for (int s = lo[cq]; s < hi[cq]; ++s) {
-                dA[s] = src[s];
-                dB[s] = src[s];
-              }
-            }
+            const u32x4 w = *reinterpret_cast<const u32x4*>(src);
+            store_unit<LINES>(dA, w);
+            store_unit<LINES>(dB, w);
           }
         }
       }
     }
   }
-  if (!live) return;
+  if (sp >= nreps) return;
   tsum = wave_sum_f64(tsum);
   if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
 }
@@ -1804,84 +1616,6 @@ hipError_t launch_pack16_range(int storage, const float* A32, int64_t col0, int6
   return hipGetLastError();
 }
 
-// rows of the 16-bit tile that fit next to the bordered pair (0: none)
-static int lds16_rows(int n) {
-  const size_t pair = (size_t)(n + 2) * lds_stride(n) * sizeof(float2);
-  for (int R = 4; R >= 1; R >>= 1)
-    if (pair + (size_t)16 * R * n * 2 <= (size_t)kLdsBuildMaxBytes) return R;
-  return 0;
-}
-
-bool build_lds16_supported(int n, int K, int64_t ncols) {
-  if (K > kLdsMaxBuckets - 1 || n > 141 || lds16_rows(n) == 0) return false;
-  const int64_t nblk = (ncols + kSortBlock - 1) / kSortBlock;
-  return nblk * nbuckets(K) <= ((int64_t)1 << 24) && ncols < ((int64_t)1 << 31);
-}
-
-size_t build_lds16_scratch_bytes(int K, int64_t ncols) {
-  const int64_t nb = nbuckets(K);
-  const int64_t nblk = (ncols + kSortBlock - 1) / kSortBlock;
-  const int64_t items_max = (ncols + 15) / 16 + 2 * nb + 1;
-  return (((size_t)nblk * nb * 4 + 255) & ~(size_t)255) + (((size_t)items_max * 16 + 16 + 255) & ~(size_t)255);
-}
-
-hipError_t launch_build_lds16(int storage, const float* cube, int K, const ColGeom* geo, int n,
-                              int64_t M, int64_t ncols, int64_t ncols_pad, const int32_t* exps,
-                              int32_t* perm, int32_t* eslot, int32_t* slot_of, void* lib,
-                              double* tau, void* scratch, hipStream_t s) {
-  const int nb = nbuckets(K);
-  const int64_t nblk = (ncols + kSortBlock - 1) / kSortBlock;
-  const int64_t items_max = (ncols + 15) / 16 + 2 * nb + 1;
-  char* p = reinterpret_cast<char*>(scratch);
-  int32_t* cnt = reinterpret_cast<int32_t*>(p);
-  p += ((size_t)nblk * nb * 4 + 255) & ~(size_t)255;
-  int4* items = reinterpret_cast<int4*>(p);
-  int32_t* nitems = reinterpret_cast<int32_t*>(items + items_max);
-  // padding slots (and defaults) first; the sort then places every column
-  hipError_t e = launch_identity_order(perm, eslot, slot_of, exps, ncols, ncols_pad, s);
-  if (e != hipSuccess) return e;
-  sort_count_kernel<<<(unsigned)nblk, kSortBlock, (size_t)nb * 4, s>>>(geo, ncols, nb, cnt);
-  sort_scan_kernel<<<1, 1024, 0, s>>>(cnt, nblk, nb, items, nitems);
-  sort_scatter_kernel<<<(unsigned)nblk, kSortBlock, (size_t)nb * 4, s>>>(geo, ncols, nb, cnt, perm,
-                                                                         slot_of, eslot);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int ls = lds_stride(n), R = lds16_rows(n);
-  const size_t lds = (size_t)(n + 2) * ls * sizeof(float2) + (size_t)16 * R * n * 2;
-  const bool full = (n % 64) == 0;
-  const bool bf = storage == PSFLIB_BF16_POW2;
-  uint16_t* Mh = reinterpret_cast<uint16_t*>(lib);
-  auto launch = [&](auto kern) -> hipError_t {
-    const void* fn = reinterpret_cast<const void*>(kern);
-    hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (err != hipSuccess) return err;
-    kern<<<(unsigned)items_max, 1024, lds, s>>>(cube, K, geo, perm, items, nitems, nb, n, ls, R, M,
-                                                Mh, tau);
-    return hipGetLastError();
-  };
-  switch (lds_e(n)) {
-    case 1:
-      e = full ? (bf ? launch(build_lds16_kernel<1, true, true>) : launch(build_lds16_kernel<1, true, false>))
-               : (bf ? launch(build_lds16_kernel<1, false, true>) : launch(build_lds16_kernel<1, false, false>));
-      break;
-    case 2:
-      e = full ? (bf ? launch(build_lds16_kernel<2, true, true>) : launch(build_lds16_kernel<2, true, false>))
-               : (bf ? launch(build_lds16_kernel<2, false, true>) : launch(build_lds16_kernel<2, false, false>));
-      break;
-    default:
-      e = bf ? launch(build_lds16_kernel<3, false, true>) : launch(build_lds16_kernel<3, false, false>);
-      break;
-  }
-  if (e != hipSuccess) return e;
-  if (ncols_pad > ncols) {
-    const int64_t g0 = ncols / 8;
-    zero_pad16_kernel<<<dim3((unsigned)((M + 255) / 256), (unsigned)(ncols_pad / 8 - g0)), 256, 0, s>>>(
-        Mh, M, ncols, g0);
-    e = hipGetLastError();
-  }
-  return e;
-}
-
 static bool build_orbit_supported(int n, int K, int N);
 static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* geo, int n, int N,
                                      int64_t M, float* A32, double* tau, void* scratch, int mode,
@@ -1973,11 +1707,11 @@ static bool orbit_sort_fits(int K, int N) {
 
 // counting sort of the base columns by bracket, and the work items
 static hipError_t orbit_sort(const ColGeom* geo, const OrbitPlan& pl, int32_t* perm,
-                             int32_t* slot_of, int32_t* eslot, hipStream_t s) {
+                             int32_t* slot_of, int32_t* eslot, int64_t ncols_pad, hipStream_t s) {
   orbit_count_kernel<<<(unsigned)pl.nblk, kSortBlock, (size_t)pl.nb * 4, s>>>(geo, pl.o, pl.nb, pl.cnt);
   sort_scan_kernel<<<1, 1024, 0, s>>>(pl.cnt, pl.nblk, pl.nb, pl.items, pl.nitems);
   orbit_scatter_kernel<<<(unsigned)pl.nblk, kSortBlock, (size_t)pl.nb * 4, s>>>(
-      geo, pl.o, pl.nb, pl.cnt, pl.reps, perm, slot_of, eslot);
+      geo, pl.o, pl.nb, pl.cnt, pl.reps, perm, slot_of, eslot, ncols_pad);
   return hipGetLastError();
 }
 
@@ -2013,7 +1747,7 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
                                      int64_t M, float* A32, double* tau, void* scratch, int mode,
                                      const float* colscale, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, s);
+  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, 0, s);
   if (e != hipSuccess) return e;
   const bool vec = (n % 32) == 0;
   if (!pair_fits_lds(n)) {  // a staged box per 32 x 32 tile
@@ -2090,7 +1824,7 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* ge
                                     int64_t M, float* A32, double* tau, void* scratch, int mode,
                                     const float* colscale, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, s);
+  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, 0, s);
   if (e != hipSuccess) return e;
   const int Np = n + 2 * kSplinePad;
   const bool vec = (n % 32) == 0;
@@ -2132,11 +1866,39 @@ static size_t orbit16_box_lds_bytes(bool cubic) {
                : (size_t)16 * kFpRegion * sizeof(float) + (size_t)2 * (2 * 8 * 33 * 16);
 }
 
+static bool orbit16_pair_fits(int n) { return orbit16_lds_bytes(n) <= (size_t)kLdsBuildMaxBytes; }
+
 // the pair in LDS with the unit tiles, or (up to kBoxMaxN) staged boxes
 bool build_orbit16_supported(int n, int K, int N) {
-  if (N % 8 != 0 || !orbit_sort_fits(K, N)) return false;
-  if (pair_fits_lds(n)) return orbit16_lds_bytes(n) <= (size_t)kLdsBuildMaxBytes;
-  return n <= kBoxMaxN && orbit16_box_lds_bytes(false) <= (size_t)kLdsBuildMaxBytes;
+  static_assert((size_t)16 * kFpRegion * sizeof(float) + (size_t)2 * (2 * 8 * 33 * 16) <= kLdsBuildMaxBytes, "");
+  return orbit_sort_fits(K, N) && (orbit16_pair_fits(n) || n <= kBoxMaxN);
+}
+
+// slots of the 16-bit storage of an N x N scene
+static int64_t padded_slots(int N) { return ((int64_t)N * N + kColPad - 1) / kColPad * kColPad; }
+
+// The slots without a column (see zero_pad16_kernel), then the column sums.
+static hipError_t orbit16_finish(const OrbitPlan& pl, int64_t M, const int32_t* slot_of, void* lib,
+                                 double* tau, hipStream_t s) {
+  const int64_t g0 = (pl.o.nreps + 7) / 8 * 4, N = pl.o.N;
+  const int tail = (int)(padded_slots(pl.o.N) / 8 - g0);  // fewer than 8
+  const int rows = tail + ((N & 1) ? 3 : 0);
+  if (rows > 0)
+    zero_pad16_kernel<<<dim3((unsigned)((M + 255) / 256), (unsigned)rows), 256, 0, s>>>(
+        reinterpret_cast<uint16_t*>(lib), M, g0, tail, slot_of, (N / 2) * N + N / 2);
+  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
+}
+
+// f(bf16, scaled, lines) as compile-time flags of the 16-bit orbit kernels
+template <typename F>
+static hipError_t orbit16_form(int storage, int n, const float* colscale, F f) {
+  auto on_lines = [&](auto bf, auto scaled) {
+    return n % 4 == 0 ? f(bf, scaled, std::true_type{}) : f(bf, scaled, std::false_type{});
+  };
+  auto on_scale = [&](auto bf) {
+    return colscale ? on_lines(bf, std::true_type{}) : on_lines(bf, std::false_type{});
+  };
+  return storage == PSFLIB_BF16_POW2 ? on_scale(std::true_type{}) : on_scale(std::false_type{});
 }
 
 // float32: the pair in LDS, or (up to kBoxMaxN) a staged box per tile
@@ -2154,27 +1916,26 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
                                 void* lib, double* tau, void* scratch, const float* colscale,
                                 hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, s);
+  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, padded_slots(N), s);
   if (e != hipSuccess) return e;
   uint16_t* Mh = reinterpret_cast<uint16_t*>(lib);
   const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
-  if (!pair_fits_lds(n)) {  // a staged box per 32 x 32 pixels
+  const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
+  if (!orbit16_pair_fits(n)) {  // a staged box per 32 x 32 pixels
     const size_t lds = orbit16_box_lds_bytes(false);
     auto launch = [&](auto kern) -> hipError_t {
       const void* fn = reinterpret_cast<const void*>(kern);
       hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (err != hipSuccess) return err;
-      kern<<<grid, 1024, lds, s>>>(cube, K, geo, pl.reps, pl.items, pl.nitems, pl.nb, n, M, 0, pl.rpr,
+      kern<<<wgrid, 1024, lds, s>>>(cube, K, geo, pl.reps, n, M, 0, pl.rpr,
                                    pl.o.nreps, Mh, pl.part, colscale);
       return hipGetLastError();
     };
-    const bool bf = storage == PSFLIB_BF16_POW2;
-    if (colscale)
-      e = bf ? launch(build_orbit16_box_kernel<true, false, true>) : launch(build_orbit16_box_kernel<false, false, true>);
-    else
-      e = bf ? launch(build_orbit16_box_kernel<true, false, false>) : launch(build_orbit16_box_kernel<false, false, false>);
+    e = orbit16_form(storage, n, colscale, [&](auto bf, auto scaled, auto lines) {
+      return launch(build_orbit16_box_kernel<bf.value, false, scaled.value, lines.value>);
+    });
     if (e != hipSuccess) return e;
-    return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
+    return orbit16_finish(pl, M, slot_of, lib, tau, s);
   }
   const int ls = lds_stride(n);
   const size_t lds = orbit16_lds_bytes(n);
@@ -2186,18 +1947,15 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
                                  pl.rpr, pl.o.nreps, Mh, pl.part, colscale);
     return hipGetLastError();
   };
-  const bool bf = storage == PSFLIB_BF16_POW2;
-  if (colscale)
-    e = bf ? launch(build_orbit16_kernel<true, true>) : launch(build_orbit16_kernel<false, true>);
-  else
-    e = bf ? launch(build_orbit16_kernel<true, false>) : launch(build_orbit16_kernel<false, false>);
+  e = orbit16_form(storage, n, colscale, [&](auto bf, auto scaled, auto lines) {
+    return launch(build_orbit16_kernel<bf.value, scaled.value, lines.value>);
+  });
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
+  return orbit16_finish(pl, M, slot_of, lib, tau, s);
 }
 
 bool build_cubic_orbit16_supported(int n, int K, int N) {
-  return N % 8 == 0 && build_cubic_orbit_supported(n, K, N) &&
-         orbit16_box_lds_bytes(true) <= (size_t)kLdsBuildMaxBytes;
+  return build_cubic_orbit_supported(n, K, N) && orbit16_box_lds_bytes(true) <= (size_t)kLdsBuildMaxBytes;
 }
 
 hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, const ColGeom* geo,
@@ -2205,27 +1963,25 @@ hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, co
                                       int32_t* slot_of, void* lib, double* tau, void* scratch,
                                       const float* colscale, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, s);
+  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, padded_slots(N), s);
   if (e != hipSuccess) return e;
   uint16_t* Mh = reinterpret_cast<uint16_t*>(lib);
-  const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
+  const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
   const size_t lds = orbit16_box_lds_bytes(true);
   const int Np = n + 2 * kSplinePad;
   auto launch = [&](auto kern) -> hipError_t {
     const void* fn = reinterpret_cast<const void*>(kern);
     hipError_t err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (err != hipSuccess) return err;
-    kern<<<grid, 1024, lds, s>>>(pairs, K, geo, pl.reps, pl.items, pl.nitems, pl.nb, n, M, Np, pl.rpr,
+    kern<<<wgrid, 1024, lds, s>>>(pairs, K, geo, pl.reps, n, M, Np, pl.rpr,
                                  pl.o.nreps, Mh, pl.part, colscale);
     return hipGetLastError();
   };
-  const bool bf = storage == PSFLIB_BF16_POW2;
-  if (colscale)
-    e = bf ? launch(build_orbit16_box_kernel<true, true, true>) : launch(build_orbit16_box_kernel<false, true, true>);
-  else
-    e = bf ? launch(build_orbit16_box_kernel<true, true, false>) : launch(build_orbit16_box_kernel<false, true, false>);
+  e = orbit16_form(storage, n, colscale, [&](auto bf, auto scaled, auto lines) {
+    return launch(build_orbit16_box_kernel<bf.value, true, scaled.value, lines.value>);
+  });
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
+  return orbit16_finish(pl, M, slot_of, lib, tau, s);
 }
 
 

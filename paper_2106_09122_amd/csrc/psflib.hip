@@ -323,36 +323,27 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
   // tile.  Bilinear: the bucketed LDS build, the pair staged whole when it
   // fits the LDS, else a box of it per tile, read by the rotation-orbit
   // builds.  The gathers from pair-interleaved copies serve what those cannot
-  // (bracket or column counts beyond the sort's bounds), and the 16-bit
-  // libraries of PSFs larger than 256 x 256 whose scene side is not a
-  // multiple of 8 (no rescale), which they write directly where the orbit
-  // builds would stage a float32 copy.  The builds write float32 columns when
-  // the flux-preserving rescale follows, or when a 16-bit library cannot be
-  // written directly; the 16-bit forms then pack those columns in a last pass.
+  // (bracket or column counts beyond the sort's bounds).
   const bool cubic = desc->rotate == PSFLIB_ROTATE_CUBIC;
   const bool flux = desc->flux == PSFLIB_FLUX_PRESERVE;
-  const bool big16 = desc->n > 256 && storage != PSFLIB_FP32 && !flux && desc->N % 8 != 0;
-  const bool lds = !big16 && (cubic ? psflib::build_cubic_orbit_supported(desc->n, K, desc->N)
-                                    : psflib::build_lds_supported(desc->n, K, desc->N));
+  const bool lds = cubic ? psflib::build_cubic_orbit_supported(desc->n, K, desc->N)
+                         : psflib::build_lds_supported(desc->n, K, desc->N);
   // Flux-preserving orbit builds take two passes (the plain build's column
   // sums, then the build with each column scaled as it is stored) instead of
   // rewriting the library.  16-bit libraries are written directly in bracket
-  // order: by quarter-turn orbits when N is a multiple of 8 (bilinear or
-  // cubic, rescaled or not), else (bilinear, not rescaled) column by column
-  // when the pair fits the LDS; the other 16-bit builds go through float32
-  // columns and a packing pass (natural order)
+  // order by quarter-turn orbits (bilinear or cubic, rescaled or not, scenes of
+  // any side); what the orbits cannot serve goes through float32 columns and a
+  // packing pass where the rescale follows or the pair fits the LDS, in natural
+  // order.
   const bool flux_orbit =
       flux && lds && (cubic || psflib::build_orbit_flux_supported(desc->n, K, desc->N));
   const bool plain16 = storage != PSFLIB_FP32 && lds && (!flux || flux_orbit);
   const bool orbit16 = plain16 && (cubic ? psflib::build_cubic_orbit16_supported(desc->n, K, desc->N)
                                          : psflib::build_orbit16_supported(desc->n, K, desc->N));
-  const bool direct16 =
-      orbit16 || (plain16 && !flux && !cubic && psflib::build_lds16_supported(desc->n, K, L.ncols));
-  const bool stage32 = storage != PSFLIB_FP32 && (lds || flux) && !direct16;
+  const bool stage32 = storage != PSFLIB_FP32 && (lds || flux) && !orbit16;
   const size_t spline_bytes = cubic ? align256(psflib::spline_scratch_bytes(K, desc->n)) : 0;
   const size_t path_bytes =
       spline_bytes + align256(orbit16 || flux_orbit ? psflib::build_orbit_scratch_bytes(K, desc->N, desc->n)
-                              : direct16 ? psflib::build_lds16_scratch_bytes(K, L.ncols)
                               : cubic && lds ? psflib::build_orbit_scratch_bytes(K, desc->N, desc->n)
                               : lds    ? psflib::build_lds_scratch_bytes(K, desc->N, desc->n)
                               : cubic  ? 0
@@ -455,13 +446,6 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
                                      reinterpret_cast<int32_t*>(lib + L.off_slot), d_lib, tau,
                                      path_tmp, nullptr, s);
     if (e != hipSuccess) return bail(e, "16-bit orbit build kernels");
-  } else if (direct16) {
-    e = psflib::launch_build_lds16(storage, d_cube, K, h->geo, desc->n, L.M, L.ncols, L.ncols_pad,
-                                   exps, reinterpret_cast<int32_t*>(lib + L.off_perm),
-                                   reinterpret_cast<int32_t*>(lib + L.off_eslot),
-                                   reinterpret_cast<int32_t*>(lib + L.off_slot), d_lib, tau,
-                                   path_tmp, s);
-    if (e != hipSuccess) return bail(e, "16-bit LDS build kernels");
   } else if (lds) {
     e = psflib::launch_build_lds(d_cube, K, h->geo, desc->n, desc->N, L.M,
                                  reinterpret_cast<float*>(bdst), tau, path_tmp, s);
@@ -484,7 +468,7 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
     e = psflib::launch_pack16(storage, A32, h->geo, L.M, L.ncols, L.ncols_pad, d_lib, s);
     if (e != hipSuccess) return bail(e, "16-bit packing kernel");
   }
-  if (storage != PSFLIB_FP32 && !direct16) {
+  if (storage != PSFLIB_FP32 && !orbit16) {
     // natural column order: slot s holds column s
     e = psflib::launch_identity_order(reinterpret_cast<int32_t*>(lib + L.off_perm),
                                       reinterpret_cast<int32_t*>(lib + L.off_eslot),

@@ -163,7 +163,7 @@ bool build_cubic_orbit_supported(int n, int K, int N);
 hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* geo, int n, int N,
                                     int64_t M, float* A32, double* tau, void* scratch, int mode,
                                     const float* colscale, hipStream_t s);
-// 16-bit cubic storage built by the same orbits (N % 8 == 0), slots as
+// 16-bit cubic storage built by the same orbits, slots as
 // launch_build_orbit16's; scratch of build_orbit_scratch_bytes(K, N, n) bytes.
 bool build_cubic_orbit16_supported(int n, int K, int N);
 hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, const ColGeom* geo,
@@ -194,26 +194,17 @@ hipError_t launch_bucket_sort(const ColGeom* geo, int64_t ncols, int K, void* sc
 // bracket order with the pair in LDS
 hipError_t launch_build_lds(const float* cube, int K, const ColGeom* geo, int n, int N, int64_t M,
                             float* A32, double* tau, void* scratch, hipStream_t s);
-// 16-bit storage built by rotation orbits (N % 8 == 0; the pair, or a box of
-// it per tile, and the unit tiles in LDS):
+// 16-bit storage built by rotation orbits (the pair, or a box of it per tile,
+// and the unit tiles in LDS):
 // slot 32 (s/8) + 8 k + s%8 holds member k of the s-th base column in
-// bracket order (perm, slot_of, eslot written here); column sums in tau.
+// bracket order, the slots left over none (perm, slot_of, eslot written here);
+// column sums in tau.
 bool build_orbit16_supported(int n, int K, int N);
 size_t build_orbit_scratch_bytes(int K, int N, int n);
 hipError_t launch_build_orbit16(int storage, const float* cube, int K, const ColGeom* geo, int n,
                                 int N, int64_t M, int32_t* perm, int32_t* eslot, int32_t* slot_of,
                                 void* lib, double* tau, void* scratch, const float* colscale,
                                 hipStream_t s);
-// 16-bit storage built directly (bilinear rotation, no column rescale, the
-// pair and a 16-bit tile in LDS): columns ordered by radial bracket (perm,
-// slot_of, eslot written here, exps per column given), mantissas written as
-// whole 8-slot groups; column sums in tau.
-bool build_lds16_supported(int n, int K, int64_t ncols);
-size_t build_lds16_scratch_bytes(int K, int64_t ncols);
-hipError_t launch_build_lds16(int storage, const float* cube, int K, const ColGeom* geo, int n,
-                              int64_t M, int64_t ncols, int64_t ncols_pad, const int32_t* exps,
-                              int32_t* perm, int32_t* eslot, int32_t* slot_of, void* lib,
-                              double* tau, void* scratch, hipStream_t s);
 // 16-bit storage from float32 columns with the exponents in geo
 hipError_t launch_pack16(int storage, const float* A32, const ColGeom* geo, int64_t M,
                          int64_t ncols, int64_t ncols_pad, void* lib, hipStream_t s);

@@ -153,3 +153,47 @@ def test_grouped_shapes(torch, storage, chunks):
     plan.close()
     for lib in libs:
         lib.close()
+
+
+# ------------------------------------------------- 16-bit orbit builds ----
+# scenes whose base columns fill, exceed or miss blocks of 8 and windows of 16,
+# an odd scene's centre column, more than one block of the sort; images with the
+# pair whole in LDS (up to 133), with staged boxes, sides not a multiple of 8
+BUILD16 = [(1, 1), (5, 2), (8, 3), (7, 6), (33, 7), (16, 8), (31, 9), (6, 10), (100, 5), (127, 11), (128, 12),
+           (133, 6), (134, 7), (136, 8), (141, 9), (142, 3), (167, 10), (9, 46), (4, 67)]
+
+
+@pytest.mark.parametrize("storage", ["bf16", "fp16"])
+@pytest.mark.parametrize("rotate,flux", [("bilinear", "none"), ("bilinear", "preserve"), ("cubic", "none"),
+                                         ("cubic", "preserve")])
+def test_build16_sides(torch, storage, rotate, flux):
+    """Columns against the float32 library's: the 16-bit rounding of a value within
+    a float32 rounding (2^-21 of the column's bound) of it.  Slots without a column
+    are zero: the products of a poisoned buffer are those of its columns."""
+    from paper_2106_09122_amd import psflib
+    t16 = torch.bfloat16 if storage == "bf16" else torch.float16
+    for n, N in BUILD16:
+        print("build16", n, N, storage, rotate, flux, flush=True)
+        cube, radii, rng = _inputs(n, N, 4, 5)
+        mode = dict(rotate=rotate, flux=flux, oob="zero")
+        d = torch.from_numpy(cube).cuda()
+        full = psflib.Library(d, radii, N, 1.0, **mode)
+        lib = psflib.Library(d, radii, N, 1.0, storage=storage, **mode)
+        _fill(lib, torch)
+        want = full.get_columns(np.arange(N * N)).double()
+        got = lib.get_columns(np.arange(N * N)).double()
+        e = lib.exponents().cpu().numpy()[:, None]
+        unit = torch.from_numpy(np.where(e < -1000, 1.0, np.ldexp(1.0, e))).cuda()
+        top = torch.from_numpy(np.where(e < -1000, 0.0, np.ldexp(1.0, e + 15))).cuda()  # at least the column's bound
+        low, high = [((want + d * 2.0 ** -21 * top) / unit).float().to(t16).double() * unit for d in (-1, 1)]
+        assert torch.all((low <= got) & (got <= high)), (n, N)
+        sums = (lib.column_sums() - full.column_sums()).abs()
+        assert torch.all(sums <= 2.0 ** -21 * n * n * top[:, 0]), (n, N)
+        z = torch.from_numpy(rng.random(N * N).astype(np.float32)).cuda()
+        err = (lib.apply(z).double() - z.double() @ got).abs()
+        assert torch.all(err <= 1e-5 * (z.double() @ got.abs())), (n, N)
+        g = torch.from_numpy(rng.random(n * n).astype(np.float32)).cuda()
+        err = (lib.apply_adjoint(g).double() - got @ g.double()).abs()
+        assert torch.all(err <= 1e-5 * (got.abs() @ g.double())), (n, N)
+        lib.close()
+        full.close()
