@@ -197,3 +197,24 @@ def test_build16_sides(torch, storage, rotate, flux):
         assert torch.all(err <= 1e-5 * (got.abs() @ g.double())), (n, N)
         lib.close()
         full.close()
+
+
+# ---------------------------------------------------- spline coefficients ----
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_spline_keeps_what_is_not_finite(torch, value):
+    """One sample that is not finite: every column that samples its PSF with a
+    weight has no finite entry under the image's centre, wherever the sample lies;
+    columns of the other PSFs are untouched (n above the filter's reach of 32)."""
+    from paper_2106_09122_amd import psflib
+    n, N = 121, 9
+    cube, radii, _ = _inputs(n, N, 5, 7)
+    clean = psflib.Library(torch.from_numpy(cube).cuda(), radii, N, 1.0, rotate="cubic")
+    cube[4, 2, 3] = value
+    lib = psflib.Library(torch.from_numpy(cube).cuda(), radii, N, 1.0, rotate="cubic")
+    far = (np.hypot(*np.meshgrid(np.arange(N) - 4.0, np.arange(N) - 4.0)) > radii[3]).ravel()
+    mid = (n // 2) * n + n // 2
+    got, want = lib.get_columns(np.arange(N * N)).cpu().numpy(), clean.get_columns(np.arange(N * N)).cpu().numpy()
+    assert not np.isfinite(got[far][:, mid]).any()
+    assert np.array_equal(got[~far], want[~far])
+    lib.close()
+    clean.close()
