@@ -281,6 +281,46 @@ __global__ __launch_bounds__(1024) void build_lds_kernel(const float* __restrict
 // ------------------------------------------------------- stable sort -----
 constexpr int kSortBlock = 1024;  // columns per block of the stable sort
 
+// Inclusive sum of v over the workgroup's threads (16 waves), fixed order.
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* tot) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t u = __shfl_up(v, off, 64);
+    if (lane >= off) v += u;
+  }
+  if (lane == 63) tot[wave] = v;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) v += tot[w];
+  __syncthreads();
+  return v;
+}
+
+// The work items of a bracket's run of c > 0 positions from `start`, one per
+// window of 16 positions, from items[first]: lane of `lanes` takes every lanes-th.
+__device__ __forceinline__ void write_items(int4* __restrict__ items, int b, int32_t start, int32_t c,
+                                            int32_t first, int lane, int lanes) {
+  for (int w = start / 16 * 16 + 16 * lane, i = lane; w < start + c; w += 16 * lanes, i += lanes) {
+    const int lo = w > start ? w : start;
+    const int hi = (w + 16 < start + c) ? w + 16 : start + c;
+    items[first + i] = make_int4(b, lo, hi - lo, w);
+  }
+}
+
+// The same for up to 1024 brackets, thread b holding bracket b's: a wave per
+// bracket (one thread each took 9 of 16 us for 10000 positions of 11 brackets).
+__device__ __forceinline__ void write_all_items(int4* __restrict__ items, int nb, int32_t start, int32_t c,
+                                                int32_t first, int32_t* s_start, int32_t* s_count,
+                                                int32_t* s_first) {
+  const int tid = threadIdx.x;
+  s_start[tid] = start;
+  s_count[tid] = c;
+  s_first[tid] = first;
+  __syncthreads();
+  for (int b = tid >> 6; b < nb; b += 16)
+    if (s_count[b] > 0) write_items(items, b, s_start[b], s_count[b], s_first[b], tid & 63, 64);
+}
+
 // One workgroup.  cnt[blk][b] becomes the first slot of bucket b's columns of
 // block blk (bucket start + the bucket's columns in earlier blocks); items
 // (bucket, first slot, length, 16-slot window start) cover every bucket along
@@ -288,8 +328,9 @@ constexpr int kSortBlock = 1024;  // columns per block of the stable sort
 __global__ __launch_bounds__(1024) void sort_scan_kernel(int32_t* __restrict__ cnt, int64_t nblk,
                                                          int nb, int4* __restrict__ items,
                                                          int32_t* __restrict__ nitems) {
-  __shared__ int32_t s_cols[1024], s_items[1024];
+  __shared__ int32_t s_cols[1024], s_items[1024], waves[16];
   __shared__ int32_t tot[kLdsMaxBuckets];
+  static_assert(kLdsMaxBuckets >= 1024, "write_all_items");
   const int tid = threadIdx.x;
   for (int b = tid; b < nb; b += 1024) {  // independent loads: no store in between
     int32_t run = 0;
@@ -301,31 +342,17 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(int32_t* __restrict__ c
   const int b0 = tid * per, b1 = (b0 + per < nb) ? b0 + per : nb;
   int my_cols = 0;
   for (int b = b0; b < b1; ++b) my_cols += tot[b];
-  s_cols[tid] = my_cols;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int c = tid >= off ? s_cols[tid - off] : 0;
-    __syncthreads();
-    s_cols[tid] += c;
-    __syncthreads();
-  }
+  const int32_t first = block_scan(my_cols, waves) - my_cols;
   // bucket starts, then the items of each bucket
-  int start = s_cols[tid] - my_cols, my_items = 0;
+  int start = first, my_items = 0;
   for (int b = b0; b < b1; ++b) {
     const int c = tot[b];
     if (c > 0) my_items += (start + c - 1) / 16 - start / 16 + 1;
     start += c;
   }
-  s_items[tid] = my_items;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int c = tid >= off ? s_items[tid - off] : 0;
-    __syncthreads();
-    s_items[tid] += c;
-    __syncthreads();
-  }
-  start = s_cols[tid] - my_cols;
-  int item = s_items[tid] - my_items;
+  const int32_t all_items = block_scan(my_items, waves);
+  start = first;
+  int item = all_items - my_items;
   for (int b = b0; b < b1; ++b) {
     const int c = tot[b];
     int32_t run = start;  // first slot of bucket b in each block
@@ -340,14 +367,18 @@ __global__ __launch_bounds__(1024) void sort_scan_kernel(int32_t* __restrict__ c
           run += v[u];
         }
     }
-    for (int w = start / 16 * 16; c > 0 && w < start + c; w += 16) {
-      const int lo = w > start ? w : start;
-      const int hi = (w + 16 < start + c) ? w + 16 : start + c;
-      items[item++] = make_int4(b, lo, hi - lo, w);
+    if (per > 1 && c > 0) {
+      write_items(items, b, start, c, item, 0, 1);
+      item += (start + c - 1) / 16 - start / 16 + 1;
     }
     start += c;
   }
-  if (tid == 1023) *nitems = s_items[1023];
+  if (tid == 1023) *nitems = all_items;
+  if (per == 1) {
+    const int32_t c = tid < nb ? tot[tid] : 0;
+    __syncthreads();
+    write_all_items(items, nb, start - c, c, item, s_cols, tot, s_items);
+  }
 }
 
 // 16-bit packing: M16[g][i][u] = RN16(A32[8g+u][i] * 2^-e), zeros past ncols.
@@ -406,23 +437,6 @@ __global__ __launch_bounds__(256) void pack16_kernel(const float* __restrict__ A
     pk.z = h[4] | (h[5] << 16);
     pk.w = h[6] | (h[7] << 16);
     __builtin_nontemporal_store(pk, Mp + grp * M + i0 + r);
-  }
-}
-
-// Zero mantissas of the slots without a column that the 16-bit orbit builds
-// leave: the `tail` whole groups from g0 (blockIdx.y below tail), then, for an
-// odd scene, members 1 to 3 of the centre column j.
-__global__ __launch_bounds__(256) void zero_pad16_kernel(uint16_t* __restrict__ Mh, int64_t M,
-                                                         int64_t g0, int tail,
-                                                         const int32_t* __restrict__ slot_of,
-                                                         int64_t j) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  if ((int)blockIdx.y < tail) {
-    *reinterpret_cast<u32x4*>(Mh + ((g0 + blockIdx.y) * M + i) * 8) = (u32x4){0u, 0u, 0u, 0u};
-  } else {
-    const int64_t slot = slot_of[j] + 8 * (int64_t)(blockIdx.y - tail + 1);
-    Mh[(slot / 8 * M + i) * 8 + slot % 8] = 0;
   }
 }
 
@@ -508,24 +522,29 @@ __global__ __launch_bounds__(kSortBlock) void orbit_count_kernel(const ColGeom* 
   for (int b = threadIdx.x; b < nb; b += kSortBlock) cnt[(int64_t)blockIdx.x * nb + b] = hist[b];
 }
 
+// Lanes of the wave with this lane's bracket (0 <= b < 2^bits; a lane outside the
+// set has b < 0 and gets no meaningful mask, nor does it enter another's): one
+// ballot per bit of the bracket number, whatever the number of brackets in the wave.
+__device__ __forceinline__ uint64_t same_bracket(int b, int bits) {
+  uint64_t m = __ballot(b >= 0);
+  for (int i = 0; i < bits; ++i) {
+    const uint64_t one = __ballot((b >> i) & 1);
+    m &= ((b >> i) & 1) ? one : ~one;
+  }
+  return m;
+}
+
+__device__ __forceinline__ int bracket_bits(int nb) { return 32 - __builtin_clz(nb); }
+
 // Stable placement of the base columns: a base's position is its block's first
 // position of the bracket plus its rank among the block's earlier bases of the
-// same bracket.  Each wave ranks its 64 bases with one ballot per bracket
-// present; then the waves take their positions in order, each adding its counts
+// same bracket.  Each wave ranks its 64 bases (same_bracket); then the waves take their positions in order, each adding its counts
 // to a per-bracket cursor in LDS that starts at the block's first positions.
-// With `perm` set (16-bit forms) also the slots of every orbit member: base
-// position s in block s/8 of 8 bases, member k in group 4 (s/8) + k, slot 32
-// (s/8) + 8 k + s%8.  Slots without a column (members 1 to 3 of the centre of an
-// odd scene, bases that fill up the last block, the slots up to ncols_pad) are
-// padding: perm -1.
 __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom* __restrict__ geo,
                                                                    OrbitGrid o, int nb,
                                                                    const int32_t* __restrict__ first,
                                                                    int32_t* __restrict__ reps,
-                                                                   int32_t* __restrict__ perm,
-                                                                   int32_t* __restrict__ slot_of,
-                                                                   int32_t* __restrict__ eslot,
-                                                                   int64_t ncols_pad) {
+                                                                   int32_t* __restrict__ nitems) {
   extern __shared__ int32_t cursor[];  // nb
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int q = tid; q < nb; q += kSortBlock) cursor[q] = first[(int64_t)blockIdx.x * nb + q];
@@ -533,17 +552,8 @@ __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom
   const bool valid = t < o.nreps;
   const int64_t j0 = valid ? orbit_base(o, t) : 0;
   const int b = valid ? bucket_of(geo, j0, nb) : -1;
-  uint64_t todo = __ballot(valid);
-  int rank = 0, count = 0;
-  while (todo) {  // uniform: one pass per bucket present in the wave
-    const int bl = __shfl(b, __builtin_ctzll(todo), 64);
-    const uint64_t m = __ballot(valid && b == bl);
-    if (valid && b == bl) {
-      rank = __popcll(m & ((1ull << lane) - 1ull));
-      count = __popcll(m);
-    }
-    todo &= ~m;
-  }
+  const uint64_t m = same_bracket(b, bracket_bits(nb));
+  const int rank = __popcll(m & ((1ull << lane) - 1ull)), count = __popcll(m);
   __syncthreads();
   int pos = 0;
   for (int w = 0; w < kSortBlock / 64; ++w) {
@@ -554,52 +564,186 @@ __global__ __launch_bounds__(kSortBlock) void orbit_scatter_kernel(const ColGeom
     }
     __syncthreads();
   }
-  if (valid) reps[pos] = (int32_t)j0;
-  if (!perm) return;
-  const int64_t whole = (o.nreps + 7) / 8 * 8;  // bases, with those that fill up the last block
-  if (!valid) pos = (int)t;
-  if (t < whole) {
-    const int32_t e = valid ? geo[j0].e : kZeroColumnExp;  // the members share the radius
-    const bool centre = valid && orbit_is_centre(j0, o.N);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int32_t slot = (pos / 8) * 32 + 8 * k + pos % 8;
-      const bool column = valid && (k == 0 || !centre);
-      const int64_t j = column ? orbit_member(j0, o.N, k) : -1;
-      perm[slot] = (int32_t)j;
-      if (column) slot_of[j] = slot;
-      eslot[slot] = e;
-    }
-  }
-  const int64_t tail = 4 * whole + t;  // fewer than 64 slots
-  if (tail < ncols_pad) {
-    perm[tail] = -1;
-    eslot[tail] = kZeroColumnExp;
+  if (valid) {
+    reps[pos] = (int32_t)j0;
+    if (orbit_is_centre(j0, o.N)) nitems[1] = pos;
   }
 }
 
-// column sums: the partial sums of the row ranges (16-bit) or tiles (float32)
-// in order, for every member
+// The whole sort of up to kSmallSort base columns in up to 1024 brackets in one
+// workgroup: the counts of every wave of 64 columns by bracket in LDS, their
+// running sums over the waves, the items, the positions; the same order and items
+// as the three kernels above.  One launch, 13 us for 4096 columns of 63 brackets
+// where the three took 18.
+constexpr int kSmallSort = 4096;
+
+__global__ __launch_bounds__(kSortBlock) void orbit_sort_kernel(const ColGeom* __restrict__ geo,
+                                                                OrbitGrid o, int nb,
+                                                                int32_t* __restrict__ reps,
+                                                                int4* __restrict__ items,
+                                                                int32_t* __restrict__ nitems) {
+  constexpr int C = kSmallSort / kSortBlock;
+  extern __shared__ int32_t cnt[];  // [waves of 64 columns][nb]
+  __shared__ int32_t tot[16], s_start[kSortBlock], s_count[kSortBlock], s_first[kSortBlock];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nw = (int)((o.nreps + 63) / 64);
+  int64_t j0[C];
+  int b[C], rank[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int64_t t = c * kSortBlock + tid;
+    j0[c] = t < o.nreps ? orbit_base(o, t) : 0;
+    b[c] = t < o.nreps ? bucket_of(geo, j0[c], nb) : -1;
+  }
+  for (int q = tid; q < nw * nb; q += kSortBlock) cnt[q] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const uint64_t m = same_bracket(b[c], bracket_bits(nb));
+    rank[c] = __popcll(m & ((1ull << lane) - 1ull));
+    if (b[c] >= 0 && rank[c] == 0) cnt[(c * 16 + wave) * nb + b[c]] = __popcll(m);
+  }
+  __syncthreads();
+  // bracket `tid`: its columns before every wave, and its total
+  int32_t run = 0;
+  if (tid < nb) {
+#pragma unroll 8
+    for (int w = 0; w < nw; ++w) {
+      const int32_t v = cnt[w * nb + tid];
+      cnt[w * nb + tid] = run;
+      run += v;
+    }
+  }
+  const int32_t start = block_scan(run, tot) - run;
+  const int32_t mine = run > 0 ? (start + run - 1) / 16 - start / 16 + 1 : 0;
+  const int32_t last = block_scan(mine, tot);
+  if (tid < nb) {
+#pragma unroll 8
+    for (int w = 0; w < nw; ++w) cnt[w * nb + tid] += start;
+  }
+  if (tid == kSortBlock - 1) nitems[0] = last;
+  write_all_items(items, nb, start, run, last - mine, s_start, s_count, s_first);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    if (b[c] < 0) continue;
+    const int32_t pos = cnt[(c * 16 + wave) * nb + b[c]] + rank[c];
+    reps[pos] = (int32_t)j0[c];
+    if (orbit_is_centre(j0[c], o.N)) nitems[1] = pos;
+  }
+}
+
+// the partial sums of base position s: row ranges (16-bit) or tiles (float32),
+// in order
+__device__ __forceinline__ double orbit_sum(const double* __restrict__ part, int nparts,
+                                            int64_t nreps, int64_t s) {
+  double t = 0.0;
+  for (int r0 = 0; r0 < nparts; r0 += 8) {  // 8 loads in flight
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = r0 + u < nparts ? part[(int64_t)(r0 + u) * nreps + s] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += v[u];
+  }
+  return t;
+}
+
+// column sums, for every member
 __global__ __launch_bounds__(256) void orbit_tau_kernel(const int32_t* __restrict__ reps, OrbitGrid o,
                                                         const double* __restrict__ part, int nparts,
                                                         double* __restrict__ tau) {
   const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (s >= o.nreps) return;
-  double t = 0.0;
-  for (int r0 = 0; r0 < nparts; r0 += 8) {  // 8 loads in flight
-    double v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = r0 + u < nparts ? part[(int64_t)(r0 + u) * o.nreps + s] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t += v[u];
-  }
+  const double t = orbit_sum(part, nparts, o.nreps, s);
   const int64_t j0 = reps[s];
-  if (orbit_is_centre(j0, o.N)) {
-    tau[j0] = t;
+  const int members = orbit_is_centre(j0, o.N) ? 1 : 4;
+  for (int k = 0; k < members; ++k) tau[orbit_member(j0, o.N, k)] = t;
+}
+
+// The end of a flux-preserving build's first pass: the float32 scale of every
+// base column, the PSF's flux over the plain column's sum, and for the 16-bit
+// forms the members' exponent from the rescaled bound; identically zero columns
+// keep scale 1 and their exponent.
+__global__ __launch_bounds__(256) void orbit_scale_kernel(const int32_t* __restrict__ reps, OrbitGrid o,
+                                                          const double* __restrict__ part, int nparts,
+                                                          int K, ColGeom* __restrict__ geo,
+                                                          const OrbitFlux fx) {
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (s >= o.nreps) return;
+  const double old = orbit_sum(part, nparts, o.nreps, s);
+  const int64_t j0 = reps[s];
+  const ColGeom g = geo[j0];
+  if (g.k < 0) {
+    fx.colscale[j0] = 1.0f;
     return;
   }
+  const double t = (K == 1) ? fx.sums[0] : (1.0 - g.w) * fx.sums[g.k] + g.w * fx.sums[g.k + 1];
+  const float sf = (float)((old != 0.0) ? t / old : 1.0);
+  fx.colscale[j0] = sf;
+  if (!fx.exps) return;
+  const double bound = (K == 1) ? (double)fx.pmax[0]
+                                : (1.0 - g.w) * (double)fx.pmax[g.k] + g.w * (double)fx.pmax[g.k + 1];
+  const int32_t e = scale_exponent(bound * fabs((double)sf));
+  const int members = orbit_is_centre(j0, o.N) ? 1 : 4;
+  for (int k = 0; k < members; ++k) {
+    const int64_t j = orbit_member(j0, o.N, k);
+    geo[j].e = e;
+    fx.exps[j] = e;
+  }
+}
+
+// The end of a 16-bit build: workgroups below nsum write column sums and the slot
+// maps: base position s in block s/8 of 8 bases, member k in group 4 (s/8) + k,
+// slot 32 (s/8) + 8 k + s%8.  Slots without a column (members 1 to 3 of the
+// centre of an odd scene, bases that fill up the last block, the slots up to
+// ncols_pad) are padding, perm -1; those that the build kernels do not write as
+// zeros, whole groups at the end (`tail` of them) and the centre's members, the
+// remaining workgroups set to zero.
+__global__ __launch_bounds__(256) void orbit16_end_kernel(const int32_t* __restrict__ reps, OrbitGrid o,
+                                                          const double* __restrict__ part, int nparts,
+                                                          const ColGeom* __restrict__ geo,
+                                                          const int32_t* __restrict__ nitems, int nsum,
+                                                          int tail, int64_t M, const Orbit16Out out) {
+  const int64_t whole = (o.nreps + 7) / 8 * 8;
+  if ((int)blockIdx.x >= nsum) {
+    const int64_t rowblocks = (M + 255) / 256, wg = (int64_t)blockIdx.x - nsum;
+    const int y = (int)(wg / rowblocks);
+    const int64_t i = (wg - y * rowblocks) * 256 + threadIdx.x;
+    if (i >= M) return;
+    uint16_t* Mh = reinterpret_cast<uint16_t*>(out.lib);
+    if (y < tail) {
+      *reinterpret_cast<u32x4*>(Mh + ((whole / 2 + y) * M + i) * 8) = (u32x4){0u, 0u, 0u, 0u};
+    } else {
+      const int32_t s = nitems[1];
+      Mh[(((int64_t)(s / 8) * 4 + y - tail + 1) * M + i) * 8 + s % 8] = 0;
+    }
+    return;
+  }
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool valid = s < o.nreps;
+  if (s < whole) {
+    const int64_t j0 = valid ? reps[s] : 0;
+    const bool centre = valid && orbit_is_centre(j0, o.N);
+    const double t = valid ? orbit_sum(part, nparts, o.nreps, s) : 0.0;
+    const int32_t e = valid ? geo[j0].e : kZeroColumnExp;  // the members share the radius
 #pragma unroll
-  for (int k = 0; k < 4; ++k) tau[orbit_member(j0, o.N, k)] = t;
+    for (int k = 0; k < 4; ++k) {
+      const int32_t slot = (int32_t)((s / 8) * 32 + 8 * k + s % 8);
+      const bool column = valid && (k == 0 || !centre);
+      const int64_t j = column ? orbit_member(j0, o.N, k) : -1;
+      out.perm[slot] = (int32_t)j;
+      out.eslot[slot] = e;
+      if (column) {
+        out.slot_of[j] = slot;
+        out.tau[j] = t;
+      }
+    }
+  }
+  const int64_t pad = 4 * whole + s;  // fewer than 64 slots
+  if (pad < out.ncols_pad) {
+    out.perm[pad] = -1;
+    out.eslot[pad] = kZeroColumnExp;
+  }
 }
 
 // the bordered pair (P_k, P_{k+1}) with its zero border, as the LDS build
@@ -1617,11 +1761,8 @@ hipError_t launch_pack16_range(int storage, const float* A32, int64_t col0, int6
 }
 
 static bool build_orbit_supported(int n, int K, int N);
-static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                     int64_t M, float* A32, double* tau, void* scratch, int mode,
-                                     const float* colscale, hipStream_t s);
 
-hipError_t launch_build_lds(const float* cube, int K, const ColGeom* geo, int n, int N, int64_t M,
+hipError_t launch_build_lds(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
                             float* A32, double* tau, void* scratch, hipStream_t s) {
   if (build_orbit_supported(n, K, N))
     return launch_build_orbit(cube, K, geo, n, N, M, A32, tau, scratch, kPlain, nullptr, s);
@@ -1666,7 +1807,7 @@ struct OrbitPlan {
   int64_t nblk, items_max;
   int32_t* cnt;
   int4* items;
-  int32_t* nitems;
+  int32_t* nitems;  // items; the centre's position
   int32_t* reps;
   double* part;
 };
@@ -1705,19 +1846,31 @@ static bool orbit_sort_fits(int K, int N) {
          (int64_t)N * N < ((int64_t)1 << 31);
 }
 
-// counting sort of the base columns by bracket, and the work items
-static hipError_t orbit_sort(const ColGeom* geo, const OrbitPlan& pl, int32_t* perm,
-                             int32_t* slot_of, int32_t* eslot, int64_t ncols_pad, hipStream_t s) {
+// Counting sort of the base columns by bracket, and the work items.  One
+// workgroup does it while the waves' counts fit its LDS beside other work
+// (kSmallSort base columns, scenes up to 128 x 128).
+static hipError_t orbit_sort(const ColGeom* geo, const OrbitPlan& pl, hipStream_t s) {
+  const size_t lds = (size_t)((pl.o.nreps + 63) / 64) * (size_t)pl.nb * 4;
+  if (pl.o.nreps <= kSmallSort && pl.nb <= kSortBlock && lds <= 49152) {
+    orbit_sort_kernel<<<1, kSortBlock, lds, s>>>(geo, pl.o, pl.nb, pl.reps, pl.items, pl.nitems);
+    return hipGetLastError();
+  }
   orbit_count_kernel<<<(unsigned)pl.nblk, kSortBlock, (size_t)pl.nb * 4, s>>>(geo, pl.o, pl.nb, pl.cnt);
   sort_scan_kernel<<<1, 1024, 0, s>>>(pl.cnt, pl.nblk, pl.nb, pl.items, pl.nitems);
   orbit_scatter_kernel<<<(unsigned)pl.nblk, kSortBlock, (size_t)pl.nb * 4, s>>>(
-      geo, pl.o, pl.nb, pl.cnt, pl.reps, perm, slot_of, eslot, ncols_pad);
+      geo, pl.o, pl.nb, pl.cnt, pl.reps, pl.nitems);
   return hipGetLastError();
 }
 
-static hipError_t orbit_finish(const OrbitPlan& pl, const int32_t* reps, int nparts, double* tau,
-                               hipStream_t s) {
-  orbit_tau_kernel<<<(unsigned)((pl.o.nreps + 255) / 256), 256, 0, s>>>(reps, pl.o, pl.part, nparts, tau);
+// What follows the kernel that left the partial sums of a float32 build: the
+// scales (first pass of a flux-preserving build) or the column sums.
+static hipError_t orbit_finish(const OrbitPlan& pl, int nparts, int mode, int K, ColGeom* geo,
+                               const OrbitFlux* fx, double* tau, hipStream_t s) {
+  const unsigned grid = (unsigned)((pl.o.nreps + 255) / 256);
+  if (mode == kSumsOnly)
+    orbit_scale_kernel<<<grid, 256, 0, s>>>(pl.reps, pl.o, pl.part, nparts, K, geo, *fx);
+  else
+    orbit_tau_kernel<<<grid, 256, 0, s>>>(pl.reps, pl.o, pl.part, nparts, tau);
   return hipGetLastError();
 }
 
@@ -1743,11 +1896,12 @@ static unsigned box_grid(int64_t total) {
   return (unsigned)(wgs < 4096 ? wgs : 4096);
 }
 
-static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                     int64_t M, float* A32, double* tau, void* scratch, int mode,
-                                     const float* colscale, hipStream_t s) {
+hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
+                              float* A32, double* tau, void* scratch, int mode,
+                              const OrbitFlux* fx, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, 0, s);
+  const float* colscale = fx ? fx->colscale : nullptr;
+  hipError_t e = mode == kScaled ? hipSuccess : orbit_sort(geo, pl, s);  // kept for the second pass
   if (e != hipSuccess) return e;
   const bool vec = (n % 32) == 0;
   if (!pair_fits_lds(n)) {  // a staged box per 32 x 32 tile
@@ -1773,7 +1927,7 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
         e = vec ? launch(build_orbit_box_kernel<true, kPlain>) : launch(build_orbit_box_kernel<false, kPlain>);
     }
     if (e != hipSuccess) return e;
-    return orbit_finish(pl, pl.reps, nruns, tau, s);
+    return orbit_finish(pl, nruns, mode, K, geo, fx, tau, s);
   }
   const dim3 grid((unsigned)pl.items_max, (unsigned)(16 / orbit_sub(pl.nt)));
   const int ls = lds_stride(n);
@@ -1797,22 +1951,11 @@ static hipError_t launch_build_orbit(const float* cube, int K, const ColGeom* ge
       e = vec ? launch(build_orbit_kernel<true, kPlain>) : launch(build_orbit_kernel<false, kPlain>);
   }
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, pl.reps, pl.nt * pl.nt, tau, s);
+  return orbit_finish(pl, pl.nt * pl.nt, mode, K, geo, fx, tau, s);
 }
 
-// The two float32 passes of a flux-preserving orbit build (see the modes above).
+// the two passes of a flux-preserving build (see the modes above)
 bool build_orbit_flux_supported(int n, int K, int N) { return K <= 8192 && build_orbit_supported(n, K, N); }
-
-hipError_t launch_build_orbit_sums(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                   int64_t M, float* A32, double* tau, void* scratch, hipStream_t s) {
-  return launch_build_orbit(cube, K, geo, n, N, M, A32, tau, scratch, kSumsOnly, nullptr, s);
-}
-
-hipError_t launch_build_orbit_scaled(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                     int64_t M, const float* colscale, float* A32, double* tau,
-                                     void* scratch, hipStream_t s) {
-  return launch_build_orbit(cube, K, geo, n, N, M, A32, tau, scratch, kScaled, colscale, s);
-}
 
 // cubic-spline orbit build from staged boxes of the padded coefficient pairs
 bool build_cubic_orbit_supported(int n, int K, int N) {
@@ -1820,11 +1963,12 @@ bool build_cubic_orbit_supported(int n, int K, int N) {
          (size_t)16 * kCbRegion * sizeof(float) <= (size_t)kLdsBuildMaxBytes;
 }
 
-hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* geo, int n, int N,
-                                    int64_t M, float* A32, double* tau, void* scratch, int mode,
-                                    const float* colscale, hipStream_t s) {
+hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int n, int N, int64_t M,
+                                    float* A32, double* tau, void* scratch, int mode,
+                                    const OrbitFlux* fx, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, nullptr, nullptr, nullptr, 0, s);
+  const float* colscale = fx ? fx->colscale : nullptr;
+  hipError_t e = mode == kScaled ? hipSuccess : orbit_sort(geo, pl, s);  // kept for the second pass
   if (e != hipSuccess) return e;
   const int Np = n + 2 * kSplinePad;
   const bool vec = (n % 32) == 0;
@@ -1851,7 +1995,7 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* ge
       e = vec ? launch(build_cubic_orbit_kernel<true, kPlain>) : launch(build_cubic_orbit_kernel<false, kPlain>);
   }
   if (e != hipSuccess) return e;
-  return orbit_finish(pl, pl.reps, nruns, tau, s);
+  return orbit_finish(pl, nruns, mode, K, geo, fx, tau, s);
 }
 
 // 16-bit orbit build: the pair (ending 16-byte aligned), then two 2 x 8 x 33 unit tiles
@@ -1874,19 +2018,15 @@ bool build_orbit16_supported(int n, int K, int N) {
   return orbit_sort_fits(K, N) && (orbit16_pair_fits(n) || n <= kBoxMaxN);
 }
 
-// slots of the 16-bit storage of an N x N scene
-static int64_t padded_slots(int N) { return ((int64_t)N * N + kColPad - 1) / kColPad * kColPad; }
-
-// The slots without a column (see zero_pad16_kernel), then the column sums.
-static hipError_t orbit16_finish(const OrbitPlan& pl, int64_t M, const int32_t* slot_of, void* lib,
-                                 double* tau, hipStream_t s) {
-  const int64_t g0 = (pl.o.nreps + 7) / 8 * 4, N = pl.o.N;
-  const int tail = (int)(padded_slots(pl.o.N) / 8 - g0);  // fewer than 8
-  const int rows = tail + ((N & 1) ? 3 : 0);
-  if (rows > 0)
-    zero_pad16_kernel<<<dim3((unsigned)((M + 255) / 256), (unsigned)rows), 256, 0, s>>>(
-        reinterpret_cast<uint16_t*>(lib), M, g0, tail, slot_of, (N / 2) * N + N / 2);
-  return orbit_finish(pl, pl.reps, pl.nranges, tau, s);
+static hipError_t orbit16_end(const OrbitPlan& pl, int64_t M, const ColGeom* geo, const Orbit16Out& out,
+                              hipStream_t s) {
+  const int64_t whole = (pl.o.nreps + 7) / 8 * 8;
+  const int tail = (int)(out.ncols_pad / 8 - whole / 2);  // groups, fewer than 8
+  const int nsum = (int)((whole + 255) / 256);
+  const int64_t zero = (int64_t)(tail + ((pl.o.N & 1) ? 3 : 0)) * ((M + 255) / 256);
+  orbit16_end_kernel<<<(unsigned)(nsum + zero), 256, 0, s>>>(pl.reps, pl.o, pl.part, pl.nranges, geo,
+                                                            pl.nitems, nsum, tail, M, out);
+  return hipGetLastError();
 }
 
 // f(bf16, scaled, lines) as compile-time flags of the 16-bit orbit kernels
@@ -1911,14 +2051,14 @@ size_t build_lds_scratch_bytes(int K, int N, int n) {
                                         : bucket_scratch_bytes(K, (int64_t)N * N);
 }
 
-hipError_t launch_build_orbit16(int storage, const float* cube, int K, const ColGeom* geo, int n,
-                                int N, int64_t M, int32_t* perm, int32_t* eslot, int32_t* slot_of,
-                                void* lib, double* tau, void* scratch, const float* colscale,
+hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* geo, int n, int N,
+                                int64_t M, const Orbit16Out& out, void* scratch, const OrbitFlux* fx,
                                 hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, padded_slots(N), s);
+  const float* colscale = fx ? fx->colscale : nullptr;
+  hipError_t e = fx ? hipSuccess : orbit_sort(geo, pl, s);  // the first pass has sorted
   if (e != hipSuccess) return e;
-  uint16_t* Mh = reinterpret_cast<uint16_t*>(lib);
+  uint16_t* Mh = reinterpret_cast<uint16_t*>(out.lib);
   const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
   const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
   if (!orbit16_pair_fits(n)) {  // a staged box per 32 x 32 pixels
@@ -1935,7 +2075,7 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
       return launch(build_orbit16_box_kernel<bf.value, false, scaled.value, lines.value>);
     });
     if (e != hipSuccess) return e;
-    return orbit16_finish(pl, M, slot_of, lib, tau, s);
+    return orbit16_end(pl, M, geo, out, s);
   }
   const int ls = lds_stride(n);
   const size_t lds = orbit16_lds_bytes(n);
@@ -1951,21 +2091,21 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, const Col
     return launch(build_orbit16_kernel<bf.value, scaled.value, lines.value>);
   });
   if (e != hipSuccess) return e;
-  return orbit16_finish(pl, M, slot_of, lib, tau, s);
+  return orbit16_end(pl, M, geo, out, s);
 }
 
 bool build_cubic_orbit16_supported(int n, int K, int N) {
   return build_cubic_orbit_supported(n, K, N) && orbit16_box_lds_bytes(true) <= (size_t)kLdsBuildMaxBytes;
 }
 
-hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, const ColGeom* geo,
-                                      int n, int N, int64_t M, int32_t* perm, int32_t* eslot,
-                                      int32_t* slot_of, void* lib, double* tau, void* scratch,
-                                      const float* colscale, hipStream_t s) {
+hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, ColGeom* geo, int n,
+                                      int N, int64_t M, const Orbit16Out& out, void* scratch,
+                                      const OrbitFlux* fx, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
-  hipError_t e = orbit_sort(geo, pl, perm, slot_of, eslot, padded_slots(N), s);
+  const float* colscale = fx ? fx->colscale : nullptr;
+  hipError_t e = fx ? hipSuccess : orbit_sort(geo, pl, s);  // the first pass has sorted
   if (e != hipSuccess) return e;
-  uint16_t* Mh = reinterpret_cast<uint16_t*>(lib);
+  uint16_t* Mh = reinterpret_cast<uint16_t*>(out.lib);
   const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
   const size_t lds = orbit16_box_lds_bytes(true);
   const int Np = n + 2 * kSplinePad;
@@ -1981,7 +2121,7 @@ hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, co
     return launch(build_orbit16_box_kernel<bf.value, true, scaled.value, lines.value>);
   });
   if (e != hipSuccess) return e;
-  return orbit16_finish(pl, M, slot_of, lib, tau, s);
+  return orbit16_end(pl, M, geo, out, s);
 }
 
 

@@ -10,32 +10,47 @@
 
 namespace psflib {
 
-// Largest value of each sampled PSF (exact float32 max); used for the 16-bit
-// column exponents.  One workgroup per PSF, four independent loads in flight
-// per thread.
-__global__ __launch_bounds__(1024) void cube_max_kernel(const float* __restrict__ cube, int64_t M,
-                                                        float* __restrict__ pmax) {
+// Largest value (exact float32 max, for the 16-bit column exponents) and sum
+// (float64, a fixed order, for the flux rescale) of each sampled PSF, each where
+// asked for.  One workgroup per PSF, four independent loads in flight per thread
+// (latency: 51 PSFs of 101^2 take 4 us, 12 with 256 threads and one load each).
+__global__ __launch_bounds__(1024) void cube_stats_kernel(const float* __restrict__ cube, int64_t M,
+                                                          float* __restrict__ pmax,
+                                                          double* __restrict__ sums) {
   __shared__ float red[16];
+  __shared__ double red64[16];
   const float* P = cube + (int64_t)blockIdx.x * M;
-  float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
-  int64_t i = threadIdx.x;
-  for (; i + 3 * 1024 < M; i += 4 * 1024) {
-    m0 = fmaxf(m0, P[i]);
-    m1 = fmaxf(m1, P[i + 1024]);
-    m2 = fmaxf(m2, P[i + 2 * 1024]);
-    m3 = fmaxf(m3, P[i + 3 * 1024]);
+  float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  double t[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = threadIdx.x; i < M; i += 4 * 1024) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = i + 1024 * u < M ? P[i + 1024 * u] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      m[u] = fmaxf(m[u], v[u]);
+      t[u] += (double)v[u];
+    }
   }
-  for (; i < M; i += 1024) m0 = fmaxf(m0, P[i]);
-  float m = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));
+  float mx = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+  double sum = (t[0] + t[1]) + (t[2] + t[3]);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  for (int off = 32; off > 0; off >>= 1) {
+    mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    sum += __shfl_xor(sum, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6] = mx;
+    red64[threadIdx.x >> 6] = sum;
+  }
   __syncthreads();
-  if (threadIdx.x < 64) {
-    m = threadIdx.x < 16 ? red[threadIdx.x] : 0.0f;
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if (threadIdx.x == 0) pmax[blockIdx.x] = m;
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 16; ++w) {
+      mx = fmaxf(mx, red[w]);
+      sum += red64[w];
+    }
+    if (pmax) pmax[blockIdx.x] = mx;
+    if (sums) sums[blockIdx.x] = sum;
   }
 }
 
@@ -55,26 +70,29 @@ __global__ __launch_bounds__(256) void pair_cube_kernel(const float* __restrict_
   }
 }
 
-// Power-of-two exponent e with m * 2^-e in [2^14, 2^15); kZeroColumnExp for
-// m == 0 (a zero column has no scale: with this exponent every scene value
-// at the column scales to exactly 0, so it can neither set a scene's
-// exponent nor overflow the 16-bit format).
-__device__ inline int32_t scale_exponent(double m) {
-  if (m == 0.0) return kZeroColumnExp;
-  int E;
-  (void)frexp(m, &E);  // m = f * 2^E, f in [0.5, 1)
-  return E - 15;
-}
+// Radii of up to kRadiiArg samples, passed with the launch; more are read from
+// device memory, an upload of its own.
+struct RadiiArg {
+  double r[kRadiiArg];
+};
 
 // One thread per column j (and per padding column up to ncols_pad).
-__global__ __launch_bounds__(256) void geometry_kernel(int N, double S,
-                                                       const double* __restrict__ radii, int K,
+template <bool ARG>
+__global__ __launch_bounds__(256) void geometry_kernel(int N, double S, const RadiiArg arg,
+                                                       const double* __restrict__ far, int K,
                                                        int interp, int oob,
                                                        const float* __restrict__ pmax,
                                                        int want_exp, ColGeom* __restrict__ geo,
                                                        int64_t ncols_pad,
                                                        int32_t* __restrict__ exps) {
 #pragma clang fp contract(off)
+  __shared__ double near[ARG ? kRadiiArg : 1];
+  if constexpr (ARG) {
+    static_assert(kRadiiArg <= 256, "one thread per radius");
+    if ((int)threadIdx.x < K) near[threadIdx.x] = arg.r[threadIdx.x];
+    __syncthreads();
+  }
+  const double* radii = ARG ? near : far;
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t ncols = (int64_t)N * N;
   if (j >= ncols_pad) return;
@@ -152,8 +170,9 @@ __global__ __launch_bounds__(256) void export_geometry_kernel(const ColGeom* __r
 
 static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-hipError_t launch_cube_max(const float* cube, int K, int64_t M, float* pmax, hipStream_t s) {
-  cube_max_kernel<<<K, 1024, 0, s>>>(cube, M, pmax);
+hipError_t launch_cube_stats(const float* cube, int K, int64_t M, float* pmax, double* sums,
+                             hipStream_t s) {
+  cube_stats_kernel<<<K, 1024, 0, s>>>(cube, M, pmax, sums);
   return hipGetLastError();
 }
 
@@ -165,11 +184,21 @@ hipError_t launch_pair_cube(const float* cube, int K, int64_t M, float* pairs, h
   return hipGetLastError();
 }
 
-hipError_t launch_geometry(int N, double S, const double* radii, int K, int interp, int oob,
-                           const float* pmax, bool want_exp, ColGeom* geo, int64_t ncols_pad,
-                           int32_t* exps, hipStream_t s) {
-  geometry_kernel<<<blocks_for(ncols_pad, 256), 256, 0, s>>>(N, S, radii, K, interp, oob, pmax,
-                                                            want_exp ? 1 : 0, geo, ncols_pad, exps);
+hipError_t launch_geometry(int N, double S, const double* h_radii, double* radii, int K, int interp,
+                           int oob, const float* pmax, bool want_exp, ColGeom* geo,
+                           int64_t ncols_pad, int32_t* exps, hipStream_t s) {
+  RadiiArg arg = {};
+  const unsigned grid = blocks_for(ncols_pad, 256);
+  if (K <= kRadiiArg) {
+    for (int k = 0; k < K; ++k) arg.r[k] = h_radii[k];
+    geometry_kernel<true><<<grid, 256, 0, s>>>(N, S, arg, nullptr, K, interp, oob, pmax,
+                                               want_exp ? 1 : 0, geo, ncols_pad, exps);
+  } else {
+    const hipError_t e = hipMemcpyAsync(radii, h_radii, (size_t)K * 8, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return e;
+    geometry_kernel<false><<<grid, 256, 0, s>>>(N, S, arg, radii, K, interp, oob, pmax,
+                                                want_exp ? 1 : 0, geo, ncols_pad, exps);
+  }
   return hipGetLastError();
 }
 

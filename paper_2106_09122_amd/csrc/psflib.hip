@@ -21,7 +21,7 @@ struct psflib_handle {
   psflib::ColGeom* geo;
   double* radii_dev;
   float* pmax;
-  std::vector<double> radii;  // host copy (source of the radii upload)
+  std::vector<double> radii;  // host copy (source of an upload of many radii)
   // streams that used the workspace (the build, geometry exports)
   mutable psflib::StreamUses ws_uses;
 };
@@ -363,8 +363,6 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
     delete h;
     return r;
   };
-  e = hipMemcpyAsync(h->radii_dev, h->radii.data(), (size_t)K * 8, hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return bail(e, "hipMemcpyAsync(radii)");
   e = psflib::pool_alloc(&tmp, tmp_bytes, dev, s);
   if (e != hipSuccess) { tmp = nullptr; return bail(e, "scratch allocation (build)"); }
   char* tp = reinterpret_cast<char*>(tmp);
@@ -382,69 +380,59 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
     e = psflib::launch_spline_pairs(d_cube, K, desc->n, path_tmp,
                                     storage != PSFLIB_FP32 ? h->pmax : nullptr, s);
     if (e != hipSuccess) return bail(e, "spline coefficient kernels");
-  } else if (storage != PSFLIB_FP32) {
-    e = psflib::launch_cube_max(d_cube, K, L.M, h->pmax, s);
-    if (e != hipSuccess) return bail(e, "cube_max kernel");
   }
-  e = psflib::launch_geometry(desc->N, desc->scene_pixscale, h->radii_dev, K, desc->interp,
-                              desc->oob, h->pmax, storage != PSFLIB_FP32, h->geo, L.ncols_pad,
-                              exps, s);
+  const bool want_max = storage != PSFLIB_FP32 && !cubic;
+  if (want_max || flux) {
+    e = psflib::launch_cube_stats(d_cube, K, L.M, want_max ? h->pmax : nullptr, sums, s);
+    if (e != hipSuccess) return bail(e, "cube statistics kernel");
+  }
+  e = psflib::launch_geometry(desc->N, desc->scene_pixscale, h->radii.data(), h->radii_dev, K,
+                              desc->interp, desc->oob, h->pmax, storage != PSFLIB_FP32, h->geo,
+                              L.ncols_pad, exps, s);
   if (e != hipSuccess) return bail(e, "geometry kernel");
   const float* cpairs = cubic ? psflib::spline_pairs_of(path_tmp, K, desc->n) : nullptr;
   void* otmp = tp + spline_bytes;  // the orbit builds' scratch
-  int32_t* perm = reinterpret_cast<int32_t*>(lib + L.off_perm);
-  int32_t* eslot = reinterpret_cast<int32_t*>(lib + L.off_eslot);
-  int32_t* slot_of = reinterpret_cast<int32_t*>(lib + L.off_slot);
+  const psflib::Orbit16Out out16 = {d_lib, tau, reinterpret_cast<int32_t*>(lib + L.off_perm),
+                                    reinterpret_cast<int32_t*>(lib + L.off_eslot),
+                                    reinterpret_cast<int32_t*>(lib + L.off_slot), L.ncols_pad};
   if (flux_orbit) {
-    // pass 1: the plain build's column sums, nothing stored
-    e = psflib::launch_psf_sums(d_cube, K, L.M, sums, s);
-    if (e != hipSuccess) return bail(e, "psf sums kernel");
+    const psflib::OrbitFlux fx = {sums, h->pmax, colscale, exps};
+    // pass 1: the plain build's column sums, nothing stored, and the scales
     float* none = reinterpret_cast<float*>(d_lib);  // not written in this pass
     e = cubic ? psflib::launch_build_cubic_orbit(cpairs, K, h->geo, desc->n, desc->N, L.M, none, tau,
-                                                 otmp, psflib::kOrbitSumsOnly, nullptr, s)
-              : psflib::launch_build_orbit_sums(d_cube, K, h->geo, desc->n, desc->N, L.M, none, tau,
-                                                otmp, s);
+                                                 otmp, psflib::kOrbitSumsOnly, &fx, s)
+              : psflib::launch_build_orbit(d_cube, K, h->geo, desc->n, desc->N, L.M, none, tau, otmp,
+                                           psflib::kOrbitSumsOnly, &fx, s);
     if (e != hipSuccess) return bail(e, "flux column-sum pass");
-    e = psflib::launch_flux_scale(h->geo, K, sums, h->pmax, L.ncols, tau, colscale, exps,
-                                  storage != PSFLIB_FP32, s);
-    if (e != hipSuccess) return bail(e, "flux scale kernel");
     // pass 2: the build, each column scaled as it is stored
+    float* dst = reinterpret_cast<float*>(bdst);
     if (orbit16)
       e = cubic ? psflib::launch_build_cubic_orbit16(storage, cpairs, K, h->geo, desc->n, desc->N, L.M,
-                                                     perm, eslot, slot_of, d_lib, tau, otmp,
-                                                     colscale, s)
-                : psflib::launch_build_orbit16(storage, d_cube, K, h->geo, desc->n, desc->N, L.M,
-                                               perm, eslot, slot_of, d_lib, tau, otmp, colscale, s);
+                                                     out16, otmp, &fx, s)
+                : psflib::launch_build_orbit16(storage, d_cube, K, h->geo, desc->n, desc->N, L.M, out16,
+                                               otmp, &fx, s);
     else
-      e = cubic ? psflib::launch_build_cubic_orbit(cpairs, K, h->geo, desc->n, desc->N, L.M,
-                                                   reinterpret_cast<float*>(bdst), tau, otmp,
-                                                   psflib::kOrbitScaled, colscale, s)
-                : psflib::launch_build_orbit_scaled(d_cube, K, h->geo, desc->n, desc->N, L.M, colscale,
-                                                    reinterpret_cast<float*>(bdst), tau, otmp, s);
+      e = cubic ? psflib::launch_build_cubic_orbit(cpairs, K, h->geo, desc->n, desc->N, L.M, dst, tau,
+                                                   otmp, psflib::kOrbitScaled, &fx, s)
+                : psflib::launch_build_orbit(d_cube, K, h->geo, desc->n, desc->N, L.M, dst, tau, otmp,
+                                             psflib::kOrbitScaled, &fx, s);
     if (e != hipSuccess) return bail(e, "flux-preserving orbit build kernels");
   } else if (cubic && orbit16) {
-    e = psflib::launch_build_cubic_orbit16(storage, psflib::spline_pairs_of(path_tmp, K, desc->n), K,
-                                           h->geo, desc->n, desc->N, L.M,
-                                           reinterpret_cast<int32_t*>(lib + L.off_perm),
-                                           reinterpret_cast<int32_t*>(lib + L.off_eslot),
-                                           reinterpret_cast<int32_t*>(lib + L.off_slot), d_lib, tau,
-                                           tp + spline_bytes, nullptr, s);
+    e = psflib::launch_build_cubic_orbit16(storage, cpairs, K, h->geo, desc->n, desc->N, L.M, out16,
+                                           otmp, nullptr, s);
     if (e != hipSuccess) return bail(e, "16-bit cubic orbit build kernels");
   } else if (cubic && lds) {
-    e = psflib::launch_build_cubic_orbit(psflib::spline_pairs_of(path_tmp, K, desc->n), K, h->geo,
-                                         desc->n, desc->N, L.M, reinterpret_cast<float*>(bdst), tau,
-                                         tp + spline_bytes, psflib::kOrbitPlain, nullptr, s);
+    e = psflib::launch_build_cubic_orbit(cpairs, K, h->geo, desc->n, desc->N, L.M,
+                                         reinterpret_cast<float*>(bdst), tau, otmp,
+                                         psflib::kOrbitPlain, nullptr, s);
     if (e != hipSuccess) return bail(e, "cubic orbit build kernels");
   } else if (cubic) {
-    e = psflib::launch_build_cubic(bstore, psflib::spline_pairs_of(path_tmp, K, desc->n), h->geo,
+    e = psflib::launch_build_cubic(bstore, cpairs, h->geo,
                                    desc->n, L.M, L.ncols, L.ncols_pad, bdst, tau, s);
     if (e != hipSuccess) return bail(e, "cubic build kernel");
   } else if (orbit16) {
-    e = psflib::launch_build_orbit16(storage, d_cube, K, h->geo, desc->n, desc->N, L.M,
-                                     reinterpret_cast<int32_t*>(lib + L.off_perm),
-                                     reinterpret_cast<int32_t*>(lib + L.off_eslot),
-                                     reinterpret_cast<int32_t*>(lib + L.off_slot), d_lib, tau,
-                                     path_tmp, nullptr, s);
+    e = psflib::launch_build_orbit16(storage, d_cube, K, h->geo, desc->n, desc->N, L.M, out16, otmp,
+                                     nullptr, s);
     if (e != hipSuccess) return bail(e, "16-bit orbit build kernels");
   } else if (lds) {
     e = psflib::launch_build_lds(d_cube, K, h->geo, desc->n, desc->N, L.M,
@@ -458,8 +446,6 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
     if (e != hipSuccess) return bail(e, "build kernel");
   }
   if (flux && !flux_orbit) {
-    e = psflib::launch_psf_sums(d_cube, K, L.M, sums, s);
-    if (e != hipSuccess) return bail(e, "psf sums kernel");
     e = psflib::launch_flux_rescale(reinterpret_cast<float*>(bdst), h->geo, K, sums, h->pmax, L.M,
                                     L.ncols, tau, exps, storage != PSFLIB_FP32, s);
     if (e != hipSuccess) return bail(e, "flux rescale kernel");

@@ -42,7 +42,19 @@ constexpr int32_t kZeroColumnExp = PSFLIB_ZERO_COLUMN_EXPONENT;  // exponent of 
 constexpr int kLdsCols = 16;         // LDS build: columns per work item (one wave each)
 constexpr int kLdsBuildMaxBytes = 163840;  // LDS build: bordered PSF pair must fit the CU's LDS
 constexpr int kSplinePad = 12;       // cubic rotation: zero pixels padded on each side before the spline filter
+constexpr int kRadiiArg = 128;       // radii passed as kernel arguments, at most
 constexpr int kLdsMaxBuckets = 8193; // LDS builds: radial brackets + the zero-column bucket, at most
+
+// Power-of-two exponent e with m * 2^-e in [2^14, 2^15); kZeroColumnExp for
+// m == 0 (a zero column has no scale: with this exponent every scene value
+// at the column scales to exactly 0, so it can neither set a scene's
+// exponent nor overflow the 16-bit format).
+__device__ inline int32_t scale_exponent(double m) {
+  if (m == 0.0) return kZeroColumnExp;
+  int E;
+  (void)frexp(m, &E);  // m = f * 2^E, f in [0.5, 1)
+  return E - 15;
+}
 
 struct Layout {
   int64_t M;          // n*n image pixels (rows of A)
@@ -128,11 +140,15 @@ __device__ __forceinline__ void cubic_weights(double t, float w[4]) {
 }
 
 // ---- kernel launchers (each returns hipGetLastError() after its launch) ----
-hipError_t launch_cube_max(const float* cube, int K, int64_t M, float* pmax, hipStream_t s);
+// largest value and float64 sum of each PSF (nullptr: not wanted)
+hipError_t launch_cube_stats(const float* cube, int K, int64_t M, float* pmax, double* sums,
+                             hipStream_t s);
 hipError_t launch_pair_cube(const float* cube, int K, int64_t M, float* pairs, hipStream_t s);
-hipError_t launch_geometry(int N, double S, const double* radii, int K, int interp, int oob,
-                           const float* pmax, bool want_exp, ColGeom* geo, int64_t ncols_pad,
-                           int32_t* exps, hipStream_t s);
+// radii: device memory for K radii when K > kRadiiArg (h_radii must then stay
+// until the stream has passed this point), else not used
+hipError_t launch_geometry(int N, double S, const double* h_radii, double* radii, int K, int interp,
+                           int oob, const float* pmax, bool want_exp, ColGeom* geo,
+                           int64_t ncols_pad, int32_t* exps, hipStream_t s);
 // Cubic-spline rotation: coefficients of every sampled PSF padded by
 // kSplinePad zeros per side ([K][Np][Np], Np = n + 2 kSplinePad) as
 // radial pairs (float2 [max(K-1,1)][Np*Np]) and their largest magnitude per
@@ -144,32 +160,45 @@ const float* spline_pairs_of(const void* scratch, int K, int n);
 hipError_t launch_build_cubic(int storage, const float* pairs, const ColGeom* geo, int n, int64_t M,
                               int64_t ncols, int64_t ncols_pad, void* lib, double* tau,
                               hipStream_t s);
-// Modes of the float32 orbit builds: plain; column sums only (nothing
-// stored); every value times its column's scale colscale[j] before it is
-// stored and summed.  The 16-bit orbit builds scale when colscale is given.
+// What a flux-preserving orbit build works with: the PSFs' sums and largest
+// values, and per base column the float32 scale.  Its first pass sums the plain
+// build's columns, nothing stored, and sets the scales and, with exps, the
+// 16-bit exponents (geo[j].e, exps[j]); the second, on the same scratch, whose
+// order of the base columns it keeps, scales every value before it is stored
+// and summed.
+struct OrbitFlux {
+  const double* sums;
+  const float* pmax;
+  float* colscale;
+  int32_t* exps;
+};
+// Modes of the float32 orbit builds: plain; the first pass; the second pass.
+// The 16-bit orbit builds are the second pass when fx is given.
 constexpr int kOrbitPlain = 0, kOrbitSumsOnly = 1, kOrbitScaled = 2;
-// The two passes of a flux-preserving bilinear orbit build: the column sums
-// of the plain build (tau), then the build scaled per column.
 bool build_orbit_flux_supported(int n, int K, int N);
-hipError_t launch_build_orbit_sums(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                   int64_t M, float* A32, double* tau, void* scratch, hipStream_t s);
-hipError_t launch_build_orbit_scaled(const float* cube, int K, const ColGeom* geo, int n, int N,
-                                     int64_t M, const float* colscale, float* A32, double* tau,
-                                     void* scratch, hipStream_t s);
+hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
+                              float* A32, double* tau, void* scratch, int mode,
+                              const OrbitFlux* fx, hipStream_t s);
 // Cubic build by quarter-turn orbits, the taps read from a box of the padded
 // coefficient pair staged per tile in LDS (float32 columns); scratch of
 // build_orbit_scratch_bytes(K, N, n) bytes.
 bool build_cubic_orbit_supported(int n, int K, int N);
-hipError_t launch_build_cubic_orbit(const float* pairs, int K, const ColGeom* geo, int n, int N,
-                                    int64_t M, float* A32, double* tau, void* scratch, int mode,
-                                    const float* colscale, hipStream_t s);
+hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int n, int N, int64_t M,
+                                    float* A32, double* tau, void* scratch, int mode,
+                                    const OrbitFlux* fx, hipStream_t s);
+// where the 16-bit orbit builds write
+struct Orbit16Out {
+  void* lib;
+  double* tau;
+  int32_t *perm, *eslot, *slot_of;
+  int64_t ncols_pad;
+};
 // 16-bit cubic storage built by the same orbits, slots as
 // launch_build_orbit16's; scratch of build_orbit_scratch_bytes(K, N, n) bytes.
 bool build_cubic_orbit16_supported(int n, int K, int N);
-hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, const ColGeom* geo,
-                                      int n, int N, int64_t M, int32_t* perm, int32_t* eslot,
-                                      int32_t* slot_of, void* lib, double* tau, void* scratch,
-                                      const float* colscale, hipStream_t s);
+hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, ColGeom* geo, int n,
+                                      int N, int64_t M, const Orbit16Out& out, void* scratch,
+                                      const OrbitFlux* fx, hipStream_t s);
 hipError_t launch_build(int storage, const float* pairs, const ColGeom* geo, int n, int64_t M,
                         int64_t ncols, int64_t ncols_pad, void* lib, double* tau, hipStream_t s);
 bool build_lds_supported(int n, int K, int N);
@@ -192,7 +221,7 @@ hipError_t launch_bucket_sort(const ColGeom* geo, int64_t ncols, int K, void* sc
 // float32 columns (A32[j*M + i]) and their float64 sums: the rotation-orbit
 // build (the pair in LDS, or a staged box of it per tile), else columns in
 // bracket order with the pair in LDS
-hipError_t launch_build_lds(const float* cube, int K, const ColGeom* geo, int n, int N, int64_t M,
+hipError_t launch_build_lds(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
                             float* A32, double* tau, void* scratch, hipStream_t s);
 // 16-bit storage built by rotation orbits (the pair, or a box of it per tile,
 // and the unit tiles in LDS):
@@ -201,9 +230,8 @@ hipError_t launch_build_lds(const float* cube, int K, const ColGeom* geo, int n,
 // column sums in tau.
 bool build_orbit16_supported(int n, int K, int N);
 size_t build_orbit_scratch_bytes(int K, int N, int n);
-hipError_t launch_build_orbit16(int storage, const float* cube, int K, const ColGeom* geo, int n,
-                                int N, int64_t M, int32_t* perm, int32_t* eslot, int32_t* slot_of,
-                                void* lib, double* tau, void* scratch, const float* colscale,
+hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* geo, int n, int N,
+                                int64_t M, const Orbit16Out& out, void* scratch, const OrbitFlux* fx,
                                 hipStream_t s);
 // 16-bit storage from float32 columns with the exponents in geo
 hipError_t launch_pack16(int storage, const float* A32, const ColGeom* geo, int64_t M,
@@ -215,12 +243,6 @@ hipError_t launch_pack16_range(int storage, const float* A32, int64_t col0, int6
 // Flux-preserving rescale of float32 columns: sums[k] = sum(P_k) (float64),
 // column j scaled by t_j / tau_j, tau_j recomputed; with want_exp the 16-bit
 // exponents (geo[j].e and exps[j]) follow the rescaled bound.
-hipError_t launch_psf_sums(const float* cube, int K, int64_t M, double* sums, hipStream_t s);
-// Per-column flux scales (and, with want_exp, exponents) from the plain
-// build's column sums, for the orbit builds' scaled pass.
-hipError_t launch_flux_scale(ColGeom* geo, int K, const double* sums, const float* pmax,
-                             int64_t ncols, const double* tau, float* colscale, int32_t* exps,
-                             bool want_exp, hipStream_t s);
 hipError_t launch_flux_rescale(float* A32, ColGeom* geo, int K, const double* sums,
                                const float* pmax, int64_t M, int64_t ncols, double* tau,
                                int32_t* exps, bool want_exp, hipStream_t s);

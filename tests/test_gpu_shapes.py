@@ -218,3 +218,29 @@ def test_spline_keeps_what_is_not_finite(torch, value):
     assert np.array_equal(got[~far], want[~far])
     lib.close()
     clean.close()
+
+
+# ------------------------------------------------------- orbit ordering ----
+# base columns below, at and above one sort block and the one-workgroup sort
+# (4096: 128 x 128), one bracket to more than the sort's threads, brackets left
+# empty, wide ones (many items each); the column of a PSF that is all k + 1 tells
+# its radial sample, so a column taken for another bracket's shows
+@pytest.mark.parametrize("N,K", [(2, 2), (63, 3), (64, 40), (65, 12), (127, 2), (128, 128), (128, 300), (129, 5),
+                                 (130, 1400), (200, 12)])
+@pytest.mark.parametrize("storage", ["fp32", "bf16"])
+def test_orbit_order(torch, N, K, storage):
+    from paper_2106_09122_amd import psflib
+    cube = np.broadcast_to(np.arange(1, K + 1, dtype=np.float32)[:, None, None], (K, 1, 1)).copy()
+    radii = np.linspace(0.1, 0.6 * N, K)
+    lib = psflib.Library(torch.from_numpy(cube).cuda(), radii, N, 1.0, storage=storage)
+    _fill(lib, torch)
+    c = np.arange(N) - 0.5 * (N - 1)
+    want = np.interp(np.hypot(*np.meshgrid(c, c)).ravel(), radii, np.arange(1, K + 1))
+    got = lib.get_columns(np.arange(N * N)).cpu().numpy()[:, 0]
+    unit = 1e-6 if storage == "fp32" else 2.0 ** -8  # float32 blend; bf16 rounding
+    assert np.all(np.abs(got - want) <= unit * want * 1.001)
+    z = torch.from_numpy(np.random.default_rng(N).random(N * N).astype(np.float32)).cuda()
+    ref = float(z.double() @ torch.from_numpy(got).cuda().double())
+    assert abs(float(lib.apply(z)[0]) - ref) <= 1e-5 * ref
+    assert np.allclose(lib.column_sums().cpu().numpy(), want, rtol=1e-6)
+    lib.close()
