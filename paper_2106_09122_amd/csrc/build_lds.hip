@@ -1025,7 +1025,8 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
 // does.  Sixteen waves per workgroup, 8.6 KiB of LDS each; no workgroup
 // barrier (a wave orders its own LDS writes and reads).
 constexpr int kFpSpan = 46;                     // box rows or columns, at most
-constexpr int kFpRegion = kFpSpan * (kFpSpan + 1);  // floats per wave (odd row stride)
+constexpr int kFpStride = kFpSpan + 1;          // odd
+constexpr int kFpRegion = kFpSpan * kFpStride;  // floats per wave
 constexpr int kBoxMaxN = 8192;  // PSF side: pixel offsets n^2 and row-range sizes stay in int
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -1047,10 +1048,15 @@ __device__ __forceinline__ void tap_origin(const G& g, double c, int a, int b, i
   r0 = (int)floor(rowf);
 }
 
+// the same for the cubic builds (see build_cubic_orbit_kernel)
+constexpr int kCbSpan = 48;                     // box rows or columns, at most
+constexpr int kCbStride = kCbSpan + 1;          // odd
+constexpr int kCbRegion = kCbSpan * kCbStride;  // floats per wave
+
 // one element from the staged box (origin: bordered row Rlo, column Clo)
 __device__ __forceinline__ float box_value(const float* __restrict__ Q, double ctux, double mstux,
-                                           double stuy, double ctuy, double c, int n, int bs,
-                                           int base) {
+                                           double stuy, double ctuy, double c, int n, int base) {
+  constexpr int bs = kFpStride;
   const Tap t = tap_coords(ctux, mstux, stuy, ctuy, c, n, bs);
   const int i = t.ok ? t.idx - base : 0;
   const float q00 = Q[i], q01 = Q[i + 1];
@@ -1063,50 +1069,57 @@ __device__ __forceinline__ float box_value(const float* __restrict__ Q, double c
 }
 
 // Stage rows [Rlo, Rlo + bh) x columns [Clo, Clo + bw) of a box into Q (row
-// stride bs), each entry the radial blend (1-w) x + w y of its pair, formed as
-// the pair kernels form their taps.  Bilinear: bordered indices of the
-// sample pair Pk, Pk1 (zero border); cubic: padded indices of the coefficient
-// pairs Pc (zero outside the Np x Np array).  The box is taken in row-major
-// order 64 entries at a time, lane l taking entry l of each step, 8 steps'
-// loads in flight before their LDS writes.
+// stride kFpStride, kCbStride), each entry the radial blend (1-w) x + w y of its
+// pair, formed as the pair kernels form their taps.  Bilinear: bordered indices
+// of the sample pair Pk, Pk1 (zero border); cubic: padded indices of the
+// coefficient pairs Pc (zero outside the Np x Np array).  A row at a time, lane l
+// its column l, 16 rows' loads in flight: the row's offset is a scalar, columns
+// outside the array load from past the plane's buffer, which gives zero, so that
+// an entry costs the blend and one LDS write.  (Taken 64 entries at a time, with
+// an index and bounds for every entry, staging was a third of the kernel's vector
+// instructions: 256^2 PSFs, 64^2 scene, float32, 320 us a build against 290 so.)
 template <bool CUBIC>
 __device__ __forceinline__ void stage_box(float* __restrict__ Q, const float* __restrict__ Pk,
                                           const float* __restrict__ Pk1,
                                           const float2* __restrict__ Pc, int n, int Np, int Rlo,
-                                          int Clo, int bh, int bw, int bs, float wk0, float wk1,
-                                          int lane) {
-  if (bh <= 0 || bw <= 0) return;  // uniform
-  const int q64 = 64 / bw, r64 = 64 - q64 * bw;
-  int rr = lane / bw, cc = lane - rr * bw;
-  while (__builtin_amdgcn_readfirstlane(rr) < bh) {  // lane 0 has the lowest entry
-    float xv[8], yv[8];
-    int dst[8];
+                                          int Clo, int bh, int bw, float wk0, float wk1, int lane) {
+  constexpr int stride = CUBIC ? kCbStride : kFpStride;
+  constexpr int kRows = 16, bytes = CUBIC ? 8 : 4;
+  const int R0 = __builtin_amdgcn_readfirstlane(CUBIC ? Rlo : Rlo - 1);
+  const int rows = __builtin_amdgcn_readfirstlane(bh);
+  const int side = CUBIC ? Np : n;
+  if (lane >= bw) return;
+  const int C = (CUBIC ? Clo : Clo - 1) + lane;
+  const uint32_t voff = (unsigned)C < (unsigned)side ? (uint32_t)C * bytes : 0x80000000u;
+  const int plane = side * side * bytes;  // side <= 8216
+  const __amdgpu_buffer_rsrc_t d0 =
+      __builtin_amdgcn_make_buffer_rsrc(CUBIC ? (void*)Pc : (void*)Pk, (short)0, plane, 0x00020000);
+  const __amdgpu_buffer_rsrc_t d1 =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(Pk1 ? Pk1 : Pk), (short)0, Pk1 ? plane : 0, 0x00020000);
+  // rows of the array: [top, end) of the box
+  const int top = R0 < 0 ? (-R0 < rows ? -R0 : rows) : 0;
+  const int end = side - R0 < rows ? (side - R0 > top ? side - R0 : top) : rows;
+  for (int r = 0; r < top; ++r) Q[r * stride + lane] = 0.0f;
+  for (int r = end; r < rows; ++r) Q[r * stride + lane] = 0.0f;
+  for (int r = top; r < end; r += kRows) {
+    float xv[kRows], yv[kRows];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int R = Rlo + rr, C = Clo + cc;
-      const bool in = rr < bh;
+    for (int k = 0; k < kRows; ++k) {
+      const int R = R0 + (r + k < end ? r + k : end - 1);  // past the end: the last row again
+      const int soff = R * side * bytes;
       if constexpr (CUBIC) {
-        const bool inner = in && (unsigned)R < (unsigned)Np && (unsigned)C < (unsigned)Np;
-        const float2 p = inner ? Pc[R * Np + C] : make_float2(0.0f, 0.0f);
-        xv[k] = p.x;
-        yv[k] = p.y;
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(d0, voff, soff, 0));
+        xv[k] = v.x;
+        yv[k] = v.y;
       } else {
-        const bool inner = in && (unsigned)(R - 1) < (unsigned)n && (unsigned)(C - 1) < (unsigned)n;
-        const int off = (R - 1) * n + (C - 1);
-        xv[k] = inner ? Pk[off] : 0.0f;
-        yv[k] = (inner && Pk1) ? Pk1[off] : 0.0f;
-      }
-      dst[k] = in ? rr * bs + cc : -1;
-      cc += r64;
-      rr += q64;
-      if (cc >= bw) {
-        cc -= bw;
-        ++rr;
+        xv[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(d0, voff, soff, 0));
+        yv[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(d1, voff, soff, 0));
       }
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (dst[k] >= 0) Q[dst[k]] = fmaf(wk1, yv[k], wk0 * xv[k]);
+    for (int k = 0; k < kRows; ++k)
+      if (r + k < end) Q[(r + k) * stride + lane] = fmaf(wk1, yv[k], wk0 * xv[k]);
   }
 }
 
@@ -1178,15 +1191,14 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
     const int Rlo = max(rmin + 1, 0), Clo = max(cmin + 1, 0);
     const int bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
     const int bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
-    const int bs = bw | 1;
     wave_lds_sync();  // the previous tile's reads are done
-    stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
+    stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, wk0, wk1, lane);
     wave_lds_sync();  // the box is staged
-    const int base = Rlo * bs + Clo;
+    const int base = Rlo * kFpStride + Clo;
     if (ab0 < ae && bb0 < be)
       orbit_block<VEC, MODE>(
           [&](double ctux, double mstux, double stuy, double ctuy) {
-            return box_value(Q, ctux, mstux, stuy, ctuy, c, n, bs, base);
+            return box_value(Q, ctux, mstux, stuy, ctuy, c, n, base);
           },
           g, c, n, o.N, M, ab0, bb0, A, tsum);
     }
@@ -1368,9 +1380,6 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
 // holds the radial blend (1-w) C_k + w C_{k+1} (zero outside the array), and a
 // pixel is the 4 x 4 weighted sum of the blend, row by row, in the order of
 // the gather form, so both give identical values.
-constexpr int kCbSpan = 48;                        // box rows or columns, at most
-constexpr int kCbRegion = kCbSpan * (kCbSpan + 1);  // floats per wave (odd row stride)
-
 __device__ __forceinline__ int clamp_origin(int v, int Np) { return v < -3 ? -3 : (v > Np + 1 ? Np + 1 : v); }
 
 // clamped tap origin (padded row and column) of image pixel (a, b)
@@ -1443,9 +1452,8 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
     }
     const int Rlo = rmin - 1, Clo = cmin - 1;
     const int bh = min(rmax - rmin + 4, kCbSpan), bw = min(cmax - cmin + 4, kCbSpan);
-    const int bs = bw | 1;
     wave_lds_sync();  // the previous tile's reads are done
-    stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
+    stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, wk0, wk1, lane);
     wave_lds_sync();  // the box is staged
     if (ab0 < ae && bb0 < be)
       orbit_block<VEC, MODE>(
@@ -1458,11 +1466,11 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
             float wy[4], wx[4];
             cubic_weights(rowf - r0f, wy);
             cubic_weights(colf - c0f, wx);
-            const float* tp = Q + (r0 - 1 - Rlo) * bs + (c0 - 1 - Clo);
+            const float* tp = Q + (r0 - 1 - Rlo) * kCbStride + (c0 - 1 - Clo);
             float V = 0.0f;
 #pragma unroll
             for (int dr = 0; dr < 4; ++dr) {
-              const float* tr = tp + dr * bs;
+              const float* tr = tp + dr * kCbStride;
               float v = wx[0] * tr[0];
               v = fmaf(wx[1], tr[1], v);
               v = fmaf(wx[2], tr[2], v);
@@ -1503,7 +1511,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
   constexpr int REGION = CUBIC ? kCbRegion : kFpRegion;
   extern __shared__ float QS[];
   const int64_t w0 = (int64_t)blockIdx.x * 16;  // the window's first base position
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
   uint16_t* tiles = reinterpret_cast<uint16_t*>(QS + 16 * REGION);
   float* Q = QS + wave * REGION;
@@ -1535,7 +1543,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
     const int ae = (a0 + 32 < rb) ? a0 + 32 : rb;
     for (int b0 = 0; b0 < n; b0 += TB) {
       const int be = (b0 + TB < n) ? b0 + TB : n;
-      int bs = 1, base = 0, Rlo = 0, Clo = 0;
+      int base = 0, Rlo = 0, Clo = 0;
       if (!blank) {  // uniform per wave: stage the box of rows [a0, ae), columns [b0, be)
         int rmin, rmax, cmin, cmax;
         {
@@ -1568,9 +1576,8 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
           bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
           bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
         }
-        bs = bw | 1;
-        base = Rlo * bs + Clo;
-        stage_box<CUBIC>(Q, Pk, Pk1, Pc, n, Np, Rlo, Clo, bh, bw, bs, wk0, wk1, lane);
+        base = Rlo * kFpStride + Clo;
+        stage_box<CUBIC>(Q, Pk, Pk1, Pc, n, Np, Rlo, Clo, bh, bw, wk0, wk1, lane);
         wave_lds_sync();  // the box is staged
       }
       for (int a1 = a0; a1 < ae; a1 += TA, buf ^= 1) {  // uniform over the workgroup
@@ -1606,10 +1613,10 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
                   float wy[4], wx[4];
                   cubic_weights(rowf - r0f, wy);
                   cubic_weights(colf - c0f, wx);
-                  const float* t = Q + (r0 - 1 - Rlo) * bs + (c0 - 1 - Clo);
+                  const float* t = Q + (r0 - 1 - Rlo) * kCbStride + (c0 - 1 - Clo);
 #pragma unroll
                   for (int dr = 0; dr < 4; ++dr) {
-                    const float* tr = t + dr * bs;
+                    const float* tr = t + dr * kCbStride;
                     float v = wx[0] * tr[0];
                     v = fmaf(wx[1], tr[1], v);
                     v = fmaf(wx[2], tr[2], v);
@@ -1617,7 +1624,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
                     val = fmaf(wy[dr], v, val);
                   }
                 } else {
-                  val = box_value(Q, ctux, mstux, stuy, ctuy, c, n, bs, base);
+                  val = box_value(Q, ctux, mstux, stuy, ctuy, c, n, base);
                 }
               }
               if constexpr (SCALED) val *= sf;

@@ -132,11 +132,11 @@ hipError_t launch_identity_order(int32_t* perm, int32_t* eslot, int32_t* slot_of
 __device__ __forceinline__ void cubic_weights(double t, float w[4]) {
 #pragma clang fp contract(off)
   constexpr double sixth = 1.0 / 6.0;  // a product, not a float64 division (within an ulp)
-  const double s = 1.0 - t;
-  w[0] = (float)(s * s * s * sixth);
-  w[1] = (float)(2.0 / 3.0 - t * t + t * t * t * 0.5);
-  w[2] = (float)(2.0 / 3.0 - s * s + s * s * s * 0.5);
-  w[3] = (float)(t * t * t * sixth);
+  const double s = 1.0 - t, s2 = s * s, t2 = t * t;
+  w[0] = (float)(s2 * (s * sixth));
+  w[1] = (float)fma(t2, fma(t, 0.5, -1.0), 2.0 / 3.0);
+  w[2] = (float)fma(s2, fma(s, 0.5, -1.0), 2.0 / 3.0);
+  w[3] = (float)(t2 * (t * sixth));
 }
 
 // ---- kernel launchers (each returns hipGetLastError() after its launch) ----
