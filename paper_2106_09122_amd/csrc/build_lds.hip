@@ -798,6 +798,9 @@ __device__ __forceinline__ float orbit_value(const float2* __restrict__ P2, doub
 // multiplied by its column's float32 scale before it is stored and summed
 // (the second pass).
 constexpr int kPlain = kOrbitPlain, kSumsOnly = kOrbitSumsOnly, kScaled = kOrbitScaled;
+// and the first pass that also keeps the base columns (A: the column of base
+// position 0), which the 16-bit builds' second pass reads
+constexpr int kBases = kOrbitScaled + 1;
 
 // 16-byte run of a column.  VEC (n a multiple of 32): the eight lanes of a tile
 // row fill a whole 128-byte line.  Otherwise the run starts at any float and
@@ -862,7 +865,7 @@ __device__ __forceinline__ int block_start(int v0, int n) {
 
 // What a wave needs of the base column it works on (the same in every lane).
 struct OrbitCol {
-  int64_t j0;
+  int64_t j0, pos;  // column and base position
   double ct, st, w;
   int k;
   float scale;  // flux-preserving scale
@@ -874,6 +877,7 @@ __device__ __forceinline__ OrbitCol load_orbit_col(const int32_t* __restrict__ r
                                                    const float* __restrict__ colscale, int64_t sp) {
   OrbitCol o;
   o.j0 = reps[sp];
+  o.pos = sp;
   const ColGeom* g = geo + o.j0;
   o.ct = g->ct;
   o.st = g->st;
@@ -897,7 +901,7 @@ template <bool VEC, int MODE, typename Value>
 __device__ __forceinline__ void orbit_block(Value value, const OrbitCol& g, double c, int n, int N,
                                             int64_t M, int ab0, int bb0, float* A, double& tsum) {
   const bool centre = orbit_is_centre(g.j0, N);
-  float* C0 = A + g.j0 * M;
+  float* C0 = A + (MODE == kBases ? g.pos : g.j0) * M;
   float* C1 = A + orbit_member(g.j0, N, 1) * M;
   float* C2 = A + orbit_member(g.j0, N, 2) * M;
   float* C3 = A + orbit_member(g.j0, N, 3) * M;
@@ -931,13 +935,17 @@ __device__ __forceinline__ void orbit_block(Value value, const OrbitCol& g, doub
       }
       if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
     }
-    if constexpr (MODE != kSumsOnly) {  // the row's runs of C0 and C2
+    if constexpr (MODE == kBases) {
+      if (VEC || n >= 4) *reinterpret_cast<f32x4u*>(C0 + (int64_t)a * n + bb) = (f32x4){x[r][0], x[r][1], x[r][2], x[r][3]};
+    } else if constexpr (MODE != kSumsOnly) {  // the row's runs of C0 and C2
       if (VEC || n >= 4) store_row_runs<VEC>(x[r], C0, C2, a, bb, n, centre);
     }
     // one row of the block at a time: bounds the live coordinate temporaries
     __builtin_amdgcn_sched_barrier(0);
   }
-  if constexpr (MODE != kSumsOnly) {
+  if constexpr (MODE == kBases) {
+    if (!VEC && n < 4) store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, true);
+  } else if constexpr (MODE != kSumsOnly) {
     if (!VEC && n < 4)
       store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, centre);
     else if (!centre)
@@ -1207,6 +1215,19 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
   }
 }
 
+// 16-bit rounding of a column's value, scaled by 2^-e (exact)
+template <bool BF16>
+__device__ __forceinline__ uint16_t round16(float val, int e) {
+  const float xs = ldexpf(val, -e);
+  if constexpr (BF16) {
+    uint32_t w = __float_as_uint(xs);
+    w += 0x7FFFu + ((w >> 16) & 1u);  // finite: round to nearest, ties to even
+    return (uint16_t)(w >> 16);
+  } else {
+    return __builtin_bit_cast(uint16_t, (_Float16)xs);
+  }
+}
+
 // 16-bit store of one unit.  Non-temporal where image rows start on 64 bytes
 // (sides that are multiples of 4: 128^2 PSFs, 128^2 scene, 274 us a build against
 // 280 with plain stores; 180^2, 90^2 scene, 350 against 365).  On other sides
@@ -1313,16 +1334,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
                               : orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
             if constexpr (SCALED) val *= sf;
             tsum += (double)val;
-            const float xs = ldexpf(val, -g.e);  // exact power-of-two scaling
-            uint32_t hv;
-            if constexpr (BF16) {
-              uint32_t w = __float_as_uint(xs);
-              w += 0x7FFFu + ((w >> 16) & 1u);  // finite: round to nearest, ties to even
-              hv = w >> 16;
-            } else {
-              hv = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)xs);
-            }
-            tile[((h * TA + li) * TP + 4 * lk + q) * 8 + u] = (uint16_t)hv;
+            tile[((h * TA + li) * TP + 4 * lk + q) * 8 + u] = round16<BF16>(val, g.e);
           }
         }
       }
@@ -1486,6 +1498,109 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
   }
 }
 
+// Copy a tile of TA x 32 units of a whole window to its members: threads 0..511
+// along rows, 512..1023 along columns; unit cu of a direction is block cu / (32
+// TA), row and column from cu % (32 TA).  Rows end at `ae`; block cq is there when
+// 8 cq < left.
+template <int TA, bool LINES>
+__device__ __forceinline__ void copy_units(const uint16_t* tile, uint16_t* __restrict__ Mh, int64_t G0,
+                                           int64_t M, int n, int a1, int ae, int b0, int64_t left, int tid) {
+  constexpr int TB = 32, TP = TB + 1;
+  const bool along_cols = tid >= 512;
+  const int cu = tid & 511, cq = cu / (TA * TB), crem = cu % (TA * TB);
+  if (cq >= 2 || 8 * cq >= left) return;
+  int r, cb;
+  if (along_cols) {
+    cb = crem / TA;
+    r = crem % TA;
+  } else {
+    r = crem >> 5;
+    cb = crem & 31;
+  }
+  const int a = a1 + r, b = b0 + cb;
+  if (a >= ae || b >= n) return;
+  uint16_t* dA;
+  uint16_t* dB;
+  if (along_cols) {
+    dA = Mh + ((G0 + 4 * cq + 1) * M + (int64_t)b * n + (n - 1 - a)) * 8;
+    dB = Mh + ((G0 + 4 * cq + 3) * M + (int64_t)(n - 1 - b) * n + a) * 8;
+  } else {
+    dA = Mh + ((G0 + 4 * cq + 0) * M + (int64_t)a * n + b) * 8;
+    dB = Mh + ((G0 + 4 * cq + 2) * M + (int64_t)(n - 1 - a) * n + (n - 1 - b)) * 8;
+  }
+  const u32x4 w = *reinterpret_cast<const u32x4*>(tile + ((cq * TA + r) * TP + cb) * 8);
+  store_unit<LINES>(dA, w);
+  store_unit<LINES>(dB, w);
+}
+
+// The second pass of a 16-bit flux-preserving build from the base columns that
+// the first pass kept (S[position][pixel], float32): a window of 16 bases and a
+// range of rows a workgroup, as the 16-bit orbit builds, the values loaded
+// instead of formed, the next tile's in flight while a tile is copied.  Bound by
+// memory: half the library's bytes read, all of them written.  Forming the values
+// again took 202 us for 101^2 PSFs of a 101^2 scene with the spline, this 80.
+template <bool BF16, bool LINES>
+__global__ __launch_bounds__(1024) void spread_orbit16_kernel(const float* __restrict__ S,
+                                                              const ColGeom* __restrict__ geo,
+                                                              const int32_t* __restrict__ reps, int n,
+                                                              int64_t M, int rpr, int64_t nreps,
+                                                              uint16_t* __restrict__ Mh,
+                                                              double* __restrict__ part,
+                                                              const float* __restrict__ colscale) {
+  constexpr int TA = 8, TB = 32, TP = TB + 1;
+  constexpr int TILE = 2 * TA * TP * 8;
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[2 * TILE];
+  const int64_t w0 = (int64_t)blockIdx.x * 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ra = (int)blockIdx.y * rpr, rb = (ra + rpr < n) ? ra + rpr : n;
+  const int64_t sp = w0 + wave;
+  const int64_t whole = (nreps + 7) / 8 * 8;
+  const int h = wave >> 3, u = wave & 7;
+  const int li = lane >> 3, lk = lane & 7;
+  const bool base = sp < nreps;
+  int e = 0;
+  float sf = 1.0f;
+  if (base) {
+    e = geo[reps[sp]].e;
+    sf = colscale[reps[sp]];
+  }
+  const float* src = S + (base ? sp : 0) * M;
+  // four values of row a from column b, zeros outside the range or the image
+  auto load = [&](int a, int b) -> f32x4 {
+    f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (!base || a >= rb || b >= n) return v;
+    const float* p = src + (int64_t)a * n + b;
+    if (b + 4 <= n) return *reinterpret_cast<const f32x4u*>(p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (b + q < n) v[q] = p[q];
+    return v;
+  };
+  double tsum = 0.0;
+  int buf = 0;
+  const int64_t G0 = w0 / 8 * 4;
+  f32x4 next = load(ra + li, 4 * lk);
+  for (int a1 = ra; a1 < rb; a1 += TA) {
+    for (int b0 = 0; b0 < n; b0 += TB, buf ^= 1) {  // uniform over the workgroup
+      uint16_t* tile = tiles + buf * TILE;
+      const f32x4 v = next;
+      const bool wrap = b0 + TB >= n;
+      next = load(a1 + (wrap ? TA : 0) + li, (wrap ? 0 : b0 + TB) + 4 * lk);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float val = v[q] * sf;
+        tsum += (double)val;
+        tile[((h * TA + li) * TP + 4 * lk + q) * 8 + u] = round16<BF16>(val, e);
+      }
+      __syncthreads();  // two buffers: see build_orbit16_kernel
+      copy_units<TA, LINES>(tile, Mh, G0, M, n, a1, rb, b0, whole - w0, tid);
+    }
+  }
+  if (!base) return;
+  tsum = wave_sum_f64(tsum);
+  if (lane == 0) part[(int64_t)blockIdx.y * nreps + sp] = tsum;
+}
+
 // 16-bit orbit build for pairs that do not fit the LDS beside the unit tiles
 // (n > 133), bilinear or cubic-spline: build_orbit16_kernel's unit tiles and copies,
 // with each wave's taps read from a staged box (as build_orbit_box_kernel and
@@ -1533,10 +1648,6 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
   const float2* Pc = reinterpret_cast<const float2*>(src0) + (CUBIC ? (int64_t)pb * Np * Np : 0);  // cubic
   const int64_t G0 = w0 / 8 * 4;
   const int li = lane / LPR, lk = lane % LPR;
-  // copy roles: threads 0..511 along rows, 512..1023 along columns; unit cu of
-  // a direction is block cu / (TA TB), row and column from cu % (TA TB)
-  const bool along_cols = tid >= 512;
-  const int cu = tid & 511, cq = cu / (TA * TB), crem = cu % (TA * TB);
   double tsum = 0.0;
   int buf = 0;
   for (int a0 = ra; a0 < rb; a0 += 32) {
@@ -1629,47 +1740,12 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
               }
               if constexpr (SCALED) val *= sf;
               tsum += (double)val;
-              const float xs = ldexpf(val, -g.e);  // exact power-of-two scaling
-              uint32_t hv;
-              if constexpr (BF16) {
-                uint32_t w = __float_as_uint(xs);
-                w += 0x7FFFu + ((w >> 16) & 1u);  // finite: round to nearest, ties to even
-                hv = w >> 16;
-              } else {
-                hv = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)xs);
-              }
-              tile[((h * TA + li) * TP + CPL * lk + q) * 8 + u] = (uint16_t)hv;
+              tile[((h * TA + li) * TP + CPL * lk + q) * 8 + u] = round16<BF16>(val, g.e);
             }
           }
         }
         __syncthreads();
-        // one unit per thread: block cq, TA rows x 32 columns
-        if (cq < 2 && w0 + 8 * cq < whole) {
-          int r, cb;
-          if (along_cols) {
-            cb = crem / TA;
-            r = crem % TA;
-          } else {
-            r = crem >> 5;
-            cb = crem & 31;
-          }
-          const int a = a1 + r, b = b0 + cb;
-          if (a < ae && b < n) {
-            const uint16_t* src = tile + ((cq * TA + r) * TP + cb) * 8;
-            uint16_t* dA;
-            uint16_t* dB;
-            if (along_cols) {
-              dA = Mh + ((G0 + 4 * cq + 1) * M + (int64_t)b * n + (n - 1 - a)) * 8;
-              dB = Mh + ((G0 + 4 * cq + 3) * M + (int64_t)(n - 1 - b) * n + a) * 8;
-            } else {
-              dA = Mh + ((G0 + 4 * cq + 0) * M + (int64_t)a * n + b) * 8;
-              dB = Mh + ((G0 + 4 * cq + 2) * M + (int64_t)(n - 1 - a) * n + (n - 1 - b)) * 8;
-            }
-            const u32x4 w = *reinterpret_cast<const u32x4*>(src);
-            store_unit<LINES>(dA, w);
-            store_unit<LINES>(dB, w);
-          }
-        }
+        copy_units<TA, LINES>(tile, Mh, G0, M, n, a1, ae, b0, whole - w0, tid);
       }
     }
   }
@@ -1874,7 +1950,7 @@ static hipError_t orbit_sort(const ColGeom* geo, const OrbitPlan& pl, hipStream_
 static hipError_t orbit_finish(const OrbitPlan& pl, int nparts, int mode, int K, ColGeom* geo,
                                const OrbitFlux* fx, double* tau, hipStream_t s) {
   const unsigned grid = (unsigned)((pl.o.nreps + 255) / 256);
-  if (mode == kSumsOnly)
+  if (mode == kSumsOnly || mode == kBases)
     orbit_scale_kernel<<<grid, 256, 0, s>>>(pl.reps, pl.o, pl.part, nparts, K, geo, *fx);
   else
     orbit_tau_kernel<<<grid, 256, 0, s>>>(pl.reps, pl.o, pl.part, nparts, tau);
@@ -1908,6 +1984,10 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
                               const OrbitFlux* fx, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
   const float* colscale = fx ? fx->colscale : nullptr;
+  if (mode == kSumsOnly && fx->bases) {
+    mode = kBases;
+    A32 = fx->bases;
+  }
   hipError_t e = mode == kScaled ? hipSuccess : orbit_sort(geo, pl, s);  // kept for the second pass
   if (e != hipSuccess) return e;
   const bool vec = (n % 32) == 0;
@@ -1929,6 +2009,9 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
         break;
       case kScaled:
         e = vec ? launch(build_orbit_box_kernel<true, kScaled>) : launch(build_orbit_box_kernel<false, kScaled>);
+        break;
+      case kBases:
+        e = vec ? launch(build_orbit_box_kernel<true, kBases>) : launch(build_orbit_box_kernel<false, kBases>);
         break;
       default:
         e = vec ? launch(build_orbit_box_kernel<true, kPlain>) : launch(build_orbit_box_kernel<false, kPlain>);
@@ -1954,6 +2037,9 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
     case kScaled:
       e = vec ? launch(build_orbit_kernel<true, kScaled>) : launch(build_orbit_kernel<false, kScaled>);
       break;
+    case kBases:
+      e = vec ? launch(build_orbit_kernel<true, kBases>) : launch(build_orbit_kernel<false, kBases>);
+      break;
     default:
       e = vec ? launch(build_orbit_kernel<true, kPlain>) : launch(build_orbit_kernel<false, kPlain>);
   }
@@ -1975,6 +2061,10 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int
                                     const OrbitFlux* fx, hipStream_t s) {
   const OrbitPlan pl = orbit_plan(K, N, n, scratch);
   const float* colscale = fx ? fx->colscale : nullptr;
+  if (mode == kSumsOnly && fx->bases) {
+    mode = kBases;
+    A32 = fx->bases;
+  }
   hipError_t e = mode == kScaled ? hipSuccess : orbit_sort(geo, pl, s);  // kept for the second pass
   if (e != hipSuccess) return e;
   const int Np = n + 2 * kSplinePad;
@@ -1997,6 +2087,9 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int
       break;
     case kScaled:
       e = vec ? launch(build_cubic_orbit_kernel<true, kScaled>) : launch(build_cubic_orbit_kernel<false, kScaled>);
+      break;
+    case kBases:
+      e = vec ? launch(build_cubic_orbit_kernel<true, kBases>) : launch(build_cubic_orbit_kernel<false, kBases>);
       break;
     default:
       e = vec ? launch(build_cubic_orbit_kernel<true, kPlain>) : launch(build_cubic_orbit_kernel<false, kPlain>);
@@ -2048,6 +2141,21 @@ static hipError_t orbit16_form(int storage, int n, const float* colscale, F f) {
   return storage == PSFLIB_BF16_POW2 ? on_scale(std::true_type{}) : on_scale(std::false_type{});
 }
 
+static hipError_t launch_spread16(int storage, const ColGeom* geo, int n, int64_t M, const OrbitPlan& pl,
+                                  const Orbit16Out& out, const OrbitFlux& fx, hipStream_t s) {
+  const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
+  const hipError_t e = orbit16_form(storage, n, fx.colscale, [&](auto bf, auto, auto lines) {
+    spread_orbit16_kernel<bf.value, lines.value><<<wgrid, 1024, 0, s>>>(
+        fx.bases, geo, pl.reps, n, M, pl.rpr, pl.o.nreps, reinterpret_cast<uint16_t*>(out.lib), pl.part,
+        fx.colscale);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  return orbit16_end(pl, M, geo, out, s);
+}
+
+size_t orbit_bases_bytes(int N, int64_t M) { return (size_t)orbit_grid(N).nreps * (size_t)M * 4; }
+
 // float32: the pair in LDS, or (up to kBoxMaxN) a staged box per tile
 static bool build_orbit_supported(int n, int K, int N) {
   return (pair_fits_lds(n) || n <= kBoxMaxN) && orbit_sort_fits(K, N);
@@ -2066,6 +2174,7 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* 
   hipError_t e = fx ? hipSuccess : orbit_sort(geo, pl, s);  // the first pass has sorted
   if (e != hipSuccess) return e;
   uint16_t* Mh = reinterpret_cast<uint16_t*>(out.lib);
+  if (fx && fx->bases) return launch_spread16(storage, geo, n, M, pl, out, *fx, s);
   const dim3 grid((unsigned)pl.items_max, (unsigned)pl.nranges);
   const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
   if (!orbit16_pair_fits(n)) {  // a staged box per 32 x 32 pixels
@@ -2113,6 +2222,7 @@ hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, Co
   hipError_t e = fx ? hipSuccess : orbit_sort(geo, pl, s);  // the first pass has sorted
   if (e != hipSuccess) return e;
   uint16_t* Mh = reinterpret_cast<uint16_t*>(out.lib);
+  if (fx && fx->bases) return launch_spread16(storage, geo, n, M, pl, out, *fx, s);
   const dim3 wgrid((unsigned)((pl.o.nreps + 15) / 16), (unsigned)pl.nranges);
   const size_t lds = orbit16_box_lds_bytes(true);
   const int Np = n + 2 * kSplinePad;

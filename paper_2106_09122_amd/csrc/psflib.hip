@@ -264,6 +264,107 @@ psflib_status psflib_library_bytes(const psflib_desc* desc, size_t* bytes) {
   return PSFLIB_OK;
 }
 
+namespace {
+
+// Temporary device memory of one call (split-K partial sums, packed scenes,
+// reduction blocks, a build's tables).  Outside stream capture it is the calling
+// stream's buffer: one per (device, stream), kept like the pool's blocks until
+// the process ends and grown on demand.  Calls on one stream run in order, so
+// every call on that stream (whatever its handle) can reuse the buffer, and
+// calls on different streams never share one (the per-thread default stream,
+// one handle for many streams, allocates from the pool).  The lock is held over the
+// call's launches, so a call from another host thread on the same stream
+// cannot slip its kernels in between them.  This adds nothing to the stream
+// per call (a stream-ordered free per call adds a marker: ~3 us between
+// kernels).  Under capture the memory is allocated from the pool inside the
+// graph instead, so every graph owns its own.  A call that gives `keep` takes
+// more than that, or what would bring all streams' buffers over kKeptBytes, from
+// the pool and gives it back.
+constexpr size_t kKeptBytes = (size_t)2 << 30;
+struct StreamBuffer {
+  int dev;
+  hipStream_t s;
+  void* p;
+  size_t bytes;
+};
+std::mutex g_sb_mu;
+std::vector<StreamBuffer> g_sb;
+
+class CallScratch {
+ public:
+  static constexpr size_t kKeepAll = ~(size_t)0;
+
+  hipError_t acquire(int dev, hipStream_t s, size_t bytes, size_t keep = kKeepAll) {
+    s_ = s;
+    if (bytes == 0) return hipSuccess;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &cs);
+    if (e != hipSuccess) return e;
+    if (cs != hipStreamCaptureStatusNone || s == hipStreamPerThread || bytes > keep)
+      return from_pool(dev, bytes);
+    lock_ = std::unique_lock<std::mutex>(g_sb_mu);
+    StreamBuffer* slot = nullptr;
+    for (auto& sb : g_sb)
+      if (sb.dev == dev && sb.s == s) slot = &sb;
+    if (slot && slot->bytes >= bytes) {
+      p_ = slot->p;
+      return hipSuccess;
+    }
+    size_t want = (size_t)1 << 20;  // grow in powers of two from 1 MiB
+    while (want < bytes) want <<= 1;
+    if (keep != kKeepAll) {
+      size_t kept = want;
+      for (auto& sb : g_sb)
+        if (&sb != slot) kept += sb.bytes;
+      if (kept > kKeptBytes) {
+        lock_.unlock();
+        return from_pool(dev, bytes);
+      }
+    }
+    e = psflib::pool_alloc(&p_, want, dev, s);
+    if (e != hipSuccess) {
+      p_ = nullptr;
+      lock_.unlock();
+      return e;
+    }
+    if (slot) {
+      // the smaller buffer goes back to the pool after the work queued on s
+      e = hipFreeAsync(slot->p, s);
+      slot->p = p_;
+      slot->bytes = want;
+    } else {
+      g_sb.push_back(StreamBuffer{dev, s, p_, want});
+    }
+    return e;
+  }
+  void* ptr() const { return p_; }
+  // after the call's launches
+  hipError_t release() {
+    hipError_t e = hipSuccess;
+    if (pooled_ && p_) e = hipFreeAsync(p_, s_);
+    pooled_ = false;
+    p_ = nullptr;
+    if (lock_.owns_lock()) lock_.unlock();
+    return e;
+  }
+  ~CallScratch() { (void)release(); }
+
+ private:
+  hipError_t from_pool(int dev, size_t bytes) {
+    const hipError_t e = psflib::pool_alloc(&p_, bytes, dev, s_);
+    if (e != hipSuccess) p_ = nullptr;
+    pooled_ = p_ != nullptr;
+    return e;
+  }
+
+  std::unique_lock<std::mutex> lock_;
+  void* p_ = nullptr;
+  bool pooled_ = false;
+  hipStream_t s_ = nullptr;
+};
+
+}  // namespace
+
 psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const double* h_radii,
                            void* d_lib, size_t lib_bytes, void* stream, psflib_handle** out) {
   psflib_status st = check_desc(desc);
@@ -352,20 +453,33 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
   const size_t sums_bytes =
       align256(flux ? (size_t)K * 8 : 0) + align256(flux_orbit ? (size_t)L.ncols * 4 : 0);
   const size_t tmp_bytes = path_bytes + stage_bytes + sums_bytes;
-  void* tmp = nullptr;
+  CallScratch tmp;
   // on failure: wait for what this build enqueued (on its own stream), then
   // release its memory
   auto bail = [&](hipError_t err, const char* what) {
     psflib_status r = device_fail(err, what);
-    if (tmp) (void)hipFreeAsync(tmp, s);
+    (void)tmp.release();
     (void)hipStreamSynchronize(s);
     (void)psflib::pool_release(h->ws, dev);
     delete h;
     return r;
   };
-  e = psflib::pool_alloc(&tmp, tmp_bytes, dev, s);
-  if (e != hipSuccess) { tmp = nullptr; return bail(e, "scratch allocation (build)"); }
-  char* tp = reinterpret_cast<char*>(tmp);
+  // A 16-bit flux-preserving build keeps its first pass's base columns (half the
+  // library's bytes) when its scratch stays within what a stream keeps and there
+  // is memory for them.  (A pool block of 100 MB costs 150 to 300 us whenever the
+  // pool was trimmed, as by a release on another stream: more than the second
+  // pass saves.)
+  constexpr size_t kKeep = (size_t)512 << 20;
+  size_t base_bytes = flux_orbit && orbit16 ? psflib::orbit_bases_bytes(desc->N, L.M) : 0;
+  if (tmp_bytes + base_bytes > kKeep) base_bytes = 0;
+  e = tmp.acquire(dev, s, tmp_bytes + base_bytes, kKeep);
+  if (e == hipErrorOutOfMemory && base_bytes > 0) {
+    (void)hipGetLastError();
+    base_bytes = 0;
+    e = tmp.acquire(dev, s, tmp_bytes, kKeep);
+  }
+  if (e != hipSuccess) return bail(e, "scratch allocation (build)");
+  char* tp = reinterpret_cast<char*>(tmp.ptr());
   void* path_tmp = tp;
   float* A32 = stage32 ? reinterpret_cast<float*>(tp + path_bytes) : reinterpret_cast<float*>(d_lib);
   double* sums = flux ? reinterpret_cast<double*>(tp + path_bytes + stage_bytes) : nullptr;
@@ -396,7 +510,8 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
                                     reinterpret_cast<int32_t*>(lib + L.off_eslot),
                                     reinterpret_cast<int32_t*>(lib + L.off_slot), L.ncols_pad};
   if (flux_orbit) {
-    const psflib::OrbitFlux fx = {sums, h->pmax, colscale, exps};
+    const psflib::OrbitFlux fx = {sums, h->pmax, colscale, exps,
+                                  base_bytes > 0 ? reinterpret_cast<float*>(tp + tmp_bytes) : nullptr};
     // pass 1: the plain build's column sums, nothing stored, and the scales
     float* none = reinterpret_cast<float*>(d_lib);  // not written in this pass
     e = cubic ? psflib::launch_build_cubic_orbit(cpairs, K, h->geo, desc->n, desc->N, L.M, none, tau,
@@ -462,9 +577,8 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
                                       L.ncols_pad, s);
     if (e != hipSuccess) return bail(e, "column order kernel");
   }
-  e = hipFreeAsync(tmp, s);
-  if (e != hipSuccess) { tmp = nullptr; return bail(e, "hipFreeAsync(build scratch)"); }
-  tmp = nullptr;
+  e = tmp.release();
+  if (e != hipSuccess) return bail(e, "hipFreeAsync(build scratch)");
   e = h->ws_uses.note(s);
   if (e != hipSuccess) return bail(e, "hipEventRecord(build)");
   *out = h;
@@ -484,82 +598,6 @@ hipError_t launch_product(const psflib_handle* h, bool adjoint, const float* in,
   return psflib::launch_matvec(h->desc.storage, h->lib, cx, in, h->L.M, h->L.ncols,
                                h->L.ncols_pad, partial, out, s);
 }
-
-// Temporary device memory of one call (split-K partial sums, packed scenes,
-// reduction blocks).  Outside stream capture it is the calling stream's
-// buffer: one per (device, stream), kept like the pool's blocks until the
-// process ends and grown on demand.  Calls on one stream run in order, so
-// every call on that stream (whatever its handle) can reuse the buffer, and
-// calls on different streams never share one.  The lock is held over the
-// call's launches, so a call from another host thread on the same stream
-// cannot slip its kernels in between them.  This adds nothing to the stream
-// per call (a stream-ordered free per call adds a marker: ~3 us between
-// kernels).  Under capture the memory is allocated from the pool inside the
-// graph instead, so every graph owns its own.
-struct StreamBuffer {
-  int dev;
-  hipStream_t s;
-  void* p;
-  size_t bytes;
-};
-std::mutex g_sb_mu;
-std::vector<StreamBuffer> g_sb;
-
-class CallScratch {
- public:
-  hipError_t acquire(int dev, hipStream_t s, size_t bytes) {
-    s_ = s;
-    if (bytes == 0) return hipSuccess;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(s, &cs);
-    if (e != hipSuccess) return e;
-    if (cs != hipStreamCaptureStatusNone) {
-      pooled_ = true;
-      return psflib::pool_alloc(&p_, bytes, dev, s);
-    }
-    lock_ = std::unique_lock<std::mutex>(g_sb_mu);
-    StreamBuffer* slot = nullptr;
-    for (auto& sb : g_sb)
-      if (sb.dev == dev && sb.s == s) slot = &sb;
-    if (slot && slot->bytes >= bytes) {
-      p_ = slot->p;
-      return hipSuccess;
-    }
-    size_t want = (size_t)1 << 20;  // grow in powers of two from 1 MiB
-    while (want < bytes) want <<= 1;
-    e = psflib::pool_alloc(&p_, want, dev, s);
-    if (e != hipSuccess) {
-      p_ = nullptr;
-      return e;
-    }
-    if (slot) {
-      // the smaller buffer goes back to the pool after the work queued on s
-      e = hipFreeAsync(slot->p, s);
-      slot->p = p_;
-      slot->bytes = want;
-    } else {
-      g_sb.push_back(StreamBuffer{dev, s, p_, want});
-    }
-    return e;
-  }
-  void* ptr() const { return p_; }
-  // after the call's launches
-  hipError_t release() {
-    hipError_t e = hipSuccess;
-    if (pooled_ && p_) e = hipFreeAsync(p_, s_);
-    pooled_ = false;
-    p_ = nullptr;
-    if (lock_.owns_lock()) lock_.unlock();
-    return e;
-  }
-  ~CallScratch() { (void)release(); }
-
- private:
-  std::unique_lock<std::mutex> lock_;
-  void* p_ = nullptr;
-  bool pooled_ = false;
-  hipStream_t s_ = nullptr;
-};
 
 psflib_status product(const psflib_handle* h, bool adjoint, const float* in, float* out,
                       hipStream_t s) {

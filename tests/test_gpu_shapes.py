@@ -199,6 +199,26 @@ def test_build16_sides(torch, storage, rotate, flux):
         full.close()
 
 
+# a library whose base columns (over 512 MiB) are not kept between the passes of a
+# flux-preserving build, beside the sizes above whose are: both forms, the pair
+# staged whole and in boxes
+@pytest.mark.parametrize("n,N,rotate", [(128, 193, "bilinear"), (193, 128, "bilinear"), (193, 128, "cubic")])
+def test_build16_flux_large(torch, n, N, rotate):
+    from paper_2106_09122_amd import psflib
+    cube, radii, _ = _inputs(n, N, 4, 6)
+    mode = dict(rotate=rotate, flux="preserve")
+    d = torch.from_numpy(cube).cuda()
+    full, lib = psflib.Library(d, radii, N, 1.0, **mode), psflib.Library(d, radii, N, 1.0, storage="bf16", **mode)
+    cols = np.concatenate([[0, N - 1, N * N // 2, N * N - 1], np.arange(5, N * N, N * N // 200)])
+    want, got = full.get_columns(cols).double(), lib.get_columns(cols).double()
+    e = lib.exponents().cpu().numpy()[cols][:, None]
+    unit, top = (torch.from_numpy(np.ldexp(1.0, e + k)).cuda() for k in (0, 15))
+    low, high = [((want + k * 2.0 ** -21 * top) / unit).float().bfloat16().double() * unit for k in (-1, 1)]
+    assert torch.all((low <= got) & (got <= high))
+    lib.close()
+    full.close()
+
+
 # ---------------------------------------------------- spline coefficients ----
 @pytest.mark.parametrize("value", [np.nan, np.inf])
 def test_spline_keeps_what_is_not_finite(torch, value):
