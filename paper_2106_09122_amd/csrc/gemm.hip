@@ -23,7 +23,7 @@
 // chains stay short.
 //
 // 16-bit, up to 256 scenes: a workgroup of 4 waves computes a 256 x TN tile
-// (TN = 128 or 256 scenes); each wave owns 64 image rows and all TN scenes
+// (TN = 64, 128 or 256 scenes); each wave owns 64 image rows and all TN scenes
 // (2 x TN/32 accumulators of 32 x 32).  K advances in stages of 32 columns
 // through a 4-slot ring, three stages ahead of use: library fragments (each
 // used by one wave only) go from HBM straight into registers, and the scene
@@ -36,6 +36,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "psflib_internal.h"
 
@@ -140,7 +141,11 @@ __global__ __launch_bounds__(256) void pack_f32_scenes_kernel(const float* __res
 //
 // NT: library loads carry the non-temporal hint, for grids with one scene
 // tile, where no other workgroup reads the same library rows.
-template <int NB, bool VEC, bool NT>
+//
+// The row pairs of images with an odd number of pixels start at any float: buffer
+// loads need no more than that, and bounds are checked for each of the two (127^2
+// PSFs, 127^2 scene, 64 scenes: 300 us, 363 with two 4-byte loads).
+template <int NB, bool NT>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_f32_kernel(
     const float* __restrict__ A, const f32x4* __restrict__ Zp, float* __restrict__ out, int64_t M,
     int64_t K, int64_t B, int64_t SB, int64_t mblocks, int64_t nblocks, int64_t splits,
@@ -180,12 +185,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_f32_kernel(
         (void*)(Zp + (int64_t)gc * SB * 64), (short)0, live ? (int)(SB * 1024) : 0, 0x00020000);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      if (VEC) {
-        ra[slot][s] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(ra_d, voff[s], 0, kAux));
-      } else {
-        ra[slot][s][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra_d, voff[s], 0, kAux));
-        ra[slot][s][1] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra_d, voff[s] + 4, 0, kAux));
-      }
+      ra[slot][s] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(ra_d, voff[s], 0, kAux));
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q)
@@ -650,8 +650,8 @@ __device__ __forceinline__ f32x16 mfma16(const u32x4 a, const u32x4 b, const f32
 
 // The 16-bit GEMM.  Workgroup = 4 waves, tile 256 image rows x TN scenes,
 // K stages of 32 columns (4 groups); each wave owns 64 rows and all TN scenes
-// (2 x TN/32 accumulators of 32 x 32: 128 registers at TN = 128, two
-// workgroups per CU; 256 at TN = 256, one).  Operands of a stage travel on
+// (2 x TN/32 accumulators of 32 x 32: 64 and 128 registers at TN = 64 and 128,
+// two workgroups per CU; 256 at TN = 256, one).  Operands of a stage travel on
 // two paths into a 4-slot ring, three stages ahead of use:
 //   library fragments (each used by one wave only) go from memory straight to
 //   registers, 4 x 16 bytes per lane per stage;
@@ -678,7 +678,7 @@ constexpr int kHUnroll = 16; // stages per main-loop iteration (a multiple of kH
 // re-measured with the current staging).  With several scene tiles the hint
 // costs the L2 reuse (B = 1024: +12%).
 template <bool BF16, int TN, bool NT>
-__global__ __launch_bounds__(kGemmThreads, TN == 128 ? 2 : 1) void gemm_h16_kernel(
+__global__ __launch_bounds__(kGemmThreads, TN <= 128 ? 2 : 1) void gemm_h16_kernel(
     const u32x4* Mp, const u32x4* Zg, const int32_t* __restrict__ fexp,
     float* __restrict__ out, int64_t M, int64_t ngroups, int64_t B, int64_t Bp, int64_t mblocks,
     int64_t nblocks, int64_t splits, int64_t stages_per_split) {
@@ -760,7 +760,9 @@ __global__ __launch_bounds__(kGemmThreads, TN == 128 ? 2 : 1) void gemm_h16_kern
   // land in a slot nobody reads again) and multiply stage ls
   auto step = [&](int64_t ls, int j) {
     // 4 + NC operations per stage, two stages issued after this one
-    if constexpr (NC == 2)
+    if constexpr (NC == 1)
+      asm volatile("s_waitcnt vmcnt(10) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else if constexpr (NC == 2)
       asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     else
       asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -923,8 +925,17 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
     const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (t >= BM) return;
     f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int p = 0; p < splits; ++p)
-      s += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(part + (int64_t)p * BM + t));
+    for (int p0 = 0; p0 < splits; p0 += 8) {  // 8 loads in flight
+      f32x4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int p = p0 + u < splits ? p0 + u : splits - 1;
+        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(part + (int64_t)p * BM + t));
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p0 + u < splits) s += v[u];
+    }
     if (fexp) {
       const int ex = -fexp[t / M];
 #pragma unroll
@@ -935,7 +946,14 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= BM) return;
     float s = 0.0f;
-    for (int p = 0; p < splits; ++p) s += part[(int64_t)p * BM + t];
+    for (int p0 = 0; p0 < splits; p0 += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(p0 + u < splits ? p0 + u : splits - 1) * BM + t];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (p0 + u < splits) s += v[u];
+    }
     out[t] = fexp ? ldexpf(s, -fexp[t / M]) : s;
   }
 }
@@ -945,15 +963,17 @@ struct GemmPlan {
   int64_t mblocks, nblocks, kunits, splits, per;  // kunits: 8-column groups (FP32) or K stages (16-bit)
 };
 
-// 16-bit kernel by batch: the 4-wave 128-scene tile up to 128 scenes (a wider
-// tile would be mostly padding; two workgroups per CU), the 4-wave 256-scene
-// tile for 128 < B <= 256 (~5% faster than two 128-wide tiles), and the
-// 8-wave 256 x 256 tile above (B = 512: 237-244 against 241-248 us per
-// product with the 128-wide tile, K split in two; B = 1024: 400-403 against
-// 406-416 us).
-enum H16Kind { kH128 = 0, kH256 = 1, kHW8 = 2 };
-static H16Kind h16_kind(int64_t bc) { return bc <= 128 ? kH128 : bc <= 256 ? kH256 : kHW8; }
-static int64_t h16_tile(int64_t bc) { return h16_kind(bc) == kH128 ? 128 : 256; }
+// 16-bit kernel by batch: the 4-wave 64-scene tile up to 64 scenes (20
+// scenes, 96^2: 42 us against 44 with the 128-scene tile, 33^2, 200^2 scene: 59
+// against 66, 16 slices each), the
+// 128-scene tile up to 128 (a wider tile would be mostly padding; two workgroups
+// per CU), the 256-scene tile for 128 < B <= 256 (~5% faster than two 128-wide
+// tiles), and the 8-wave 256 x 256 tile above (B = 512: 237-244 against 241-248
+// us per product with the 128-wide tile, K split in two; B = 1024: 400-403
+// against 406-416 us).
+enum H16Kind { kH64 = 0, kH128 = 1, kH256 = 2, kHW8 = 3 };
+static H16Kind h16_kind(int64_t bc) { return bc <= 64 ? kH64 : bc <= 128 ? kH128 : bc <= 256 ? kH256 : kHW8; }
+static int64_t h16_tile(int64_t bc) { return h16_kind(bc) == kH64 ? 64 : h16_kind(bc) == kH128 ? 128 : 256; }
 
 // FP32 scene blocks of 32 per workgroup tile: 1 for batches of at most 32
 static int f32_nb(int64_t bc) { return bc <= 32 ? 1 : 2; }
@@ -964,6 +984,16 @@ static int64_t f32_scene_blocks(int64_t bc) {
   return (bc + 32 * nb - 1) / (32 * nb) * nb;
 }
 
+constexpr int64_t kMaxSplits = 64;  // slices of K
+
+// K units of each of c slices: whole accumulation blocks in FP32, whole turns of
+// the ring in the 16-bit forms (whose odd stages are guarded one by one: 50^2,
+// 100^2 scene, 200 scenes: 16 slices of 20 stages 45 us, 18 of 18 51)
+static int64_t slice_units(int64_t units, int64_t c, bool f32) {
+  const int64_t per = (units + c - 1) / c, whole = f32 ? kF32Block : kHRing;
+  return (per + whole - 1) / whole * whole;
+}
+
 static GemmPlan plan_gemm(int storage, int64_t M, int64_t ncols, int64_t ncols_pad, int64_t bc) {
   GemmPlan p;
   const bool f32 = storage == PSFLIB_FP32;
@@ -971,48 +1001,57 @@ static GemmPlan plan_gemm(int storage, int64_t M, int64_t ncols, int64_t ncols_p
   p.mblocks = (M + tm - 1) / tm;
   p.nblocks = (bc + tn - 1) / tn;
   p.kunits = f32 ? (ncols + 7) / 8 : (ncols_pad / 8) / kHG;
-  // split K if the tile grid is smaller than the GPU: FP32 aims at two
-  // workgroups per CU; the 16-bit kernels at one (an extra K slice costs a
-  // partial-image round trip that a second workgroup per CU does not repay).
-  // The 8-wave kernel splits only while whole extra rounds of tiles fit
-  // (192 tiles stay unsplit: 384 workgroups would leave half the GPU idle in
-  // their second round too).
-  const int64_t want = f32 ? 512 : 256;
   const int64_t tiles = p.mblocks * p.nblocks;
-  int64_t s = (!f32 && h16_kind(bc) == kHW8) ? want / tiles : (want + tiles - 1) / tiles;
-  if (s > 16) s = 16;
-  if (s > p.kunits) s = p.kunits;
-  if (s < 1) s = 1;
-  p.per = (p.kunits + s - 1) / s;
-  if (f32) p.per = (p.per + kF32Block - 1) / kF32Block * kF32Block;  // whole accumulation blocks
+  int64_t s = 1;
+  if (!f32 && h16_kind(bc) == kHW8) {
+    // the 8-wave kernel splits K only while whole extra rounds of tiles fit (192
+    // tiles stay unsplit: 384 workgroups would leave half the GPU idle in their
+    // second round too)
+    s = 256 / tiles;
+    if (s > 16) s = 16;
+    if (s > p.kunits) s = p.kunits;
+    if (s < 1) s = 1;
+  } else {
+    // The number of slices of K with the least work: rounds of workgroups (two to
+    // a CU at a time in FP32, one in the 16-bit forms, whose partial images a second
+    // one does not repay) times the K units of a slice, plus the partial images'
+    // round trip in units of the library's bytes, and half a unit a slice (FP32:
+    // one) for the reduction's chain.  (96^2, 20 scenes, FP32: 36 tiles,
+    // 15 slices make 540 workgroups and a second round of 28, 87 us; 12 slices, 70.
+    // 33^2, 200^2 scene, 20 scenes: 5 tiles, 16 slices fill 80
+    // CUs, 163 us; 63, 74.)
+    const int64_t slots = f32 ? 512 : 256;
+    const int64_t unit = tm * (f32 ? 32 : 2 * 8 * kHG);      // library bytes of a K unit of a tile
+    const int64_t partial = 8 * tm * std::min(bc, tn);       // written and read, a slice of a tile
+    double best = 0.0;
+    for (int64_t c = 1; c <= kMaxSplits && c <= p.kunits; ++c) {
+      const int64_t per = slice_units(p.kunits, c, f32);
+      const int64_t wgs = tiles * ((p.kunits + per - 1) / per);
+      double cost = (double)((wgs + slots - 1) / slots) * (double)per;
+      if (wgs > tiles)
+        cost += (double)wgs * (double)partial / ((double)unit * (double)slots) + (f32 ? 1.0 : 0.5) * (double)c;
+      if (c == 1 || cost < best) {
+        best = cost;
+        s = c;
+      }
+    }
+  }
+  p.per = f32 || h16_kind(bc) != kHW8 ? slice_units(p.kunits, s, f32) : (p.kunits + s - 1) / s;
   p.splits = (p.kunits + p.per - 1) / p.per;  // no empty slice
   if (p.splits < 1) p.splits = 1;
   return p;
 }
 
-template <int NB, bool VEC, bool NT>
-static hipError_t launch_gemm_f32_t(unsigned grid, const float* A, const f32x4* Zp, float* dst,
-                                    int64_t M, int64_t K, int64_t B, int64_t SB, const GemmPlan& p,
-                                    hipStream_t s) {
-  gemm_f32_kernel<NB, VEC, NT><<<grid, kGemmThreads, 0, s>>>(A, Zp, dst, M, K, B, SB, p.mblocks,
-                                                             p.nblocks, p.splits, p.per);
-  return hipGetLastError();
-}
-
-// variant bits: 4 = two scene blocks per wave, 2 = even M (8-byte row pairs), 1 = non-temporal
-static hipError_t launch_gemm_f32(int variant, unsigned grid, const float* A, const f32x4* Zp,
+// two: two scene blocks per wave; nt: non-temporal library loads
+static hipError_t launch_gemm_f32(bool two, bool nt, unsigned grid, const float* A, const f32x4* Zp,
                                   float* dst, int64_t M, int64_t K, int64_t B, int64_t SB,
                                   const GemmPlan& p, hipStream_t s) {
-  switch (variant) {
-    case 0: return launch_gemm_f32_t<1, false, false>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 1: return launch_gemm_f32_t<1, false, true>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 2: return launch_gemm_f32_t<1, true, false>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 3: return launch_gemm_f32_t<1, true, true>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 4: return launch_gemm_f32_t<2, false, false>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 5: return launch_gemm_f32_t<2, false, true>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    case 6: return launch_gemm_f32_t<2, true, false>(grid, A, Zp, dst, M, K, B, SB, p, s);
-    default: return launch_gemm_f32_t<2, true, true>(grid, A, Zp, dst, M, K, B, SB, p, s);
-  }
+  auto launch = [&](auto kern) {
+    kern<<<grid, kGemmThreads, 0, s>>>(A, Zp, dst, M, K, B, SB, p.mblocks, p.nblocks, p.splits, p.per);
+    return hipGetLastError();
+  };
+  if (two) return nt ? launch(gemm_f32_kernel<2, true>) : launch(gemm_f32_kernel<2, false>);
+  return nt ? launch(gemm_f32_kernel<1, true>) : launch(gemm_f32_kernel<1, false>);
 }
 
 template <bool BF16, int TN, bool NT>
@@ -1037,18 +1076,20 @@ static hipError_t launch_gemm_h16(bool bf, H16Kind kind, bool nt, unsigned grid,
                                                      p.nblocks, p.splits, p.per);
     return hipGetLastError();
   }
-  const bool wide = kind == kH256;
-  const int v = (bf ? 4 : 0) + (wide ? 2 : 0) + (nt ? 1 : 0);
-  switch (v) {
-    case 0: return launch_gemm_h16_t<false, 128, false>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 1: return launch_gemm_h16_t<false, 128, true>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 2: return launch_gemm_h16_t<false, 256, false>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 3: return launch_gemm_h16_t<false, 256, true>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 4: return launch_gemm_h16_t<true, 128, false>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 5: return launch_gemm_h16_t<true, 128, true>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    case 6: return launch_gemm_h16_t<true, 256, false>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-    default: return launch_gemm_h16_t<true, 256, true>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
-  }
+  auto launch = [&](auto b, auto tn, auto t) {
+    return launch_gemm_h16_t<b.value, tn.value, t.value>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
+  };
+  auto by_hint = [&](auto b, auto tn) {
+    return nt ? launch(b, tn, std::true_type{}) : launch(b, tn, std::false_type{});
+  };
+  auto by_tile = [&](auto b) {
+    switch (kind) {
+      case kH64: return by_hint(b, std::integral_constant<int, 64>{});
+      case kH128: return by_hint(b, std::integral_constant<int, 128>{});
+      default: return by_hint(b, std::integral_constant<int, 256>{});
+    }
+  };
+  return bf ? by_tile(std::true_type{}) : by_tile(std::false_type{});
 }
 
 static int64_t chunk_of(int B) { return B < kMaxBatchChunk ? B : kMaxBatchChunk; }
@@ -1125,9 +1166,8 @@ hipError_t launch_batched(int storage, const void* lib, const Cols16& cx, const 
         pack_f32_scenes_kernel<false><<<pgrid, 256, 0, s>>>(Zc, ncols, bc, ngroups, SB, Zp);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
-      const int variant = (f32_nb(bc) == 2 ? 4 : 0) + ((M % 2) == 0 ? 2 : 0) + (p.nblocks == 1 ? 1 : 0);
-      e = launch_gemm_f32(variant, grid, reinterpret_cast<const float*>(lib), Zp, dst, M, ncols, bc,
-                          SB, p, s);
+      e = launch_gemm_f32(f32_nb(bc) == 2, p.nblocks == 1, grid, reinterpret_cast<const float*>(lib), Zp,
+                          dst, M, ncols, bc, SB, p, s);
     } else {
       const bool bf = storage == PSFLIB_BF16_POW2;
       const bool vec = (ncols % 8) == 0 && (reinterpret_cast<uintptr_t>(Zc) % 16) == 0;
@@ -1168,7 +1208,7 @@ hipError_t launch_batched(int storage, const void* lib, const Cols16& cx, const 
       if (e != hipSuccess) return e;
       const u32x4* Mp = reinterpret_cast<const u32x4*>(lib);
       const H16Kind kind = h16_kind(bc);
-      e = launch_gemm_h16(bf, kind, (kind == kH128 || kind == kH256) && p.nblocks == 1, grid, Mp, Zg, fexp, dst, M,
+      e = launch_gemm_h16(bf, kind, kind != kHW8 && p.nblocks == 1, grid, Mp, Zg, fexp, dst, M,
                           ngroups, bc, Bp, p, s);
     }
     if (e != hipSuccess) return e;

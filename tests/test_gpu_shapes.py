@@ -264,3 +264,25 @@ def test_orbit_order(torch, N, K, storage):
     assert abs(float(lib.apply(z)[0]) - ref) <= 1e-5 * ref
     assert np.allclose(lib.column_sums().cpu().numpy(), want, rtol=1e-6)
     lib.close()
+
+
+# ------------------------------------------------------------ batched ----
+# scenes at the edges of every tile (32, 64, 128, 256) and of the kernels' ranges;
+# images of an odd number of pixels, smaller and larger than a tile of 256; one
+# slice of columns, several, and more than 16 (a narrow image, a wide scene)
+@pytest.mark.parametrize("storage", ["fp32", "bf16", "fp16"])
+@pytest.mark.parametrize("n,N", [(1, 3), (3, 150), (16, 16), (17, 100), (31, 33), (33, 90), (64, 31)])
+def test_batched_shapes(torch, n, N, storage):
+    """Non-negative terms: 1e-5 relative for the float32 sums, and for the 16-bit
+    forms a rounding of each scene value (half a unit of its mantissa: 2^-8, 2^-11)."""
+    lib, A, rng = _library(torch, n, N, storage)
+    tol = 1e-5 + {"fp32": 0.0, "bf16": 2.0 ** -8, "fp16": 2.0 ** -11}[storage]
+    for B in (1, 7, 32, 33, 64, 65, 128, 129, 257):
+        print("batched", n, N, storage, B, flush=True)
+        Z = torch.from_numpy(rng.uniform(0.5, 1.0, (B, N * N)).astype(np.float32)).cuda()
+        out = torch.full((B, n * n), float("nan"), device="cuda")
+        lib.apply_batched(Z, out=out)
+        ref = Z.double() @ A
+        assert torch.all((out.double() - ref).abs() <= tol * ref + 1e-300), B
+        assert torch.equal(out, lib.apply_batched(Z))
+    lib.close()
