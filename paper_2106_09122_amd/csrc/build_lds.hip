@@ -901,7 +901,7 @@ template <bool VEC, int MODE, typename Value>
 __device__ __forceinline__ void orbit_block(Value value, const OrbitCol& g, double c, int n, int N,
                                             int64_t M, int ab0, int bb0, float* A, double& tsum) {
   const bool centre = orbit_is_centre(g.j0, N);
-  float* C0 = A + (MODE == kBases ? g.pos : g.j0) * M;
+  float* C0 = A + g.j0 * M;
   float* C1 = A + orbit_member(g.j0, N, 1) * M;
   float* C2 = A + orbit_member(g.j0, N, 2) * M;
   float* C3 = A + orbit_member(g.j0, N, 3) * M;
@@ -935,21 +935,78 @@ __device__ __forceinline__ void orbit_block(Value value, const OrbitCol& g, doub
       }
       if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
     }
-    if constexpr (MODE == kBases) {
-      if (VEC || n >= 4) *reinterpret_cast<f32x4u*>(C0 + (int64_t)a * n + bb) = (f32x4){x[r][0], x[r][1], x[r][2], x[r][3]};
-    } else if constexpr (MODE != kSumsOnly) {  // the row's runs of C0 and C2
-      if (VEC || n >= 4) store_row_runs<VEC>(x[r], C0, C2, a, bb, n, centre);
-    }
+    // the row's runs of C0 and C2
+    if (VEC || n >= 4) store_row_runs<VEC>(x[r], C0, C2, a, bb, n, centre);
     // one row of the block at a time: bounds the live coordinate temporaries
     __builtin_amdgcn_sched_barrier(0);
   }
-  if constexpr (MODE == kBases) {
-    if (!VEC && n < 4) store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, true);
-  } else if constexpr (MODE != kSumsOnly) {
-    if (!VEC && n < 4)
-      store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, centre);
-    else if (!centre)
-      store_column_runs<VEC>(x, C1, C3, ab, bb, n);
+  if (!VEC && n < 4)
+    store_block_scalar(x, C0, C1, C2, C3, ab, bb, n, centre);
+  else if (!centre)
+    store_column_runs<VEC>(x, C1, C3, ab, bb, n);
+}
+
+// the modes that store no turned member
+constexpr bool base_only(int mode) { return mode == kSumsOnly || mode == kBases; }
+
+// The tile of a base column whose turns are not stored: neighbouring lanes take
+// neighbouring pixels, lane (i, k) those at rows a0 + i + 8 p, columns b0 + k + 8
+// q, so that the taps of a step lie close together in LDS (1.2 to 1.5 lanes to a
+// bank where lanes four pixels apart put 2.3) and the steps past the image's edge
+// are left out whole: 101^2 takes 169 steps of 64 pixels a column instead of 256.
+// (First pass for 101^2 PSFs of a 101^2 scene with the spline: 186 us with the
+// blocks of orbit_block, 154 so.)
+template <int MODE, typename Value>
+__device__ __forceinline__ void orbit_patch(Value value, const OrbitCol& g, double c, int n, int64_t M,
+                                            int a0, int b0, int lane, float* A, double& tsum) {
+  const int li = lane >> 3, lk = lane & 7;
+  float* C0 = A + g.pos * M;
+  double ctux[4], mstux[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+#pragma clang fp contract(off)
+    const double ux = (double)(b0 + lk + 8 * q) - c;
+    ctux[q] = g.ct * ux;
+    mstux[q] = (-g.st) * ux;
+  }
+  auto rows = [&](auto whole) {  // whole: a tile inside the image, no bounds to test
+    for (int p = 0; p < 4 && (whole.value || a0 + 8 * p < n); ++p) {  // uniform
+      const int a = a0 + li + 8 * p;
+      double stuy, ctuy;
+      {
+#pragma clang fp contract(off)
+        const double uy = (double)a - c;
+        stuy = g.st * uy;
+        ctuy = g.ct * uy;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = b0 + lk + 8 * q;
+        if (!whole.value && b0 + 8 * q >= n) break;  // uniform
+        if (whole.value || (a < n && b < n)) {
+          const float x = value(ctux[q], mstux[q], stuy, ctuy);
+          tsum += (double)x;
+          if constexpr (MODE == kBases) C0[(int64_t)a * n + b] = x;
+        }
+        if (q == 1) __builtin_amdgcn_sched_barrier(0);  // two elements in flight
+      }
+    }
+  };
+  if (a0 + 32 <= n && b0 + 32 <= n)
+    rows(std::true_type{});
+  else
+    rows(std::false_type{});
+}
+
+// a 32 x 32 tile at (a0, b0) of a base column
+template <bool VEC, int MODE, typename Value>
+__device__ __forceinline__ void orbit_tile(Value value, const OrbitCol& g, double c, int n, int N,
+                                           int64_t M, int a0, int b0, int lane, float* A, double& tsum) {
+  if constexpr (base_only(MODE)) {
+    orbit_patch<MODE>(value, g, c, n, M, a0, b0, lane, A, tsum);
+  } else {
+    const int ab0 = a0 + 4 * (lane >> 3), bb0 = b0 + 4 * (lane & 7);
+    if (ab0 < n && bb0 < n) orbit_block<VEC, MODE>(value, g, c, n, N, M, ab0, bb0, A, tsum);
   }
 }
 
@@ -990,7 +1047,6 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
   if (!zero_bucket) stage_pair(P2, cube, bkt, K, n, ls, M, tid);
   __syncthreads();
   const double c = (double)(n - 1) * 0.5;
-  const int li = lane >> 3, lk = lane & 7;
   const int ntiles = nt * nt, nwork = (last - first) * ntiles;
   if (wave >= nwork) return;  // no barrier below
   OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, first + wave / ntiles);
@@ -998,19 +1054,17 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
     const int sp = first + t / ntiles, tile = t % ntiles;
     const OrbitCol next = load_orbit_col<MODE>(reps, geo, colscale, first + min(t + 16, nwork - 1) / ntiles);
     const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
-    const int ab0 = 32 * (tile / nt) + 4 * li, bb0 = 32 * (tile % nt) + 4 * lk;
+    const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
     double tsum = 0.0;
-    if (ab0 < n && bb0 < n) {
-      if (zero_bucket)  // identically zero orbit
-        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, N, M, ab0,
-                               bb0, A, tsum);
-      else
-        orbit_block<VEC, MODE>(
-            [&](double ctux, double mstux, double stuy, double ctuy) {
-              return orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
-            },
-            g, c, n, N, M, ab0, bb0, A, tsum);
-    }
+    if (zero_bucket)  // identically zero orbit
+      orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, N, M, a0, b0,
+                            lane, A, tsum);
+    else
+      orbit_tile<VEC, MODE>(
+          [&](double ctux, double mstux, double stuy, double ctuy) {
+            return orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
+          },
+          g, c, n, N, M, a0, b0, lane, A, tsum);
     tsum = wave_sum_f64(tsum);
     if (lane == 0) part[(int64_t)tile * nreps + sp] = tsum;
     g = next;
@@ -1154,7 +1208,6 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* Q = QS + wave * kFpRegion;
   const double c = (double)(n - 1) * 0.5;
-  const int li = lane >> 3, lk = lane & 7;
   const int ntiles = nt * nt;
   const int nruns = (ntiles + run - 1) / run;
   const uint32_t rounds = (total + 16 * gridDim.x - 1) / (16 * gridDim.x);
@@ -1167,11 +1220,9 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
     double tsum = 0.0;
     for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
     const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
-    const int ab0 = a0 + 4 * li, bb0 = b0 + 4 * lk;
     if (g.k < 0) {  // identically zero orbit
-      if (ab0 < n && bb0 < n)
-        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M,
-                               ab0, bb0, A, tsum);
+      orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
+                            lane, A, tsum);
       continue;
     }
     const float* Pk = cube + (int64_t)g.k * M;
@@ -1179,7 +1230,7 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
     const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
     // the tile's pixels (from the first row and column that its blocks reach)
     // and their box of bordered rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-    const int at = block_start<VEC>(a0, n), bt = block_start<VEC>(b0, n);
+    const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
     const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
     int rmin, rmax, cmin, cmax;
     {
@@ -1203,12 +1254,11 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
     stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, wk0, wk1, lane);
     wave_lds_sync();  // the box is staged
     const int base = Rlo * kFpStride + Clo;
-    if (ab0 < ae && bb0 < be)
-      orbit_block<VEC, MODE>(
+    orbit_tile<VEC, MODE>(
           [&](double ctux, double mstux, double stuy, double ctuy) {
             return box_value(Q, ctux, mstux, stuy, ctuy, c, n, base);
           },
-          g, c, n, o.N, M, ab0, bb0, A, tsum);
+          g, c, n, o.N, M, a0, b0, lane, A, tsum);
     }
     tsum = wave_sum_f64(tsum);
     if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
@@ -1245,7 +1295,7 @@ __device__ __forceinline__ void store_unit(uint16_t* p, const u32x4 w) {
 // 16-bit orbit build.  A window of 16 bases is two blocks; block h's member k is group
 // 4 (w0/8 + h) + k, whose unit at an image pixel holds the 8 bases' member
 // values there.  The item's rows are walked in tiles of 8 x 32 pixels: every
-// wave forms its base column's tile (lane (i, k): row i, columns 4k..4k+3),
+// wave forms its base column's tile (lane (i, k): row i, columns k + 8 q),
 // rounds the values into an LDS tile [2][8][33][8] (unit-major: the 8 bases of
 // a block and pixel are one 16-byte LDS word; one unit of padding per row
 // keeps the column-wise reads conflict-free), and after one barrier half the
@@ -1311,7 +1361,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
     for (int b0 = 0; b0 < n; b0 += TB, buf ^= 1) {
       uint16_t* tile = tiles + buf * TILE;
       if (live) {
-        const int a = a0 + li, bb = b0 + 4 * lk;
+        const int a = a0 + li;
         if (a < rb) {
           double stuy, ctuy;
           {
@@ -1322,11 +1372,13 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
           }
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            if (bb + q >= n) continue;
+            if (b0 + 8 * q >= n) break;  // uniform
+            const int b = b0 + lk + 8 * q;
+            if (b >= n) continue;
             double ctux, mstux;
             {
 #pragma clang fp contract(off)
-              const double ux = (double)(bb + q) - c;
+              const double ux = (double)b - c;
               ctux = g.ct * ux;
               mstux = (-g.st) * ux;
             }
@@ -1334,7 +1386,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
                               : orbit_value(P2, ctux, mstux, stuy, ctuy, c, n, ls, wk0, wk1);
             if constexpr (SCALED) val *= sf;
             tsum += (double)val;
-            tile[((h * TA + li) * TP + 4 * lk + q) * 8 + u] = round16<BF16>(val, g.e);
+            tile[((h * TA + li) * TP + lk + 8 * q) * 8 + u] = round16<BF16>(val, g.e);
           }
         }
       }
@@ -1421,7 +1473,6 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
   float* Q = QS + wave * kCbRegion;
   const double c = (double)(n - 1) * 0.5;
   const double pad = (double)kSplinePad;
-  const int li = lane >> 3, lk = lane & 7;
   const int ntiles = nt * nt;
   const int nruns = (ntiles + run - 1) / run;
   const uint32_t rounds = (total + 16 * gridDim.x - 1) / (16 * gridDim.x);
@@ -1434,18 +1485,16 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
     double tsum = 0.0;
     for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
     const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
-    const int ab0 = a0 + 4 * li, bb0 = b0 + 4 * lk;
     if (g.k < 0) {  // identically zero orbit
-      if (ab0 < n && bb0 < n)
-        orbit_block<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M,
-                               ab0, bb0, A, tsum);
+      orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
+                            lane, A, tsum);
       continue;
     }
     const float2* src = pairs + (int64_t)g.k * Np * Np;
     const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
     // the tile's pixels (from the first row and column that its blocks reach)
     // and their box of padded rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-    const int at = block_start<VEC>(a0, n), bt = block_start<VEC>(b0, n);
+    const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
     const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
     int rmin, rmax, cmin, cmax;
     {
@@ -1467,8 +1516,7 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
     wave_lds_sync();  // the previous tile's reads are done
     stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, wk0, wk1, lane);
     wave_lds_sync();  // the box is staged
-    if (ab0 < ae && bb0 < be)
-      orbit_block<VEC, MODE>(
+    orbit_tile<VEC, MODE>(
           [&](double ctux, double mstux, double stuy, double ctuy) {
 #pragma clang fp contract(off)
             const double rowf = c + (mstux + ctuy) + pad;
@@ -1491,7 +1539,7 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
             }
             return V;
           },
-          g, c, n, o.N, M, ab0, bb0, A, tsum);
+          g, c, n, o.N, M, a0, b0, lane, A, tsum);
     }
     tsum = wave_sum_f64(tsum);
     if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
@@ -1694,7 +1742,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
       for (int a1 = a0; a1 < ae; a1 += TA, buf ^= 1) {  // uniform over the workgroup
         uint16_t* tile = tiles + buf * TILE;
         if (live) {
-          const int a = a1 + li, bb = b0 + CPL * lk;
+          const int a = a1 + li;
           if (a < ae) {
             double stuy, ctuy;
             {
@@ -1705,11 +1753,13 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
             }
 #pragma unroll
             for (int q = 0; q < CPL; ++q) {
-              if (bb + q >= n) continue;
+              if (b0 + LPR * q >= n) break;  // uniform
+              const int b = b0 + lk + LPR * q;
+              if (b >= n) continue;
               double ctux, mstux;
               {
 #pragma clang fp contract(off)
-                const double ux = (double)(bb + q) - c;
+                const double ux = (double)b - c;
                 ctux = g.ct * ux;
                 mstux = (-g.st) * ux;
               }
@@ -1740,7 +1790,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
               }
               if constexpr (SCALED) val *= sf;
               tsum += (double)val;
-              tile[((h * TA + li) * TP + CPL * lk + q) * 8 + u] = round16<BF16>(val, g.e);
+              tile[((h * TA + li) * TP + lk + LPR * q) * 8 + u] = round16<BF16>(val, g.e);
             }
           }
         }
@@ -2005,13 +2055,13 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
     };
     switch (mode) {
       case kSumsOnly:
-        e = vec ? launch(build_orbit_box_kernel<true, kSumsOnly>) : launch(build_orbit_box_kernel<false, kSumsOnly>);
+        e = launch(build_orbit_box_kernel<false, kSumsOnly>);
         break;
       case kScaled:
         e = vec ? launch(build_orbit_box_kernel<true, kScaled>) : launch(build_orbit_box_kernel<false, kScaled>);
         break;
       case kBases:
-        e = vec ? launch(build_orbit_box_kernel<true, kBases>) : launch(build_orbit_box_kernel<false, kBases>);
+        e = launch(build_orbit_box_kernel<false, kBases>);
         break;
       default:
         e = vec ? launch(build_orbit_box_kernel<true, kPlain>) : launch(build_orbit_box_kernel<false, kPlain>);
@@ -2032,13 +2082,13 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
   };
   switch (mode) {
     case kSumsOnly:
-      e = vec ? launch(build_orbit_kernel<true, kSumsOnly>) : launch(build_orbit_kernel<false, kSumsOnly>);
+      e = launch(build_orbit_kernel<false, kSumsOnly>);
       break;
     case kScaled:
       e = vec ? launch(build_orbit_kernel<true, kScaled>) : launch(build_orbit_kernel<false, kScaled>);
       break;
     case kBases:
-      e = vec ? launch(build_orbit_kernel<true, kBases>) : launch(build_orbit_kernel<false, kBases>);
+      e = launch(build_orbit_kernel<false, kBases>);
       break;
     default:
       e = vec ? launch(build_orbit_kernel<true, kPlain>) : launch(build_orbit_kernel<false, kPlain>);
@@ -2083,13 +2133,13 @@ hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int
   };
   switch (mode) {
     case kSumsOnly:
-      e = vec ? launch(build_cubic_orbit_kernel<true, kSumsOnly>) : launch(build_cubic_orbit_kernel<false, kSumsOnly>);
+      e = launch(build_cubic_orbit_kernel<false, kSumsOnly>);
       break;
     case kScaled:
       e = vec ? launch(build_cubic_orbit_kernel<true, kScaled>) : launch(build_cubic_orbit_kernel<false, kScaled>);
       break;
     case kBases:
-      e = vec ? launch(build_cubic_orbit_kernel<true, kBases>) : launch(build_cubic_orbit_kernel<false, kBases>);
+      e = launch(build_cubic_orbit_kernel<false, kBases>);
       break;
     default:
       e = vec ? launch(build_cubic_orbit_kernel<true, kPlain>) : launch(build_cubic_orbit_kernel<false, kPlain>);
