@@ -678,7 +678,7 @@ constexpr int kHUnroll = 16; // stages per main-loop iteration (a multiple of kH
 // re-measured with the current staging).  With several scene tiles the hint
 // costs the L2 reuse (B = 1024: +12%).
 template <bool BF16, int TN, bool NT>
-__global__ __launch_bounds__(kGemmThreads, TN <= 128 ? 2 : 1) void gemm_h16_kernel(
+__device__ __forceinline__ void gemm_h16_tile(
     const u32x4* Mp, const u32x4* Zg, const int32_t* __restrict__ fexp,
     float* __restrict__ out, int64_t M, int64_t ngroups, int64_t B, int64_t Bp, int64_t mblocks,
     int64_t nblocks, int64_t splits, int64_t stages_per_split) {
@@ -793,6 +793,25 @@ __global__ __launch_bounds__(kGemmThreads, TN <= 128 ? 2 : 1) void gemm_h16_kern
 #pragma unroll
     for (int u = 0; u < NU; ++u)
       store_acc(acc[t][u], dst, M, B, m0 + 64 * wave + 32 * t, n0 + 32 * u, lane, fexp, !split);
+}
+
+template <bool BF16, int TN, bool NT>
+__global__ __launch_bounds__(kGemmThreads, TN == 128 ? 2 : 1) void gemm_h16_kernel(
+    const u32x4* Mp, const u32x4* Zg, const int32_t* __restrict__ fexp, float* __restrict__ out,
+    int64_t M, int64_t ngroups, int64_t B, int64_t Bp, int64_t mblocks, int64_t nblocks,
+    int64_t splits, int64_t stages_per_split) {
+  gemm_h16_tile<BF16, TN, NT>(Mp, Zg, fexp, out, M, ngroups, B, Bp, mblocks, nblocks, splits,
+                              stages_per_split);
+}
+
+// the 64-scene tile: one scene block, so library loads always carry the hint
+template <bool BF16>
+__global__ __launch_bounds__(kGemmThreads, 2) void gemm_h16_n64_kernel(
+    const u32x4* Mp, const u32x4* Zg, const int32_t* __restrict__ fexp, float* __restrict__ out,
+    int64_t M, int64_t ngroups, int64_t B, int64_t Bp, int64_t mblocks, int64_t nblocks,
+    int64_t splits, int64_t stages_per_split) {
+  gemm_h16_tile<BF16, 64, true>(Mp, Zg, fexp, out, M, ngroups, B, Bp, mblocks, nblocks, splits,
+                                stages_per_split);
 }
 
 // The 16-bit GEMM for batches above 256 scenes: 8 waves (two per SIMD, so one
@@ -1076,6 +1095,14 @@ static hipError_t launch_gemm_h16(bool bf, H16Kind kind, bool nt, unsigned grid,
                                                      p.nblocks, p.splits, p.per);
     return hipGetLastError();
   }
+  if (kind == kH64) {
+    auto launch = [&](auto kern) {
+      kern<<<grid, kGemmThreads, 0, s>>>(Mp, Zg, fexp, dst, M, ngroups, B, Bp, p.mblocks, p.nblocks,
+                                         p.splits, p.per);
+      return hipGetLastError();
+    };
+    return bf ? launch(gemm_h16_n64_kernel<true>) : launch(gemm_h16_n64_kernel<false>);
+  }
   auto launch = [&](auto b, auto tn, auto t) {
     return launch_gemm_h16_t<b.value, tn.value, t.value>(grid, Mp, Zg, fexp, dst, M, ngroups, B, Bp, p, s);
   };
@@ -1083,11 +1110,8 @@ static hipError_t launch_gemm_h16(bool bf, H16Kind kind, bool nt, unsigned grid,
     return nt ? launch(b, tn, std::true_type{}) : launch(b, tn, std::false_type{});
   };
   auto by_tile = [&](auto b) {
-    switch (kind) {
-      case kH64: return by_hint(b, std::integral_constant<int, 64>{});
-      case kH128: return by_hint(b, std::integral_constant<int, 128>{});
-      default: return by_hint(b, std::integral_constant<int, 256>{});
-    }
+    return kind == kH128 ? by_hint(b, std::integral_constant<int, 128>{})
+                         : by_hint(b, std::integral_constant<int, 256>{});
   };
   return bf ? by_tile(std::true_type{}) : by_tile(std::false_type{});
 }
