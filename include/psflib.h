@@ -185,8 +185,10 @@ psflib_status psflib_library_bytes(const psflib_desc* desc, size_t* bytes);
  * interpolated to offset r, Q = (1-w) P_k + w P_{k+1}, rotated about the array
  * centre so that +x turns to the position angle (output pixel at offset u from
  * the centre samples Q at R(-theta) u), bilinearly with zero padding.
- * Takes the handle's device workspace (per-column geometry) and temporary
- * build buffers from the library's device pool, stream-ordered on `stream`. */
+ * Takes the handle's device workspace (per-column geometry) from the library's
+ * device pool, stream-ordered on `stream`, and temporary build buffers from the
+ * buffer of `stream` (see the conventions above), or from the pool and back to
+ * it what is more than 512 MiB, or would bring all streams' buffers above 2 GiB. */
 psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const double* h_radii,
                            void* d_lib, size_t lib_bytes, void* stream, psflib_handle** out);
 
