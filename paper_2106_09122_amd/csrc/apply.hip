@@ -761,9 +761,13 @@ static AdjShape adj_shape(bool f32, int64_t M, int64_t units) {
   // multiple of them of about 1 MiB of the library each where it is larger than
   // that, so that the CUs finish together (256^2, bf16: 1.22 ms against 1.30
   // with resident workgroups only; 128^2, bf16, of 0.5 instead of 1 MiB: 89
-  // against 85 us).
+  // against 85 us; 181^2 PSFs of two row blocks, 200^2 scene: 415 against 404).
+  // Float32 libraries of three row blocks and more, whose workgroups' ranges lie
+  // further apart, take half as much each (200^2 PSFs, 128^2 scene: 412 against
+  // 420 us; in 16 bits it makes no difference, 256^2 1214 to 1225 us either way).
   const int64_t bytes = columns * std::min(M, sh.block_rows) * (f32 ? 4 : 16);
-  const int64_t turns = std::max<int64_t>(1, (bytes + ((int64_t)256 << 20)) / ((int64_t)512 << 20));
+  const int64_t turn = (int64_t)(f32 && sh.nb >= 3 ? 256 : 512) << 20;
+  const int64_t turns = std::max<int64_t>(1, (bytes + turn / 2) / turn);
   const int64_t want = std::max<int64_t>(1, 512 * turns / sh.nb);
   const int64_t groups = f32 ? (units + sh.c - 1) / sh.c : units, quantum = sh.split ? 1 : waves;
   sh.per_wg = std::max<int64_t>(1, ((groups + want - 1) / want + quantum - 1) / quantum) * quantum;
