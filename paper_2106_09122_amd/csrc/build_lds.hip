@@ -1650,7 +1650,7 @@ __global__ __launch_bounds__(1024) void spread_orbit16_kernel(const float* __res
 }
 
 // 16-bit orbit build for pairs that do not fit the LDS beside the unit tiles
-// (n > 133), bilinear or cubic-spline: build_orbit16_kernel's unit tiles and copies,
+// (n > 131), bilinear or cubic-spline: build_orbit16_kernel's unit tiles and copies,
 // with each wave's taps read from a staged box (as build_orbit_box_kernel and
 // build_cubic_orbit_kernel) of the 32 x 32 pixels it forms as 32 / TA tiles of
 // TA x 32.  LDS: 16 box regions, then the two unit tiles; the cubic boxes are

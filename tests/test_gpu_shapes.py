@@ -158,9 +158,9 @@ def test_grouped_shapes(torch, storage, chunks):
 # ------------------------------------------------- 16-bit orbit builds ----
 # scenes whose base columns fill, exceed or miss blocks of 8 and windows of 16,
 # an odd scene's centre column, more than one block of the sort; images with the
-# pair whole in LDS (up to 133), with staged boxes, sides not a multiple of 8
+# pair whole in LDS (up to 131), with staged boxes, sides not a multiple of 8
 BUILD16 = [(1, 1), (5, 2), (8, 3), (7, 6), (33, 7), (16, 8), (31, 9), (6, 10), (100, 5), (127, 11), (128, 12),
-           (133, 6), (134, 7), (136, 8), (141, 9), (142, 3), (167, 10), (9, 46), (4, 67)]
+           (131, 5), (132, 5), (133, 6), (134, 7), (136, 8), (141, 9), (142, 3), (167, 10), (9, 46), (4, 67)]
 
 
 @pytest.mark.parametrize("storage", ["bf16", "fp16"])
