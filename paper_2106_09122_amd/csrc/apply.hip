@@ -485,6 +485,14 @@ __device__ __forceinline__ float wave_sums(float (&v)[V], int lane) {
   return v[0];
 }
 
+// Sum of value q of the workgroup's waves, in pairs.
+template <int NW, int V>
+__device__ __forceinline__ float waves_sum(const float (&red)[NW][V], int q) {
+  static_assert(NW == 8, "pairs of pairs of pairs");
+  return ((red[0][q] + red[1][q]) + (red[2][q] + red[3][q])) +
+         ((red[4][q] + red[5][q]) + (red[6][q] + red[7][q]));
+}
+
 // The rounds of one wave, in order: column groups first, first + stride, ...
 // below end, each in `rounds` rounds.  load(buffer, group, round) issues a
 // round's loads, use(buffer, round) multiplies them, finish(group) follows a
@@ -600,9 +608,7 @@ __global__ __launch_bounds__(kAdjThreads, 4) void adjoint_f32_kernel(const float
       if (lane % (64 / C) == 0) red[buf][wave][lane / (64 / C)] = tot;
       __syncthreads();  // the other buffer's readers are behind the previous one
       if (tid < C && grp * C + tid < ncols) {
-        tot = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) tot += red[buf][w][tid];
+        tot = waves_sum(red[buf], tid);
         out[(int64_t)blockIdx.y * out_stride + grp * C + tid] = tot;
       }
       buf ^= 1;
@@ -630,7 +636,10 @@ __global__ __launch_bounds__(kAdjThreads, 4) void adjoint_h16_kernel(const u32x4
                                                                      int64_t per_wg,
                                                                      int64_t out_stride,
                                                                      int apply_exp) {
-  constexpr int SUB = 2;  // sums per slot: shorter rounding chains
+  // Two sums per slot over a round, added to the slot's total when it ends: a chain
+  // of U / 2 products, then one of at most 32 rounds (256 steps of 64 rows in one
+  // chain had 1.3 times the error, and the rounds cost no time: the loads bound it).
+  constexpr int SUB = 2;
   constexpr int NW = kAdjThreads / 64;
   constexpr int W = SPLIT ? NW : 1;  // waves on one group
   extern __shared__ f32x4 gs4[];
@@ -657,8 +666,9 @@ __global__ __launch_bounds__(kAdjThreads, 4) void adjoint_h16_kernel(const u32x4
     for (int t = tid; t < rounds * U * W * 64; t += kAdjThreads) gs[t] = t < rows ? g[row0 + t] : 0.0f;
     __syncthreads();
   };
-  float acc[SUB][8] = {};
+  float total[8] = {};
   auto use = [&](const Buf& b, int r) {
+    float acc[SUB][8] = {};
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float gv = gs[(sub + W * (r * U + u)) * 64 + lane];
@@ -668,14 +678,16 @@ __global__ __launch_bounds__(kAdjThreads, 4) void adjoint_h16_kernel(const u32x4
       for (int q = 0; q < 8; ++q) acc[u % SUB][q] = fmaf(f[q], gv, acc[u % SUB][q]);
       __builtin_amdgcn_sched_barrier(0);  // one load unpacked at a time
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) total[q] += acc[0][q] + acc[1][q];
   };
   int buf = 0;
   auto finish = [&](int64_t grp) {
     float sum[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      sum[q] = acc[0][q] + acc[1][q];
-      acc[0][q] = acc[1][q] = 0.0f;
+      sum[q] = total[q];
+      total[q] = 0.0f;
     }
     float tot = wave_sums<8>(sum, lane);
     bool writes = lane % 8 == 0;
@@ -685,11 +697,7 @@ __global__ __launch_bounds__(kAdjThreads, 4) void adjoint_h16_kernel(const u32x4
       __syncthreads();  // the other buffer's readers are behind the previous one
       writes = tid < 8;
       q = tid;
-      if (writes) {
-        tot = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) tot += red[buf][w][q];
-      }
+      if (writes) tot = waves_sum(red[buf], q);
       buf ^= 1;
     }
     if (writes) {
