@@ -943,7 +943,7 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
   if constexpr (VEC) {
     const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (t >= BM) return;
-    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
     for (int p0 = 0; p0 < splits; p0 += 8) {  // 8 loads in flight
       f32x4 v[8];
 #pragma unroll
@@ -953,8 +953,11 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (p0 + u < splits) s += v[u];
+        if (p0 + u < splits)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) sum[q] += (double)v[u][q];
     }
+    f32x4 s = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
     if (fexp) {
       const int ex = -fexp[t / M];
 #pragma unroll
@@ -964,15 +967,16 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
   } else {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= BM) return;
-    float s = 0.0f;
+    double sum = 0.0;
     for (int p0 = 0; p0 < splits; p0 += 8) {
       float v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(p0 + u < splits ? p0 + u : splits - 1) * BM + t];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (p0 + u < splits) s += v[u];
+        if (p0 + u < splits) sum += (double)v[u];
     }
+    const float s = (float)sum;
     out[t] = fexp ? ldexpf(s, -fexp[t / M]) : s;
   }
 }
