@@ -764,9 +764,16 @@ static AdjShape adj_shape(bool f32, int64_t M, int64_t units) {
   // against 31 us), and where a column fills whole rounds of all the waves:
   // 8 KiB at a time of one column then read better than 1 KiB of eight (128^2
   // PSFs, 256^2 scene, fp16: 317 against 330 us; 200^2 and 128^2, fp32, whose
-  // rounds would be a fifth empty: 460 against 417 us).
+  // rounds would be a fifth empty: 460 against 417 us).  In between, a column per wave
+  // makes one round of 192 to 232 workgroups of 8 columns, enough to fill the memory,
+  // where shared columns leave some CUs 7 and some 6 of them (128^2, bf16, 112^2 scene,
+  // 1568 groups: 62.2 us against 66.3; 116^2 67 against 70; 120^2, 1800, a tie at 71;
+  // 124^2, 1928: 77.0 against 74.6; float32, 40^2 18.4 against 19.6, 44^2 a tie at 22;
+  // 16-bit columns of one round a wave some longer: 64^2, 122^2 scene, 1864, 22.3
+  // against 23.5, 140^2, 2456, 32.6 against 28.1).
   const int64_t share = (steps + waves - 1) / waves, columns = sh.nb * units;
-  sh.split = steps >= waves && (columns < 1536 || (columns >= 2048 && share >= kAdjLoads &&
+  const int64_t many = f32 || share > kAdjLoads ? 1856 : 2048;
+  sh.split = steps >= waves && (columns < 1536 || (columns >= many && share >= kAdjLoads &&
                                                    8 * waves * padded(share, 1) <= 9 * steps));
   const int64_t wsteps = sh.split ? share : steps;
   // columns at a time: as few as leave at most an eighth of a column's rounds
@@ -795,6 +802,25 @@ static AdjShape adj_shape(bool f32, int64_t M, int64_t units) {
   const int64_t want = std::max<int64_t>(1, 512 * turns / sh.nb);
   const int64_t groups = f32 ? (units + sh.c - 1) / sh.c : units, quantum = sh.split ? 1 : waves;
   sh.per_wg = std::max<int64_t>(1, ((groups + want - 1) / want + quantum - 1) / quantum) * quantum;
+  // 16-bit libraries of up to two such turns, shared columns: near that number, the
+  // groups per workgroup that leave the fullest CU the fewest, each workgroup
+  // costing a tenth of a group more for its copy of g, and a CU with a single
+  // workgroup, whose barriers nothing covers, a twentieth (128^2, 160^2 scene: 800
+  // workgroups of 4 groups, 16 on the fullest CU, 136 us; 458 of 7, 14 groups, 125;
+  // 70^2 scene: 308 of 2, 4 groups, 32.6 us; 206 of 3, 29.2).  Groups of fewer rows
+  // gain nothing by it (96^2, 100^2 scene: 31.3 us so, 34.0 by the count).
+  if (!f32 && sh.split && turns <= 2 && sh.block_rows >= 12288) {
+    const int64_t near = sh.per_wg;
+    int64_t best = INT64_MAX;
+    for (int64_t p = std::max<int64_t>(1, near / 2); p <= 2 * near; ++p) {
+      const int64_t k = (sh.nb * ((groups + p - 1) / p) + 255) / 256;  // workgroups on the fullest CU
+      const int64_t cost = k * (10 * p + 1) * (k == 1 ? 21 : 20);
+      if (cost < best) {
+        best = cost;
+        sh.per_wg = p;
+      }
+    }
+  }
   sh.grid_x = (groups + sh.per_wg - 1) / sh.per_wg;
   return sh;
 }
