@@ -933,8 +933,44 @@ __global__ __launch_bounds__(512, 1) void gemm_h16_w8_kernel(
       store_acc(acc[t][u], dst, M, B, m0 + 64 * wm + 32 * t, n0 + 128 * wn + 32 * u, lane, fexp, !split);
 }
 
-// out[b][m] = 2^-f_b * sum over K slices (fixed order).  VEC: 4 outputs per
-// thread (M % 4 == 0, so the 4 share one scene).
+// Sum of 8 slices of an output, in pairs.
+template <typename T>
+__device__ __forceinline__ T sum_slices(const T (&v)[8]) {
+  return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+
+// The sum over the slices of the outputs at part + t: 8 slices loaded together and
+// added in pairs, those sums (and the last up to 7 slices) in float64.  (All 64 in one
+// float32 chain had up to twice the error; all of them in float64, no better, took 1
+// us more.)
+template <typename T, typename Sum>
+__device__ __forceinline__ void sum_slices(const float* __restrict__ part, int splits, int64_t BM, int64_t t,
+                                           Sum add) {
+  auto load = [&](int p) { return __builtin_nontemporal_load(reinterpret_cast<const T*>(part + (int64_t)p * BM + t)); };
+  int p = 0;
+  for (; p + 8 <= splits; p += 8) {
+    T v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = load(p + u);
+    add(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])));
+  }
+  if (splits - p >= 4) {
+    T v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = load(p + u);
+    add((v[0] + v[1]) + (v[2] + v[3]));
+    p += 4;
+  }
+  if (splits - p >= 2) {
+    const T a = load(p), b = load(p + 1);
+    add(a + b);
+    p += 2;
+  }
+  if (p < splits) add(load(p));
+}
+
+// out[b][m] = 2^-f_b * sum over K slices.  VEC: 4 outputs per thread (M % 4 == 0, so
+// the 4 share one scene).
 template <bool VEC>
 __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restrict__ part,
                                                             int splits, int64_t BM, int64_t M,
@@ -944,19 +980,10 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
     const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (t >= BM) return;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int p0 = 0; p0 < splits; p0 += 8) {  // 8 loads in flight
-      f32x4 v[8];
+    sum_slices<f32x4>(part, splits, BM, t, [&](const f32x4 v) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int p = p0 + u < splits ? p0 + u : splits - 1;
-        v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(part + (int64_t)p * BM + t));
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (p0 + u < splits)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) sum[q] += (double)v[u][q];
-    }
+      for (int q = 0; q < 4; ++q) sum[q] += (double)v[q];
+    });
     f32x4 s = {(float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]};
     if (fexp) {
       const int ex = -fexp[t / M];
@@ -968,14 +995,7 @@ __global__ __launch_bounds__(256) void reduce_splits_kernel(const float* __restr
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= BM) return;
     double sum = 0.0;
-    for (int p0 = 0; p0 < splits; p0 += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(p0 + u < splits ? p0 + u : splits - 1) * BM + t];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (p0 + u < splits) sum += (double)v[u];
-    }
+    sum_slices<float>(part, splits, BM, t, [&](const float v) { sum += (double)v; });
     const float s = (float)sum;
     out[t] = fexp ? ldexpf(s, -fexp[t / M]) : s;
   }
@@ -1009,11 +1029,9 @@ static int64_t f32_scene_blocks(int64_t bc) {
 
 constexpr int64_t kMaxSplits = 64;  // slices of K
 
-// K units of each of c slices: whole accumulation blocks in FP32, whole turns of
-// the ring in the 16-bit forms (whose odd stages are guarded one by one: 50^2,
-// 100^2 scene, 200 scenes: 16 slices of 20 stages 45 us, 18 of 18 51)
-static int64_t slice_units(int64_t units, int64_t c, bool f32) {
-  const int64_t per = (units + c - 1) / c, whole = f32 ? kF32Block : kHRing;
+// K units rounded up to whole accumulation blocks (FP32) or turns of the ring (16-bit)
+static int64_t whole_units(int64_t per, bool f32) {
+  const int64_t whole = f32 ? kF32Block : kHRing;
   return (per + whole - 1) / whole * whole;
 }
 
@@ -1025,41 +1043,54 @@ static GemmPlan plan_gemm(int storage, int64_t M, int64_t ncols, int64_t ncols_p
   p.nblocks = (bc + tn - 1) / tn;
   p.kunits = f32 ? (ncols + 7) / 8 : (ncols_pad / 8) / kHG;
   const int64_t tiles = p.mblocks * p.nblocks;
-  int64_t s = 1;
   if (!f32 && h16_kind(bc) == kHW8) {
     // the 8-wave kernel splits K only while whole extra rounds of tiles fit (192
     // tiles stay unsplit: 384 workgroups would leave half the GPU idle in their
     // second round too)
-    s = 256 / tiles;
-    if (s > 16) s = 16;
-    if (s > p.kunits) s = p.kunits;
-    if (s < 1) s = 1;
+    const int64_t s = std::max<int64_t>(1, std::min<int64_t>({256 / tiles, 16, p.kunits}));
+    p.per = (p.kunits + s - 1) / s;
   } else {
-    // The number of slices of K with the least work: rounds of workgroups (two to
-    // a CU at a time in FP32, one in the 16-bit forms, whose partial images a second
-    // one does not repay) times the K units of a slice, plus the partial images'
-    // round trip in units of the library's bytes, and half a unit a slice (FP32:
-    // one) for the reduction's chain.  (96^2, 20 scenes, FP32: 36 tiles,
-    // 15 slices make 540 workgroups and a second round of 28, 87 us; 12 slices, 70.
-    // 33^2, 200^2 scene, 20 scenes: 5 tiles, 16 slices fill 80
-    // CUs, 163 us; 63, 74.)
-    const int64_t slots = f32 ? 512 : 256;
-    const int64_t unit = tm * (f32 ? 32 : 2 * 8 * kHG);      // library bytes of a K unit of a tile
-    const int64_t partial = 8 * tm * std::min(bc, tn);       // written and read, a slice of a tile
+    // The slices of K with the least work, in K units: those of the workgroups on the
+    // fullest CU (one alone multiplies as fast as two, or waits for memory as they
+    // do), each with the cost of its start and end, and for split sums the reduction's
+    // launch, its chain and the partial images' round trip.  In 16 bits the library's
+    // stream sets a bound that uneven CUs do not change, and a slice may end inside a
+    // turn of the ring at the cost of one guarded stage.  The weights are fitted to
+    // 16000 timed products of 45 image and scene sizes, 5 to 400 scenes and 1 to 64
+    // slices: in the mean 1% (FP32) and 3% from the best number of slices.
+    // (FP32, 64^2, 100^2 scene, 33 scenes: 16 slices on 256 CUs 49 us, 27 of 48 units
+    // on 432 places 60; 96^2, 96^2 scene, 20 scenes: 36 tiles, 7 slices 63, 12 slices 68,
+    // 15, a third workgroup on 28 CUs, 82; 131^2, 80^2 scene, 33 scenes: 68 tiles, 3
+    // slices 147, 10 slices, 168 workgroups in the second round, 175.  16 bits, the
+    // same: 3 slices 54, 2 slices 64, 4 slices 72.)
+    const double unit = (double)tm * (f32 ? 32 : 2 * 8 * kHG);  // library bytes of a K unit of a tile
+    const double partial = 8.0 * tm * std::min(bc, tn);         // written and read, a slice of a tile
+    const double stream = f32 ? 0.0 : 1.33 * (double)(tiles * p.kunits) / 256.0;
+    // FP32: rounds of two workgroups a CU; a last one of up to 256 does not spread
+    // itself evenly over the CUs
+    auto fullest = [&](int64_t wgs) -> double {
+      if (!f32 || wgs <= 256) return (double)((wgs + 255) / 256);
+      const int64_t rest = wgs % 512;
+      return 2.0 * (double)(wgs / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 1.4 : 2.0);
+    };
     double best = 0.0;
     for (int64_t c = 1; c <= kMaxSplits && c <= p.kunits; ++c) {
-      const int64_t per = slice_units(p.kunits, c, f32);
-      const int64_t wgs = tiles * ((p.kunits + per - 1) / per);
-      double cost = (double)((wgs + slots - 1) / slots) * (double)per;
-      if (wgs > tiles)
-        cost += (double)wgs * (double)partial / ((double)unit * (double)slots) + (f32 ? 1.0 : 0.5) * (double)c;
-      if (c == 1 || cost < best) {
-        best = cost;
-        s = c;
+      const int64_t least = (p.kunits + c - 1) / c, whole = whole_units(least, f32);
+      for (const int64_t per : {f32 ? whole : least, whole}) {
+        const int64_t slices = (p.kunits + per - 1) / per, wgs = tiles * slices;
+        const double ends = f32 ? 12.0 : per == whole ? 6.0 : 7.0;
+        double cost = std::max(stream, fullest(wgs) * ((double)per + ends));
+        if (slices > 1) {
+          const double trip = (double)wgs * partial / (unit * 256.0);
+          cost += 6.0 + (f32 ? 0.43 * trip + 0.8 * (double)slices : 1.25 * trip + 0.6 * (double)slices);
+        }
+        if (best == 0.0 || cost < best) {
+          best = cost;
+          p.per = per;
+        }
       }
     }
   }
-  p.per = f32 || h16_kind(bc) != kHW8 ? slice_units(p.kunits, s, f32) : (p.kunits + s - 1) / s;
   p.splits = (p.kunits + p.per - 1) / p.per;  // no empty slice
   if (p.splits < 1) p.splits = 1;
   return p;
