@@ -369,17 +369,24 @@ static MvShape mv_shape(int storage, int64_t M, int64_t ncols, int64_t ncols_pad
   }
   sh.one = false;
   if (f32) {
-    // 1024 rows per workgroup; below 8192 rows 512 or 256, whichever leaves few
-    // threads past the end (96^2 with 1024: 52 us, with 256: 59 us; 64^2 with 512:
-    // 14.5 us, with 1024: 16.1 us; 80^2 with 256: 27 us, with 512: 32 us)
+    // 1024 rows per workgroup; small images of small libraries 512 or 256, whichever
+    // leaves few threads past the end (96^2 with 1024: 52 us, with 256: 59 us; 64^2 with
+    // 512: 14.5 us, with 1024: 16.1 us; 80^2 with 256: 27 us, with 512: 32 us).  Large
+    // libraries of small images read better in the longer pieces (72^2, 181^2 scene: 1024
+    // rows 110 us, 512 rows 121; 80^2: 127, 256 rows 145; 56^2, 256^2 scene: 122 and 140;
+    // 80^2, 80^2 scene: 29.0 and 25.6).
     sh.r = 4;
-    sh.rt = M >= 8192 ? 256 : padded(512) * 32 <= M * 33 ? 128 : 64;
+    const bool large = (M >= 4608 && ncols >= 8192) || M * ncols >= 100000000;
+    sh.rt = M >= 8192 || large ? 256 : padded(512) * 32 <= M * 33 ? 128 : 64;
   } else {
     // 2048 rows where they leave few threads past the end, else 512, and fewer
     // rows per thread for small images (bf16: 101^2, 2048: 39 us, 512: 43 us; 96^2
-    // 37 and 31 us)
+    // 37 and 31 us); with many columns 2048 rows of smaller images too, and where
+    // they leave up to an eighth past the end (64^2, 181^2 scene 43.1 against 50.5; 96^2
+    // 96 against 102; 150^2 scene 64^2 36 against 33, 96^2 equal).
     sh.r = 8;
-    sh.rt = M >= 8192 && padded(2048) * 11 <= M * 12 ? 256 : 64;
+    const bool many = ncols_pad >= 30000;
+    sh.rt = M >= (many ? 4096 : 8192) && padded(2048) * (many ? 8 : 11) <= M * (many ? 9 : 12) ? 256 : 64;
     if (sh.rt == 64)
       while (sh.r > 2 && padded(sh.r * 64) * 8 > M * 9 && padded(sh.r * 32) < padded(sh.r * 64)) sh.r /= 2;
   }
