@@ -2204,7 +2204,20 @@ static hipError_t launch_spread16(int storage, const ColGeom* geo, int n, int64_
   return orbit16_end(pl, M, geo, out, s);
 }
 
-size_t orbit_bases_bytes(int N, int64_t M) { return (size_t)orbit_grid(N).nreps * (size_t)M * 4; }
+// Base columns worth keeping between the passes.  The cubic values cost more than
+// their way through memory at any size (128^2, 176^2 scene, bf16: 0.84 ms against
+// 1.22).  Bilinear ones do where the 256 MiB last-level cache cannot hold them: 128^2,
+// 128^2 scene, 256 MiB, 283 us kept, 308 formed again; 144^2 scene 401 and 366; 176^2
+// 565 and 481.  From boxes (n > 131) kept all the same (256^2, 80^2 scene, 400 MiB: 557
+// and 623).  On sides that are not multiples of 4, whose stores of parts of lines
+// need the cache too, up to 80 MiB (101^2, 60^2 scene, 35 MiB: 79 and 85; 101^2, 99
+// MiB: 180 and 158; 150^2, 60^2 scene, 77 MiB: 144 and 201; 90^2, 174 MiB: 354 and 318).
+size_t orbit_bases_bytes(int n, int N, bool cubic) {
+  const size_t bytes = (size_t)orbit_grid(N).nreps * (size_t)n * (size_t)n * 4;
+  const size_t most = cubic || (n % 4 == 0 && !orbit16_pair_fits(n)) ? ~(size_t)0
+                                                                     : (size_t)(n % 4 == 0 ? 256 : 80) << 20;
+  return bytes <= most ? bytes : 0;
+}
 
 // float32: the pair in LDS, or (up to kBoxMaxN) a staged box per tile
 static bool build_orbit_supported(int n, int K, int N) {

@@ -465,12 +465,12 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
     return r;
   };
   // A 16-bit flux-preserving build keeps its first pass's base columns (half the
-  // library's bytes) when its scratch stays within what a stream keeps and there
-  // is memory for them.  (A pool block of 100 MB costs 150 to 300 us whenever the
+  // library's bytes) where that pays, its scratch stays within what a stream keeps and
+  // there is memory for them.  (A pool block of 100 MB costs 150 to 300 us whenever the
   // pool was trimmed, as by a release on another stream: more than the second
   // pass saves.)
   constexpr size_t kKeep = (size_t)512 << 20;
-  size_t base_bytes = flux_orbit && orbit16 ? psflib::orbit_bases_bytes(desc->N, L.M) : 0;
+  size_t base_bytes = flux_orbit && orbit16 ? psflib::orbit_bases_bytes(desc->n, desc->N, cubic) : 0;
   if (tmp_bytes + base_bytes > kKeep) base_bytes = 0;
   e = tmp.acquire(dev, s, tmp_bytes + base_bytes, kKeep);
   if (e == hipErrorOutOfMemory && base_bytes > 0) {

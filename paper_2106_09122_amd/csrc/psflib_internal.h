@@ -173,8 +173,8 @@ struct OrbitFlux {
   int32_t* exps;
   float* bases;  // orbit_bases_bytes, or nullptr: the second pass forms the values again
 };
-// 16-bit builds: the base columns kept between the passes
-size_t orbit_bases_bytes(int N, int64_t M);
+// 16-bit builds: the base columns to keep between the passes, 0 for none
+size_t orbit_bases_bytes(int n, int N, bool cubic);
 // Modes of the float32 orbit builds: plain; the first pass; the second pass.
 // The 16-bit orbit builds are the second pass when fx is given.
 constexpr int kOrbitPlain = 0, kOrbitSumsOnly = 1, kOrbitScaled = 2;
