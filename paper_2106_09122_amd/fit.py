@@ -19,6 +19,10 @@ from . import psflib
 from .psflib import _psfop
 
 
+def _stream(dev):
+    return torch.cuda.current_stream(dev).cuda_stream
+
+
 class _Simulate(torch.autograd.Function):
     """simulate for library objects with an apply and apply_adjoint of their own."""
 
@@ -59,11 +63,22 @@ def loss_and_grad(lib, theta, counts, var, K, rmax):
     capturing stream)."""
     if type(lib) is psflib.Library:
         return _psfop.loss_and_grad(lib, theta, counts, var, float(K), float(rmax))
-    th = theta.detach().to(device=counts.device, dtype=torch.float64).clone().requires_grad_(True)
-    with torch.enable_grad():
-        L = chi2(simulate(lib, render_disk(th, lib.N, lib.S, rmax)), counts, var, K)
-        dth, = torch.autograd.grad(L, th)
-    return L.detach(), dth
+    # the same chain with the object's own products
+    dev = counts.device
+    th = theta.detach().to(device=dev, dtype=torch.float64).contiguous()
+    S = lib.apply(render_disk(th, lib.N, lib.S, rmax))
+    M = S.numel()
+    for name, x in (("counts", counts), ("var", var)):
+        if not (isinstance(x, torch.Tensor) and x.dtype == torch.float64 and x.device == dev and x.numel() == M):
+            raise ValueError(f"{name} must be a float64 tensor of {M} elements on {dev}")
+    D, V = counts.contiguous(), var.contiguous()
+    L = torch.empty((), dtype=torch.float64, device=dev)
+    gS = torch.empty_like(S)
+    psflib.chi2(M, float(K), S.data_ptr(), D.data_ptr(), V.data_ptr(), L.data_ptr(), gS.data_ptr(), _stream(dev))
+    gZ = lib.apply_adjoint(gS)
+    dth = torch.empty(5, dtype=torch.float64, device=dev)
+    psflib.render_disk_grad(lib.N, lib.S, rmax, th.data_ptr(), gZ.data_ptr(), dth.data_ptr(), _stream(dev))
+    return L, dth
 
 
 def fit_disk(lib, counts, var, K, theta0, rmax, steps: int = 64, lr: float = 0.05):
