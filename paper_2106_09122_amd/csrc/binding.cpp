@@ -16,7 +16,8 @@
 
 namespace {
 
-PyObject* g_error = nullptr;  // psflib.PsflibError, kept for the life of the module
+PyObject* g_error = nullptr;   // psflib.PsflibError, kept for the life of the module
+PyObject* g_native = nullptr;  // fit._native: whether a library's products are its class's
 
 // PsflibError(status, where, message), from any thread
 [[noreturn]] void raise_status(psflib_status st, const char* where) {
@@ -186,7 +187,14 @@ struct Simulate : torch::autograd::Function<Simulate> {
   }
   static variable_list backward(AutogradContext* ctx, variable_list g) {
     auto lib = c10::static_intrusive_pointer_cast<LibRef>(ctx->saved_data["lib"].toCapsule());
-    return {product(lib->get(), true, g[0].contiguous().to(at::kFloat), "g"), at::Tensor()};
+    const at::Tensor gS = g[0].contiguous().to(at::kFloat);
+    {
+      py::gil_scoped_acquire gil;
+      const py::handle o(lib->o);
+      if (g_native && !py::handle(g_native)(o).cast<bool>())  // an adjoint put in its place since
+        return {o.attr("apply_adjoint")(gS).cast<at::Tensor>(), at::Tensor()};
+    }
+    return {product(lib->get(), true, gS, "g"), at::Tensor()};
   }
 };
 
@@ -295,6 +303,7 @@ std::tuple<at::Tensor, at::Tensor> loss_and_grad(py::handle self, const at::Tens
 PYBIND11_MODULE(_psfop, m) {
   m.doc() = "Native calls of the psflib binding.";
   m.def("set_error", [](py::object cls) { g_error = cls.release().ptr(); });
+  m.def("set_native", [](py::object f) { g_native = f.release().ptr(); });
   m.def("current_stream", [](const at::Device& d) { return reinterpret_cast<uintptr_t>(current_stream(d)); });
   m.def("apply", &apply);
   m.def("apply_adjoint", &apply_adjoint);

@@ -23,6 +23,20 @@ def _stream(dev):
     return torch.cuda.current_stream(dev).cuda_stream
 
 
+_OWN = psflib.Library.apply, psflib.Library.apply_adjoint
+
+
+def _native(lib) -> bool:
+    """Whether lib's products are those of psflib.Library: not overridden, and not
+    replaced on the class or the object (a counter, a wrapper), which are called."""
+    if type(lib) is not psflib.Library or (psflib.Library.apply, psflib.Library.apply_adjoint) != _OWN:
+        return False
+    return "apply" not in lib.__dict__ and "apply_adjoint" not in lib.__dict__
+
+
+_psfop.set_native(_native)  # asked again by a backward pass
+
+
 class _Simulate(torch.autograd.Function):
     """simulate for library objects with an apply and apply_adjoint of their own."""
 
@@ -38,7 +52,7 @@ class _Simulate(torch.autograd.Function):
 
 def simulate(lib: "psflib.Library", Z: torch.Tensor) -> torch.Tensor:
     """S = A Z, differentiable in Z (backward: A^T g)."""
-    if type(lib) is psflib.Library:
+    if _native(lib):
         return _psfop.simulate(lib, Z)
     return _Simulate.apply(Z, lib)
 
@@ -61,7 +75,7 @@ def loss_and_grad(lib, theta, counts, var, K, rmax):
     dL/dS, A^T (dL/dS), and dL/dtheta through the renderer's gradient.  Not to
     be captured in a graph (psflib_chi2 and psflib_render_disk_grad refuse a
     capturing stream)."""
-    if type(lib) is psflib.Library:
+    if _native(lib):
         return _psfop.loss_and_grad(lib, theta, counts, var, float(K), float(rmax))
     # the same chain with the object's own products
     dev = counts.device

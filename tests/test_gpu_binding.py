@@ -58,3 +58,66 @@ def test_loss_and_grad_of_other_objects(fitting):
         assert own.calls == [("apply", me, False), ("adjoint", me, False)]
         assert torch.equal(L1, L) and torch.equal(g1, g)
         assert L1.shape == L.shape and not L1.requires_grad and not g1.requires_grad
+
+
+def _step(fit, lib, th, counts, var, K):
+    t = th.clone().requires_grad_(True)
+    L = fit.chi2(fit.simulate(lib, fit.render_disk(t, lib.N, lib.S, RMAX)), counts, var, K)
+    L.backward()
+    return L.detach(), t.grad
+
+
+@pytest.mark.parametrize("where", ["instance", "class", "subclass"])
+def test_replaced_products_are_called(fitting, monkeypatch, where):
+    from paper_2106_09122_amd import psflib
+    torch, fit, lib, th, counts, var, K = fitting
+    want = _step(fit, lib, th, counts, var, K)
+    calls = []
+
+    def counted(name):
+        plain = getattr(psflib.Library, name)
+
+        def call(*a):
+            calls.append(name)
+            return plain(*((lib,) + a if where == "instance" else a))
+        return call
+
+    own = {name: counted(name) for name in ("apply", "apply_adjoint")}
+    if where == "subclass":
+        monkeypatch.setattr(lib, "__class__", type("Counted", (psflib.Library,), own))
+    else:
+        for name, f in own.items():
+            monkeypatch.setattr(lib if where == "instance" else psflib.Library, name, f)
+    L, g = _step(fit, lib, th, counts, var, K)
+    assert calls == ["apply", "apply_adjoint"]
+    assert torch.equal(L, want[0]) and torch.equal(g, want[1])
+    L, g = fit.loss_and_grad(lib, th, counts, var, K, RMAX)
+    assert calls == ["apply", "apply_adjoint"] * 2
+    monkeypatch.undo()
+    lib.apply(torch.zeros(lib.ncols, device="cuda"))
+    assert len(calls) == 4
+
+
+def test_adjoint_replaced_after_the_forward_pass(fitting, monkeypatch):
+    """A backward pass looks the adjoint up when it runs; what it raises comes out."""
+    torch, fit, lib, th, counts, var, K = fitting
+    Z = torch.rand(lib.ncols, device="cuda", requires_grad=True)
+    plain = lib.apply_adjoint
+    calls = []
+
+    def counted(g):
+        calls.append(g.shape)
+        return plain(g)
+
+    S = fit.simulate(lib, Z)
+    monkeypatch.setattr(lib, "apply_adjoint", counted)
+    S.sum().backward()
+    assert len(calls) == 1 and torch.equal(Z.grad, plain(torch.ones(lib.M, device="cuda")))
+
+    def refuses(g):
+        raise ValueError("not today")
+
+    S = fit.simulate(lib, Z)
+    monkeypatch.setattr(lib, "apply_adjoint", refuses)
+    with pytest.raises(ValueError, match="not today"):
+        S.sum().backward()
