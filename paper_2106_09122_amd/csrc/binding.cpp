@@ -75,6 +75,16 @@ bool is_float_on(const at::Tensor& t, const at::Device& d) {
               std::to_string(size) + " elements");
 }
 
+// x as a tensor.  What is not one has, with few exceptions, no method of this name:
+// the AttributeError of a call of it.
+const at::Tensor& tensor_with(py::handle x, const char* method) {
+  if (!THPVariable_Check(x.ptr())) {
+    (void)py::getattr(x, method);
+    raise_value("a tensor is expected");
+  }
+  return THPVariable_Unpack(x.ptr());
+}
+
 at::Tensor vec(py::handle x, int64_t size, const at::Device& d, const char* name) {
   if (!THPVariable_Check(x.ptr())) bad_vec(name, d, size);
   const at::Tensor& t = THPVariable_Unpack(x.ptr());
@@ -198,7 +208,8 @@ struct Simulate : torch::autograd::Function<Simulate> {
   }
 };
 
-at::Tensor simulate(py::handle lib, const at::Tensor& Z) {
+at::Tensor simulate(py::handle lib, py::handle scene) {
+  const at::Tensor Z = tensor_with(scene, "contiguous");
   auto ref = c10::make_intrusive<LibRef>(lib);
   py::gil_scoped_release nogil;
   return Simulate::apply(Z, std::move(ref));
@@ -238,24 +249,25 @@ struct RenderDisk : torch::autograd::Function<RenderDisk> {
   }
 };
 
-at::Tensor render_disk(const at::Tensor& theta, int64_t N, double S, double rmax) {
+at::Tensor render_disk(py::handle theta, int64_t N, double S, double rmax) {
+  const at::Tensor th = tensor_with(theta, "detach");
   py::gil_scoped_release nogil;
-  return RenderDisk::apply(theta, N, S, rmax);
+  return RenderDisk::apply(th, N, S, rmax);
 }
 
-at::Tensor float64_vec(const at::Tensor& x, const char* name, int64_t M, const at::Device& d) {
-  if (x.scalar_type() != at::kDouble || x.device() != d || x.numel() != M)
-    raise_value(std::string(name) + " must be a float64 tensor of " + std::to_string(M) + " elements on " +
-                d.str());
-  return x.contiguous();
+at::Tensor float64_vec(py::handle x, const char* name, int64_t M, const at::Device& d) {
+  if (THPVariable_Check(x.ptr())) {
+    const at::Tensor& t = THPVariable_Unpack(x.ptr());
+    if (t.scalar_type() == at::kDouble && t.device() == d && t.numel() == M) return t.contiguous();
+  }
+  raise_value(std::string(name) + " must be a float64 tensor of " + std::to_string(M) + " elements on " +
+              d.str());
 }
 
 // (loss, dL/dS)
-std::tuple<at::Tensor, at::Tensor> misfit(const at::Tensor& S, const at::Tensor& counts,
-                                          const at::Tensor& var, double K) {
+std::tuple<at::Tensor, at::Tensor> misfit(const at::Tensor& S, const at::Tensor& D, const at::Tensor& V,
+                                          double K) {
   const int64_t M = S.numel();
-  const at::Tensor D = float64_vec(counts, "counts", M, S.device());
-  const at::Tensor V = float64_vec(var, "var", M, S.device());
   at::Tensor loss = at::empty({}, D.options().memory_format(std::nullopt));
   at::Tensor grad = at::empty_like(S);
   check(psflib_chi2(M, K, S.data_ptr<float>(), D.data_ptr<double>(), V.data_ptr<double>(),
@@ -265,11 +277,9 @@ std::tuple<at::Tensor, at::Tensor> misfit(const at::Tensor& S, const at::Tensor&
 }
 
 struct Chi2 : torch::autograd::Function<Chi2> {
-  static at::Tensor forward(AutogradContext* ctx, const at::Tensor& model, const at::Tensor& counts,
-                            const at::Tensor& var, double K) {
-    const at::Tensor S = model.detach().contiguous();
-    if (S.scalar_type() != at::kFloat) raise_value("model must be a float32 image");
-    auto [loss, grad] = misfit(S, counts, var, K);
+  static at::Tensor forward(AutogradContext* ctx, const at::Tensor& model, const at::Tensor& D,
+                            const at::Tensor& V, double K) {
+    auto [loss, grad] = misfit(model.detach().contiguous(), D, V, K);
     ctx->save_for_backward({grad});
     return loss;
   }
@@ -279,21 +289,27 @@ struct Chi2 : torch::autograd::Function<Chi2> {
   }
 };
 
-at::Tensor chi2(const at::Tensor& model, const at::Tensor& counts, const at::Tensor& var, double K) {
+at::Tensor chi2(py::handle model, py::handle counts, py::handle var, double K) {
+  const at::Tensor S = tensor_with(model, "detach");
+  if (S.scalar_type() != at::kFloat) raise_value("model must be a float32 image");
+  const at::Tensor D = float64_vec(counts, "counts", S.numel(), S.device());
+  const at::Tensor V = float64_vec(var, "var", S.numel(), S.device());
   py::gil_scoped_release nogil;
-  return Chi2::apply(model, counts, var, K);
+  return Chi2::apply(S, D, V, K);
 }
 
-std::tuple<at::Tensor, at::Tensor> loss_and_grad(py::handle self, const at::Tensor& theta,
-                                                 const at::Tensor& counts, const at::Tensor& var,
-                                                 double K, double rmax) {
+std::tuple<at::Tensor, at::Tensor> loss_and_grad(py::handle self, py::handle theta, py::handle counts,
+                                                 py::handle var, double K, double rmax) {
   const Lib lib = lib_of(self);
   const int64_t N = self.attr("N").cast<int64_t>();
   const double S = self.attr("S").cast<double>();
+  at::Tensor th = tensor_with(theta, "detach");
+  const at::Tensor D = float64_vec(counts, "counts", lib.M, lib.device);
+  const at::Tensor V = float64_vec(var, "var", lib.M, lib.device);
   py::gil_scoped_release nogil;
-  const at::Tensor th = theta.detach().to(counts.device(), at::kDouble).contiguous();
+  th = th.detach().to(D.device(), at::kDouble).contiguous();
   const at::Tensor image = product(lib, false, render(th, N, S, rmax), "scene");
-  auto [loss, gS] = misfit(image, counts, var, K);
+  auto [loss, gS] = misfit(image, D, V, K);
   const at::Tensor gZ = product(lib, true, gS, "g");
   return {loss, render_grad(th, N, S, rmax, gZ)};
 }

@@ -121,3 +121,17 @@ def test_adjoint_replaced_after_the_forward_pass(fitting, monkeypatch):
     monkeypatch.setattr(lib, "apply_adjoint", refuses)
     with pytest.raises(ValueError, match="not today"):
         S.sum().backward()
+
+
+def test_arguments_that_are_not_tensors(fitting):
+    torch, fit, lib, th, counts, var, K = fitting
+    S = lib.apply(torch.zeros(lib.ncols, device="cuda"))
+    for c, v in ((counts.cpu().numpy(), var), (None, var), (counts, var.cpu().numpy()), (counts, 1.0)):
+        with pytest.raises(ValueError, match="must be a float64 tensor"):
+            fit.chi2(S, c, v, K)
+    with pytest.raises(ValueError, match="must be a float64 tensor"):
+        fit.loss_and_grad(lib, th, counts, var.cpu().numpy(), K, RMAX)
+    with pytest.raises(AttributeError):
+        fit.simulate(lib, np.zeros(lib.ncols, np.float32))
+    with pytest.raises(AttributeError):
+        fit.loss_and_grad(lib, np.zeros(5), counts, var, K, RMAX)
