@@ -249,8 +249,15 @@ struct RenderDisk : torch::autograd::Function<RenderDisk> {
   }
 };
 
+// the disk's parameters: the kernels read five values
+const at::Tensor& disk_parameters(py::handle theta) {
+  const at::Tensor& t = tensor_with(theta, "detach");
+  if (t.numel() < 5) raise_value("theta must have 5 elements, got " + std::to_string(t.numel()));
+  return t;
+}
+
 at::Tensor render_disk(py::handle theta, int64_t N, double S, double rmax) {
-  const at::Tensor th = tensor_with(theta, "detach");
+  const at::Tensor th = disk_parameters(theta);
   py::gil_scoped_release nogil;
   return RenderDisk::apply(th, N, S, rmax);
 }
@@ -303,7 +310,7 @@ std::tuple<at::Tensor, at::Tensor> loss_and_grad(py::handle self, py::handle the
   const Lib lib = lib_of(self);
   const int64_t N = self.attr("N").cast<int64_t>();
   const double S = self.attr("S").cast<double>();
-  at::Tensor th = tensor_with(theta, "detach");
+  at::Tensor th = disk_parameters(theta);
   const at::Tensor D = float64_vec(counts, "counts", lib.M, lib.device);
   const at::Tensor V = float64_vec(var, "var", lib.M, lib.device);
   py::gil_scoped_release nogil;

@@ -23,3 +23,16 @@ def test_chi2_arguments_that_are_not_tensors():
 def test_disk_parameters_that_are_not_tensors():
     with pytest.raises(AttributeError):
         fit.render_disk(np.ones(5), 4, 1.0, 8.0)
+
+
+@pytest.mark.parametrize("numel", [0, 1, 4])
+def test_fewer_parameters_than_the_disk_has(numel):
+    """The renderer reads five values: fewer are refused."""
+    with pytest.raises(ValueError, match="theta must have 5 elements"):
+        fit.render_disk(torch.ones(numel, dtype=torch.float64), 4, 1.0, 8.0)
+
+    class Grid:
+        N, S = 4, 1.0
+
+    with pytest.raises(ValueError, match="theta must have 5 elements"):
+        fit.loss_and_grad(Grid(), torch.ones(numel), torch.ones(4).double(), torch.ones(4).double(), 1.0, 8.0)

@@ -135,3 +135,11 @@ def test_arguments_that_are_not_tensors(fitting):
         fit.simulate(lib, np.zeros(lib.ncols, np.float32))
     with pytest.raises(AttributeError):
         fit.loss_and_grad(lib, np.zeros(5), counts, var, K, RMAX)
+
+
+def test_more_parameters_than_the_disk_has(fitting):
+    """The disk is drawn from the first five of a longer vector; a shorter one is
+    refused (tests/test_binding_errors.py)."""
+    torch, fit, lib, th, counts, var, K = fitting
+    longer = torch.cat([th, torch.ones(1, dtype=torch.float64, device="cuda")])
+    assert torch.equal(fit.render_disk(longer, lib.N, lib.S, RMAX), fit.render_disk(th, lib.N, lib.S, RMAX))
