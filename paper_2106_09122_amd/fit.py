@@ -80,7 +80,8 @@ def loss_and_grad(lib, theta, counts, var, K, rmax):
     # the same chain with the object's own products
     dev = counts.device
     th = theta.detach().to(device=dev, dtype=torch.float64).contiguous()
-    S = lib.apply(render_disk(th, lib.N, lib.S, rmax))
+    Z = render_disk(th, lib.N, lib.S, rmax)
+    S = lib.apply(Z)
     M = S.numel()
     for name, x in (("counts", counts), ("var", var)):
         if not (isinstance(x, torch.Tensor) and x.dtype == torch.float64 and x.device == dev and x.numel() == M):
