@@ -3,9 +3,10 @@
 // stream and the C ABI call without the interpreter in between, and the
 // differentiable operations (simulation, disk renderer, chi-square) as C++
 // autograd functions, whose backward pass needs no Python either.  Everything
-// else of the binding is Python (psflib.py, fit.py).  Per call on the host: a
-// product 8.2 us through ctypes, 4.3 us here, of which the C call takes 3.2; a
-// fit step through autograd 130-215 us, 70-85 us here.
+// else of the binding is Python (psflib.py, fit.py).  Per call on the host (20^2
+// PSFs and scene, where the GPU waits for it): a product 8 to 11 us through ctypes,
+// 3.3 to 4.8 here, of which the C call takes 3.2; a fit step through autograd 190 us,
+// 110 here (77 to 120 from one process to the next, half of it torch's engine).
 #include <c10/hip/HIPStream.h>
 #include <torch/extension.h>
 
@@ -59,11 +60,31 @@ struct Lib {
   at::Device device;
 };
 
+// attribute names, made once (a string for every lookup is a third of its time)
+struct Names {
+  PyObject *handle = PyUnicode_InternFromString("_handle"), *h = PyUnicode_InternFromString("h"),
+           *ncols = PyUnicode_InternFromString("ncols"), *M = PyUnicode_InternFromString("M"),
+           *device = PyUnicode_InternFromString("device");
+};
+const Names& names() {
+  static const Names* n = new Names();
+  return *n;
+}
+
+py::object attr(py::handle o, PyObject* name) {
+  PyObject* r = PyObject_GetAttr(o.ptr(), name);
+  if (!r) throw py::error_already_set();
+  return py::reinterpret_steal<py::object>(r);
+}
+
+const psflib_handle* handle_of(py::handle o) {  // o.h; with the GIL
+  py::object h = attr(o, names().h);
+  return h.is_none() ? nullptr : reinterpret_cast<const psflib_handle*>(h.cast<uintptr_t>());
+}
+
 Lib lib_of(py::handle o) {  // with the GIL
-  py::object h = o.attr("h");
-  return Lib{h.is_none() ? nullptr : reinterpret_cast<const psflib_handle*>(h.cast<uintptr_t>()),
-             o.attr("ncols").cast<int64_t>(), o.attr("M").cast<int64_t>(),
-             o.attr("device").cast<at::Device>()};
+  return Lib{handle_of(o), attr(o, names().ncols).cast<int64_t>(), attr(o, names().M).cast<int64_t>(),
+             attr(o, names().device).cast<at::Device>()};
 }
 
 bool is_float_on(const at::Tensor& t, const at::Device& d) {
@@ -163,18 +184,22 @@ py::object apply_batched(py::handle self, py::handle scenes, py::handle out, py:
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
-// A Python library object held by the graph (released with the GIL).
+// What a graph holds of a library: its handle object (psflib._Handle), whose handle is
+// read when it is used, and the library itself weakly.  Released with the GIL.
 struct LibRef : torch::CustomClassHolder {
-  PyObject* o;
-  explicit LibRef(py::handle h) : o(h.inc_ref().ptr()) {}
+  py::object handle, library;
+  Lib lib;  // when the forward pass ran
+  explicit LibRef(py::handle o)
+      : handle(attr(o, names().handle)), library(py::weakref(o)), lib(lib_of(o)) {}
   ~LibRef() override {
-    if (!Py_IsInitialized()) return;
+    if (!Py_IsInitialized()) {
+      handle.release();
+      library.release();
+      return;
+    }
     py::gil_scoped_acquire gil;
-    Py_DECREF(o);
-  }
-  Lib get() const {
-    py::gil_scoped_acquire gil;
-    return lib_of(o);
+    handle = py::object();
+    library = py::object();
   }
 };
 
@@ -191,20 +216,23 @@ at::Tensor product(const Lib& lib, bool adjoint, const at::Tensor& x, const char
 }
 
 struct Simulate : torch::autograd::Function<Simulate> {
-  static at::Tensor forward(AutogradContext* ctx, const at::Tensor& Z, c10::intrusive_ptr<LibRef> lib) {
-    ctx->saved_data["lib"] = c10::IValue::make_capsule(lib);
-    return product(lib->get(), false, Z.contiguous(), "scene");
+  static at::Tensor forward(AutogradContext* ctx, const at::Tensor& Z, c10::intrusive_ptr<LibRef> ref) {
+    ctx->saved_data["lib"] = c10::IValue::make_capsule(ref);
+    return product(ref->lib, false, Z.contiguous(), "scene");
   }
   static variable_list backward(AutogradContext* ctx, variable_list g) {
-    auto lib = c10::static_intrusive_pointer_cast<LibRef>(ctx->saved_data["lib"].toCapsule());
+    auto ref = c10::static_intrusive_pointer_cast<LibRef>(ctx->saved_data["lib"].toCapsule());
     const at::Tensor gS = g[0].contiguous().to(at::kFloat);
+    Lib lib = ref->lib;
     {
       py::gil_scoped_acquire gil;
-      const py::handle o(lib->o);
-      if (g_native && !py::handle(g_native)(o).cast<bool>())  // an adjoint put in its place since
+      const py::object o = ref->library();
+      if (!o.is_none() && g_native && !py::handle(g_native)(o).cast<bool>())
+        // another adjoint than the class's has been put in its place
         return {o.attr("apply_adjoint")(gS).cast<at::Tensor>(), at::Tensor()};
+      lib.h = handle_of(ref->handle);
     }
-    return {product(lib->get(), true, gS, "g"), at::Tensor()};
+    return {product(lib, true, gS, "g"), at::Tensor()};
   }
 };
 

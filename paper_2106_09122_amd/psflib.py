@@ -14,6 +14,7 @@ device pointers as integers.  :class:`Library` wraps them for torch tensors.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 
 import numpy as np
@@ -337,6 +338,28 @@ class Grouped:
 
 
 # ------------------------------------------------------- torch wrapper -----
+class _Handle:
+    """A C handle and the buffer it refers to, released with the last reference: a
+    :class:`Library`'s, or that of a graph whose backward pass needs them.  (A graph
+    that held the Library itself would be a cycle no collector sees when the library
+    holds one of its own images.)"""
+    __slots__ = ("h", "buf")
+
+    def __init__(self, h, buf):
+        self.h, self.buf = h, buf
+
+    def close(self):
+        if self.h:
+            destroy(self.h)
+            self.h = None
+
+    def __del__(self):
+        try:
+            self.close()
+        except Exception:
+            pass
+
+
 class Library:
     """A built PSF library on the current GPU.
 
@@ -364,8 +387,18 @@ class Library:
         self.device = cube.device
         self.buf = torch.empty(self.nbytes, dtype=torch.uint8, device=self.device)
         s = self._stream(stream)
-        self.h = build(self.desc, self.cube.data_ptr(), self.radii, self.buf.data_ptr(), self.nbytes, s)
+        self._handle = _Handle(build(self.desc, self.cube.data_ptr(), self.radii, self.buf.data_ptr(),
+                                     self.nbytes, s), self.buf)
         self.M, self.ncols = self.n * self.n, self.N * self.N
+
+    def _set_h(self, h):
+        if "_handle" in self.__dict__:
+            self._handle.h = h
+        else:
+            self._handle = _Handle(h, None)
+
+    #: the C handle, None after close()
+    h = property(operator.attrgetter("_handle.h"), _set_h)
 
     def _stream(self, stream):
         if stream is None:
@@ -410,11 +443,12 @@ class Library:
 
     def close(self):
         if getattr(self, "h", None):
-            destroy(self.h)
-            self.h = None
+            self._handle.close()
 
     def __del__(self):
+        # the handle goes with its last reference; a close() of a subclass is called
         try:
-            self.close()
+            if type(self).close is not Library.close:
+                self.close()
         except Exception:
             pass

@@ -143,3 +143,75 @@ def test_more_parameters_than_the_disk_has(fitting):
     torch, fit, lib, th, counts, var, K = fitting
     longer = torch.cat([th, torch.ones(1, dtype=torch.float64, device="cuda")])
     assert torch.equal(fit.render_disk(longer, lib.N, lib.S, RMAX), fit.render_disk(th, lib.N, lib.S, RMAX))
+
+
+def test_graph_keeps_the_library(fitting):
+    torch, fit, lib, th, counts, var, K = fitting
+    from paper_2106_09122_amd import psflib
+    d = synth.config_inputs(1)
+    Z = torch.rand(lib.ncols, device="cuda", requires_grad=True)
+    want = lib.apply_adjoint(torch.ones(lib.M, device="cuda"))
+    other = psflib.Library(torch.from_numpy(d["cube"]).cuda(), d["radii"], d["N"], d["S"])
+    S = fit.simulate(other, Z)
+    del other
+    gc.collect()
+    junk = [torch.full((lib.nbytes // 4,), 7.0, device="cuda") for _ in range(4)]  # would take freed memory
+    S.sum().backward()
+    assert torch.equal(Z.grad, want)
+    del junk
+
+
+def test_library_that_holds_a_graph_is_freed(fitting):
+    """An image of its own kept on the library: a cycle that ends with the last
+    outside reference."""
+    torch, fit, lib, th, counts, var, K = fitting
+    from paper_2106_09122_amd import psflib
+    d = synth.config_inputs(1)
+    Z = torch.rand(lib.ncols, device="cuda", requires_grad=True)
+    gc.collect()
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    other = psflib.Library(torch.from_numpy(d["cube"]).cuda(), d["radii"], d["N"], d["S"])
+    other.last = fit.simulate(other, Z)
+    gone = weakref.ref(other)
+    del other
+    gc.collect()
+    assert gone() is None
+    assert torch.cuda.memory_allocated() == before
+
+
+def test_library_closed_between_the_passes(fitting):
+    torch, fit, lib, th, counts, var, K = fitting
+    from paper_2106_09122_amd import psflib
+    Z = torch.rand(lib.ncols, device="cuda", requires_grad=True)
+    S = fit.simulate(lib, Z)
+    lib.close()
+    with pytest.raises(psflib.PsflibError) as e:
+        S.sum().backward()
+    assert e.value.status == psflib.ERR_INVALID_ARG
+    with pytest.raises(psflib.PsflibError):
+        lib.apply(Z.detach())
+
+
+def test_backward_on_another_thread_and_stream(fitting):
+    torch, fit, lib, th, counts, var, K = fitting
+    want = _step(fit, lib, th, counts, var, K)
+    t = th.clone().requires_grad_(True)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        L = fit.chi2(fit.simulate(lib, fit.render_disk(t, lib.N, lib.S, RMAX)), counts, var, K)
+    raised = []
+
+    def run():
+        try:
+            L.backward()
+        except BaseException as e:  # noqa: BLE001  (handed to the test)
+            raised.append(e)
+
+    th2 = threading.Thread(target=run)
+    th2.start()
+    th2.join()
+    assert not raised
+    torch.cuda.synchronize()
+    assert torch.equal(L.detach(), want[0]) and torch.equal(t.grad, want[1])
