@@ -279,7 +279,8 @@ namespace {
 // kernels).  Under capture the memory is allocated from the pool inside the
 // graph instead, so every graph owns its own.  A call that gives `keep` takes
 // more than that, or what would bring all streams' buffers over kKeptBytes, from
-// the pool and gives it back.
+// the pool and gives it back; so it does when there is no memory for the rounded
+// size of a buffer.
 constexpr size_t kKeptBytes = (size_t)2 << 30;
 struct StreamBuffer {
   int dev;
@@ -325,7 +326,9 @@ class CallScratch {
     if (e != hipSuccess) {
       p_ = nullptr;
       lock_.unlock();
-      return e;
+      if (keep == kKeepAll || e != hipErrorOutOfMemory) return e;
+      (void)hipGetLastError();
+      return from_pool(dev, bytes);
     }
     if (slot) {
       // the smaller buffer goes back to the pool after the work queued on s
