@@ -184,7 +184,7 @@ hipError_t launch_pair_cube(const float* cube, int K, int64_t M, float* pairs, h
   return hipGetLastError();
 }
 
-hipError_t launch_geometry(int N, double S, const double* h_radii, double* radii, int K, int interp,
+hipError_t launch_geometry(int N, double S, const double* h_radii, const double* radii, int K, int interp,
                            int oob, const float* pmax, bool want_exp, ColGeom* geo,
                            int64_t ncols_pad, int32_t* exps, hipStream_t s) {
   RadiiArg arg = {};
@@ -194,8 +194,6 @@ hipError_t launch_geometry(int N, double S, const double* h_radii, double* radii
     geometry_kernel<true><<<grid, 256, 0, s>>>(N, S, arg, nullptr, K, interp, oob, pmax,
                                                want_exp ? 1 : 0, geo, ncols_pad, exps);
   } else {
-    const hipError_t e = hipMemcpyAsync(radii, h_radii, (size_t)K * 8, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return e;
     geometry_kernel<false><<<grid, 256, 0, s>>>(N, S, arg, radii, K, interp, oob, pmax,
                                                 want_exp ? 1 : 0, geo, ncols_pad, exps);
   }

@@ -4,6 +4,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <list>
 #include <map>
 #include <mutex>
 #include <new>
@@ -272,9 +273,10 @@ namespace {
 // the process ends and grown on demand.  Calls on one stream run in order, so
 // every call on that stream (whatever its handle) can reuse the buffer, and
 // calls on different streams never share one (the per-thread default stream,
-// one handle for many streams, allocates from the pool).  The lock is held over the
-// call's launches, so a call from another host thread on the same stream
-// cannot slip its kernels in between them.  This adds nothing to the stream
+// one handle for many streams, allocates from the pool).  The buffer's lock is
+// held over the call's launches, so a call from another host thread on the same
+// stream cannot slip its kernels in between them; calls on other streams and
+// devices do not wait for it.  This adds nothing to the stream
 // per call (a stream-ordered free per call adds a marker: ~3 us between
 // kernels).  Under capture the memory is allocated from the pool inside the
 // graph instead, so every graph owns its own.  A call that gives `keep` takes
@@ -283,13 +285,16 @@ namespace {
 // size of a buffer.
 constexpr size_t kKeptBytes = (size_t)2 << 30;
 struct StreamBuffer {
-  int dev;
-  hipStream_t s;
-  void* p;
-  size_t bytes;
+  StreamBuffer(int d, hipStream_t st) : dev(d), s(st) {}
+  const int dev;
+  const hipStream_t s;
+  std::mutex mu;  // p and bytes, over a call's launches
+  void* p = nullptr;
+  size_t bytes = 0;
 };
-std::mutex g_sb_mu;
-std::vector<StreamBuffer> g_sb;
+std::mutex g_sb_mu;             // the two below; never held over a HIP call
+std::list<StreamBuffer> g_sb;   // entries stay where they are
+size_t g_sb_bytes = 0;          // of all buffers
 
 class CallScratch {
  public:
@@ -303,42 +308,38 @@ class CallScratch {
     if (e != hipSuccess) return e;
     if (cs != hipStreamCaptureStatusNone || s == hipStreamPerThread || bytes > keep)
       return from_pool(dev, bytes);
-    lock_ = std::unique_lock<std::mutex>(g_sb_mu);
-    StreamBuffer* slot = nullptr;
-    for (auto& sb : g_sb)
-      if (sb.dev == dev && sb.s == s) slot = &sb;
-    if (slot && slot->bytes >= bytes) {
-      p_ = slot->p;
+    StreamBuffer& sb = buffer_of(dev, s);
+    lock_ = std::unique_lock<std::mutex>(sb.mu);
+    if (sb.bytes >= bytes) {
+      p_ = sb.p;
       return hipSuccess;
     }
     size_t want = (size_t)1 << 20;  // grow in powers of two from 1 MiB
     while (want < bytes) want <<= 1;
-    if (keep != kKeepAll) {
-      size_t kept = want;
-      for (auto& sb : g_sb)
-        if (&sb != slot) kept += sb.bytes;
-      if (kept > kKeptBytes) {
-        lock_.unlock();
-        return from_pool(dev, bytes);
+    {
+      std::lock_guard<std::mutex> all(g_sb_mu);
+      if (keep != kKeepAll && g_sb_bytes - sb.bytes + want > kKeptBytes)
+        want = 0;
+      else
+        g_sb_bytes += want - sb.bytes;
+    }
+    if (want > 0) {
+      e = psflib::pool_alloc(&p_, want, dev, s);
+      if (e == hipSuccess) {
+        // the smaller buffer goes back to the pool after the work queued on s
+        if (sb.p) e = hipFreeAsync(sb.p, s);
+        sb.p = p_;
+        sb.bytes = want;
+        return e;
       }
-    }
-    e = psflib::pool_alloc(&p_, want, dev, s);
-    if (e != hipSuccess) {
       p_ = nullptr;
-      lock_.unlock();
-      if (keep == kKeepAll || e != hipErrorOutOfMemory) return e;
-      (void)hipGetLastError();
-      return from_pool(dev, bytes);
+      std::lock_guard<std::mutex> all(g_sb_mu);
+      g_sb_bytes -= want - sb.bytes;
     }
-    if (slot) {
-      // the smaller buffer goes back to the pool after the work queued on s
-      e = hipFreeAsync(slot->p, s);
-      slot->p = p_;
-      slot->bytes = want;
-    } else {
-      g_sb.push_back(StreamBuffer{dev, s, p_, want});
-    }
-    return e;
+    lock_.unlock();
+    if (want > 0 && (keep == kKeepAll || e != hipErrorOutOfMemory)) return e;
+    if (want > 0) (void)hipGetLastError();
+    return from_pool(dev, bytes);
   }
   void* ptr() const { return p_; }
   // after the call's launches
@@ -353,6 +354,12 @@ class CallScratch {
   ~CallScratch() { (void)release(); }
 
  private:
+  static StreamBuffer& buffer_of(int dev, hipStream_t s) {
+    std::lock_guard<std::mutex> all(g_sb_mu);
+    for (auto& sb : g_sb)
+      if (sb.dev == dev && sb.s == s) return sb;
+    return g_sb.emplace_back(dev, s);
+  }
   hipError_t from_pool(int dev, size_t bytes) {
     const hipError_t e = psflib::pool_alloc(&p_, bytes, dev, s_);
     if (e != hipSuccess) p_ = nullptr;
@@ -473,6 +480,12 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
   // pool was trimmed, as by a release on another stream: more than the second
   // pass saves.)
   constexpr size_t kKeep = (size_t)512 << 20;
+  if (K > psflib::kRadiiArg) {
+    // before the stream's buffer is taken: the copy from pageable memory may wait for
+    // the stream
+    e = hipMemcpyAsync(h->radii_dev, h->radii.data(), (size_t)K * 8, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return bail(e, "hipMemcpyAsync(radii)");
+  }
   size_t base_bytes = flux_orbit && orbit16 ? psflib::orbit_bases_bytes(desc->n, desc->N, cubic) : 0;
   if (tmp_bytes + base_bytes > kKeep) base_bytes = 0;
   e = tmp.acquire(dev, s, tmp_bytes + base_bytes, kKeep);

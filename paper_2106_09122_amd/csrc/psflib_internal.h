@@ -144,9 +144,8 @@ __device__ __forceinline__ void cubic_weights(double t, float w[4]) {
 hipError_t launch_cube_stats(const float* cube, int K, int64_t M, float* pmax, double* sums,
                              hipStream_t s);
 hipError_t launch_pair_cube(const float* cube, int K, int64_t M, float* pairs, hipStream_t s);
-// radii: device memory for K radii when K > kRadiiArg (h_radii must then stay
-// until the stream has passed this point), else not used
-hipError_t launch_geometry(int N, double S, const double* h_radii, double* radii, int K, int interp,
+// radii: the radii in device memory when K > kRadiiArg, else not used
+hipError_t launch_geometry(int N, double S, const double* h_radii, const double* radii, int K, int interp,
                            int oob, const float* pmax, bool want_exp, ColGeom* geo,
                            int64_t ncols_pad, int32_t* exps, hipStream_t s);
 // Cubic-spline rotation: coefficients of every sampled PSF padded by

@@ -23,7 +23,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["memory"])
+@pytest.mark.parametrize("what", ["memory", "streams"])
 def test_host_streams(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and "host_streams ok" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
