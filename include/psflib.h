@@ -98,9 +98,11 @@ typedef enum { PSFLIB_OOB_CLAMP = 0, PSFLIB_OOB_ZERO = 1 } psflib_oob;
  *             can write whole 16-byte groups: slot 32b + 8k + u holds the
  *             k-th quarter turn about the star of the u-th of the b-th eight
  *             base columns (one quadrant, and the centre of an odd scene,
- *             sorted by radial bracket), the slots left over no column; images
- *             above 8192 x 8192 or more than 8192 PSFs keep the natural order
- *             (slot j = column j).  The slot
+ *             sorted by radial bracket), the slots left over no column.  The
+ *             natural order (slot j = column j) where the sort's bounds are
+ *             exceeded: more than 8192 PSFs, or ceil(base columns / 1024) *
+ *             max(n_psf, 2) above 2^24 (e.g. a 4096 x 4096 scene with more
+ *             than 4096 PSFs).  The slot
  *             order is part of the library buffer (see psflib_library_bytes);
  *             psflib_get_columns reads columns by index whatever the order.
  *             Products accumulate in float32. */
