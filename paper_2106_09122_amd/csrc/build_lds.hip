@@ -388,11 +388,9 @@ template <bool BF16>
 __global__ __launch_bounds__(256) void pack16_kernel(const float* __restrict__ A32,
                                                      const ColGeom* __restrict__ geo,
                                                      int64_t M, int64_t ncols,
-                                                     u32x4* __restrict__ Mp, int64_t g0,
-                                                     int64_t col0) {
-  // groups g0 + blockIdx.y; column j of the float32 source at A32 + (j - col0) M
+                                                     u32x4* __restrict__ Mp) {
   const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2;
-  const int64_t grp = g0 + blockIdx.y;
+  const int64_t grp = blockIdx.y;
   if (i0 >= M) return;
   const bool pair = (M % 2) == 0;  // then i0 + 1 < M and the 8-byte loads are aligned
   float v[8][2];
@@ -404,7 +402,7 @@ __global__ __launch_bounds__(256) void pack16_kernel(const float* __restrict__ A
     ex[u] = 0;
     if (j < ncols) {
       ex[u] = geo[j].e;
-      const float* src = A32 + (j - col0) * M + i0;
+      const float* src = A32 + j * M + i0;
       if (pair) {
         typedef float f32x2 __attribute__((ext_vector_type(2)));
         const f32x2 t = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(src));
@@ -1033,7 +1031,7 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
                                                            int nt, int64_t nreps,
                                                            float* __restrict__ A,
                                                            double* __restrict__ part,
-    const float* __restrict__ colscale) {
+                                                           const float* __restrict__ colscale) {
   extern __shared__ float2 P2[];
   if ((int)blockIdx.x >= *nitems) return;  // uniform: surplus workgroups of the upper bound
   const int4 it = items[blockIdx.x];
@@ -1089,7 +1087,6 @@ __global__ __launch_bounds__(1024) void build_orbit_kernel(const float* __restri
 constexpr int kFpSpan = 46;                     // box rows or columns, at most
 constexpr int kFpStride = kFpSpan + 1;          // odd
 constexpr int kFpRegion = kFpSpan * kFpStride;  // floats per wave
-constexpr int kBoxMaxN = 8192;  // PSF side: pixel offsets n^2 and row-range sizes stay in int
 
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1203,7 +1200,7 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
                                                                OrbitGrid o, int n, int64_t M, int nt, int run, uint32_t total,
                                                                float* __restrict__ A,
                                                                double* __restrict__ part,
-    const float* __restrict__ colscale) {
+                                                               const float* __restrict__ colscale) {
   extern __shared__ float QS[];  // 16 regions of kFpRegion floats
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* Q = QS + wave * kFpRegion;
@@ -1219,46 +1216,46 @@ __global__ __launch_bounds__(1024) void build_orbit_box_kernel(const float* __re
     const OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, sp);
     double tsum = 0.0;
     for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
-    const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
-    if (g.k < 0) {  // identically zero orbit
-      orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
-                            lane, A, tsum);
-      continue;
-    }
-    const float* Pk = cube + (int64_t)g.k * M;
-    const float* Pk1 = (K > 1) ? Pk + M : nullptr;
-    const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
-    // the tile's pixels (from the first row and column that its blocks reach)
-    // and their box of bordered rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-    const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
-    const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
-    int rmin, rmax, cmin, cmax;
-    {
-      int r0, c0;
-      tap_origin(g, c, at, bt, r0, c0);
-      rmin = rmax = r0;
-      cmin = cmax = c0;
-#pragma unroll
-      for (int k = 1; k < 4; ++k) {
-        tap_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, r0, c0);
-        rmin = min(rmin, r0);
-        rmax = max(rmax, r0);
-        cmin = min(cmin, c0);
-        cmax = max(cmax, c0);
+      const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
+      if (g.k < 0) {  // identically zero orbit
+        orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
+                              lane, A, tsum);
+        continue;
       }
-    }
-    const int Rlo = max(rmin + 1, 0), Clo = max(cmin + 1, 0);
-    const int bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
-    const int bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
-    wave_lds_sync();  // the previous tile's reads are done
-    stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, wk0, wk1, lane);
-    wave_lds_sync();  // the box is staged
-    const int base = Rlo * kFpStride + Clo;
-    orbit_tile<VEC, MODE>(
-          [&](double ctux, double mstux, double stuy, double ctuy) {
-            return box_value(Q, ctux, mstux, stuy, ctuy, c, n, base);
-          },
-          g, c, n, o.N, M, a0, b0, lane, A, tsum);
+      const float* Pk = cube + (int64_t)g.k * M;
+      const float* Pk1 = (K > 1) ? Pk + M : nullptr;
+      const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
+      // the tile's pixels (from the first row and column that its blocks reach)
+      // and their box of bordered rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
+      const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
+      const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
+      int rmin, rmax, cmin, cmax;
+      {
+        int r0, c0;
+        tap_origin(g, c, at, bt, r0, c0);
+        rmin = rmax = r0;
+        cmin = cmax = c0;
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+          tap_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, r0, c0);
+          rmin = min(rmin, r0);
+          rmax = max(rmax, r0);
+          cmin = min(cmin, c0);
+          cmax = max(cmax, c0);
+        }
+      }
+      const int Rlo = max(rmin + 1, 0), Clo = max(cmin + 1, 0);
+      const int bh = min(max(min(rmax + 2, n + 1) - Rlo + 1, 0), kFpSpan);
+      const int bw = min(max(min(cmax + 2, n + 1) - Clo + 1, 0), kFpSpan);
+      wave_lds_sync();  // the previous tile's reads are done
+      stage_box<false>(Q, Pk, Pk1, nullptr, n, 0, Rlo, Clo, bh, bw, wk0, wk1, lane);
+      wave_lds_sync();  // the box is staged
+      const int base = Rlo * kFpStride + Clo;
+      orbit_tile<VEC, MODE>(
+            [&](double ctux, double mstux, double stuy, double ctuy) {
+              return box_value(Q, ctux, mstux, stuy, ctuy, c, n, base);
+            },
+            g, c, n, o.N, M, a0, b0, lane, A, tsum);
     }
     tsum = wave_sum_f64(tsum);
     if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
@@ -1317,7 +1314,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_kernel(const float* __rest
                                                              int rpr, int64_t nreps,
                                                              uint16_t* __restrict__ Mh,
                                                              double* __restrict__ part,
-    const float* __restrict__ colscale) {
+                                                             const float* __restrict__ colscale) {
   constexpr int TA = 8, TB = 32, TP = TB + 1;
   constexpr int TILE = 2 * TA * TP * 8;  // uint16 per buffer
   extern __shared__ float2 P2[];  // bordered pair, then the two tile buffers
@@ -1467,7 +1464,7 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
                                                                  OrbitGrid o, int n, int64_t M, int nt, int run, uint32_t total,
                                                                  float* __restrict__ A,
                                                                  double* __restrict__ part,
-    const float* __restrict__ colscale) {
+                                                                 const float* __restrict__ colscale) {
   extern __shared__ float QS[];  // 16 regions of kCbRegion floats
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* Q = QS + wave * kCbRegion;
@@ -1484,62 +1481,62 @@ __global__ __launch_bounds__(1024) void build_cubic_orbit_kernel(const float2* _
     const OrbitCol g = load_orbit_col<MODE>(reps, geo, colscale, sp);
     double tsum = 0.0;
     for (int tile = r * run; tile < min((r + 1) * run, ntiles); ++tile) {
-    const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
-    if (g.k < 0) {  // identically zero orbit
-      orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
-                            lane, A, tsum);
-      continue;
-    }
-    const float2* src = pairs + (int64_t)g.k * Np * Np;
-    const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
-    // the tile's pixels (from the first row and column that its blocks reach)
-    // and their box of padded rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
-    const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
-    const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
-    int rmin, rmax, cmin, cmax;
-    {
-      int r0, c0;
-      cubic_origin(g, c, at, bt, Np, r0, c0);
-      rmin = rmax = r0;
-      cmin = cmax = c0;
-#pragma unroll
-      for (int k = 1; k < 4; ++k) {
-        cubic_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, Np, r0, c0);
-        rmin = min(rmin, r0);
-        rmax = max(rmax, r0);
-        cmin = min(cmin, c0);
-        cmax = max(cmax, c0);
+      const int a0 = 32 * (tile / nt), b0 = 32 * (tile % nt);
+      if (g.k < 0) {  // identically zero orbit
+        orbit_tile<VEC, MODE>([](double, double, double, double) { return 0.0f; }, g, c, n, o.N, M, a0, b0,
+                              lane, A, tsum);
+        continue;
       }
-    }
-    const int Rlo = rmin - 1, Clo = cmin - 1;
-    const int bh = min(rmax - rmin + 4, kCbSpan), bw = min(cmax - cmin + 4, kCbSpan);
-    wave_lds_sync();  // the previous tile's reads are done
-    stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, wk0, wk1, lane);
-    wave_lds_sync();  // the box is staged
-    orbit_tile<VEC, MODE>(
-          [&](double ctux, double mstux, double stuy, double ctuy) {
-#pragma clang fp contract(off)
-            const double rowf = c + (mstux + ctuy) + pad;
-            const double colf = c + (ctux + stuy) + pad;
-            const double r0f = floor(rowf), c0f = floor(colf);
-            const int r0 = clamp_origin((int)r0f, Np), c0 = clamp_origin((int)c0f, Np);
-            float wy[4], wx[4];
-            cubic_weights(rowf - r0f, wy);
-            cubic_weights(colf - c0f, wx);
-            const float* tp = Q + (r0 - 1 - Rlo) * kCbStride + (c0 - 1 - Clo);
-            float V = 0.0f;
+      const float2* src = pairs + (int64_t)g.k * Np * Np;
+      const float wk0 = (float)(1.0 - g.w), wk1 = (float)g.w;
+      // the tile's pixels (from the first row and column that its blocks reach)
+      // and their box of padded rows [Rlo, Rlo + bh) and columns [Clo, Clo + bw)
+      const int at = base_only(MODE) ? a0 : block_start<VEC>(a0, n), bt = base_only(MODE) ? b0 : block_start<VEC>(b0, n);
+      const int ae = (a0 + 32 < n) ? a0 + 32 : n, be = (b0 + 32 < n) ? b0 + 32 : n;
+      int rmin, rmax, cmin, cmax;
+      {
+        int r0, c0;
+        cubic_origin(g, c, at, bt, Np, r0, c0);
+        rmin = rmax = r0;
+        cmin = cmax = c0;
 #pragma unroll
-            for (int dr = 0; dr < 4; ++dr) {
-              const float* tr = tp + dr * kCbStride;
-              float v = wx[0] * tr[0];
-              v = fmaf(wx[1], tr[1], v);
-              v = fmaf(wx[2], tr[2], v);
-              v = fmaf(wx[3], tr[3], v);
-              V = fmaf(wy[dr], v, V);
-            }
-            return V;
-          },
-          g, c, n, o.N, M, a0, b0, lane, A, tsum);
+        for (int k = 1; k < 4; ++k) {
+          cubic_origin(g, c, (k & 1) ? ae - 1 : at, (k & 2) ? be - 1 : bt, Np, r0, c0);
+          rmin = min(rmin, r0);
+          rmax = max(rmax, r0);
+          cmin = min(cmin, c0);
+          cmax = max(cmax, c0);
+        }
+      }
+      const int Rlo = rmin - 1, Clo = cmin - 1;
+      const int bh = min(rmax - rmin + 4, kCbSpan), bw = min(cmax - cmin + 4, kCbSpan);
+      wave_lds_sync();  // the previous tile's reads are done
+      stage_box<true>(Q, nullptr, nullptr, src, n, Np, Rlo, Clo, bh, bw, wk0, wk1, lane);
+      wave_lds_sync();  // the box is staged
+      orbit_tile<VEC, MODE>(
+            [&](double ctux, double mstux, double stuy, double ctuy) {
+#pragma clang fp contract(off)
+              const double rowf = c + (mstux + ctuy) + pad;
+              const double colf = c + (ctux + stuy) + pad;
+              const double r0f = floor(rowf), c0f = floor(colf);
+              const int r0 = clamp_origin((int)r0f, Np), c0 = clamp_origin((int)c0f, Np);
+              float wy[4], wx[4];
+              cubic_weights(rowf - r0f, wy);
+              cubic_weights(colf - c0f, wx);
+              const float* tp = Q + (r0 - 1 - Rlo) * kCbStride + (c0 - 1 - Clo);
+              float V = 0.0f;
+#pragma unroll
+              for (int dr = 0; dr < 4; ++dr) {
+                const float* tr = tp + dr * kCbStride;
+                float v = wx[0] * tr[0];
+                v = fmaf(wx[1], tr[1], v);
+                v = fmaf(wx[2], tr[2], v);
+                v = fmaf(wx[3], tr[3], v);
+                V = fmaf(wy[dr], v, V);
+              }
+              return V;
+            },
+            g, c, n, o.N, M, a0, b0, lane, A, tsum);
     }
     tsum = wave_sum_f64(tsum);
     if (lane == 0) part[(int64_t)r * o.nreps + sp] = tsum;
@@ -1666,7 +1663,7 @@ __global__ __launch_bounds__(1024) void build_orbit16_box_kernel(const float* __
                                                                  int rpr, int64_t nreps,
                                                                  uint16_t* __restrict__ Mh,
                                                                  double* __restrict__ part,
-    const float* __restrict__ colscale) {
+                                                                 const float* __restrict__ colscale) {
   constexpr int TA = CUBIC ? 4 : 8, TB = 32, TP = TB + 1;
   constexpr int CPL = (TA * TB) / 64;      // pixels of a tile row per lane
   constexpr int LPR = TB / CPL;            // lanes per tile row
@@ -1821,14 +1818,12 @@ static bool pair_fits_lds(int n) {
   return (size_t)(n + 2) * (n + 2) * sizeof(float2) <= (size_t)kLdsBuildMaxBytes;
 }
 
-static bool orbit_sort_fits(int K, int N);
-
 bool build_lds_supported(int n, int K, int N) {
-  // the bordered pair fits the LDS whole, or (up to kBoxMaxN) the orbit
-  // builds stage a box of it per tile; the bucket histograms (8 B per bucket)
-  // must fit the sort kernels' LDS
+  // the bordered pair fits the LDS whole, or the orbit builds stage a box of it per
+  // tile (sides are at most 8192: pixel offsets stay in int); the bucket histograms (8
+  // B per bucket) must fit the sort kernels' LDS
   if (K > 8192) return false;
-  return pair_fits_lds(n) || (n <= kBoxMaxN && orbit_sort_fits(K, N));
+  return pair_fits_lds(n) || build_orbit_supported(K, N);
 }
 
 static int nbuckets(int K) { return ((K > 1) ? K - 1 : 1) + 1; }
@@ -1842,8 +1837,6 @@ size_t bucket_scratch_bytes(int K, int64_t ncols) {
   b += ((size_t)ncols * 4 + 255) & ~(size_t)255;            // order
   return b;
 }
-
-
 
 hipError_t launch_bucket_sort(const ColGeom* geo, int64_t ncols, int K, void* scratch,
                               BucketPlan* plan, hipStream_t s) {
@@ -1877,27 +1870,18 @@ hipError_t launch_bucket_sort(const ColGeom* geo, int64_t ncols, int K, void* sc
 
 hipError_t launch_pack16(int storage, const float* A32, const ColGeom* geo, int64_t M,
                          int64_t ncols, int64_t ncols_pad, void* lib, hipStream_t s) {
-  return launch_pack16_range(storage, A32, 0, 0, ncols_pad / 8, geo, M, ncols, lib, s);
-}
-
-hipError_t launch_pack16_range(int storage, const float* A32, int64_t col0, int64_t g0, int64_t g1,
-                               const ColGeom* geo, int64_t M, int64_t ncols, void* lib,
-                               hipStream_t s) {
-  if (g1 <= g0) return hipSuccess;
-  const dim3 pgrid((unsigned)((M + 511) / 512), (unsigned)(g1 - g0));
+  const dim3 pgrid((unsigned)((M + 511) / 512), (unsigned)(ncols_pad / 8));
   u32x4* Mp = reinterpret_cast<u32x4*>(lib);
   if (storage == PSFLIB_BF16_POW2)
-    pack16_kernel<true><<<pgrid, 256, 0, s>>>(A32, geo, M, ncols, Mp, g0, col0);
+    pack16_kernel<true><<<pgrid, 256, 0, s>>>(A32, geo, M, ncols, Mp);
   else
-    pack16_kernel<false><<<pgrid, 256, 0, s>>>(A32, geo, M, ncols, Mp, g0, col0);
+    pack16_kernel<false><<<pgrid, 256, 0, s>>>(A32, geo, M, ncols, Mp);
   return hipGetLastError();
 }
 
-static bool build_orbit_supported(int n, int K, int N);
-
 hipError_t launch_build_lds(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
                             float* A32, double* tau, void* scratch, hipStream_t s) {
-  if (build_orbit_supported(n, K, N))
+  if (build_orbit_supported(K, N))
     return launch_build_orbit(cube, K, geo, n, N, M, A32, tau, scratch, kPlain, nullptr, s);
   if (!pair_fits_lds(n)) return hipErrorInvalidValue;  // larger pairs: the orbit builds only
   const int64_t ncols = (int64_t)N * N;
@@ -1972,7 +1956,7 @@ size_t build_orbit_scratch_bytes(int K, int N, int n) {
          al256((size_t)pl.o.nreps * 4) + al256((size_t)pl.nt * pl.nt * pl.o.nreps * 8);
 }
 
-static bool orbit_sort_fits(int K, int N) {
+bool build_orbit_supported(int K, int N) {
   const OrbitGrid o = orbit_grid(N);
   const int64_t nblk = (o.nreps + kSortBlock - 1) / kSortBlock;
   return K <= kLdsMaxBuckets - 1 && nblk * nbuckets(K) <= ((int64_t)1 << 24) &&
@@ -2097,15 +2081,7 @@ hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int
   return orbit_finish(pl, pl.nt * pl.nt, mode, K, geo, fx, tau, s);
 }
 
-// the two passes of a flux-preserving build (see the modes above)
-bool build_orbit_flux_supported(int n, int K, int N) { return K <= 8192 && build_orbit_supported(n, K, N); }
-
 // cubic-spline orbit build from staged boxes of the padded coefficient pairs
-bool build_cubic_orbit_supported(int n, int K, int N) {
-  return K <= 8192 && n <= kBoxMaxN && orbit_sort_fits(K, N) &&
-         (size_t)16 * kCbRegion * sizeof(float) <= (size_t)kLdsBuildMaxBytes;
-}
-
 hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int n, int N, int64_t M,
                                     float* A32, double* tau, void* scratch, int mode,
                                     const OrbitFlux* fx, hipStream_t s) {
@@ -2162,11 +2138,9 @@ static size_t orbit16_box_lds_bytes(bool cubic) {
 
 static bool orbit16_pair_fits(int n) { return orbit16_lds_bytes(n) <= (size_t)kLdsBuildMaxBytes; }
 
-// the pair in LDS with the unit tiles, or (up to kBoxMaxN) staged boxes
-bool build_orbit16_supported(int n, int K, int N) {
-  static_assert((size_t)16 * kFpRegion * sizeof(float) + (size_t)2 * (2 * 8 * 33 * 16) <= kLdsBuildMaxBytes, "");
-  return orbit_sort_fits(K, N) && (orbit16_pair_fits(n) || n <= kBoxMaxN);
-}
+static_assert((size_t)16 * kFpRegion * sizeof(float) + (size_t)2 * (2 * 8 * 33 * 16) <= kLdsBuildMaxBytes &&
+              (size_t)16 * kCbRegion * sizeof(float) + (size_t)2 * (2 * 4 * 33 * 16) <= kLdsBuildMaxBytes,
+              "the boxes and unit tiles fit the LDS");
 
 static hipError_t orbit16_end(const OrbitPlan& pl, int64_t M, const ColGeom* geo, const Orbit16Out& out,
                               hipStream_t s) {
@@ -2219,14 +2193,8 @@ size_t orbit_bases_bytes(int n, int N, bool cubic) {
   return bytes <= most ? bytes : 0;
 }
 
-// float32: the pair in LDS, or (up to kBoxMaxN) a staged box per tile
-static bool build_orbit_supported(int n, int K, int N) {
-  return (pair_fits_lds(n) || n <= kBoxMaxN) && orbit_sort_fits(K, N);
-}
-
 size_t build_lds_scratch_bytes(int K, int N, int n) {
-  return build_orbit_supported(n, K, N) ? build_orbit_scratch_bytes(K, N, n)
-                                        : bucket_scratch_bytes(K, (int64_t)N * N);
+  return build_orbit_supported(K, N) ? build_orbit_scratch_bytes(K, N, n) : bucket_scratch_bytes(K, (int64_t)N * N);
 }
 
 hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* geo, int n, int N,
@@ -2273,10 +2241,6 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* 
   return orbit16_end(pl, M, geo, out, s);
 }
 
-bool build_cubic_orbit16_supported(int n, int K, int N) {
-  return build_cubic_orbit_supported(n, K, N) && orbit16_box_lds_bytes(true) <= (size_t)kLdsBuildMaxBytes;
-}
-
 hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, ColGeom* geo, int n,
                                       int N, int64_t M, const Orbit16Out& out, void* scratch,
                                       const OrbitFlux* fx, hipStream_t s) {
@@ -2303,6 +2267,5 @@ hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, Co
   if (e != hipSuccess) return e;
   return orbit16_end(pl, M, geo, out, s);
 }
-
 
 }  // namespace psflib

@@ -437,8 +437,8 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
   // (bracket or column counts beyond the sort's bounds).
   const bool cubic = desc->rotate == PSFLIB_ROTATE_CUBIC;
   const bool flux = desc->flux == PSFLIB_FLUX_PRESERVE;
-  const bool lds = cubic ? psflib::build_cubic_orbit_supported(desc->n, K, desc->N)
-                         : psflib::build_lds_supported(desc->n, K, desc->N);
+  const bool orbit = psflib::build_orbit_supported(K, desc->N);
+  const bool lds = cubic ? orbit : psflib::build_lds_supported(desc->n, K, desc->N);
   // Flux-preserving orbit builds take two passes (the plain build's column
   // sums, then the build with each column scaled as it is stored) instead of
   // rewriting the library.  16-bit libraries are written directly in bracket
@@ -446,16 +446,12 @@ psflib_status psflib_build(const psflib_desc* desc, const float* d_cube, const d
   // any side); what the orbits cannot serve goes through float32 columns and a
   // packing pass where the rescale follows or the pair fits the LDS, in natural
   // order.
-  const bool flux_orbit =
-      flux && lds && (cubic || psflib::build_orbit_flux_supported(desc->n, K, desc->N));
-  const bool plain16 = storage != PSFLIB_FP32 && lds && (!flux || flux_orbit);
-  const bool orbit16 = plain16 && (cubic ? psflib::build_cubic_orbit16_supported(desc->n, K, desc->N)
-                                         : psflib::build_orbit16_supported(desc->n, K, desc->N));
+  const bool flux_orbit = flux && orbit;
+  const bool orbit16 = storage != PSFLIB_FP32 && orbit;
   const bool stage32 = storage != PSFLIB_FP32 && (lds || flux) && !orbit16;
   const size_t spline_bytes = cubic ? align256(psflib::spline_scratch_bytes(K, desc->n)) : 0;
   const size_t path_bytes =
-      spline_bytes + align256(orbit16 || flux_orbit ? psflib::build_orbit_scratch_bytes(K, desc->N, desc->n)
-                              : cubic && lds ? psflib::build_orbit_scratch_bytes(K, desc->N, desc->n)
+      spline_bytes + align256(orbit    ? psflib::build_orbit_scratch_bytes(K, desc->N, desc->n)
                               : lds    ? psflib::build_lds_scratch_bytes(K, desc->N, desc->n)
                               : cubic  ? 0
                                        : (size_t)((K > 1) ? (K - 1) : 1) * (size_t)L.M * 8);

@@ -177,14 +177,14 @@ size_t orbit_bases_bytes(int n, int N, bool cubic);
 // Modes of the float32 orbit builds: plain; the first pass; the second pass.
 // The 16-bit orbit builds are the second pass when fx is given.
 constexpr int kOrbitPlain = 0, kOrbitSumsOnly = 1, kOrbitScaled = 2;
-bool build_orbit_flux_supported(int n, int K, int N);
+// scenes and PSF counts that the orbits' sort takes (images of any size)
+bool build_orbit_supported(int K, int N);
 hipError_t launch_build_orbit(const float* cube, int K, ColGeom* geo, int n, int N, int64_t M,
                               float* A32, double* tau, void* scratch, int mode,
                               const OrbitFlux* fx, hipStream_t s);
 // Cubic build by quarter-turn orbits, the taps read from a box of the padded
 // coefficient pair staged per tile in LDS (float32 columns); scratch of
 // build_orbit_scratch_bytes(K, N, n) bytes.
-bool build_cubic_orbit_supported(int n, int K, int N);
 hipError_t launch_build_cubic_orbit(const float* pairs, int K, ColGeom* geo, int n, int N, int64_t M,
                                     float* A32, double* tau, void* scratch, int mode,
                                     const OrbitFlux* fx, hipStream_t s);
@@ -197,7 +197,6 @@ struct Orbit16Out {
 };
 // 16-bit cubic storage built by the same orbits, slots as
 // launch_build_orbit16's; scratch of build_orbit_scratch_bytes(K, N, n) bytes.
-bool build_cubic_orbit16_supported(int n, int K, int N);
 hipError_t launch_build_cubic_orbit16(int storage, const float* pairs, int K, ColGeom* geo, int n,
                                       int N, int64_t M, const Orbit16Out& out, void* scratch,
                                       const OrbitFlux* fx, hipStream_t s);
@@ -230,7 +229,6 @@ hipError_t launch_build_lds(const float* cube, int K, ColGeom* geo, int n, int N
 // slot 32 (s/8) + 8 k + s%8 holds member k of the s-th base column in
 // bracket order, the slots left over none (perm, slot_of, eslot written here);
 // column sums in tau.
-bool build_orbit16_supported(int n, int K, int N);
 size_t build_orbit_scratch_bytes(int K, int N, int n);
 hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* geo, int n, int N,
                                 int64_t M, const Orbit16Out& out, void* scratch, const OrbitFlux* fx,
@@ -238,10 +236,6 @@ hipError_t launch_build_orbit16(int storage, const float* cube, int K, ColGeom* 
 // 16-bit storage from float32 columns with the exponents in geo
 hipError_t launch_pack16(int storage, const float* A32, const ColGeom* geo, int64_t M,
                          int64_t ncols, int64_t ncols_pad, void* lib, hipStream_t s);
-// the same for groups [g0, g1), column j of the source at A32 + (j - col0) M
-hipError_t launch_pack16_range(int storage, const float* A32, int64_t col0, int64_t g0, int64_t g1,
-                               const ColGeom* geo, int64_t M, int64_t ncols, void* lib,
-                               hipStream_t s);
 // Flux-preserving rescale of float32 columns: sums[k] = sum(P_k) (float64),
 // column j scaled by t_j / tau_j, tau_j recomputed; with want_exp the 16-bit
 // exponents (geo[j].e and exps[j]) follow the rescaled bound.
