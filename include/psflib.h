@@ -118,10 +118,11 @@ typedef enum { PSFLIB_FP32 = 0, PSFLIB_BF16_POW2 = 1, PSFLIB_FP16_POW2 = 2 } psf
  *            PSF Q, neighbours outside the n x n frame counting as zero.
  *  CUBIC     the cubic B-spline interpolating Q extended by zeros (the
  *            interpolation order the paper's rotate() uses by default): the
- *            spline coefficients of Q padded by 12 zero pixels per side (exact
- *            recursive filter, mirror boundary at the padded edge), sampled
- *            with the 4 x 4 cubic B-spline weights; coefficients beyond the
- *            padded array count as zero.  Entries can be slightly negative
+ *            spline coefficients of Q padded by 12 zero pixels per side
+ *            (recursive filter in float64, mirror boundary at the padded edge;
+ *            samples more than 32 away, with weights below 5e-19, are left
+ *            out), sampled with the 4 x 4 cubic B-spline weights; coefficients
+ *            beyond the padded array count as zero.  Entries can be slightly negative
  *            (spline overshoot); the 16-bit exponent bound then uses the
  *            largest |coefficient| of each sampled PSF in place of its largest
  *            value. */

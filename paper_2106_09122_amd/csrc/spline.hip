@@ -30,10 +30,14 @@ constexpr double kPole = -0.26794919243112270;  // sqrt(3) - 2
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// The recursions forget geometrically (|z|^kTail = 5e-19, below the float64
-// rounding of the terms kept), so a line is cut into segments of kSeg samples,
-// one thread each: the causal recursion starts at zero kTail samples before the
-// segment and runs kTail past it, the anticausal one back from there.  A whole
+// The recursions forget geometrically (|z|^kTail = 5e-19), so a line is cut into
+// segments of kSeg samples, one thread each: the causal recursion starts at zero kTail
+// samples before the segment and runs kTail past it, the anticausal one back from
+// there.  What is dropped is a few 5e-19 of the line's samples more than kTail away:
+// below the float64 rounding of the terms kept where the line's contrast is moderate,
+// 5e-11 of the faint coefficients where it is 1e-10 (a coronagraph's), under the
+// float32 rounding that follows up to 1e-13 (at 1e-14 3e-7); zeros more than kTail
+// samples from the nearest other sample stay zero.  A whole
 // line per thread (one chain of 4 Np dependent steps through LDS) took 74 us for
 // 51 PSFs of 101^2 with the pairs and the maxima in passes of their own, all
 // latency; the segments, nine loads of a cached sample per sample, take 21 us.
