@@ -14,12 +14,12 @@
 // blocks and scene blocks: each operand tile is then fetched from HBM once
 // per XCD and re-read from that XCD's L2.  When the tile grid is too small to
 // fill the GPU, K is split across workgroups and a second kernel adds the
-// slices in a fixed order.
+// slices in a fixed order: eight at a time in float32 pairs, those in float64.
 //
 // FP32: each wave computes 64 image rows x 64 scenes (32 for batches of at
 // most 32) on its own, streaming library rows from HBM straight into
 // registers and pre-arranged scene fragments from L2, four groups of 8
-// columns ahead; accumulation is blocked in two levels so float32 rounding
+// columns ahead; accumulation is blocked in three levels so float32 rounding
 // chains stay short.
 //
 // 16-bit, up to 256 scenes: a workgroup of 4 waves computes a 256 x TN tile
@@ -94,6 +94,7 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t w, int64_t T) {
 // of four MFMA steps.
 constexpr int kF32Ring = 4;    // 8-column groups in flight per wave
 constexpr int kF32Block = 16;  // groups per inner accumulation block (a multiple of kF32Ring)
+constexpr int kF32Run = 16;    // blocks per accumulation in registers
 
 template <bool VEC>
 __global__ __launch_bounds__(256) void pack_f32_scenes_kernel(const float* __restrict__ Z,
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(256) void pack_f32_scenes_kernel(const float* __res
 
 // A workgroup is 4 independent waves, each computing 64 image rows x 32*NB
 // scenes with v_mfma_f32_32x32x2f32.  Nothing is shared between waves, so
-// there is no LDS and no barrier: each wave streams its library rows straight
+// there is no barrier, and no LDS but for sums: each wave streams its library rows straight
 // from HBM into registers and its scene fragments from L2, kF32Ring groups
 // of 8 columns ahead of use.
 //
@@ -135,9 +136,11 @@ __global__ __launch_bounds__(256) void pack_f32_scenes_kernel(const float* __res
 // accumulation blocks with no bounds tests.  Rows past the image read the
 // next column (finite values, never stored) or zero.
 //
-// Accumulation is blocked in two levels (kF32Block groups, then the slice)
-// so float32 rounding chains stay short; split-K slices are added by
-// reduce_splits_kernel in a fixed order.
+// Accumulation is blocked in three levels (kF32Block groups, kF32Run blocks, then
+// the slice) so float32 rounding chains stay short whatever the number of slices;
+// the third level's sums are in LDS, each lane's its own, for slices of more than
+// a run only (LONG).  (128^2, 256 scenes, one slice of 128 blocks: root mean square error
+// 1.7e-7 with two levels.)  Split-K slices are added by reduce_splits_kernel.
 //
 // NT: library loads carry the non-temporal hint, for grids with one scene
 // tile, where no other workgroup reads the same library rows.
@@ -145,12 +148,13 @@ __global__ __launch_bounds__(256) void pack_f32_scenes_kernel(const float* __res
 // The row pairs of images with an odd number of pixels start at any float: buffer
 // loads need no more than that, and bounds are checked for each of the two (127^2
 // PSFs, 127^2 scene, 64 scenes: 300 us, 363 with two 4-byte loads).
-template <int NB, bool NT>
+template <int NB, bool NT, bool LONG>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_f32_kernel(
     const float* __restrict__ A, const f32x4* __restrict__ Zp, float* __restrict__ out, int64_t M,
     int64_t K, int64_t B, int64_t SB, int64_t mblocks, int64_t nblocks, int64_t splits,
     int64_t gper) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
+  extern __shared__ f32x4 runs[];  // LONG: [4 waves][2][NB][4][64 lanes]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t tile = xcd_tile(blockIdx.x, mblocks * nblocks * splits);
@@ -204,26 +208,63 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_f32_kernel(
 #pragma unroll
     for (int r = 0; r < kF32Ring; ++r) issue(g0 + r, r);
   }
-  for (int blk = 0; blk < nblk; ++blk) {
-    const int gb = g0 + blk * kF32Block;
+  // LONG: the sums of the runs so far, in the lane's own place
+  auto run_sum = [&](int t, int q, int r4) -> f32x4& {
+    return runs[((wave * 2 + t) * NB + q) * 256 + r4 * 64 + lane];
+  };
+  auto quad = [&](int t, int q, int r4) {
+    const f32x16& v = tot[t][q];
+    return (f32x4){v[4 * r4], v[4 * r4 + 1], v[4 * r4 + 2], v[4 * r4 + 3]};
+  };
+  for (int blk = 0; blk < nblk;) {
+    const int end = LONG && blk + kF32Run < nblk ? blk + kF32Run : nblk;
+    const bool first = blk == 0;
+    for (; blk < end; ++blk) {
+      const int gb = g0 + blk * kF32Block;
 #pragma unroll
-    for (int j = 0; j < kF32Block; ++j) {
-      const int slot = j % kF32Ring;
+      for (int j = 0; j < kF32Block; ++j) {
+        const int slot = j % kF32Ring;
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int q = 0; q < NB; ++q)
+          for (int q = 0; q < NB; ++q)
 #pragma unroll
-          for (int t = 0; t < 2; ++t)
-            acc[t][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[slot][s][t], rb[slot][q][s],
-                                                            (j == 0 && s == 0) ? zero16 : acc[t][q],
-                                                            0, 0, 0);
-      issue(gb + j + kF32Ring, slot);
+            for (int t = 0; t < 2; ++t)
+              acc[t][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(ra[slot][s][t], rb[slot][q][s],
+                                                              (j == 0 && s == 0) ? zero16 : acc[t][q],
+                                                              0, 0, 0);
+        issue(gb + j + kF32Ring, slot);
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) tot[t][q] += acc[t][q];
     }
+    if constexpr (LONG) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            f32x4 v = quad(t, q, r4);
+            if (!first) v += run_sum(t, q, r4);
+            run_sum(t, q, r4) = v;
+          }
+          tot[t][q] = zero16;
+          __builtin_amdgcn_sched_barrier(0);  // few of them in registers at a time
+        }
+    }
+  }
+  if constexpr (LONG) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int q = 0; q < NB; ++q) tot[t][q] += acc[t][q];
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tot[t][q][4 * r4 + e] = run_sum(t, q, r4)[e];
   }
 
   // lane holds scene column l % 32 and MFMA rows 8(r/4) + 4h + r%4, i.e. image
@@ -1100,12 +1141,19 @@ static GemmPlan plan_gemm(int storage, int64_t M, int64_t ncols, int64_t ncols_p
 static hipError_t launch_gemm_f32(bool two, bool nt, unsigned grid, const float* A, const f32x4* Zp,
                                   float* dst, int64_t M, int64_t K, int64_t B, int64_t SB,
                                   const GemmPlan& p, hipStream_t s) {
-  auto launch = [&](auto kern) {
-    kern<<<grid, kGemmThreads, 0, s>>>(A, Zp, dst, M, K, B, SB, p.mblocks, p.nblocks, p.splits, p.per);
+  auto launch = [&](auto nb, auto ntl, auto lng) {
+    constexpr int NB = decltype(nb)::value;
+    constexpr bool LONG = decltype(lng)::value;
+    const size_t lds = LONG ? (size_t)kGemmThreads * 2 * NB * 64 : 0;
+    gemm_f32_kernel<NB, decltype(ntl)::value, LONG><<<grid, kGemmThreads, lds, s>>>(
+        A, Zp, dst, M, K, B, SB, p.mblocks, p.nblocks, p.splits, p.per);
     return hipGetLastError();
   };
-  if (two) return nt ? launch(gemm_f32_kernel<2, true>) : launch(gemm_f32_kernel<2, false>);
-  return nt ? launch(gemm_f32_kernel<1, true>) : launch(gemm_f32_kernel<1, false>);
+  auto pick = [&](auto nb, auto ntl) {
+    return p.per > kF32Block * kF32Run ? launch(nb, ntl, std::true_type()) : launch(nb, ntl, std::false_type());
+  };
+  auto blocks = [&](auto nb) { return nt ? pick(nb, std::true_type()) : pick(nb, std::false_type()); };
+  return two ? blocks(std::integral_constant<int, 2>()) : blocks(std::integral_constant<int, 1>());
 }
 
 template <bool BF16, int TN, bool NT>

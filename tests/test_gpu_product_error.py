@@ -48,3 +48,23 @@ def test_matvec_chunks(n, N):
     print("matvec rounding", n, N, err / UNIT, flush=True)
     assert err <= UNIT
     lib.close()
+
+
+# Slices of many blocks of 128 columns (wide batches, whose tiles fill the GPU): the
+# rounding of a chain of k near equal non-negative terms is 0.42 sqrt(k / 3) of a unit
+# in the mean, for 128 blocks in runs of 16, then 8 runs, 0.8 units in all; 2.8 in one chain
+@pytest.mark.parametrize("n,N,B", [(128, 128, 200), (96, 96, 400), (64, 181, 256), (101, 101, 100), (45, 128, 1024)])
+def test_batched_long_slices(n, N, B):
+    import torch
+    from paper_2106_09122_amd import psflib
+    rng = np.random.default_rng([n, N, B])
+    cube = torch.from_numpy((rng.random((3, n, n)) ** 3).astype(np.float32)).cuda()
+    lib = psflib.Library(cube, np.linspace(0.0, 0.3 * N, 3), N, 1.0)
+    A = torch.cat([lib.get_columns(np.arange(j, min(j + 4096, N * N))) for j in range(0, N * N, 4096)])
+    Z = torch.from_numpy(rng.random((B, N * N)).astype(np.float32)).cuda()
+    out = lib.apply_batched(Z)
+    pick = [0, 31, 32, B - 1]
+    err = _rms(out[pick], Z[pick].double() @ A.double())
+    print("batched rounding", n, N, B, err / UNIT, flush=True)
+    assert err <= UNIT
+    lib.close()
