@@ -242,7 +242,8 @@ psflib_status psflib_apply_adjoint(const psflib_handle* h, const float* d_g, flo
  * FP32 storage runs float32 matrix-core products; the 16-bit forms round each
  * scene to the storage format with a per-scene power-of-two scale (so the
  * scaled scene spans [2^14, 2^15) at its largest) and run 16-bit matrix-core
- * products with float32 accumulation.  B = 1 runs psflib_apply instead (the
+ * products with float32 accumulation; slices of a split K are added in a fixed
+ * order, with float64 sums past eight.  B = 1 runs psflib_apply instead (the
  * matvec streams the library faster).  Temporaries (packed scenes, K-split
  * partial images; up to ~100 MiB at 128 x 128 with 1024 scenes per pass) sit
  * in the buffer of `stream` (see the conventions above). */

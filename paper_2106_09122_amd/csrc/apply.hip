@@ -8,7 +8,7 @@
 // threads apart) and walks columns with 16 independent 16-byte non-temporal
 // loads in flight; the threads of a workgroup are RT along the rows and CT along
 // the columns, whose sums are added through LDS, and it writes a partial image;
-// a second kernel adds the partials of every row in chunk order.  (Doing that
+// a second kernel adds the partials of every row in pairs, in a fixed order.  (Doing that
 // sum in the last workgroup to finish each row block needs a device-scope
 // release per workgroup, which writes back the XCD's L2: measured slower than
 // the extra launch.)  Few columns take one launch: workgroups of 1024 threads
@@ -802,9 +802,13 @@ static AdjShape adj_shape(bool f32, int64_t M, int64_t units) {
   // against 85 us; 181^2 PSFs of two row blocks, 200^2 scene: 415 against 404).
   // Float32 libraries of three row blocks and more, whose workgroups' ranges lie
   // further apart, take half as much each (200^2 PSFs, 128^2 scene: 412 against
-  // 420 us; in 16 bits it makes no difference, 256^2 1214 to 1225 us either way).
+  // 420 us), and libraries of 2 GiB and more of several long row blocks a quarter
+  // (256^2, bf16: 1231 against 1268 us, 160^2 scene, fp16 475 against 489; one row
+  // block, 128^2 PSFs, 256^2 scene, bf16: 315 against 310; blocks of 8448 rows, 129^2
+  // PSFs, 256^2 scene, float32: 659 against 645).
   const int64_t bytes = columns * std::min(M, sh.block_rows) * (f32 ? 4 : 16);
-  const int64_t turn = (int64_t)(f32 && sh.nb >= 3 ? 256 : 512) << 20;
+  const bool far = sh.nb >= 2 && sh.block_rows >= 12288 && bytes >= (int64_t)2 << 30;
+  const int64_t turn = (int64_t)(far ? 128 : f32 && sh.nb >= 3 ? 256 : 512) << 20;
   const int64_t turns = std::max<int64_t>(1, (bytes + turn / 2) / turn);
   const int64_t want = std::max<int64_t>(1, 512 * turns / sh.nb);
   const int64_t groups = f32 ? (units + sh.c - 1) / sh.c : units, quantum = sh.split ? 1 : waves;
