@@ -1095,18 +1095,20 @@ static GemmPlan plan_gemm(int storage, int64_t M, int64_t ncols, int64_t ncols_p
     // fullest CU (one alone multiplies as fast as two, or waits for memory as they
     // do), each with the cost of its start and end, and for split sums the reduction's
     // launch, its chain and the partial images' round trip.  In 16 bits the library's
-    // stream sets a bound that uneven CUs do not change, and a slice may end inside a
+    // stream sets a bound that uneven CUs do not change (but not for the 256-scene
+    // tile, whose products take longer than its stream), and a slice may end inside a
     // turn of the ring at the cost of one guarded stage.  The weights are fitted to
-    // 16000 timed products of 45 image and scene sizes, 5 to 400 scenes and 1 to 64
+    // 18000 timed products of 62 image and scene sizes, 5 to 400 scenes and 1 to 64
     // slices: in the mean 1% (FP32) and 3% from the best number of slices.
     // (FP32, 64^2, 100^2 scene, 33 scenes: 16 slices on 256 CUs 49 us, 27 of 48 units
     // on 432 places 60; 96^2, 96^2 scene, 20 scenes: 36 tiles, 7 slices 63, 12 slices 68,
     // 15, a third workgroup on 28 CUs, 82; 131^2, 80^2 scene, 33 scenes: 68 tiles, 3
     // slices 147, 10 slices, 168 workgroups in the second round, 175.  16 bits, the
-    // same: 3 slices 54, 2 slices 64, 4 slices 72.)
+    // same: 3 slices 54, 2 slices 64, 4 slices 72; 128^2, 200 scenes: 64 tiles, 4 slices
+    // 138, 3 slices on 192 CUs 155.)
     const double unit = (double)tm * (f32 ? 32 : 2 * 8 * kHG);  // library bytes of a K unit of a tile
     const double partial = 8.0 * tm * std::min(bc, tn);         // written and read, a slice of a tile
-    const double stream = f32 ? 0.0 : 1.33 * (double)(tiles * p.kunits) / 256.0;
+    const double stream = f32 || tn == 256 ? 0.0 : 1.33 * (double)(tiles * p.kunits) / 256.0;
     // FP32: rounds of two workgroups a CU; a last one of up to 256 does not spread
     // itself evenly over the CUs
     auto fullest = [&](int64_t wgs) -> double {
