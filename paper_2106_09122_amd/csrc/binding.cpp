@@ -18,7 +18,9 @@
 namespace {
 
 PyObject* g_error = nullptr;   // psflib.PsflibError, kept for the life of the module
-PyObject* g_native = nullptr;  // fit._native: whether a library's products are its class's
+// psflib.Library and its products, kept for the life of the module
+PyTypeObject* g_library = nullptr;
+PyObject *g_apply = nullptr, *g_adjoint = nullptr;
 
 // PsflibError(status, where, message), from any thread
 [[noreturn]] void raise_status(psflib_status st, const char* where) {
@@ -64,7 +66,8 @@ struct Lib {
 struct Names {
   PyObject *handle = PyUnicode_InternFromString("_handle"), *h = PyUnicode_InternFromString("h"),
            *ncols = PyUnicode_InternFromString("ncols"), *M = PyUnicode_InternFromString("M"),
-           *device = PyUnicode_InternFromString("device");
+           *device = PyUnicode_InternFromString("device"), *apply = PyUnicode_InternFromString("apply"),
+           *adjoint = PyUnicode_InternFromString("apply_adjoint");
 };
 const Names& names() {
   static const Names* n = new Names();
@@ -80,6 +83,19 @@ py::object attr(py::handle o, PyObject* name) {
 const psflib_handle* handle_of(py::handle o) {  // o.h; with the GIL
   py::object h = attr(o, names().h);
   return h.is_none() ? nullptr : reinterpret_cast<const psflib_handle*>(h.cast<uintptr_t>());
+}
+
+// Whether o's products are those of psflib.Library: not overridden, and not replaced
+// on the class or the object (a counter, a wrapper), which are called.  With the GIL.
+// A fit step asks twice (in Python that took 2 us of its 130).
+bool is_native(py::handle o) {
+  if (!g_library || Py_TYPE(o.ptr()) != g_library ||
+      PyDict_GetItem(g_library->tp_dict, names().apply) != g_apply ||
+      PyDict_GetItem(g_library->tp_dict, names().adjoint) != g_adjoint)
+    return false;
+  py::object own = py::reinterpret_steal<py::object>(PyObject_GenericGetDict(o.ptr(), nullptr));
+  if (!own) throw py::error_already_set();
+  return !PyDict_GetItem(own.ptr(), names().apply) && !PyDict_GetItem(own.ptr(), names().adjoint);
 }
 
 Lib lib_of(py::handle o) {  // with the GIL
@@ -227,7 +243,7 @@ struct Simulate : torch::autograd::Function<Simulate> {
     {
       py::gil_scoped_acquire gil;
       const py::object o = ref->library();
-      if (!o.is_none() && g_native && !py::handle(g_native)(o).cast<bool>())
+      if (!o.is_none() && !is_native(o))
         // another adjoint than the class's has been put in its place
         return {o.attr("apply_adjoint")(gS).cast<at::Tensor>(), at::Tensor()};
       lib.h = handle_of(ref->handle);
@@ -354,7 +370,12 @@ std::tuple<at::Tensor, at::Tensor> loss_and_grad(py::handle self, py::handle the
 PYBIND11_MODULE(_psfop, m) {
   m.doc() = "Native calls of the psflib binding.";
   m.def("set_error", [](py::object cls) { g_error = cls.release().ptr(); });
-  m.def("set_native", [](py::object f) { g_native = f.release().ptr(); });
+  m.def("set_library", [](py::object cls) {
+    g_apply = py::object(cls.attr("apply")).release().ptr();
+    g_adjoint = py::object(cls.attr("apply_adjoint")).release().ptr();
+    g_library = reinterpret_cast<PyTypeObject*>(cls.release().ptr());
+  });
+  m.def("is_native", &is_native);
   m.def("current_stream", [](const at::Device& d) { return reinterpret_cast<uintptr_t>(current_stream(d)); });
   m.def("apply", &apply);
   m.def("apply_adjoint", &apply_adjoint);

@@ -23,18 +23,8 @@ def _stream(dev):
     return torch.cuda.current_stream(dev).cuda_stream
 
 
-_OWN = psflib.Library.apply, psflib.Library.apply_adjoint
-
-
-def _native(lib) -> bool:
-    """Whether lib's products are those of psflib.Library: not overridden, and not
-    replaced on the class or the object (a counter, a wrapper), which are called."""
-    if type(lib) is not psflib.Library or (psflib.Library.apply, psflib.Library.apply_adjoint) != _OWN:
-        return False
-    return "apply" not in lib.__dict__ and "apply_adjoint" not in lib.__dict__
-
-
-_psfop.set_native(_native)  # asked again by a backward pass
+_psfop.set_library(psflib.Library)
+_native = _psfop.is_native  # asked again by a backward pass
 
 
 class _Simulate(torch.autograd.Function):
