@@ -102,10 +102,9 @@ typedef enum { PSFLIB_OOB_CLAMP = 0, PSFLIB_OOB_ZERO = 1 } psflib_oob;
  *             natural order (slot j = column j) where the sort's bounds are
  *             exceeded: more than 8192 PSFs, or ceil(base columns / 1024) *
  *             max(n_psf, 2) above 2^24 (e.g. a 4096 x 4096 scene with more
- *             than 4096 PSFs).  The slot
- *             order is part of the library buffer (see psflib_library_bytes);
- *             psflib_get_columns reads columns by index whatever the order.
- *             Products accumulate in float32. */
+ *             than 4096 PSFs).  The slot order is part of the library buffer
+ *             (see psflib_library_bytes); psflib_get_columns reads columns by
+ *             index whatever the order.  Products accumulate in float32. */
 typedef enum { PSFLIB_FP32 = 0, PSFLIB_BF16_POW2 = 1, PSFLIB_FP16_POW2 = 2 } psflib_storage;
 
 /* Exponent e_j of an identically zero column in the 16-bit forms (its
