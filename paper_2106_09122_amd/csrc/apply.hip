@@ -392,11 +392,19 @@ static MvShape mv_shape(int storage, int64_t M, int64_t ncols, int64_t ncols_pad
   }
   const int64_t rows = (int64_t)sh.r * sh.rt;
   sh.rowblocks = (M + rows - 1) / rows;
-  int64_t want = (mv_target_workgroups(sh.rt, sh.r) + sh.rowblocks - 1) / sh.rowblocks;
-  if (want < 1) want = 1;
-  int64_t chunk = (units + want - 1) / want;
-  chunk = (chunk + 15) / 16 * 16;
-  if (!f32 && chunk > kMv16MaxChunkGroups) chunk = kMv16MaxChunkGroups;
+  // As many chunks as keep the workgroups within the target: a few more than two a
+  // CU cost their CUs a third turn (120^2, 150^2 scene, bf16: 522 workgroups 110 us, 464
+  // 99; 96^2, 128^2 scene, float32: 104 and 89).  One chunk a row block more where chunks
+  // are so short that the next longer ones, whole blocks of 16, would leave a seventh of
+  // the target idle (200^2, 40^2 scene, bf16: 260 workgroups 25 us, 140 32).
+  const int64_t target = mv_target_workgroups(sh.rt, sh.r);
+  auto chunk_of = [&](int64_t want) {
+    const int64_t chunk = ((units + want - 1) / want + 15) / 16 * 16;
+    return !f32 && chunk > kMv16MaxChunkGroups ? (int64_t)kMv16MaxChunkGroups : chunk;
+  };
+  int64_t chunk = chunk_of(std::max<int64_t>(1, target / sh.rowblocks));
+  if ((units + chunk - 1) / chunk * sh.rowblocks * 7 < target * 6)
+    chunk = chunk_of((target + sh.rowblocks - 1) / sh.rowblocks);
   sh.chunk = chunk;
   sh.nchunks = (units + chunk - 1) / chunk;
   return sh;
