@@ -2184,12 +2184,12 @@ static hipError_t launch_spread16(int storage, const ColGeom* geo, int n, int64_
 // 128^2 scene, 256 MiB, 283 us kept, 308 formed again; 144^2 scene 401 and 366; 176^2
 // 565 and 481.  From boxes (n > 131) kept all the same (256^2, 80^2 scene, 400 MiB: 557
 // and 623).  On sides that are not multiples of 4, whose stores of parts of lines
-// need the cache too, up to 80 MiB (101^2, 60^2 scene, 35 MiB: 79 and 85; 101^2, 99
+// need the cache too, up to 88 MiB (101^2, 60^2 scene, 35 MiB: 79 and 85; 101^2, 99
 // MiB: 180 and 158; 150^2, 60^2 scene, 77 MiB: 144 and 201; 90^2, 174 MiB: 354 and 318).
 size_t orbit_bases_bytes(int n, int N, bool cubic) {
   const size_t bytes = (size_t)orbit_grid(N).nreps * (size_t)n * (size_t)n * 4;
   const size_t most = cubic || (n % 4 == 0 && !orbit16_pair_fits(n)) ? ~(size_t)0
-                                                                     : (size_t)(n % 4 == 0 ? 256 : 80) << 20;
+                                                                     : (size_t)(n % 4 == 0 ? 256 : 88) << 20;
   return bytes <= most ? bytes : 0;
 }
 
